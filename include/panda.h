@@ -121,8 +121,9 @@ void panda_default_options(panda_options* opt);
 
 /* Z-score normalisation of one network in place (Sec. II-A; NormalizeNetwork
  * in Sec. II-C): mean and population standard deviation over all rows*cols
- * entries, then M <- (M - mean) / std.  Reductions in FP64, two passes.
- * Needs panda_normalize_workspace_bytes() bytes of workspace (a few KB).
+ * entries, then M <- (M - mean) / std.  Moments in FP64, merged without
+ * cancellation.
+ * Needs panda_normalize_workspace_bytes() bytes of workspace (some 30 KB).
  * Synchronises the stream.  Returns PANDA_ERR_NONFINITE (M untouched) if an
  * entry is NaN/Inf, PANDA_ERR_DEGENERATE (M untouched) if the standard
  * deviation is 0. */
@@ -133,12 +134,13 @@ panda_status panda_normalize(float* M, int64_t rows, int64_t cols, void* workspa
 /* The same z-score with a choice of scope (PANDA_ZSCORE_*) and normaliser
  * (ddof 0: divide the sum of squared deviations by the count n; ddof 1: by
  * n - 1).  M is rows x cols, row-major, contiguous, device memory, changed in
- * place.  Moments in FP64, two passes.  Returns PANDA_ERR_NONFINITE (M
+ * place.  Moments in FP64, merged without cancellation.  Returns PANDA_ERR_NONFINITE (M
  * untouched) for a NaN/Inf entry; PANDA_ERR_DEGENERATE (M untouched) if the
  * network, or under the row / row + column scopes any row / column, has zero
  * spread (or fewer than ddof + 1 entries).  Needs
  * panda_normalize_ex_workspace_bytes(rows, cols, zscore_mode) bytes of
- * workspace (0 for invalid arguments; about 16 (rows + cols) bytes).
+ * workspace (0 for invalid arguments; about 16 (rows + cols) bytes, and under
+ * the row + column scope 16 cols more for every 256 rows, up to 64 times).
  * Synchronises the stream.  panda_normalize is zscore_mode GLOBAL, ddof 0. */
 size_t panda_normalize_ex_workspace_bytes(int64_t rows, int64_t cols, int32_t zscore_mode);
 panda_status panda_normalize_ex(float* M, int64_t rows, int64_t cols, int32_t zscore_mode,

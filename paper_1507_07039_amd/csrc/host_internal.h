@@ -42,10 +42,9 @@ struct Carver {
   }
 };
 
-constexpr size_t kZsScratch = kZsBlocks + 8;  // doubles
 // Scratch (doubles) of a z-score of a rows x cols network with the given
-// scope: the global form's block partials, or 8 flags plus the per-row and
-// per-column moments.
+// scope: the global form's block moments, or 8 flags plus the per-row and
+// per-column moments and the column chunks' moments.
 size_t zscore_scratch_doubles(int64_t rows, int64_t cols, int32_t mode);
 // Diagonal and off-diagonal value of the z-scored identity of order n; false
 // if its standard deviation is 0.

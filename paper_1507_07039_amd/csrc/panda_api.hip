@@ -228,33 +228,38 @@ bool identity_zscore(int64_t n, int32_t mode, int32_t ddof, double* dv, double* 
 
 size_t zscore_scratch_doubles(int64_t rows, int64_t cols, int32_t mode) {
   if (mode == PANDA_ZSCORE_GLOBAL) return kZsScratch;
-  const size_t rc = 8 + 2 * (size_t)rows + (mode == PANDA_ZSCORE_ROWCOL ? 2 * (size_t)cols : 0);
+  const size_t rc = 8 + 2 * (size_t)rows +
+                    (mode == PANDA_ZSCORE_ROWCOL
+                         ? 2 * (size_t)cols * (1 + (size_t)zs_col_chunks(rows)) : 0);
   return rc > kZsScratch ? rc : kZsScratch;
 }
 
 panda_status zscore(float* M, int64_t rows, int64_t cols, int64_t ld, int32_t mode, int32_t ddof,
                     double* scratch, hipStream_t s) {
+  // apply skips a refused matrix on the device, so it is enqueued before the
+  // verdict is read back and the GPU does not wait for the host
   if (mode == PANDA_ZSCORE_GLOBAL) {
     HIP_TRY(launch_zscore_stats(M, rows, cols, ld, scratch, s, ddof));
+    HIP_TRY(launch_zscore_apply(M, rows, cols, ld, scratch, s));
     double tail[3];
     HIP_TRY(hipMemcpyAsync(tail, scratch + kZsBlocks, sizeof tail, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (tail[2] != 0.0) return fail(PANDA_ERR_NONFINITE, "network contains NaN or Inf%s");
     if (!(tail[1] > 0.0)) return fail(PANDA_ERR_DEGENERATE, "network is constant (std = 0)%s");
-    HIP_TRY(launch_zscore_apply(M, rows, cols, ld, scratch, s));
     return PANDA_OK;
   }
   double* flags = scratch;
   double2* rs = reinterpret_cast<double2*>(scratch + 8);
   double2* cs = mode == PANDA_ZSCORE_ROWCOL ? rs + rows : nullptr;
-  HIP_TRY(launch_zscore_rc_stats(M, rows, cols, ld, ddof, flags, rs, cs, s));
+  HIP_TRY(launch_zscore_rc_stats(M, rows, cols, ld, ddof, flags, rs, cs, cs ? cs + cols : nullptr,
+                                 s));
+  HIP_TRY(launch_zscore_rc_apply(M, rows, cols, ld, rs, cs, flags, s));
   double f[2];
   HIP_TRY(hipMemcpyAsync(f, flags, sizeof f, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (f[0] != 0.0) return fail(PANDA_ERR_NONFINITE, "network contains NaN or Inf%s");
   if (f[1] != 0.0)
     return fail(PANDA_ERR_DEGENERATE, "a row or column of the network is constant (std = 0)%s");
-  HIP_TRY(launch_zscore_rc_apply(M, rows, cols, ld, rs, cs, s));
   return PANDA_OK;
 }
 

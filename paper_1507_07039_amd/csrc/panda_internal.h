@@ -240,18 +240,29 @@ hipError_t launch_row_sqnorms(const float* M, int64_t rows, int64_t cols, int64_
 hipError_t launch_col_sqnorms(const float* M, int64_t rows, int64_t cols, int64_t ld, double* out,
                               double* scratch, const int32_t* gate, hipStream_t s);
 
-// Z-score (Sec. II-A) on a strided matrix; scratch holds kZsBlocks + 8 doubles.
+// Z-score (Sec. II-A) on a strided matrix; scratch holds kZsScratch doubles:
+// the moments (mean, std, non-finite flag) at kZsBlocks, the blocks' moments
+// (3 doubles each) from kZsPart on.
 constexpr int kZsBlocks = 1024;
+constexpr int kZsPart = kZsBlocks + 8;
+constexpr size_t kZsScratch = kZsPart + 3 * (size_t)kZsBlocks;
 hipError_t launch_zscore_stats(const float* M, int64_t rows, int64_t cols, int64_t ld,
                                double* scratch, hipStream_t s, int ddof = 0);
 // Per-row moments (rs, one per row) and, when cs is given, per-column
-// moments (cs, one per column) as (mean, std); flags[0] / flags[1] are set
-// for a NaN/Inf entry / a row or column of zero spread.  apply: per-row
-// z-score, or (row z + column z) / sqrt 2 when cs is given.
+// moments (cs, one per column) as (mean, 1 / std); cpart: zs_col_chunks(rows)
+// x cols double2 of scratch for the columns.  flags[0] / flags[1] are set for
+// a NaN/Inf entry / a row or column of zero spread, and then the matrix is
+// left alone by apply: per-row z-score, or (row z + column z) / sqrt 2 when
+// cs is given.
+constexpr int64_t kZsColChunks = 64;
+int64_t zs_col_chunks(int64_t rows);
 hipError_t launch_zscore_rc_stats(const float* M, int64_t rows, int64_t cols, int64_t ld, int ddof,
-                                  double* flags, double2* rs, double2* cs, hipStream_t s);
+                                  double* flags, double2* rs, double2* cs, double2* cpart,
+                                  hipStream_t s);
 hipError_t launch_zscore_rc_apply(float* M, int64_t rows, int64_t cols, int64_t ld,
-                                  const double2* rs, const double2* cs, hipStream_t s);
+                                  const double2* rs, const double2* cs, const double* flags,
+                                  hipStream_t s);
+// Skipped on the device where the moments refuse the matrix.
 hipError_t launch_zscore_apply(float* M, int64_t rows, int64_t cols, int64_t ld,
                                const double* scratch, hipStream_t s);
 hipError_t launch_fill_identity(float* M, int64_t n, int64_t ld, hipStream_t s);

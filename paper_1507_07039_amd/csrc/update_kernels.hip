@@ -332,127 +332,288 @@ __global__ __launch_bounds__(kRT) void k_col_sqnorms_sum(const double* __restric
 }
 
 // ---- z-score --------------------------------------------------------------
-// scratch layout: [0, kZsBlocks) block partials, then
-// [kZsBlocks + 0] mean, [+1] std, [+2] 1.0 if any entry is NaN or Inf.
-__global__ __launch_bounds__(kRT) void k_zs_sum(const float* __restrict__ M, int64_t rows,
-                                                int64_t cols, int64_t ld, double* scratch,
-                                                int pass) {
-  __shared__ double red[4];
-  const int64_t n = rows * cols;
-  const double mean = pass ? scratch[kZsBlocks] : 0.0;
-  double s = 0.0, bad = 0.0;
-  for (int64_t e = (int64_t)blockIdx.x * kRT + threadIdx.x; e < n; e += (int64_t)gridDim.x * kRT) {
-    const double x = (double)M[(e / cols) * ld + e % cols];
-    if (!isfinite(x)) bad += 1.0;
-    s += pass ? (x - mean) * (x - mean) : x;
+// Moments of a set of entries: count, mean, sum of squared deviations from
+// that mean.  Two sets merge without cancellation (Chan, Golub & LeVeque,
+// "Updating formulae and a pairwise algorithm for computing sample
+// variances", 1979).
+struct Mom {
+  double n, mean, m2;
+};
+__device__ __forceinline__ void mom_add(Mom& a, double n, double mean, double m2) {
+  if (n <= 0.0) return;
+  const double tot = a.n + n, d = mean - a.mean, f = n / tot;
+  a.mean += d * f;
+  a.m2 += m2 + d * d * (a.n * f);
+  a.n = tot;
+}
+// Moments of v[0 .. cnt-1]: two passes in registers.
+template <int U>
+__device__ __forceinline__ void mom_add_run(Mom& a, const float (&v)[U], int cnt) {
+  double s = 0.0, q = 0.0;
+  if (cnt == U) {  // a whole run, without the selects
+#pragma unroll
+    for (int k = 0; k < U; ++k) s += (double)v[k];
+    const double mean = s * (1.0 / U);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const double d = (double)v[k] - mean;
+      q += d * d;
+    }
+    mom_add(a, (double)U, mean, q);
+    return;
   }
-  const double tot = block_sum(s, red);
-  double nb = 0.0;
-  if (!pass) nb = block_sum(bad, red);
+#pragma unroll
+  for (int k = 0; k < U; ++k) s += k < cnt ? (double)v[k] : 0.0;
+  const double mean = cnt ? s / (double)cnt : 0.0;
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const double d = k < cnt ? (double)v[k] - mean : 0.0;
+    q += d * d;
+  }
+  mom_add(a, (double)cnt, mean, q);
+}
+// The moments of a block's threads, merged about their common mean (the same
+// in every thread).  The mean is taken relative to thread 0's, so that equal
+// entries give an m2 of exactly 0 whatever their number.
+__device__ __forceinline__ Mom mom_block(const Mom& a, double* red) {
+  __shared__ double ref;
+  __syncthreads();
+  if (threadIdx.x == 0) ref = a.mean;
+  __syncthreads();
+  const double r = ref;
+  Mom t;
+  t.n = block_sum(a.n, red);
+  const double off = block_sum(a.n * (a.mean - r), red);
+  t.mean = t.n > 0.0 ? r + off / t.n : 0.0;
+  const double d = a.mean - t.mean;
+  t.m2 = block_sum(a.n > 0.0 ? a.m2 + a.n * d * d : 0.0, red);
+  return t;
+}
+
+// Global scope, one pass: chunks of kRT x 4 x U entries of one row (the whole
+// matrix is one row where its rows are contiguous) go to the blocks in turn;
+// a thread holds its 4 U entries of a chunk in registers and takes their mean
+// and squared deviations there, so the matrix is read once at the rate of
+// memory and nothing cancels.  An entry that is NaN or Inf makes its block's
+// m2 NaN.  Scratch: mean, std and the non-finite flag at [kZsBlocks],
+// [kZsBlocks + 1], [kZsBlocks + 2]; the block moments from kZsPart on.
+// 18000 x 18000: two passes of 733 us (a 64-bit division per entry to find
+// its row) -> one of 0.3 ms.
+template <bool VEC, int U>
+__global__ __launch_bounds__(kRT) void k_zs_moments(const float* __restrict__ M, int64_t rows,
+                                                    int64_t cols, int64_t ld, int64_t per_row,
+                                                    double* __restrict__ scratch) {
+  __shared__ double red[4];
+  constexpr int64_t kChunk = (int64_t)kRT * 4 * U;
+  Mom a{0.0, 0.0, 0.0};
+  const int64_t nch = rows * per_row;
+  for (int64_t ch = blockIdx.x; ch < nch; ch += gridDim.x) {
+    const int64_t r = ch / per_row, c0 = (ch - r * per_row) * kChunk;
+    const float* row = M + r * ld;
+    const int64_t left = cols - c0;  // entries of the row from this chunk on
+    float v[4 * U];
+    int cnt = 0;
+    if (VEC) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t o = ((int64_t)u * kRT + threadIdx.x) * 4;
+        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (o + 3 < left) {
+          x = *reinterpret_cast<const float4*>(row + c0 + o);
+        } else if (o < left) {
+          x.x = row[c0 + o];
+          if (o + 1 < left) x.y = row[c0 + o + 1];
+          if (o + 2 < left) x.z = row[c0 + o + 2];
+        }
+        v[4 * u] = x.x; v[4 * u + 1] = x.y; v[4 * u + 2] = x.z; v[4 * u + 3] = x.w;
+        const int64_t k = left - o;
+        cnt += k >= 4 ? 4 : k > 0 ? (int)k : 0;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4 * U; ++u) {
+        const int64_t o = (int64_t)u * kRT + threadIdx.x;
+        v[u] = o < left ? row[c0 + o] : 0.0f;
+        cnt += o < left ? 1 : 0;
+      }
+    }
+    mom_add_run(a, v, cnt);  // a thread's entries inside the row come first
+  }
+  const Mom t = mom_block(a, red);
   if (threadIdx.x == 0) {
-    scratch[blockIdx.x] = tot;
-    if (!pass && nb > 0.0) scratch[kZsBlocks + 2] = 1.0;  // every writer stores the same 1.0
+    double* p = scratch + kZsPart + 3 * (int64_t)blockIdx.x;
+    p[0] = t.n;
+    p[1] = t.mean;
+    p[2] = t.m2;
   }
 }
 
-__global__ __launch_bounds__(kRT) void k_zs_finish(double* scratch, int64_t n, int pass,
-                                                   int ddof) {
+// The blocks' moments merged: mean, std (divisor n - ddof; 0 when there is
+// no degree of freedom) and the non-finite flag.  One block.
+__global__ __launch_bounds__(kRT) void k_zs_finish(double* scratch, int nb, int ddof) {
   __shared__ double red[4];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < kZsBlocks; i += kRT) s += scratch[i];
-  const double tot = block_sum(s, red);
+  Mom a{0.0, 0.0, 0.0};
+  double bad = 0.0;
+  for (int i = threadIdx.x; i < nb; i += kRT) {
+    const double* p = scratch + kZsPart + 3 * i;
+    if (p[0] > 0.0 && !isfinite(p[2])) bad = 1.0;
+    mom_add(a, p[0], p[1], p[2]);
+  }
+  const Mom t = mom_block(a, red);
+  const double nbad = block_sum(bad, red);
   if (threadIdx.x == 0) {
-    if (!pass) {
-      scratch[kZsBlocks] = tot / (double)n;
+    scratch[kZsBlocks] = t.mean;
+    scratch[kZsBlocks + 1] = t.n - ddof >= 1.0 ? sqrt(t.m2 / (t.n - ddof)) : 0.0;
+    scratch[kZsBlocks + 2] = nbad > 0.0 ? 1.0 : 0.0;
+  }
+}
+
+// M <- (M - mean) / std, skipped where the moments were refused (std = 0 or
+// a non-finite entry).  The chunks are taken from the matrix's end, whose
+// entries the moments pass read last and the last-level cache still holds.
+// Bound by memory: 18000 x 18000 in 463 us (5.6 TB/s); 643 us with two 64-bit
+// divisions for the row and an FP64 one per entry.
+template <bool VEC, int U>
+__global__ __launch_bounds__(kRT) void k_zs_apply(float* __restrict__ M, int64_t rows,
+                                                  int64_t cols, int64_t ld, int64_t per_row,
+                                                  const double* __restrict__ scratch) {
+  constexpr int64_t kChunk = (int64_t)kRT * 4 * U;
+  const double mean = scratch[kZsBlocks], sd = scratch[kZsBlocks + 1];
+  if (!(sd > 0.0) || scratch[kZsBlocks + 2] != 0.0) return;
+  const double inv = 1.0 / sd;
+  auto z = [&](float x) { return (float)(((double)x - mean) * inv); };
+  const int64_t nch = rows * per_row;
+  for (int64_t k = blockIdx.x; k < nch; k += gridDim.x) {
+    const int64_t ch = nch - 1 - k;
+    const int64_t r = ch / per_row, c0 = (ch - r * per_row) * kChunk;
+    float* row = M + r * ld + c0;
+    const int64_t left = cols - c0;
+    if (VEC) {
+      float4 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t o = ((int64_t)u * kRT + threadIdx.x) * 4;
+        if (o + 3 < left) x[u] = *reinterpret_cast<const float4*>(row + o);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t o = ((int64_t)u * kRT + threadIdx.x) * 4;
+        if (o + 3 < left) {
+          *reinterpret_cast<float4*>(row + o) =
+              make_float4(z(x[u].x), z(x[u].y), z(x[u].z), z(x[u].w));
+        } else {
+          for (int64_t e = o; e < left && e < o + 4; ++e) row[e] = z(row[e]);
+        }
+      }
     } else {
-      // std = 0 (a constant network, or no degree of freedom) is reported
-      scratch[kZsBlocks + 1] = n - ddof >= 1 ? sqrt(tot / (double)(n - ddof)) : 0.0;
+#pragma unroll
+      for (int u = 0; u < 4 * U; ++u) {
+        const int64_t o = (int64_t)u * kRT + threadIdx.x;
+        if (o < left) row[o] = z(row[o]);
+      }
     }
   }
 }
 
-__global__ __launch_bounds__(kRT) void k_zs_clear(double* scratch) {
-  for (int i = threadIdx.x; i < kZsBlocks + 8; i += kRT) scratch[i] = 0.0;
-}
-
-__global__ __launch_bounds__(kRT) void k_zs_apply(float* __restrict__ M, int64_t rows,
-                                                  int64_t cols, int64_t ld,
-                                                  const double* __restrict__ scratch) {
-  const double mean = scratch[kZsBlocks], sd = scratch[kZsBlocks + 1];
-  const int64_t n = rows * cols;
-  for (int64_t e = (int64_t)blockIdx.x * kRT + threadIdx.x; e < n; e += (int64_t)gridDim.x * kRT) {
-    float* p = M + (e / cols) * ld + e % cols;
-    *p = (float)(((double)*p - mean) / sd);
-  }
-}
-
 // Z-score per row, or row + column (scopes of the z-score of Sec. II-A).
-// flags[0] = 1 if an entry is NaN/Inf, flags[1] = 1 if a row or column has
-// zero spread (every writer stores the same 1.0).  Moments in FP64, two
-// passes; sd = 0 when fewer than ddof + 1 entries.
+// rs and cs hold (mean, 1 / std).  flags[0] = 1 if an entry is NaN/Inf,
+// flags[1] = 1 if a row or column has zero spread (every writer stores the
+// same 1.0).  Moments in FP64; std = 0 when fewer than ddof + 1 entries.
+__device__ __forceinline__ void zs_put(double2* out, double n, double mean, double m2, int ddof,
+                                       double* flags) {
+  const double sd = n - ddof >= 1.0 ? sqrt(m2 / (n - ddof)) : 0.0;
+  *out = make_double2(mean, 1.0 / sd);
+  if (!(sd > 0.0)) flags[1] = 1.0;  // NaN too: flags[0] is set with it
+}
 __global__ __launch_bounds__(kRT) void k_zs_rows(const float* __restrict__ M, int64_t cols,
                                                  int64_t ld, int ddof, double2* __restrict__ rs,
                                                  double* flags) {
   __shared__ double red[4];
+  constexpr int U = 16;
   const float* row = M + (int64_t)blockIdx.x * ld;
-  double s = 0.0, bad = 0.0;
-  for (int64_t j = threadIdx.x; j < cols; j += kRT) {
-    const double x = (double)row[j];
-    if (!isfinite(x)) bad += 1.0;
-    s += x;
+  Mom a{0.0, 0.0, 0.0};
+  for (int64_t j0 = 0; j0 < cols; j0 += kRT * U) {
+    float v[U];
+    int cnt = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t j = j0 + (int64_t)u * kRT + threadIdx.x;
+      v[u] = j < cols ? row[j] : 0.0f;
+      cnt += j < cols ? 1 : 0;
+    }
+    mom_add_run(a, v, cnt);
   }
-  const double mean = block_sum(s, red) / (double)cols;
-  const double nb = block_sum(bad, red);
-  double q = 0.0;
-  for (int64_t j = threadIdx.x; j < cols; j += kRT) {
-    const double d = (double)row[j] - mean;
-    q += d * d;
-  }
-  const double qs = block_sum(q, red);
+  const Mom t = mom_block(a, red);
   if (threadIdx.x == 0) {
-    const double sd = cols - ddof >= 1 ? sqrt(qs / (double)(cols - ddof)) : 0.0;
-    rs[blockIdx.x] = make_double2(mean, sd);
-    if (nb > 0.0) flags[0] = 1.0;
-    if (!(sd > 0.0)) flags[1] = 1.0;
+    if (!isfinite(t.m2)) flags[0] = 1.0;
+    zs_put(rs + blockIdx.x, t.n, t.mean, t.m2, ddof, flags);
   }
 }
 
-// Column moments, one thread per column walking down the rows (coalesced
-// across the wave).
-__global__ __launch_bounds__(kRT) void k_zs_cols(const float* __restrict__ M, int64_t rows,
-                                                 int64_t cols, int64_t ld, int ddof,
-                                                 double2* __restrict__ cs, double* flags) {
+// Column moments: a block takes kRT columns of kZsColRows rows (coalesced
+// across the wave), sixteen loads in flight per thread, and leaves its
+// moments in part[chunk][column]; the finish merges the chunks.  One thread
+// walking a whole column leaves most of the chip idle: 18000 x 18000 in 71
+// blocks.
+__global__ __launch_bounds__(kRT) void k_zs_cols_part(const float* __restrict__ M, int64_t rows,
+                                                      int64_t cols, int64_t ld, int64_t chunk,
+                                                      double2* __restrict__ part) {
+  constexpr int U = 16;
   const int64_t j = (int64_t)blockIdx.x * kRT + threadIdx.x;
   if (j >= cols) return;
-  double s = 0.0;
-  for (int64_t i = 0; i < rows; ++i) s += (double)M[i * ld + j];
-  const double mean = s / (double)rows;
-  double q = 0.0;
-  for (int64_t i = 0; i < rows; ++i) {
-    const double d = (double)M[i * ld + j] - mean;
-    q += d * d;
+  const int64_t r0 = (int64_t)blockIdx.y * chunk;
+  const int64_t r1 = r0 + chunk < rows ? r0 + chunk : rows;
+  Mom a{0.0, 0.0, 0.0};
+  for (int64_t i = r0; i < r1; i += U) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i + u < r1 ? M[(i + u) * ld + j] : 0.0f;
+    mom_add_run(a, v, (int)(r1 - i < U ? r1 - i : U));
   }
-  const double sd = rows - ddof >= 1 ? sqrt(q / (double)(rows - ddof)) : 0.0;
-  cs[j] = make_double2(mean, sd);
-  if (!(sd > 0.0)) flags[1] = 1.0;
+  part[(int64_t)blockIdx.y * cols + j] = make_double2(a.mean, a.m2);
+}
+__global__ __launch_bounds__(kRT) void k_zs_cols_sum(const double2* __restrict__ part, int64_t rows,
+                                                     int64_t cols, int64_t chunk, int nch,
+                                                     int ddof, double2* __restrict__ cs,
+                                                     double* flags) {
+  const int64_t j = (int64_t)blockIdx.x * kRT + threadIdx.x;
+  if (j >= cols) return;
+  Mom a{0.0, 0.0, 0.0};
+  for (int c = 0; c < nch; ++c) {
+    const double2 p = part[(int64_t)c * cols + j];
+    const int64_t n = rows - (int64_t)c * chunk;
+    mom_add(a, (double)(n < chunk ? n : chunk), p.x, p.y);
+  }
+  zs_put(cs + j, a.n, a.mean, a.m2, ddof, flags);
 }
 
+// Four columns of one row per thread; blockIdx.y walks the rows.  Skipped
+// where the flags refuse the matrix.
 __global__ __launch_bounds__(kRT) void k_zs_apply_rc(float* __restrict__ M, int64_t rows,
                                                      int64_t cols, int64_t ld,
                                                      const double2* __restrict__ rs,
-                                                     const double2* __restrict__ cs) {
-  const int64_t n = rows * cols;
-  for (int64_t e = (int64_t)blockIdx.x * kRT + threadIdx.x; e < n; e += (int64_t)gridDim.x * kRT) {
-    const int64_t i = e / cols, j = e % cols;
-    float* p = M + i * ld + j;
-    const double x = (double)*p;
+                                                     const double2* __restrict__ cs,
+                                                     const double* __restrict__ flags) {
+  if (flags[0] != 0.0 || flags[1] != 0.0) return;
+  constexpr int U = 4;
+  const double r2 = 1.0 / sqrt(2.0);
+  const int64_t j0 = (int64_t)blockIdx.x * kRT * U + threadIdx.x;
+  double2 c[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (cs && j0 + u * kRT < cols) c[u] = cs[j0 + u * kRT];
+  for (int64_t i = blockIdx.y; i < rows; i += gridDim.y) {
     const double2 r = rs[i];
-    const double zr = (x - r.x) / r.y;
-    if (cs) {
-      const double2 c = cs[j];
-      *p = (float)((zr + (x - c.x) / c.y) / sqrt(2.0));
-    } else {
-      *p = (float)zr;
+    float* row = M + i * ld;
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (j0 + u * kRT < cols) v[u] = row[j0 + u * kRT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (j0 + u * kRT >= cols) continue;
+      const double x = (double)v[u], zr = (x - r.x) * r.y;
+      row[j0 + u * kRT] = cs ? (float)((zr + (x - c[u].x) * c[u].y) * r2) : (float)zr;
     }
   }
 }
@@ -621,36 +782,81 @@ hipError_t launch_col_sqnorms(const float* M, int64_t rows, int64_t cols, int64_
   return hipGetLastError();
 }
 
+// Chunking of the global z-score's passes: the whole matrix as one row where
+// its rows are contiguous; 16-byte accesses where every row starts on 16
+// bytes; chunks of 8192 entries once those fill every block, else of 1024.
+namespace {
+struct ZsPlan {
+  int64_t rows, cols, ld, per_row;
+  bool vec, large;
+};
+ZsPlan zs_plan(const float* M, int64_t rows, int64_t cols, int64_t ld) {
+  ZsPlan p;
+  const bool flat = ld == cols || rows == 1;
+  p.rows = flat ? 1 : rows;
+  p.cols = flat ? rows * cols : cols;
+  p.ld = flat ? p.cols : ld;
+  p.vec = reinterpret_cast<uintptr_t>(M) % 16 == 0 && (flat || ld % 4 == 0);
+  const int64_t big = (int64_t)kRT * 32;
+  p.large = rows * cols >= big * kZsBlocks && p.cols >= big;
+  const int64_t chunk = p.large ? big : (int64_t)kRT * 4;
+  p.per_row = (p.cols + chunk - 1) / chunk;
+  return p;
+}
+}  // namespace
+
 hipError_t launch_zscore_stats(const float* M, int64_t rows, int64_t cols, int64_t ld,
                                double* scratch, hipStream_t s, int ddof) {
-  const int64_t n = rows * cols;
-  k_zs_clear<<<1, kRT, 0, s>>>(scratch);
-  k_zs_sum<<<kZsBlocks, kRT, 0, s>>>(M, rows, cols, ld, scratch, 0);
-  k_zs_finish<<<1, kRT, 0, s>>>(scratch, n, 0, ddof);
-  k_zs_sum<<<kZsBlocks, kRT, 0, s>>>(M, rows, cols, ld, scratch, 1);
-  k_zs_finish<<<1, kRT, 0, s>>>(scratch, n, 1, ddof);
+  const ZsPlan p = zs_plan(M, rows, cols, ld);
+  const int64_t nch = p.rows * p.per_row;
+  const unsigned nb = (unsigned)(nch < kZsBlocks ? nch : kZsBlocks);
+  auto* fn = p.vec ? (p.large ? k_zs_moments<true, 8> : k_zs_moments<true, 1>)
+                   : (p.large ? k_zs_moments<false, 8> : k_zs_moments<false, 1>);
+  fn<<<dim3(nb), kRT, 0, s>>>(M, p.rows, p.cols, p.ld, p.per_row, scratch);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  k_zs_finish<<<1, kRT, 0, s>>>(scratch, (int)nb, ddof);
   return hipGetLastError();
 }
 
+int64_t zs_col_chunks(int64_t rows) {
+  const int64_t n = (rows + 255) / 256;
+  return n < kZsColChunks ? n : kZsColChunks;
+}
+
 hipError_t launch_zscore_rc_stats(const float* M, int64_t rows, int64_t cols, int64_t ld, int ddof,
-                                  double* flags, double2* rs, double2* cs, hipStream_t s) {
+                                  double* flags, double2* rs, double2* cs, double2* cpart,
+                                  hipStream_t s) {
   k_zs_flags_clear<<<1, kRT, 0, s>>>(flags);
   k_zs_rows<<<dim3((unsigned)rows), kRT, 0, s>>>(M, cols, ld, ddof, rs, flags);
-  if (cs)
-    k_zs_cols<<<dim3((unsigned)((cols + kRT - 1) / kRT)), kRT, 0, s>>>(M, rows, cols, ld, ddof, cs,
-                                                                         flags);
+  if (cs) {
+    const int64_t nch = zs_col_chunks(rows), chunk = (rows + nch - 1) / nch;
+    const unsigned gx = (unsigned)((cols + kRT - 1) / kRT);
+    const unsigned gy = (unsigned)((rows + chunk - 1) / chunk);  // no empty chunk
+    k_zs_cols_part<<<dim3(gx, gy), kRT, 0, s>>>(M, rows, cols, ld, chunk, cpart);
+    k_zs_cols_sum<<<dim3(gx), kRT, 0, s>>>(cpart, rows, cols, chunk, (int)gy, ddof, cs, flags);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_zscore_rc_apply(float* M, int64_t rows, int64_t cols, int64_t ld,
-                                  const double2* rs, const double2* cs, hipStream_t s) {
-  k_zs_apply_rc<<<grid_for(rows * cols, 4096), kRT, 0, s>>>(M, rows, cols, ld, rs, cs);
+                                  const double2* rs, const double2* cs, const double* flags,
+                                  hipStream_t s) {
+  const int64_t gx = (cols + kRT * 4 - 1) / (kRT * 4);
+  int64_t gy = (8192 + gx - 1) / gx;
+  if (gy > rows) gy = rows;
+  k_zs_apply_rc<<<dim3((unsigned)gx, (unsigned)gy), kRT, 0, s>>>(M, rows, cols, ld, rs, cs, flags);
   return hipGetLastError();
 }
 
 hipError_t launch_zscore_apply(float* M, int64_t rows, int64_t cols, int64_t ld,
                                const double* scratch, hipStream_t s) {
-  k_zs_apply<<<grid_for(rows * cols, 4096), kRT, 0, s>>>(M, rows, cols, ld, scratch);
+  const ZsPlan p = zs_plan(M, rows, cols, ld);
+  const int64_t nch = p.rows * p.per_row;
+  const unsigned nb = (unsigned)(nch < 4096 ? nch : 4096);
+  auto* fn = p.vec ? (p.large ? k_zs_apply<true, 8> : k_zs_apply<true, 1>)
+                   : (p.large ? k_zs_apply<false, 8> : k_zs_apply<false, 1>);
+  fn<<<dim3(nb), kRT, 0, s>>>(M, p.rows, p.cols, p.ld, p.per_row, scratch);
   return hipGetLastError();
 }
 

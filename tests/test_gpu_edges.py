@@ -54,3 +54,54 @@ def test_mlp_grad_slots(torch, pd, n):
     for got, want in zip(WS.unpack(host(g)), WS.unpack(gw)):
         got, want = np.asarray(got), np.asarray(want)
         assert np.linalg.norm(got - want) <= 1e-2 * max(np.linalg.norm(want), 1e-30)
+
+
+# ------------------------------------------------------------------- z-score --
+# entries of one 1024-entry chunk and either side; a matrix past the size from
+# which chunks hold 8192 entries; both also off 16-byte alignment
+@pytest.mark.parametrize("rows,cols", [(1, 1), (1, 2), (3, 341), (32, 32), (25, 41), (1, 4097),
+                                       (2900, 2900)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_normalize_chunks(torch, pd, rows, cols, off):
+    """Against numpy's moments; one FP32 rounding of an FP64 value."""
+    rng = np.random.default_rng(rows * 7 + cols)
+    M = f32r(rng.normal(3.0, 2.0, size=rows * cols))
+    buf = torch.zeros(rows * cols + off + 3, device="cuda")
+    buf[off:off + M.size] = cuda(torch, M)
+    t = buf[off:off + M.size].view(rows, cols)
+    if M.size == 1:
+        with pytest.raises(pd.PandaError) as e:
+            pd.normalize(t)
+        assert e.value.code == pd.ERR_DEGENERATE
+        return
+    pd.normalize(t)
+    want = ((M - M.mean()) / M.std()).reshape(rows, cols)
+    assert np.abs(host(t) - want).max() <= 2e-7 * max(1.0, np.abs(want).max())
+    assert not buf[:off].any() and not buf[off + M.size:].any()
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 7), (300, 300), (2900, 2900)])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_normalize_refuses_equal_entries(torch, pd, rows, cols, mode):
+    t = torch.full((rows, cols), 0.1, device="cuda")
+    with pytest.raises(pd.PandaError) as e:
+        pd.normalize(t, mode=mode)
+    assert e.value.code == pd.ERR_DEGENERATE
+    assert torch.all(t == torch.tensor(0.1, device="cuda"))
+    t[rows - 1, cols - 1] = float("inf")
+    with pytest.raises(pd.PandaError) as e:
+        pd.normalize(t, mode=mode)
+    assert e.value.code == pd.ERR_NONFINITE
+
+
+# one, two and many row chunks of the column moments, and their remainders
+@pytest.mark.parametrize("rows,cols", [(2, 300), (256, 33), (257, 1025), (513, 700), (20000, 5)])
+def test_normalize_rowcol_chunks(torch, pd, rows, cols):
+    rng = np.random.default_rng(rows + cols)
+    M = f32r(rng.normal(-1.0, 3.0, size=(rows, cols)))
+    t = cuda(torch, M)
+    pd.normalize(t, mode=2)
+    r = (M - M.mean(1, keepdims=True)) / M.std(1, keepdims=True)
+    c = (M - M.mean(0, keepdims=True)) / M.std(0, keepdims=True)
+    want = (r + c) / np.sqrt(2.0)
+    assert np.abs(host(t) - want).max() <= 2e-7 * max(1.0, np.abs(want).max())
