@@ -14,6 +14,7 @@
 // the remainder split stream-K style), described at k_rect_streamk.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 
 #include "panda_internal.h"
@@ -1259,16 +1260,17 @@ __global__ __launch_bounds__(kFixThreads) void k_rect_fixup(int64_t nMT, int64_t
     float s[GRP];
 #pragma unroll
     for (int q = 0; q < GRP; ++q) s[q] = part[t * E + threadIdx.x + (q0 + q) * kFixThreads];
-    for (int64_t c = 1; c < S; c += 2) {
-      float v[2][GRP];
+    constexpr int CH = 2;
+    for (int64_t c = 1; c < S; c += CH) {
+      float v[CH][GRP];
 #pragma unroll
-      for (int k = 0; k < 2; ++k)
+      for (int k = 0; k < CH; ++k)
         if (c + k < S)
 #pragma unroll
           for (int q = 0; q < GRP; ++q)
             v[k][q] = part[((c + k) * T + t) * E + threadIdx.x + (q0 + q) * kFixThreads];
 #pragma unroll
-      for (int k = 0; k < 2; ++k)
+      for (int k = 0; k < CH; ++k)
         if (c + k < S)
 #pragma unroll
           for (int q = 0; q < GRP; ++q) s[q] += v[k][q];
@@ -1299,16 +1301,22 @@ __global__ __launch_bounds__(kFixThreads) void k_rect_fixup(int64_t nMT, int64_t
   epi.end_tile(qb * nTiles + tile, red);
 }
 
-// Blocks of kernel `fn` (nt threads each) the whole GPU runs at once.
-inline int64_t resident_blocks(const void* fn, int nt = kThreads) {
-  int dev = 0, cus = 0, occ = 0;
+inline int64_t device_cus() {
+  int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus <= 0)
     cus = 256;
+  return cus;
+}
+
+// Blocks of kernel `fn` (nt threads each) the whole GPU runs at once.
+inline int64_t resident_blocks(const void* fn, int nt = kThreads) {
+  const int64_t cus = device_cus();
+  int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, nt, 0) != hipSuccess || occ <= 0)
     occ = 1;
-  return (int64_t)cus * occ;
+  return cus * occ;
 }
 
 // Launch of a rectangular product over an Mp x Np output with K = Kp; part
@@ -1319,30 +1327,40 @@ hipError_t launch_rect(const typename G::Ops& ops, int64_t Mp, int64_t Np, int64
   // computed once per kernel (a function-local static: thread-safe initialisation)
   static const int64_t resident =
       resident_blocks(reinterpret_cast<const void*>(&k_rect_streamk<G, Epi>), G::NT);
+  static const int64_t cus = device_cus();
   const int64_t nMT = Mp / G::BM, nNT = Np / G::BN;
   const int64_t nTiles = nMT * nNT, U = Kp / G::BK;
-  int64_t nb = resident;
-  if (nb > nTiles) nb = nTiles;
-  const int64_t T = nTiles - (nTiles / nb) * nb;
   // K-chunks per tail tile: the smallest S with the least cost, counted in
   // K-steps: the largest block load (with start-up per item) plus the fix-up,
   // which reads S partials per entry; the partials must fit the scratch
-  // (2 * kMaxStreamKBlocks tiles of 64 x 128)
+  // (2 * kMaxStreamKBlocks tiles of 64 x 128).
   const int64_t cap = 2 * kMaxStreamKBlocks * 64 * 128 / (G::BM * G::BN);
   constexpr int64_t kItemCost = 8;
-  int64_t S = 1, best = T ? ((T + nb - 1) / nb) * (U + kItemCost) : 0;
+  // A product of fewer tiles than CUs is all tail: with S = 1 a block per
+  // tile would leave the other CUs idle for the whole of K.  Blocks of one CU
+  // share its matrix cores (n of them run about 0.6 n times as long as one
+  // alone), and cutting must save more than the fix-up's launch (about ten
+  // K-steps).  A + W at 200 x 4000 split-BF16 (32 tiles): 151 -> 48 us; a
+  // product of 440 tiles gains nothing from it (0.97x).
+  const bool starved = nTiles < cus;
+  const int64_t T = starved ? nTiles : nTiles % std::min(resident, nTiles);
+  int64_t S = 1, best = T ? ((T + resident - 1) / resident) * (U + kItemCost) : 0;
   for (int64_t c = 2; T && c <= 64 && c <= U && T * c <= cap; ++c) {
-    const int64_t load = ((T * c + nb - 1) / nb) * ((U + c - 1) / c + kItemCost) + c;
+    const int64_t steps = (U + c - 1) / c + kItemCost, per_cu = (T * c + cus - 1) / cus;
+    const int64_t load = starved ? (per_cu > 1 ? 6 * per_cu * steps / 10 : steps) + c + 10
+                                 : ((T * c + resident - 1) / resident) * steps + c;
     if (load < best) {
       best = load;
       S = c;
     }
   }
+  // whole rounds of `nb` tiles, then the items of the tail (see the kernel)
+  const int64_t nb = starved ? std::min(T * S, resident) : std::min(resident, nTiles);
   k_rect_streamk<G, Epi><<<dim3((unsigned)nb), dim3(G::NT), 0, s>>>(ops, nMT, nTiles, U, S, epi,
                                                                      part, gate);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (T == 0 || S == 1) return hipSuccess;
+  if (T == 0 || S == 1) return hipSuccess;  // (starved with S = 1: one whole round)
   k_rect_fixup<G, Epi><<<dim3((unsigned)(T * kFixParts<G>)), dim3(kFixThreads), 0, s>>>(
       nMT, nTiles, nb, S, part, epi, gate);
   return hipGetLastError();

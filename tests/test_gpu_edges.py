@@ -105,3 +105,21 @@ def test_normalize_rowcol_chunks(torch, pd, rows, cols):
     c = (M - M.mean(0, keepdims=True)) / M.std(0, keepdims=True)
     want = (r + c) / np.sqrt(2.0)
     assert np.abs(host(t) - want).max() <= 2e-7 * max(1.0, np.abs(want).max())
+
+
+# ------------------------------------------------- similarity, K split by tiles --
+# one tile and one K-step; one tile with a long K; tiles below, at and above
+# the CU count; K not a multiple of anything
+@pytest.mark.parametrize("M,K,N", [(1, 16, 1), (64, 4096, 128), (65, 4097, 129), (200, 3000, 2000),
+                                   (512, 1001, 4096), (513, 999, 4097)])
+def test_tanimoto_split_k(torch, pd, M, K, N):
+    """|dT| <= 2 K u sum_k |x_k y_k| / sqrt(den) + 4 u |T| (FP32 accumulation
+    in any order)."""
+    X = f32r(I.random_dense(M + K, (M, K)))
+    Y = f32r(I.random_dense(N + K, (K, N), -2.0, 2.0))
+    got = host(pd.tanimoto(cuda(torch, X), cuda(torch, Y)))
+    dot = X @ Y
+    den = (X ** 2).sum(1)[:, None] + (Y ** 2).sum(0)[None, :] - np.abs(dot)
+    want = dot / np.sqrt(den)
+    bound = 2 * K * U * (np.abs(X) @ np.abs(Y)) / np.sqrt(den) + 4 * U * np.abs(want) + 1e-30
+    assert np.all(np.abs(got - want) <= bound)
