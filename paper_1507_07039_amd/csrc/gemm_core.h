@@ -1340,7 +1340,7 @@ hipError_t launch_rect(const typename G::Ops& ops, int64_t Mp, int64_t Np, int64
   // tile would leave the other CUs idle for the whole of K.  Blocks of one CU
   // share its matrix cores (n of them run about 0.6 n times as long as one
   // alone), and cutting must save more than the fix-up's launch (about ten
-  // K-steps).  A + W at 200 x 4000 split-BF16 (32 tiles): 151 -> 48 us; a
+  // K-steps).  A + W at 200 x 4000 split-BF16 (32 tiles): 151 -> 33 + 13 us; a
   // product of 440 tiles gains nothing from it (0.97x).
   const bool starved = nTiles < cus;
   const int64_t T = starved ? nTiles : nTiles % std::min(resident, nTiles);
