@@ -62,7 +62,12 @@ typedef enum {
 
 /* Arithmetic of the similarity products (norms, denominators, h and the
  * diagonal rule are FP64 in both forms; the state W, P, C is FP32):
- *   PANDA_PREC_FP32    FP32 matrix-core products, FP32 accumulation.
+ *   PANDA_PREC_FP32    products of the whole FP32 operands, FP32 accumulation.
+ *                      A single network forms them on bf16 matrix cores from
+ *                      three bf16 terms per operand that add up to it exactly
+ *                      (six products; the ones left out are below the
+ *                      rounding of the accumulation); a batch on FP32 matrix
+ *                      cores.
  *   PANDA_PREC_BF16X3  every operand split as x = hi + lo (bf16, round to
  *                      nearest even) and each product formed as
  *                      hi*hi + hi*lo + lo*hi on bf16 matrix cores with FP32

@@ -213,12 +213,10 @@ panda_status upload_insts(panda_batch* b) {
     d.csq = c.csq;
     d.corder = c.corder;
     d.st = c.st;
-    d.Wh = c.Wh;
-    d.Wl = c.Wl;
-    d.Wth = c.Wth;
-    d.Wtl = c.Wtl;
-    d.Ph = c.Ph;
-    d.Pl = c.Pl;
+    d.Wr = c.Wr;
+    d.Wt = c.Wt;
+    d.Pp = c.Pp;
+    d.np = c.np;
     d.nh = (c.Nep / bm) * (c.Nap / bn);
     d.chunk = chunk;
     d.splits = (c.Nap + chunk - 1) / chunk;

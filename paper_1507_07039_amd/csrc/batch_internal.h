@@ -29,9 +29,10 @@ struct BInst {
   double* csq;
   const uint32_t* corder;
   DevState* st;
-  // split-BF16 batches: operand planes of W (row-major, and gene-major as
-  // W^T) and of P's off-diagonal part; null in FP32 batches
-  bf16_t *Wh, *Wl, *Wth, *Wtl, *Ph, *Pl;
+  // np operand planes of W (row-major, and gene-major as W^T) and of P's
+  // off-diagonal part; np = 0: none
+  Planes Wr, Wt, Pp;
+  int32_t np;
   int64_t nh;      // h partials written by the chosen A + W tiling
   int64_t splits;  // K splits of the W W^T partials for the chosen chunk
   int64_t chunk;   // K columns per split

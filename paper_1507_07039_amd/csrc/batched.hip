@@ -69,7 +69,7 @@ struct PhResp {
     const int64_t m0 = (local % nMT) * G::BM, n0 = (local / nMT) * G::BN;
     G g;
     if constexpr (B3)
-      g.run(OpsB3{d.Ph, d.Pl, d.Nep, d.Wth, d.Wtl, d.Nep}, m0, n0, 0, d.Nep, smem);
+      g.run(OpsB3{d.Pp, d.Wt}, m0, n0, 0, d.Nep, smem);
     else
       g.run(OpsF32{d.P, d.Nep, W, d.Nap}, m0, n0, 0, d.Nep, smem);
     EpiStoreT epi{d.R, d.Nap, d.Ne, d.Na, d.nP, d.nWc, d.dP, W, d.Nap};
@@ -96,7 +96,7 @@ struct PhAvail {
     const int64_t m0 = (local % nMT) * G::BM, n0 = (local / nMT) * G::BN;
     G g;
     if constexpr (B3)
-      g.run(OpsB3F{d.Wh, d.Wl, d.Nap, d.C, d.Nap, d.Nep}, m0, n0, 0, d.Nap, smem);
+      g.run(OpsB3F{d.Wr, d.C, d.Nap, d.Nep}, m0, n0, 0, d.Nap, smem);
     else
       g.run(OpsF32{Wold, d.Nap, d.C, d.Nap}, m0, n0, 0, d.Nap, smem);
     EpiWUpdate epi{Wold, d.R,   d.W[ws ^ 1], d.Nap, d.Ne,       d.Na,    d.nWr,
@@ -126,7 +126,7 @@ struct PhCoop {
     if (ke > d.Nap) ke = d.Nap;
     G g;
     if constexpr (B3)
-      g.run(OpsB3{d.Wh, d.Wl, d.Nap, d.Wh, d.Wl, d.Nap}, m0, n0, kb, ke, smem);
+      g.run(OpsB3{d.Wr, d.Wr}, m0, n0, kb, ke, smem);
     else
       g.run(OpsF32{W, d.Nap, W, d.Nap}, m0, n0, kb, ke, smem);
     float* ps = d.ppart + sp * d.Nep * d.Nep;
@@ -151,7 +151,7 @@ struct PhCoreg {
     const double nval = coreg_norm_load(d.nWc, I, J, d.Na);
     G g;
     if constexpr (B3)
-      g.run(OpsB3{d.Wth, d.Wtl, d.Nep, d.Wth, d.Wtl, d.Nep}, I * kCB, J * kCB, 0, d.Nep, smem);
+      g.run(OpsB3{d.Wt, d.Wt}, I * kCB, J * kCB, 0, d.Nep, smem);
     else
       g.run(OpsF32{W, d.Nap, W, d.Nap}, I * kCB, J * kCB, 0, d.Nep, smem);
     coreg_epilogue<SIGT, false>(g, smem, I, J, d.C, d.Nap, d.Na, nval, alpha, d.cstat, d.csq, d.Nap);
@@ -251,10 +251,9 @@ __global__ __launch_bounds__(kUT) void k_batch_planes(const BInst* __restrict__ 
     float v = 0.0f;
     if (r < d.Ne && c < d.Na) {
       v = W[r * d.Nap + c];
-      bf16_t h, l;
-      upd::split_bf16(v, h, l);
-      d.Wh[r * d.Nap + c] = h;
-      d.Wl[r * d.Nap + c] = l;
+      bf16_t o[3];
+      upd::split_planes<2>(v, o);
+      for (int p = 0; p < 2; ++p) d.Wr.p[p * d.Wr.stride + plane_index<32>(d.Wr.rows, r, c)] = o[p];
     }
     tile[rr][tx] = v;
   }
@@ -262,10 +261,9 @@ __global__ __launch_bounds__(kUT) void k_batch_planes(const BInst* __restrict__ 
   for (int cc = ty; cc < 64; cc += kUT / 64) {
     const int64_t c = c0 + cc, r = r0 + tx;
     if (r < d.Ne && c < d.Na) {
-      bf16_t h, l;
-      upd::split_bf16(tile[tx][cc], h, l);
-      d.Wth[c * d.Nep + r] = h;
-      d.Wtl[c * d.Nep + r] = l;
+      bf16_t o[3];
+      upd::split_planes<2>(tile[tx][cc], o);
+      for (int p = 0; p < 2; ++p) d.Wt.p[p * d.Wt.stride + plane_index<32>(d.Wt.rows, c, r)] = o[p];
     }
   }
 }
@@ -278,7 +276,7 @@ __global__ __launch_bounds__(kUT) void k_batch_coop_finalize(const BInst* __rest
   if (d.st->run_pc == 0) return;
   const int64_t e = ((int64_t)blockIdx.x - fl.seg_first[seg]) * kUT + threadIdx.x;
   upd::coop_finalize_entry(e, d.ppart, (int)d.splits, d.Nep, d.nWr, d.P, d.Nep, d.Ne, alpha,
-                           sigma_from_T ? d.Tside : nullptr, d.Ph, d.Pl);
+                           sigma_from_T ? d.Tside : nullptr, d.Pp, d.np);
 }
 
 // Eq. 6: blocks [0, Ne) are rows of P, the rest cover the rows of C, one

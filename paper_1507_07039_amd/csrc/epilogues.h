@@ -77,8 +77,11 @@ struct EpiStoreT {
 // A = T(W, C) (Eq. 4) folded into the W update of Eq. 2, with the tile's
 // share of the h sum of Eq. 7.  The new W goes to a second buffer because
 // the old one is still an operand of other blocks.  C's diagonal term
-// W_ij * C_jj is added to the product from the FP64 vector cd.
-struct EpiWUpdate {
+// W_ij * C_jj is added to the product from the FP64 vector cd.  PL: the old W
+// is given as its three planes (and Wnew may be R: an entry's operands are
+// read by the thread that stores it).
+template <bool PL>
+struct EpiWUpdateT {
   const float* Wold;
   const float* R;
   float* Wnew;
@@ -90,12 +93,18 @@ struct EpiWUpdate {
   int32_t h_undamped;
   double* hpart;
   double hsum;
+  Planes wp;
+  __device__ __forceinline__ float w_old(int64_t r, int64_t c) const {
+    if constexpr (PL)
+      return join_planes(wp, r, c);
+    else
+      return Wold[r * ld + c];
+  }
   // the entry's old W and R, fetched ahead by epi_tile where it can
   using Pre = float2;
   __device__ __forceinline__ Pre fetch(int64_t r, int64_t c) const {
     if (r < Ne && c < Na) {
-      const int64_t o = r * ld + c;
-      return make_float2(Wold[o], R[o]);
+      return make_float2(w_old(r, c), R[r * ld + c]);
     }
     return make_float2(0.0f, 0.0f);
   }
@@ -126,7 +135,7 @@ struct EpiWUpdate {
     for (int k = 0; k < NE; ++k) {
       const int64_t rr = r[k] < Ne ? r[k] : Ne - 1, cc = c[k] < Na ? c[k] : Na - 1;
       const int64_t o = rr * ld + cc;
-      const double w = Wold[o];
+      const double w = w_old(rr, cc);
       double dot = (double)acc[k];
       dot += w * cd[cc];
       const double a = tanimoto(dot, nx[rr], ny[cc]);
@@ -148,32 +157,59 @@ struct EpiWUpdate {
   }
 };
 
-// Tile configurations.  Rectangular products: 64 x 128 tiles (N_e = 700 pads
-// to 704 = 11 x 64), 4 waves side by side.  Symmetric C product: 128 x 128.
+using EpiWUpdate = EpiWUpdateT<false>;
+
+// Tile configurations.  FP32 matrix cores (stand-alone similarity, batches,
+// the co-expression prior): rectangular products on 64 x 128 tiles, 4 waves
+// side by side, symmetric ones on 128 x 128.
 using RectF32 = BlockGemm<64, 128, 1, 4, true, false, 16>;
-using RectF32P = BlockGemm<64, 128, 1, 4, true, false, 16, true>;  // A product, packed C
-using RectB3 = BlockGemmB3<64, 128, 1, 4>;  // R: K = N_e is short, register staging wins
+using RectB3 = BlockGemmB3<64, 128, 1, 4>;  // batched R: K = N_e is short, register staging wins
 static_assert(RectF32::BM == RectB3::BM && RectF32::BN == RectB3::BN, "one tile grid");
-// The split-BF16 A product moves its operands by direct loads into LDS, and
-// the memory side bounds it: 256 x 128 tiles move half the bytes per MFMA of
-// 64 x 128 ones.  Eight waves of 64 x 64, two per SIMD, so that one wave's
-// waits (loads landing, barriers) are covered by the other's MFMAs: 6-8 %
-// faster than four waves of 64 x 128 at T=700, G=18000 (same products in the
-// same order per entry).  N_e is padded to the tile (704 -> 768) by clamped
-// reads; waves whose rows all lie in the padding skip their MFMAs.  (A block
-// spanning all of N_e with a 64-gene strip of C reads C once but re-reads
-// W's planes per block: 2.6 ms against 1.46 ms.)
-using RectB3D = BlockGemmB3P<256, 128, 4, 2>;
-using RectB3DP = BlockGemmB3P<256, 128, 4, 2, true, 3, 32, true>;  // the same on packed C
 using SymF32 = BlockGemm<128, 128, 2, 2, false, false, 16>;
-using SymB3 = BlockGemmB3P<128, 128, 2, 2, false, 2>;  // direct-to-LDS, two stages (two blocks per CU)
 using CoopF32 = BlockGemm<64, 64, 2, 2, true, true, 32>;
 using CoopB3 = BlockGemmB3<64, 64, 2, 2>;
-// The single-network W W^T partials: each block's K chunk is ~70 K-tiles, long
-// enough for the direct-to-LDS pipeline with three stages (two K-tiles in
-// flight while one is multiplied); same products in the same order.
-using CoopB3P = BlockGemmB3P<64, 64, 2, 2, false, 3>;
 static_assert(CoopF32::BK == CoopB3::BK, "one K split");
+// The products of a single network on bf16 planes, NP = 2 (split-BF16 form)
+// or 3 (FP32 form).  The FP32 form runs on them too because six bf16 products
+// of exact planes take 6/16 of the FP32 matrix cores' time for the same
+// result: at T=700, G=18000 A + W went from 4.17 ms on v_mfma_f32_32x32x2f32
+// (109 TFLOP/s, 70 % of those cores' peak) to 2.51 (1090 TFLOP/s of bf16, 89 %
+// of what a large library product reaches on the card, both at its
+// power-limited clock), C update + R from 2.30 to 1.22, with a smaller error
+// against 64 bits (kFolds).
+//   Rect: the A product.  The memory side bounds it, so 256 x 128 tiles (half
+//   the bytes per MFMA of 64 x 128), eight waves of 64 x 64, two per SIMD, so
+//   that one wave's waits (loads landing, barriers) are covered by the
+//   other's MFMAs: 6-8 % faster than four waves of 64 x 128 at T=700, G=18000.
+//   N_e is padded to the tile (704 -> 768) by clamped reads; waves whose rows
+//   all lie in the padding skip their MFMAs.  (A block spanning all of N_e with
+//   a 64-gene strip of C reads C once but re-reads W's planes per block: 2.6 ms
+//   against 1.46 ms.)  Three planes take K-tiles of 16: the registers of a
+//   32-deep one (fragments and the next tile's, three planes each) do not fit
+//   two waves per SIMD, and its 24 MFMAs per wave are those of a 32-deep tile
+//   of two planes.
+//   RectP: the same on packed C.
+//   Sym: the C update and R, two blocks per CU; two stages of 32 for two
+//   planes, three of 16 for three (72 KB).
+//   Coop: the W W^T partials; a block's K chunk is long enough for the
+//   direct-to-LDS pipeline with three stages.
+template <int NP>
+struct Tiles;
+template <>
+struct Tiles<2> {
+  using Rect = BlockGemmB3P<256, 128, 4, 2>;
+  using RectP = BlockGemmB3P<256, 128, 4, 2, true, 3, 32, true>;
+  using Sym = BlockGemmB3P<128, 128, 2, 2, false, 2>;
+  using Coop = BlockGemmB3P<64, 64, 2, 2, false, 3>;
+};
+template <>
+struct Tiles<3> {
+  using Rect = BlockGemmB3P<256, 128, 4, 2, true, 3, 16, false, 3>;
+  using RectP = BlockGemmB3P<256, 128, 4, 2, true, 3, 16, true, 3>;
+  using Sym = BlockGemmB3P<128, 128, 2, 2, false, 3, 16, false, 3>;
+  using Coop = BlockGemmB3P<64, 64, 2, 2, false, 3, 32, false, 3>;
+};
+using SymB3 = Tiles<2>::Sym;
 
 // ------------------------------------------------------------------------
 // C update of Eq. 5 on the upper tiles of T(W^T, W).  Within a tile only the

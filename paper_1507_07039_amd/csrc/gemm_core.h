@@ -78,11 +78,6 @@ __device__ __forceinline__ bf16_t to_bf16(float x) {
 __device__ __forceinline__ float from_bf16(bf16_t b) {
   return (float)__builtin_bit_cast(__bf16, b);
 }
-// x = hi + lo + O(2^-17 |x|): hi = bf16(x), lo = bf16(x - hi).
-__device__ __forceinline__ void split_bf16(float x, bf16_t& hi, bf16_t& lo) {
-  hi = to_bf16(x);
-  lo = to_bf16(x - from_bf16(hi));
-}
 
 // ======================================================== FP32 main loop ==
 // One operand's MN x BK tile: global -> registers -> LDS.  KC: the operand
@@ -335,35 +330,32 @@ struct BlockGemm {
 };
 
 // ================================================== split-BF16 main loop ==
-// Both operands are stored K-contiguous as two bf16 planes (hi, lo) with
-// x = hi + lo: X_hi/X_lo[m][k] and Yt_hi/Yt_lo[n][k] (Yt = Y transposed).
-// Each product is hi*hi + hi*lo + lo*hi on v_mfma_f32_32x32x16_bf16 with an
-// FP32 accumulator; the dropped lo*lo term and the rounding of lo bound the
-// relative error of each product term by about 2^-16.
+// Both operands are stored as bf16 planes (see Planes; X[m][k] and Yt[n][k], Yt
+// = Y transposed), multiplied on v_mfma_f32_32x32x16_bf16 with an FP32
+// accumulator.
+//   Two planes (x = hi + lo): hi*hi + hi*lo + lo*hi; the dropped lo*lo term
+//   and the rounding of lo bound the relative error of each product term by
+//   about 2^-16.
+//   Three planes (x = hi + mid + lo exactly, 8 bits each, see split_pair3):
+//   the six products down to 2^-16 of the leading one; the dropped ones are
+//   2^-23 of a term at most (2^-25 on average, of either sign), below the
+//   rounding of an FP32 accumulation.
 struct OpsB3 {
-  const bf16_t* Xh;
-  const bf16_t* Xl;
-  int64_t ldx;
-  const bf16_t* Yh;
-  const bf16_t* Yl;
-  int64_t ldy;
+  Planes X;
+  Planes Y;
   int64_t mrows = INT64_MAX;  // rows of X that exist (loaders may clamp to them)
 };
 // The same with Y an FP32 symmetric matrix (Yt = Y, rows read K-contiguous)
-// that is split into hi/lo while it is staged.
+// that is split into its planes as its fragments are read.
 struct OpsB3F {
-  const bf16_t* Xh;
-  const bf16_t* Xl;
-  int64_t ldx;
+  Planes X;
   const float* Y;
   int64_t ldy;
   int64_t mrows = INT64_MAX;  // rows of X that exist (loaders may clamp to them)
 };
 // ... with Y stored packed (packed_tile).
 struct OpsB3FP {
-  const bf16_t* Xh;
-  const bf16_t* Xl;
-  int64_t ldx;
+  Planes X;
   const float* Yp;
   int64_t mrows = INT64_MAX;
 };
@@ -388,15 +380,16 @@ struct TileLoadB3 {
   __device__ __forceinline__ static int swz(int row, int chunk) {
     return row * BK + ((chunk ^ ((row / RG) & (CPR - 1))) << 3);
   }
-  __device__ __forceinline__ void load(const bf16_t* __restrict__ H, const bf16_t* __restrict__ L,
-                                       int64_t ld, int64_t mn0, int64_t k0, int t) {
+  __device__ __forceinline__ void load(const Planes& P, int64_t mn0, int64_t k0, int t) {
+    static_assert(BK == plane_kt(2), "one K-tile of the planes");
     if (!ALL && t >= MN * CPR) return;
     const int c = (t % CPR) * 8;
+    const bf16_t* H = P.p + plane_index<BK>(P.rows, mn0, k0) + c;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int r = t / CPR + i * RP;
-      h[i] = *reinterpret_cast<const u4*>(H + (mn0 + r) * ld + k0 + c);
-      l[i] = *reinterpret_cast<const u4*>(L + (mn0 + r) * ld + k0 + c);
+      h[i] = *reinterpret_cast<const u4*>(H + r * BK);
+      l[i] = *reinterpret_cast<const u4*>(H + P.stride + r * BK);
     }
   }
   __device__ __forceinline__ void store(bf16_t* lds, int t) const {
@@ -435,7 +428,7 @@ struct BlockGemmB3 {
 
   __device__ __forceinline__ static void load_y(LY& ly, const Ops& o, int64_t n0, int64_t k0,
                                                 int t) {
-    ly.load(o.Yh, o.Yl, o.ldy, n0, k0, t);
+    ly.load(o.Y, n0, k0, t);
   }
 
   __device__ __forceinline__ void run(const Ops& o, int64_t m0, int64_t n0, int64_t kbeg,
@@ -457,7 +450,7 @@ struct BlockGemmB3 {
     LY ly;
     const int64_t nk = (kend - kbeg) / BK;
     if (nk > 0) {
-      lx.load(o.Xh, o.Xl, o.ldx, m0, kbeg, t);
+      lx.load(o.X, m0, kbeg, t);
       load_y(ly, o, n0, kbeg, t);
       lx.store(xs, t);
       ly.store(ys, t);
@@ -470,7 +463,7 @@ struct BlockGemmB3 {
       const int cur = (int)(kt & 1);
       const bool more = kt + 1 < nk;
       if (more) {
-        lx.load(o.Xh, o.Xl, o.ldx, m0, kbeg + (kt + 1) * BK, t);
+        lx.load(o.X, m0, kbeg + (kt + 1) * BK, t);
         load_y(ly, o, n0, kbeg + (kt + 1) * BK, t);
       }
       const bf16_t* xc = xs + cur * XS;
@@ -592,6 +585,25 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsign
   l = __builtin_bit_cast(unsigned, __builtin_convertvector((fl2){a - ha, b - hb}, bh2));
 }
 
+// Two floats as three bf16 each, x = hi + mid + lo exactly: hi = the upper 16
+// bits of x (truncated, so that no finite x overflows), mid = RNE(x - hi), lo
+// = x - hi - mid, which has at most 8 significant bits (both differences are
+// exact).
+__device__ __forceinline__ void split_pair3(float a, float b, unsigned (&o)[3]) {
+  typedef float fl2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bh2 __attribute__((ext_vector_type(2)));
+  const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
+  o[0] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);  // upper halves of b : a
+  const float ra = a - __builtin_bit_cast(float, ua & 0xffff0000u);
+  const float rb = b - __builtin_bit_cast(float, ub & 0xffff0000u);
+  const unsigned m = __builtin_bit_cast(unsigned, __builtin_convertvector((fl2){ra, rb}, bh2));
+  o[1] = m;
+  const float la = ra - __builtin_bit_cast(float, m << 16);
+  const float lb = rb - __builtin_bit_cast(float, m & 0xffff0000u);
+  o[2] = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, lb), __builtin_bit_cast(unsigned, la),
+                               0x07060302u);
+}
+
 // YF32: Y is the FP32 symmetric matrix split as its fragments are read;
 // otherwise Y is given as bf16 hi/lo planes like X (no split arithmetic).
 // The STAGES stage buffers are carved from the caller's shared memory.
@@ -603,12 +615,25 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsign
 // 4-byte read per k.  Both rows of a fragment read's two half-waves differ
 // by 8 in k, and their 16-byte chunks are XOR-swizzled by that bit, so the
 // two half-waves use different banks.
+// NP: planes of each operand (2 or 3), and the products of a K-step with it.
 template <int BM_, int BN_, int WM, int WN, bool YF32 = true, int STAGES = 3, int BK_ = 32,
-          bool YP = false>
+          bool YP = false, int NP = 2>
 struct BlockGemmB3P {
   using Ops = typename std::conditional<
       YP, OpsB3FP, typename std::conditional<YF32, OpsB3F, OpsB3>::type>::type;
-  static_assert(!YP || (YF32 && BN_ == (int)kPT && kPT % BK_ == 0 && BK_ == 32),
+  static_assert(NP == 2 || NP == 3, "two or three planes");
+  static constexpr int NPROD = NP == 2 ? 3 : 6;  // products per K-step and accumulator
+  // Three planes over a long K: after every kFoldTiles K-tiles the accumulator
+  // is added to a running sum and cleared (run<true>).  The matrix cores align
+  // the 16 products of an MFMA to the accumulator and drop what lies below it,
+  // which takes a little off every small product (hi * lo, mid * mid) once the
+  // accumulator is large: over all of K = 18000 in one accumulator the sums of
+  // a late iteration, whose terms are coherent, came out 6e-6 low; folded
+  // every 1008 the error against 64 bits (W after five iterations at T=700,
+  // G=18000: 1.1e-7) is below that of v_mfma_f32_32x32x2f32 (5.8e-7).
+  static constexpr bool kFolds = NP == 3;
+  static constexpr int kFoldTiles = (int)(kFoldK / BK_) / 3 * 3;
+  static_assert(!YP || (YF32 && BN_ == (int)kPT && kPT % BK_ == 0 && (BK_ == 32 || BK_ == 16)),
                 "packed Y: FP32 rows of one packed column block, K-tiles inside a block");
   // one block per CU (its stages fill most of the LDS): the epilogue has
   // the registers to fetch its per-entry operands 16 at a time (see epi_tile)
@@ -632,37 +657,38 @@ struct BlockGemmB3P {
   using PY = TileLoadB3<BN, NT, BK>;
   static constexpr int CPR = BK / 8;  // 16-byte chunks per bf16 row
   static constexpr int XQ = BM * CPR; // chunks per X plane
-  static constexpr int YQ = YF32 ? BN * (BK / 4) : 2 * BN * CPR;  // chunks of the Y tile
-  static constexpr int STAGE_BYTES = (2 * XQ + YQ) * 16;
+  static constexpr int YQ = YF32 ? BN * (BK / 4) : NP * BN * CPR;  // chunks of the Y tile
+  static constexpr int STAGE_BYTES = (NP * XQ + YQ) * 16;
   static constexpr int MAIN_BYTES = STAGES * STAGE_BYTES;
-  static constexpr int XI = 2 * XQ / 64, YI = YQ / 64;  // wave-instructions per stage
-  static_assert((2 * XQ) % 64 == 0 && YQ % 64 == 0 && (XI + YI) % WAVES == 0, "load split");
+  static constexpr int XI = NP * XQ / 64, YI = YQ / 64;  // wave-instructions per stage
+  static_assert((NP * XQ) % 64 == 0 && YQ % 64 == 0 && (XI + YI) % WAVES == 0, "load split");
   static constexpr int IPW = (XI + YI) / WAVES;  // loads per wave and stage
-  static constexpr int PER = 2 * TM + 2 * TN;   // 16-byte fragment reads per k-step
+  static constexpr int YR = YF32 ? 2 : NP;       // 16-byte reads of a Y fragment
+  static constexpr int PER = NP * TM + YR * TN;  // 16-byte fragment reads per k-step
   static constexpr int NR = KS * PER;
   // This wave's loads of one stage: wave-instruction q * WAVES + w of the
   // stage, so which operand (and plane) a load q reads is fixed at compile
   // time.
-  static constexpr int XPW = XI / WAVES;  // X loads per wave (both planes)
-  static constexpr int XPP = XPW / 2;     // ... per plane
-  static constexpr int YPP = YI / WAVES / 2;  // Y loads per wave and plane (bf16 Y)
-  static_assert(XI % (2 * WAVES) == 0, "X planes split evenly over the waves");
-  static_assert(YF32 || YI % (2 * WAVES) == 0, "Y planes split evenly over the waves");
+  static constexpr int XPW = XI / WAVES;  // X loads per wave (all planes)
+  static constexpr int XPP = XPW / NP;    // ... per plane
+  static constexpr int YPP = YI / WAVES / NP;  // Y loads per wave and plane (bf16 Y)
+  static_assert(XI % (NP * WAVES) == 0, "X planes split evenly over the waves");
+  static_assert(YF32 || YI % (NP * WAVES) == 0, "Y planes split evenly over the waves");
 
   floatx16 acc[TM][TN];
   int lane, wm, wn;
 
   struct Frag {  // operands of one K-tile
-    bf16x8 xh[KS][TM], xl[KS][TM], yh[KS][TN], yl[KS][TN];
+    bf16x8 x[NP][KS][TM], y[NP][KS][TN];
   };
   struct Raw {
     u4 r[NR];
   };
+  using Split = unsigned[NP][KS][TN][4];  // split pairs of the FP32 Y fragments
   struct Dma {
-    const char* xh;  // uniform bases at K-tile 0 of the range
-    const char* xl;
-    const char* yh;  // Y (FP32) or its hi plane
-    const char* yl;
+    const char* x[NP];  // uniform bases at K-tile 0 of the range
+    const char* y[NP];  // Y (FP32, y[0]) or its planes
+    size_t xstep, ystep;  // bytes from one K-tile to the next
     unsigned voff[IPW];  // per lane
     unsigned wofs;       // this wave's LDS offset within a stage
     // packed Y: its base, the column block, the range start, and the per-lane
@@ -676,7 +702,12 @@ struct BlockGemmB3P {
     if constexpr (!YP) return false;
     return d.jb > (d.kbeg + (int64_t)kt * BK) / kPT;
   }
-  static constexpr int YSTEP = YF32 ? BK * 4 : BK * 2;  // bytes per K-tile along a Y row
+  static constexpr int KT = plane_kt(NP);  // K depth of the planes' tiles
+  static_assert(BK % KT == 0 && (BK == 16 || BK == 32), "whole plane tiles per K-tile");
+  // bytes from a plane's (row r0, K-tile start) to row r, 16-byte chunk c of it
+  __device__ __forceinline__ static unsigned plane_off(int64_t rows, int64_t r, int c) {
+    return (unsigned)(((c / (KT / 8)) * rows * KT + r * KT + (c % (KT / 8)) * 8) * 2);
+  }
 
   __device__ __forceinline__ static unsigned lds_addr(const void* p) {
     return (unsigned)(size_t)(const __attribute__((address_space(3))) char*)p;
@@ -684,17 +715,25 @@ struct BlockGemmB3P {
 
   __device__ __forceinline__ void setup(const Ops& o, int64_t m0, int64_t n0, int64_t kbeg, int w,
                                         Dma& d) const {
-    d.xh = reinterpret_cast<const char*>(o.Xh + m0 * o.ldx + kbeg);
-    d.xl = reinterpret_cast<const char*>(o.Xl + m0 * o.ldx + kbeg);
-    if constexpr (YP) {
-      d.yh = d.yl = nullptr;  // per K-tile, from the packed tile (dma_at)
-    } else if constexpr (YF32) {
-      d.yh = reinterpret_cast<const char*>(o.Y + n0 * o.ldy + kbeg);
-      d.yl = d.yh;
-    } else {
-      d.yh = reinterpret_cast<const char*>(o.Yh + n0 * o.ldy + kbeg);
-      d.yl = reinterpret_cast<const char*>(o.Yl + n0 * o.ldy + kbeg);
+#pragma unroll
+    for (int pl = 0; pl < NP; ++pl) {
+      d.x[pl] = reinterpret_cast<const char*>(o.X.p + pl * o.X.stride +
+                                              plane_index<KT>(o.X.rows, m0, kbeg));
+      if constexpr (YP)
+        d.y[pl] = nullptr;  // per K-tile, from the packed tile (dma_at)
+      else if constexpr (YF32)
+        d.y[pl] = reinterpret_cast<const char*>(o.Y + n0 * o.ldy + kbeg);
+      else
+        d.y[pl] = reinterpret_cast<const char*>(o.Y.p + pl * o.Y.stride +
+                                                plane_index<KT>(o.Y.rows, n0, kbeg));
     }
+    d.xstep = (size_t)o.X.rows * BK * 2;
+    if constexpr (YP)
+      d.ystep = 0;
+    else if constexpr (YF32)
+      d.ystep = BK * 4;
+    else
+      d.ystep = (size_t)o.Y.rows * BK * 2;
     d.wofs = (unsigned)w * 1024u;
     if constexpr (YP) {
       d.yp = reinterpret_cast<const char*>(o.Yp);
@@ -710,7 +749,7 @@ struct BlockGemmB3P {
         // rows past the operand's end (M padded to the tile) re-read its last
         // row; their outputs are never stored
         const int64_t rr = (m0 + r < o.mrows ? m0 + r : o.mrows - 1) - m0;
-        d.voff[q] = (unsigned)((rr * o.ldx + chunk * 8) * 2);
+        d.voff[q] = plane_off(o.X.rows, rr, chunk);
       } else if constexpr (YP) {
         const int p = ((q - XPW) * WAVES + w) * 64 + lane;
         const int r = p / (BK / 4), slot = p % (BK / 4);
@@ -729,7 +768,7 @@ struct BlockGemmB3P {
         const int p = (((q - XPW) % YPP) * WAVES + w) * 64 + lane;
         const int r = p / CPR, slot = p % CPR;
         const int chunk = slot ^ ((r / PY::RG) & (CPR - 1));
-        d.voff[q] = (unsigned)(((int64_t)r * o.ldy + chunk * 8) * 2);
+        d.voff[q] = plane_off(o.Y.rows, r, chunk);
       }
     }
   }
@@ -739,10 +778,8 @@ struct BlockGemmB3P {
   __device__ __forceinline__ static void dma_at(const Dma& d, int q, int kt, unsigned sb) {
     const char* b;
     unsigned vo = d.voff[q];
-    if (q < XPP) {
-      b = d.xh + (size_t)kt * (BK * 2);
-    } else if (q < XPW) {
-      b = d.xl + (size_t)kt * (BK * 2);
+    if (q < XPW) {
+      b = d.x[q / XPP] + (size_t)kt * d.xstep;
     } else if constexpr (YP) {
       const int64_t k = d.kbeg + (int64_t)kt * BK, kb = k / kPT, kk = k % kPT;
       if (d.jb > kb) {  // tile (kb, jb): rows k, read as stored
@@ -751,10 +788,8 @@ struct BlockGemmB3P {
       } else {          // tile (jb, kb): rows n, columns kk ..
         b = d.yp + (size_t)(packed_tile(d.jb, kb) * (kPT * kPT) + kk) * 4;
       }
-    } else if (YF32 || q < XPW + YPP) {
-      b = d.yh + (size_t)kt * YSTEP;
     } else {
-      b = d.yl + (size_t)kt * YSTEP;
+      b = d.y[YF32 ? 0 : (q - XPW) / (YPP > 0 ? YPP : 1)] + (size_t)kt * d.ystep;
     }
     lds_dma16(vo, b, sb + d.wofs + (unsigned)(q * WAVES) * 1024u);
   }
@@ -770,7 +805,7 @@ struct BlockGemmB3P {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = wn * (BN / WN) + j * 32 + (lane & 31);
-      adT[j] = 2u * XQ * 16 + (unsigned)(8 * khalf) * (unsigned)(kPT * 4) +
+      adT[j] = (unsigned)NP * XQ * 16 + (unsigned)(8 * khalf) * (unsigned)(kPT * 4) +
                (((unsigned)(n >> 2) ^ (unsigned)(8 * khalf)) << 4) + 4u * (n & 3);
     }
   }
@@ -782,8 +817,8 @@ struct BlockGemmB3P {
                                               const unsigned (&adT)[TN], int r) {
     if constexpr (TR) {
       const int ks = r / PER, q = r % PER;
-      if (q >= 2 * TM) {
-        const int j = (q - 2 * TM) / 2, h = (q - 2 * TM) % 2;
+      if (q >= NP * TM) {
+        const int j = (q - NP * TM) / 2, h = (q - NP * TM) % 2;
         const char* b = st + adT[j] + (unsigned)((16 * ks + 4 * h) * kPT * 4);
         return (u4){*reinterpret_cast<const unsigned*>(b),
                     *reinterpret_cast<const unsigned*>(b + kPT * 4),
@@ -804,22 +839,23 @@ struct BlockGemmB3P {
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const unsigned off = 2u * PX::swz(mrow + i * 32, chunk);
-        ad[PER * ks + 2 * i] = off;
-        ad[PER * ks + 2 * i + 1] = 2u * BM * BK + off;
+#pragma unroll
+        for (int pl = 0; pl < NP; ++pl) ad[PER * ks + NP * i + pl] = off + 2u * pl * BM * BK;
       }
       const int c0 = 4 * ks + 2 * khalf;
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int n = wn * (BN / WN) + j * 32 + (lane & 31);
         if constexpr (YF32) {
-          const unsigned yb = 2u * XQ * 16 + 4u * n * BK;
+          const unsigned yb = (unsigned)NP * XQ * 16 + 4u * n * BK;
           const int f = yswz(n);
-          ad[PER * ks + 2 * TM + 2 * j] = yb + 4u * ((c0 ^ f) << 2);
-          ad[PER * ks + 2 * TM + 2 * j + 1] = yb + 4u * (((c0 + 1) ^ f) << 2);
+          ad[PER * ks + NP * TM + 2 * j] = yb + 4u * ((c0 ^ f) << 2);
+          ad[PER * ks + NP * TM + 2 * j + 1] = yb + 4u * (((c0 + 1) ^ f) << 2);
         } else {
-          const unsigned off = 2u * XQ * 16 + 2u * PY::swz(n, chunk);
-          ad[PER * ks + 2 * TM + 2 * j] = off;                     // hi plane
-          ad[PER * ks + 2 * TM + 2 * j + 1] = off + 2u * BN * BK;  // lo plane
+          const unsigned off = (unsigned)NP * XQ * 16 + 2u * PY::swz(n, chunk);
+#pragma unroll
+          for (int pl = 0; pl < NP; ++pl)
+            ad[PER * ks + NP * TM + NP * j + pl] = off + 2u * pl * BN * BK;
         }
       }
     }
@@ -833,73 +869,65 @@ struct BlockGemmB3P {
   }
 
   // Split pair sp of the next tile's FP32 Y fragments (4 pairs per fragment).
-  __device__ __forceinline__ static void split_at(const Raw& rw, unsigned (&h)[KS][TN][4],
-                                                  unsigned (&l)[KS][TN][4], int sp) {
+  __device__ __forceinline__ static void split_at(const Raw& rw, Split& o, int sp) {
     const int fi = sp / 4, pr = sp % 4, ks = fi / TN, j = fi % TN;
-    const f4 v = __builtin_bit_cast(f4, rw.r[PER * ks + 2 * TM + 2 * j + pr / 2]);
-    if (pr % 2 == 0)
-      split_pair(v.x, v.y, h[ks][j][pr], l[ks][j][pr]);
+    const f4 v = __builtin_bit_cast(f4, rw.r[PER * ks + NP * TM + 2 * j + pr / 2]);
+    const float a = pr % 2 == 0 ? v.x : v.z, b = pr % 2 == 0 ? v.y : v.w;
+    unsigned t[3];
+    if constexpr (NP == 2)
+      split_pair(a, b, t[0], t[1]);
     else
-      split_pair(v.z, v.w, h[ks][j][pr], l[ks][j][pr]);
-    // keep the pair here, between its MFMAs (the compiler would otherwise sink
-    // it to the end of the K-tile, next to its first use)
-    asm volatile("" : "+v"(h[ks][j][pr]), "+v"(l[ks][j][pr]));
+      split_pair3(a, b, t);
+#pragma unroll
+    for (int pl = 0; pl < NP; ++pl) {
+      o[pl][ks][j][pr] = t[pl];
+      // keep the pair here, between its MFMAs (the compiler would otherwise
+      // sink it to the end of the K-tile, next to its first use)
+      asm volatile("" : "+v"(o[pl][ks][j][pr]));
+    }
   }
   static constexpr int NSP = YF32 ? KS * TN * 4 : 0;  // split pairs per K-tile
 
   // Fragments of a K-tile from its LDS reads (and split pairs).
-  __device__ __forceinline__ static void assemble(const Raw& rw, const unsigned (&h)[KS][TN][4],
-                                                  const unsigned (&l)[KS][TN][4], Frag& f) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        f.xh[ks][i] = __builtin_bit_cast(bf16x8, rw.r[PER * ks + 2 * i]);
-        f.xl[ks][i] = __builtin_bit_cast(bf16x8, rw.r[PER * ks + 2 * i + 1]);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        if constexpr (YF32) {
-          f.yh[ks][j] = __builtin_bit_cast(bf16x8, (u4){h[ks][j][0], h[ks][j][1], h[ks][j][2], h[ks][j][3]});
-          f.yl[ks][j] = __builtin_bit_cast(bf16x8, (u4){l[ks][j][0], l[ks][j][1], l[ks][j][2], l[ks][j][3]});
-        } else {
-          f.yh[ks][j] = __builtin_bit_cast(bf16x8, rw.r[PER * ks + 2 * TM + 2 * j]);
-          f.yl[ks][j] = __builtin_bit_cast(bf16x8, rw.r[PER * ks + 2 * TM + 2 * j + 1]);
-        }
-      }
-    }
-  }
-  __device__ __forceinline__ static void split(const Raw& rw, Frag& f) {
-    unsigned h[KS][TN][4], l[KS][TN][4];
-#pragma unroll
-    for (int sp = 0; sp < NSP; ++sp) split_at(rw, h, l, sp);
-    assemble(rw, h, l, f);
-  }
-
-  __device__ __forceinline__ void mfma(const Frag& f) {
+  __device__ __forceinline__ static void assemble(const Raw& rw, const Split& sp, Frag& f) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int pl = 0; pl < NP; ++pl) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          f.x[pl][ks][i] = __builtin_bit_cast(bf16x8, rw.r[PER * ks + NP * i + pl]);
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.xh[ks][i], f.yl[ks][j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.xl[ks][i], f.yh[ks][j], acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.xh[ks][i], f.yh[ks][j], acc[i][j], 0, 0, 0);
+          if constexpr (YF32)
+            f.y[pl][ks][j] = __builtin_bit_cast(
+                bf16x8, (u4){sp[pl][ks][j][0], sp[pl][ks][j][1], sp[pl][ks][j][2], sp[pl][ks][j][3]});
+          else
+            f.y[pl][ks][j] = __builtin_bit_cast(bf16x8, rw.r[PER * ks + NP * TM + NP * j + pl]);
         }
+      }
   }
-  // One MFMA of a K-tile: m = ((ks * 3 + product) * TM + i) * TN + j.  Each
-  // accumulator sees its products in the order of mfma() (so results are
-  // the same bit for bit), while consecutive MFMAs go to different
-  // accumulators and never wait for each other.
+  __device__ __forceinline__ static void split(const Raw& rw, Frag& f) {
+    Split sp;
+#pragma unroll
+    for (int k = 0; k < NSP; ++k) split_at(rw, sp, k);
+    assemble(rw, sp, f);
+  }
+
+  // One MFMA of a K-tile: m = ((ks * NPROD + product) * TM + i) * TN + j.
+  // Consecutive MFMAs go to different accumulators and never wait for each
+  // other; the small products of a K-step come before the leading one.
   __device__ __forceinline__ void mfma_at(const Frag& f, int m) {
-    const int j = m % TN, i = (m / TN) % TM, p = (m / TN / TM) % 3, ks = m / TN / TM / 3;
-    if (p == 0)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.xh[ks][i], f.yl[ks][j], acc[i][j], 0, 0, 0);
-    else if (p == 1)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.xl[ks][i], f.yh[ks][j], acc[i][j], 0, 0, 0);
-    else
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.xh[ks][i], f.yh[ks][j], acc[i][j], 0, 0, 0);
+    constexpr int XP[6] = {2, 0, 1, 1, 0, 0}, YPL[6] = {0, 2, 1, 0, 1, 0};
+    constexpr int X2[3] = {0, 1, 0}, Y2[3] = {1, 0, 0};
+    const int j = m % TN, i = (m / TN) % TM, p = (m / TN / TM) % NPROD, ks = m / TN / TM / NPROD;
+    const int xp = NP == 2 ? X2[p % 3] : XP[p], yp = NP == 2 ? Y2[p % 3] : YPL[p];
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.x[xp][ks][i], f.y[yp][ks][j], acc[i][j],
+                                                        0, 0, 0);
+  }
+  __device__ __forceinline__ void mfma(const Frag& f) {
+#pragma unroll
+    for (int m = 0; m < KS * NPROD * TM * TN; ++m) mfma_at(f, m);
   }
 
   // K-tile kt whose STAGES successors exist: stage `rd` holds tile kt + 1,
@@ -913,7 +941,7 @@ struct BlockGemmB3P {
   __device__ __forceinline__ void full_step(const Dma& d, const unsigned (&ad)[NR],
                                             const unsigned (&adT)[TN], int kt, const char* rd,
                                             const char* fr, Frag& cur) {
-    constexpr int NM = KS * TM * TN * 3;  // MFMAs per K-tile
+    constexpr int NM = KS * TM * TN * NPROD;  // MFMAs per K-tile
     constexpr int NRM = (NR + 1) / 2;     // MFMAs followed by reads
     static_assert(IPW <= NM, "one direct load per MFMA slot at most");
     wait_vmem<(STAGES - 2) * IPW>();  // tile kt + 1 landed (later ones may be in flight)
@@ -921,7 +949,7 @@ struct BlockGemmB3P {
     __builtin_amdgcn_sched_barrier(0);
     const unsigned sb = lds_addr(fr);
     Raw rw;
-    unsigned h[KS][TN][4], l[KS][TN][4];
+    Split sp;
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
       mfma_at(cur, m);
@@ -930,13 +958,13 @@ struct BlockGemmB3P {
 #pragma unroll
         for (int r = 2 * m; r < 2 * m + 2 && r < NR; ++r) rw.r[r] = read_r<TR>(rd, ad, adT, r);
       } else if (m - NRM < NSP) {
-        split_at(rw, h, l, m - NRM);
+        split_at(rw, sp, m - NRM);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int m = NM; m < NRM + NSP; ++m) split_at(rw, h, l, m - NRM);  // left over
-    assemble(rw, h, l, cur);
+    for (int m = NM; m < NRM + NSP; ++m) split_at(rw, sp, m - NRM);  // left over
+    assemble(rw, sp, cur);
   }
 
   // Packed Y: K-tiles [0, ksplit) of the range lie below the diagonal.
@@ -965,8 +993,80 @@ struct BlockGemmB3P {
     }
   }
 
+  // The running sum of a thread's entries, 16 bytes per thread at a time (its
+  // own entries: no other thread reads them): the first LQ of its kFoldQ
+  // chunks in LDS past the stages, the others in the block's slot in memory.
+  static constexpr int kFoldQ = TM * TN * 4;
+  template <int LQ>
+  static constexpr int fold_lds_bytes() { return LQ * NT * 16; }
+  template <int LQ>
+  __device__ __forceinline__ f4* fold_at(char* smem, float* slot, int c) const {
+    return c < LQ ? reinterpret_cast<f4*>(smem + MAIN_BYTES) + c * NT + threadIdx.x
+                  : reinterpret_cast<f4*>(slot) + (c - LQ) * NT + threadIdx.x;
+  }
+  template <int LQ>
+  __device__ __forceinline__ void fold(char* smem, float* slot, bool first) {
+#pragma unroll
+    for (int c = kFoldQ - 1; c >= 0; --c) {  // (memory first: its loads take longer)
+      floatx16& a = acc[c / 4 / TN][c / 4 % TN];
+      f4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = a[4 * (c % 4) + e];
+        a[4 * (c % 4) + e] = 0.0f;
+      }
+      if (!first) v += *fold_at<LQ>(smem, slot, c);
+      *fold_at<LQ>(smem, slot, c) = v;
+    }
+  }
+  template <int LQ>
+  __device__ __forceinline__ void unfold(char* smem, float* slot) {
+#pragma unroll
+    for (int c = kFoldQ - 1; c >= 0; --c) {
+      const f4 v = *fold_at<LQ>(smem, slot, c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[c / 4 / TN][c / 4 % TN][4 * (c % 4) + e] += v[e];
+    }
+  }
+  // The product over a long K (three planes).  Packed Y restarts the loop
+  // after every fold: its two loops with the fold between their steps spill
+  // 288 registers.
+  template <int LQ>
+  __device__ __forceinline__ void run_long(const Ops& o, int64_t m0, int64_t n0, int64_t kbeg,
+                                           int64_t kend, char* smem, float* slot) {
+    if constexpr (!YP) {
+      run<LQ>(o, m0, n0, kbeg, kend, smem, slot);
+    } else {
+      constexpr int64_t kSeg = (int64_t)kFoldTiles * BK;
+      for (int64_t k = kbeg;; k += kSeg) {
+        const bool last = k + kSeg >= kend;
+        run(o, m0, n0, k, last ? kend : k + kSeg, smem);
+        if (last) {
+          if (k != kbeg) unfold<LQ>(smem, slot);
+          return;
+        }
+        fold<LQ>(smem, slot, k == kbeg);
+      }
+    }
+  }
+
+  // LQ >= 0: fold a long K (see run_long).
+  template <int LQ = -1>
   __device__ __forceinline__ void run(const Ops& o, int64_t m0, int64_t n0, int64_t kbeg,
-                                      int64_t kend, char* smem) {
+                                      int64_t kend, char* smem, float* slot = nullptr) {
+    constexpr bool FOLD = LQ >= 0;
+    static_assert(!FOLD || STAGES == 3, "folded in the three-stage loop");
+    int to_fold = kFoldTiles;
+    bool folded = false;
+    // n more K-tiles are in the accumulator; whether it was folded for them
+    auto stepped = [&](int n) {
+      to_fold -= n;
+      if (to_fold > 0) return false;
+      if constexpr (FOLD) fold<LQ>(smem, slot, !folded);
+      folded = true;
+      to_fold = kFoldTiles;
+      return true;
+    };
     char* const s0 = smem;
     char* const s1 = smem + STAGE_BYTES;
     char* const s2 = smem + (STAGES == 3 ? 2 * STAGE_BYTES : 0);
@@ -1030,21 +1130,39 @@ struct BlockGemmB3P {
       // allocator hundreds of spilled registers).  Reads of tile kt + 1.
       const int ksplit = YP ? ksplit_of(d, nk) : 0;
       auto stg = [&](int k) { const int m = k % 3; return m == 0 ? s0 : m == 1 ? s1 : s2; };
-      for (; kt + 5 < nk && kt + 3 < ksplit; kt += 3) {
-        full_step<true>(d, ad, adT, kt, s1, s0, cur);
-        full_step<true>(d, ad, adT, kt + 1, s2, s1, cur);
-        full_step<true>(d, ad, adT, kt + 2, s0, s2, cur);
+      // runs of whole loop steps up to the next fold
+      for (;;) {
+        const int end = FOLD && kt + to_fold < ksplit - 3 ? kt + to_fold : ksplit - 3;
+        const int kt0 = kt;
+        for (; kt + 5 < nk && kt < end; kt += 3) {
+          full_step<true>(d, ad, adT, kt, s1, s0, cur);
+          full_step<true>(d, ad, adT, kt + 1, s2, s1, cur);
+          full_step<true>(d, ad, adT, kt + 2, s0, s2, cur);
+        }
+        if (!FOLD || !stepped(kt - kt0)) break;
       }
-      for (; kt + 5 < nk && kt + 1 < ksplit; ++kt)
+      for (; kt + 5 < nk && kt + 1 < ksplit; ++kt) {
         full_step<true>(d, ad, adT, kt, stg(kt + 1), stg(kt), cur);
-      for (; kt + 5 < nk && kt % 3 != 0; ++kt)
+        if constexpr (FOLD) to_fold -= 1;
+      }
+      for (; kt + 5 < nk && kt % 3 != 0; ++kt) {
         full_step<false>(d, ad, adT, kt, stg(kt + 1), stg(kt), cur);
-      for (; kt + 5 < nk; kt += 3) {
-        full_step<false>(d, ad, adT, kt, s1, s0, cur);
-        full_step<false>(d, ad, adT, kt + 1, s2, s1, cur);
-        full_step<false>(d, ad, adT, kt + 2, s0, s2, cur);
+        if constexpr (FOLD) to_fold -= 1;
+      }
+      for (;;) {
+        const int end = FOLD && kt + to_fold < nk - 5 ? kt + to_fold : nk - 5;
+        const int kt0 = kt;
+        for (; kt < end; kt += 3) {
+          full_step<false>(d, ad, adT, kt, s1, s0, cur);
+          full_step<false>(d, ad, adT, kt + 1, s2, s1, cur);
+          full_step<false>(d, ad, adT, kt + 2, s0, s2, cur);
+        }
+        if (!FOLD || !stepped(kt - kt0)) break;
       }
       for (; kt < nk; ++kt) tail_step(d, ad, adT, kt, nk, stg(kt + 1), stg(kt), cur);
+      if constexpr (FOLD) {
+        if (folded) unfold<LQ>(smem, slot);
+      }
     } else {
       static_assert(!YP, "packed Y takes three stages");
       for (; kt + 3 < nk; kt += 2) {
@@ -1078,6 +1196,33 @@ struct BlockGemmB3P {
       }
   }
 };
+
+// Block GEMMs whose sums over a long K are folded (BlockGemmB3P of three
+// planes): run over [kbeg, kend) with the running sum in `slot`.
+template <class G, class = void>
+struct folds_k : std::false_type {};
+template <class G>
+struct folds_k<G, std::void_t<decltype(G::kFolds)>> : std::integral_constant<bool, G::kFolds> {};
+template <class G>
+__host__ __device__ constexpr int rect_fold_lds() {  // chunks of the running sum kept in LDS
+  if constexpr (folds_k<G>::value) return 7;
+  else return 0;
+}
+template <class G>
+__host__ __device__ constexpr int rect_smem_bytes() {
+  if constexpr (folds_k<G>::value)
+    return G::MAIN_BYTES + G::template fold_lds_bytes<rect_fold_lds<G>()>();
+  else
+    return G::MAIN_BYTES;
+}
+template <class G>
+__device__ __forceinline__ void run_rect(G& g, const typename G::Ops& ops, int64_t m0, int64_t n0,
+                                         int64_t kbeg, int64_t kend, char* smem, float* slot) {
+  if constexpr (folds_k<G>::value)
+    g.template run_long<rect_fold_lds<G>()>(ops, m0, n0, kbeg, kend, smem, slot);
+  else
+    g.run(ops, m0, n0, kbeg, kend, smem);
+}
 
 // ======================================================= tile schedule ==
 // A grid of nb blocks (as many as the GPU runs at once) covers nTiles output
@@ -1185,9 +1330,11 @@ __device__ __forceinline__ void epi_tile(const G& g, Epi& epi, int64_t m0, int64
 template <class G, class Epi>
 __global__ __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(G::WAVES_PER_EU)))
 void k_rect_streamk(typename G::Ops ops, int64_t nMT, int64_t nTiles, int64_t U, int64_t S,
-                    Epi epi, float* __restrict__ part, const int32_t* gate) {
+                    Epi epi, float* __restrict__ part, float* __restrict__ fold,
+                    const int32_t* gate) {
   if (gate && *gate == 0) return;
-  __shared__ __align__(16) char smem[G::MAIN_BYTES];
+  __shared__ __align__(16) char smem[rect_smem_bytes<G>()];
+  float* const slot = fold + (int64_t)blockIdx.x * (G::BM * G::BN);
   __shared__ double red[G::NT / 64];
   const int64_t nb = gridDim.x;
   const int64_t L = xcd_tile(blockIdx.x, nb);
@@ -1196,14 +1343,14 @@ void k_rect_streamk(typename G::Ops ops, int64_t nMT, int64_t nTiles, int64_t U,
   for (int64_t r = 0; r < R; ++r) {
     const int64_t tile = r * nb + L;
     const int64_t m0 = (tile % nMT) * G::BM, n0 = (tile / nMT) * G::BN;
-    g.run(ops, m0, n0, 0, U * G::BK, smem);
+    run_rect(g, ops, m0, n0, 0, U * G::BK, smem, slot);
     epi_tile(g, epi, m0, n0);
     epi.end_tile(tile, red);
   }
   for (int64_t i = L; i < T * S; i += nb) {
     const int64_t c = i / T, tile = nFull + i % T;
     const int64_t m0 = (tile % nMT) * G::BM, n0 = (tile / nMT) * G::BN;
-    g.run(ops, m0, n0, c * U / S * G::BK, (c + 1) * U / S * G::BK, smem);
+    run_rect(g, ops, m0, n0, c * U / S * G::BK, (c + 1) * U / S * G::BK, smem, slot);
     if (S == 1) {
       epi_tile(g, epi, m0, n0);
       epi.end_tile(tile, red);
@@ -1301,6 +1448,8 @@ __global__ __launch_bounds__(kFixThreads) void k_rect_fixup(int64_t nMT, int64_t
   epi.end_tile(qb * nTiles + tile, red);
 }
 
+constexpr int64_t kFoldBlocks = 256;  // folding slots of a rectangular product
+
 inline int64_t device_cus() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -1323,11 +1472,14 @@ inline int64_t resident_blocks(const void* fn, int nt = kThreads) {
 // holds 2 * kMaxStreamKBlocks tiles of split-tile scratch.
 template <class G, class Epi>
 hipError_t launch_rect(const typename G::Ops& ops, int64_t Mp, int64_t Np, int64_t Kp, Epi epi,
-                       float* part, const int32_t* gate, hipStream_t s) {
+                       float* part, const int32_t* gate, hipStream_t s, float* fold = nullptr) {
   // computed once per kernel (a function-local static: thread-safe initialisation)
-  static const int64_t resident =
+  static const int64_t fits =
       resident_blocks(reinterpret_cast<const void*>(&k_rect_streamk<G, Epi>), G::NT);
+  int64_t resident = fits;
   static const int64_t cus = device_cus();
+  // blocks with a folding slot of their own
+  if (folds_k<G>::value && resident > kFoldBlocks) resident = kFoldBlocks;
   const int64_t nMT = Mp / G::BM, nNT = Np / G::BN;
   const int64_t nTiles = nMT * nNT, U = Kp / G::BK;
   // K-chunks per tail tile: the smallest S with the least cost, counted in
@@ -1357,7 +1509,7 @@ hipError_t launch_rect(const typename G::Ops& ops, int64_t Mp, int64_t Np, int64
   // whole rounds of `nb` tiles, then the items of the tail (see the kernel)
   const int64_t nb = starved ? std::min(T * S, resident) : std::min(resident, nTiles);
   k_rect_streamk<G, Epi><<<dim3((unsigned)nb), dim3(G::NT), 0, s>>>(ops, nMT, nTiles, U, S, epi,
-                                                                     part, gate);
+                                                                     part, fold, gate);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (T == 0 || S == 1) return hipSuccess;  // (starved with S = 1: one whole round)

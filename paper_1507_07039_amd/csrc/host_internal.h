@@ -79,6 +79,9 @@ struct panda_ctx {
   panda_options opt;
   panda::Rule rule;
   hipStream_t stream;
+  // W, the W being written, and R.  In the FP32 form of a single network the
+  // three are one buffer: the planes hold W exactly, A reads R there and leaves
+  // the new W in its place, and the next R replaces that (see w_in_place)
   float* W[2];
   float* R;
   float* P;
@@ -86,6 +89,7 @@ struct panda_ctx {
   float* Tside;
   float* ppart;   // split-K partial products of W W^T
   float* skpart;  // stream-K partial tiles (single-network schedule only)
+  float* fold;    // running sums of the A product over long K (FP32 form, else null)
   double* dP;     // diagonal of P (FP64; P holds zero there)
   double* dC;     // diagonal of C
   double* nP;     // |P_i.|^2
@@ -98,12 +102,13 @@ struct panda_ctx {
   double* csq;
   double* zs;
   uint32_t* corder;  // launch order of the upper C tiles
-  uint32_t* corder_r;  // the same with the R tiles of the next iteration (split-BF16)
+  uint32_t* corder_r;  // the same with the R tiles of the next iteration (not in a batch)
+  bool w_in_place;  // W and R share a buffer (FP32 form of a single network)
   bool r_next;  // R holds T(P, W) of the current state (computed by the last C update)
   panda::DevState* st;
-  bool b3;  // split-BF16 products
+  int np;       // bf16 planes of the operands: 2 (split-BF16) or 3 (FP32); 0: none (FP32 batch)
   bool packed;  // C stored as its upper tiles (packed_tile)
-  panda::bf16_t *Wh, *Wl, *Wth, *Wtl, *Ph, *Pl;  // split planes (C stays FP32)
+  panda::Planes Wr, Wt, Pp;  // of W, W^T and P without its diagonal (C stays FP32)
   panda::DevState* host;  // pinned
   panda::DevState* snap;  // pinned, two slots: states copied ahead (run_loaded)
   hipEvent_t snap_ev[2];
@@ -132,6 +137,10 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
 panda_status ctx_setup(panda_ctx* c, int64_t Ne, int64_t Na, const panda_options& o,
                        const LayoutSpec& spec, char* base, hipStream_t stream);
 void ctx_free(panda_ctx* c);
+// The current W of a loaded context as an FP32 matrix (leading dimension
+// Nap), for callers between iterations; R, which may share its buffer, is
+// computed again by the next iteration.
+panda_status ctx_current_w(panda_ctx* c, float** W);
 // Launch-order table of the upper C tiles (synchronises the context's stream).
 panda_status ctx_fill_order(panda_ctx* c);
 

@@ -69,9 +69,13 @@ namespace panda {
 
 LayoutSpec single_spec(int64_t Ne, int64_t Na, bool packed_c, int32_t precision) {
   const int64_t Nep = round_up(Ne, kPadE), Nap = round_up(Na, kPadA);
-  const int64_t blocks = precision == PANDA_PREC_BF16X3 ? 512 : 1024;
-  const int64_t nh = std::max(rect_tiles(Nep, Nap), rect_hpart_slots_b3(Nep, Nap));
-  return LayoutSpec{false, nh, coop_splits(Nep, Nap, blocks), packed_c};
+  // K chunks of W W^T: the FP32 form's are kept short enough for one
+  // accumulator where that at most doubles their number
+  const bool fp32 = precision != PANDA_PREC_BF16X3;
+  int64_t splits = coop_splits(Nep, Nap, fp32 ? 1024 : 512);
+  const int64_t whole = (Nap + kFoldK - 1) / kFoldK;
+  if (fp32 && whole <= 2 * splits) splits = std::max(splits, whole);
+  return LayoutSpec{false, avail_hpart_slots(Nep, Nap), splits, packed_c};
 }
 
 // Workspace layout shared by the size queries and the contexts.
@@ -80,16 +84,25 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   const int64_t Nep = round_up(Ne, kPadE), Nap = round_up(Na, kPadA);
   Carver cv{base};
   const size_t nw = (size_t)Nep * (size_t)Nap;
+  // bf16 planes of the operands: two, or three for the FP32 form
+  const int np = precision == PANDA_PREC_BF16X3 ? 2 : spec.batched ? 0 : 3;
+  const bool in_place = np == 3;  // one buffer for W and R
   float* w0 = cv.take<float>(nw);
-  float* w1 = cv.take<float>(nw);
-  float* r = cv.take<float>(nw);
-  // slack after P: the next-R tiles of the FP32 form read its last row past N_e
-  float* p = cv.take<float>((size_t)Nep * Nep + (size_t)next_r_p_slack(Nep));
+  float* w1 = in_place ? w0 : cv.take<float>(nw);
+  float* r = in_place ? w0 : cv.take<float>(nw);
+  float* p = cv.take<float>((size_t)Nep * Nep);
   float* cc = cv.take<float>(spec.packed_c ? (size_t)packed_floats(Nap) : (size_t)Nap * Nap);
   float* ts = cv.take<float>((size_t)Nep * Nep);
   const int splits = (int)spec.ppart_splits;
-  float* pp = cv.take<float>((size_t)splits * Nep * Nep);
-  float* sk = spec.batched ? nullptr : cv.take<float>(rect_partial_floats());
+  // Two pairs of the FP32 form share memory: the W W^T partials (from the
+  // partial products to the P finalisation) and the A product's folding
+  // scratch; the A product's split tiles and the planes of W^T, which are
+  // written after it and last read by the C update before the next one.
+  const size_t npp = (size_t)splits * Nep * Nep, nfold = rect_fold_floats(Nap, np);
+  float* pp = cv.take<float>(std::max(npp, nfold));
+  const size_t nsk = spec.batched ? 0 : rect_partial_floats();
+  float* sk = cv.take<float>(in_place ? std::max(nsk, (3 * nw + 1) / 2) : nsk);
+  if (spec.batched) sk = nullptr;
   double* dp = cv.take<double>((size_t)Nep);
   double* dc = cv.take<double>((size_t)Nap);
   double* np_ = cv.take<double>((size_t)Nep);
@@ -106,19 +119,14 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   double* zs = cv.take<double>(zscore_scratch_doubles(nid, nid, PANDA_ZSCORE_ROWCOL));
   uint32_t* co = cv.take<uint32_t>((size_t)coreg_tiles(Nap));
   DevState* st = cv.take<DevState>(1);
-  // split-BF16 operand planes
-  const bool b3 = precision == PANDA_PREC_BF16X3;
   uint32_t* cor = !spec.batched
                       ? cv.take<uint32_t>((size_t)(coreg_tiles(Nap) + next_r_tiles(Nep, Nap)))
                       : nullptr;
-  bf16_t* sh[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  if (b3) {
-    sh[0] = cv.take<bf16_t>(nw);                   // W hi, row-major
-    sh[1] = cv.take<bf16_t>(nw);                   // W lo
-    sh[2] = cv.take<bf16_t>(nw);                   // W^T hi, gene-major
-    sh[3] = cv.take<bf16_t>(nw);                   // W^T lo
-    sh[4] = cv.take<bf16_t>((size_t)Nep * Nep);    // P hi, zero diagonal
-    sh[5] = cv.take<bf16_t>((size_t)Nep * Nep);    // P lo
+  Planes wr{nullptr, (int64_t)nw, Nep}, wt{nullptr, (int64_t)nw, Nap}, pl{nullptr, Nep * Nep, Nep};
+  if (np) {
+    wr.p = cv.take<bf16_t>(np * nw);  // W
+    wt.p = in_place ? reinterpret_cast<bf16_t*>(sk) : cv.take<bf16_t>(np * nw);  // W^T
+    pl.p = cv.take<bf16_t>(np * (size_t)Nep * Nep);  // P, zero diagonal
   }
   if (c) {
     c->Nep = Nep;
@@ -131,6 +139,7 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
     c->Tside = ts;
     c->ppart = pp;
     c->skpart = sk;
+    c->fold = nfold ? pp : nullptr;
     c->dP = dp;
     c->dC = dc;
     c->nP = np_;
@@ -140,22 +149,20 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
     c->colscr = scr;
     c->splits = splits;
     c->hpart = hp;
-    c->nh = b3 ? rect_hpart_slots_b3(c->Nep, c->Nap) : rect_tiles(c->Nep, c->Nap);  // h partials the A + W tiling writes
+    c->nh = avail_hpart_slots(c->Nep, c->Nap);  // h partials of the A + W product
     c->cstat = cs;
     c->csq = cq;
     c->zs = zs;
     c->corder = co;
     c->corder_r = cor;
+    c->w_in_place = in_place;
     c->r_next = false;
     c->st = st;
-    c->b3 = b3;
+    c->np = np;
     c->packed = spec.packed_c;
-    c->Wh = sh[0];
-    c->Wl = sh[1];
-    c->Wth = sh[2];
-    c->Wtl = sh[3];
-    c->Ph = sh[4];
-    c->Pl = sh[5];
+    c->Wr = wr;
+    c->Wt = wt;
+    c->Pp = pl;
   }
   return cv.off;
 }
@@ -313,86 +320,54 @@ panda_status enqueue_iteration(panda_ctx* c) {
   PANDA_TRY(mark(c, PANDA_PHASE_R));
   // Eq. 3: R = T(P, W), K = N_e (computed by the last C update unless the
   // state is new)
-  const bool next_r = c->corder_r != nullptr;
-  if (next_r) {
-    if (!c->r_next) {
-      if (c->b3)
-        HIP_TRY(launch_resp_tiles_b3(c->Ph, c->Pl, c->Nep, c->dP, c->Wth, c->Wtl, c->Nep,
-                                     c->Nap, c->Ne, c->Na, Wold, c->Nap, c->nP, c->nWc, c->R,
-                                     active, s));
-      else
-        HIP_TRY(launch_resp_tiles(c->P, c->Nep, c->dP, c->Nap, c->Ne, c->Na, Wold, c->Nap,
-                                  c->nP, c->nWc, c->R, active, s));
-    }
-  } else if (c->b3)
-    HIP_TRY(launch_resp_b3(c->Ph, c->Pl, c->Nep, c->dP, c->Wth, c->Wtl, c->Nep, c->Nep, c->Nap,
-                           c->Ne, c->Na, Wold, c->Nap, c->nP, c->nWc, c->R, c->skpart, active, s));
-  else
-    HIP_TRY(launch_resp(c->P, c->Nep, c->dP, Wold, c->Nap, c->Nep, c->Nap, c->Ne, c->Na, c->nP,
-                        c->nWc, c->R, c->skpart, active, s));
+  if (!c->r_next)
+    HIP_TRY(launch_resp_tiles(c->Pp, c->Wt, c->np, c->Nep, c->dP, c->Nap, c->Ne, c->Na, Wold,
+                              c->Nap, c->nP, c->nWc, c->R, active, s));
   PANDA_TRY(mark(c, PANDA_PHASE_AW));
   // Eq. 4 + Eq. 2 + Eq. 7 partials: A = T(W, C), K = N_a
-  if (c->b3)
-    HIP_TRY(launch_avail_wupdate_b3(c->Wh, c->Wl, Wold, c->C, c->dC, c->R, Wnew, c->Nap, c->Nep,
-                                    c->Nap, c->Ne, c->Na, c->nWr, c->nC, c->rule, c->hpart,
-                                    c->skpart, active, s, c->packed));
-  else
-    HIP_TRY(launch_avail_wupdate(Wold, c->C, c->dC, c->R, Wnew, c->Nap, c->Nep, c->Nap, c->Ne,
-                                 c->Na, c->nWr, c->nC, c->rule, c->hpart, c->skpart, active, s,
-                                 c->packed));
+  HIP_TRY(launch_avail_wupdate(c->Wr, c->np, Wold, c->C, c->dC, c->R, Wnew, c->Nap, c->Nep, c->Nap,
+                               c->Ne, c->Na, c->nWr, c->nC, c->rule, c->hpart, c->skpart,
+                               c->fold, active, s, c->packed));
   PANDA_TRY(mark(c, PANDA_PHASE_H));
   HIP_TRY(launch_finish_h(c->hpart, c->nh, c->Ne * c->Na, c->st, c->rule, s));
-  // squared norms (and split planes) of the new W
-  HIP_TRY(launch_w_norms(Wnew, c->Ne, c->Na, c->Nap, c->Nep, c->nWr, c->nWc, c->colscr, c->Wh,
-                         c->Wl, c->Wth, c->Wtl, c->Nep, run_pc, s));
+  // squared norms and planes of the new W
+  HIP_TRY(launch_w_norms(Wnew, c->Ne, c->Na, c->Nap, c->Nep, c->nWr, c->nWc, c->colscr, c->Wr,
+                         c->Wt, c->np, run_pc, s));
   PANDA_TRY(mark(c, PANDA_PHASE_PPART));
   // Eq. 5, P: T(W_i., W_m.) of the new W
-  if (c->b3)
-    HIP_TRY(launch_coop_partial_b3(c->Wh, c->Wl, c->Nap, c->Nep, c->Nap, c->splits, c->ppart,
-                                   run_pc, s));
-  else
-    HIP_TRY(launch_coop_partial(Wnew, c->Nap, c->Nep, c->Nap, c->splits, c->ppart, run_pc, s));
+  HIP_TRY(launch_coop_partial(c->Wr, c->np, c->Nep, c->Nap, c->splits, c->ppart, run_pc, s));
   PANDA_TRY(mark(c, PANDA_PHASE_PFIN));
+  float* const tside = c->rule.sigma_from_T ? c->Tside : nullptr;
+  double* const csq = c->rule.sigma_from_T ? c->csq : nullptr;
   HIP_TRY(launch_coop_finalize(c->ppart, c->splits, c->Nep, c->nWr, c->P, c->Nep, c->Ne, c->rule,
-                               c->rule.sigma_from_T ? c->Tside : nullptr, c->Ph, c->Pl, run_pc,
-                               s));
-  // Eq. 6 for P, and |P_i.|^2, before the C update when it also computes
-  // the next R (which needs them)
-  if (next_r)
-    HIP_TRY(launch_diagonals(c->P, c->Nep, c->dP, c->Ne,
-                             c->rule.sigma_from_T ? c->Tside : nullptr, c->nP, c->dC, c->Nap,
-                             c->Na, c->cstat, c->rule.sigma_from_T ? c->csq : nullptr,
-                             coreg_slots(c->Nap), c->nC, c->rule, c->st, s, kDiagP));
+                               tside, c->Pp, c->np, run_pc, s));
+  // Eq. 6 for P, and |P_i.|^2, before the C update, which also computes the
+  // next R (which needs them)
+  HIP_TRY(launch_diagonals(c->P, c->Nep, c->dP, c->Ne, tside, c->nP, c->dC, c->Nap, c->Na, c->cstat,
+                           csq, coreg_slots(c->Nap), c->nC, c->rule, c->st, s, kDiagP));
   PANDA_TRY(mark(c, PANDA_PHASE_C));
   // Eq. 5, C: T(W_.k, W_.j) of the new W, upper tiles, mirrored (and the
   // next iteration's R = T(P, W) of the new P and W)
-  if (next_r && c->b3)
-    HIP_TRY(launch_coreg_update_next_r_b3(c->Wth, c->Wtl, c->Nep, c->Nep, c->C, c->Nap, c->Nap,
-                                          c->Na, c->nWc, c->rule, c->cstat, c->csq, c->corder_r,
-                                          run_pc, s, c->packed, c->Ph, c->Pl, c->dP, c->nP,
-                                          Wnew, c->Nap, c->Ne, c->R));
-  else if (next_r)
-    HIP_TRY(launch_coreg_update_next_r(Wnew, c->Nap, c->Nep, c->C, c->Nap, c->Nap, c->Na, c->nWc,
-                                       c->rule, c->cstat, c->csq, c->corder_r, run_pc, s,
-                                       c->packed, c->P, c->dP, c->nP, c->Ne, c->R));
-  else if (c->b3)
-    HIP_TRY(launch_coreg_update_b3(c->Wth, c->Wtl, c->Nep, c->Nep, c->C, c->Nap,
-                                   c->Nap, c->Na, c->nWc, c->rule, c->cstat, c->csq, c->corder,
-                                   run_pc, s, c->packed));
-  else
-    HIP_TRY(launch_coreg_update(Wnew, c->Nap, c->Nep, c->C, c->Nap, c->Nap, c->Na, c->nWc,
-                                c->rule, c->cstat, c->csq, c->corder, run_pc, s, c->packed));
+  HIP_TRY(launch_coreg_update_next_r(c->Wt, c->np, c->Nep, c->C, c->Nap, c->Nap, c->Na,
+                                     c->nWc, c->rule, c->cstat, c->csq, c->corder_r, run_pc, s,
+                                     c->packed, c->Pp, c->dP, c->nP, Wnew, c->Nap, c->Ne, c->R));
   PANDA_TRY(mark(c, PANDA_PHASE_DIAG));
-  // Eq. 6, and |P_i.|^2, |C_.j|^2 for the next iteration
-  HIP_TRY(launch_diagonals(c->P, c->Nep, c->dP, c->Ne, c->rule.sigma_from_T ? c->Tside : nullptr,
-                           c->nP, c->dC, c->Nap, c->Na, c->cstat,
-                           c->rule.sigma_from_T ? c->csq : nullptr, coreg_slots(c->Nap), c->nC,
-                           c->rule, c->st, s, next_r ? kDiagC : kDiagBoth));
-  c->r_next = next_r;
+  // Eq. 6 for C, and |C_.j|^2 for the next iteration
+  HIP_TRY(launch_diagonals(c->P, c->Nep, c->dP, c->Ne, tside, c->nP, c->dC, c->Nap, c->Na, c->cstat,
+                           csq, coreg_slots(c->Nap), c->nC, c->rule, c->st, s, kDiagC));
+  c->r_next = true;
   PANDA_TRY(mark(c, PANDA_NPHASE));
   if (c->timing) c->npend += 1;
   c->enqueued += 1;
   return PANDA_OK;
+}
+
+// Whether the buffer that W shares holds R and the planes alone hold W: after
+// an iteration that updated P and C (the one that converges does not, unless
+// update_last: then its W stays where the A product left it and the planes
+// hold the W before).  The state is that of the last read-back.
+bool w_in_planes(const panda_ctx* c) {
+  return c->w_in_place && c->r_next && (!c->host->conv || c->rule.update_last);
 }
 
 panda_status copy_in(float* dst, int64_t ldd, const float* src, int64_t rows, int64_t cols,
@@ -405,6 +380,15 @@ panda_status copy_in(float* dst, int64_t ldd, const float* src, int64_t rows, in
 }  // namespace
 
 namespace panda {
+
+panda_status ctx_current_w(panda_ctx* c, float** W) {
+  *W = c->W[c->executed & 1];
+  if (w_in_planes(c)) {
+    HIP_TRY(launch_join_planes(c->Wr, c->Ne, c->Na, *W, c->Nap, c->stream));
+    c->r_next = false;
+  }
+  return PANDA_OK;
+}
 
 // Enqueue ahead and read h back every poll_every iterations; iterations
 // enqueued past convergence are no-ops on the device.
@@ -692,8 +676,7 @@ size_t panda_workspace_bytes(int64_t Ne, int64_t Na, const panda_options* opt) {
   return ctx_layout(Ne, Na, opt ? opt->precision : PANDA_PREC_FP32,
                     single_spec(Ne, Na, opt && opt->packed_c,
                                 opt ? opt->precision : PANDA_PREC_FP32),
-                    nullptr,
-                    nullptr);
+                    nullptr, nullptr);
 }
 
 panda_status panda_ctx_create(int64_t Ne, int64_t Na, const panda_options* opt, void* workspace,
@@ -714,8 +697,7 @@ panda_status panda_ctx_create(int64_t Ne, int64_t Na, const panda_options* opt, 
   panda_ctx* c = new (std::nothrow) panda_ctx();
   if (!c) return fail(PANDA_ERR_ARG, "ctx_create: out of host memory%s");
   st = ctx_setup(c, Ne, Na, o, single_spec(Ne, Na, o.packed_c != 0, o.precision),
-                 static_cast<char*>(workspace),
-                 stream);
+                 static_cast<char*>(workspace), stream);
   if (st != PANDA_OK) {
     delete c;
     return st;
@@ -736,7 +718,7 @@ panda_status panda_ctx_load(panda_ctx* c, const float* W, const float* P, const 
   hipStream_t s = c->stream;
   const int64_t Ne = c->Ne, Na = c->Na, Nep = c->Nep, Nap = c->Nap;
   HIP_TRY(hipMemsetAsync(c->W[0], 0, (size_t)Nep * Nap * 4, s));
-  HIP_TRY(hipMemsetAsync(c->W[1], 0, (size_t)Nep * Nap * 4, s));
+  if (!c->w_in_place) HIP_TRY(hipMemsetAsync(c->W[1], 0, (size_t)Nep * Nap * 4, s));
   HIP_TRY(hipMemsetAsync(c->P, 0, (size_t)Nep * Nep * 4, s));
   if (!c->packed) HIP_TRY(hipMemsetAsync(c->C, 0, (size_t)Nap * Nap * 4, s));
   HIP_TRY(hipMemsetAsync(c->Tside, 0, (size_t)Nep * Nep * 4, s));
@@ -782,21 +764,15 @@ panda_status panda_ctx_load(panda_ctx* c, const float* W, const float* P, const 
     HIP_TRY(launch_take_diag_packed(c->C, Na, c->dC, s));
   else
     HIP_TRY(launch_take_diag(c->C, Na, Nap, c->dC, s));
-  if (c->b3) {
-    // planes of the loaded state; padding and the P/C diagonals stay zero
-    const size_t nw = (size_t)Nep * Nap;
-    HIP_TRY(hipMemsetAsync(c->Wh, 0, nw * 2, s));
-    HIP_TRY(hipMemsetAsync(c->Wl, 0, nw * 2, s));
-    HIP_TRY(hipMemsetAsync(c->Wth, 0, nw * 2, s));
-    HIP_TRY(hipMemsetAsync(c->Wtl, 0, nw * 2, s));
-    HIP_TRY(hipMemsetAsync(c->Ph, 0, (size_t)Nep * Nep * 2, s));
-    HIP_TRY(hipMemsetAsync(c->Pl, 0, (size_t)Nep * Nep * 2, s));
-    HIP_TRY(launch_split_offdiag(c->P, Ne, Nep, c->Ph, c->Pl, s));
+  if (c->np) {
+    // planes of the loaded P; its padding and diagonal stay zero
+    HIP_TRY(hipMemsetAsync(c->Pp.p, 0, (size_t)c->np * Nep * Nep * 2, s));
+    HIP_TRY(launch_split_offdiag(c->P, Ne, Nep, c->Pp, c->np, s));
   }
   // norms (and planes) of W exactly as an iteration computes them, so a
   // stored state resumes bit for bit
-  HIP_TRY(launch_w_norms(c->W[0], Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wh, c->Wl,
-                         c->Wth, c->Wtl, Nep, nullptr, s));
+  HIP_TRY(launch_w_norms(c->W[0], Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt, c->np,
+                         nullptr, s));
   PANDA_TRY(ctx_fill_order(c));
   // h partial slots the A + W product never writes add zeros
   HIP_TRY(hipMemsetAsync(c->hpart, 0, (size_t)c->nh * sizeof(double), s));
@@ -832,10 +808,11 @@ panda_status panda_ctx_store(panda_ctx* c, float* W, float* P, float* C, double*
   panda_status st = read_state(c);
   if (st != PANDA_OK) return st;
   hipStream_t s = c->stream;
-  const float* Wc = c->W[c->executed & 1];
-  if (W)
-    HIP_TRY(hipMemcpy2DAsync(W, (size_t)c->Na * 4, Wc, (size_t)c->Nap * 4, (size_t)c->Na * 4,
-                             (size_t)c->Ne, hipMemcpyDeviceToDevice, s));
+  if (W && w_in_planes(c))
+    HIP_TRY(launch_join_planes(c->Wr, c->Ne, c->Na, W, c->Na, s));
+  else if (W)
+    HIP_TRY(hipMemcpy2DAsync(W, (size_t)c->Na * 4, c->W[c->executed & 1], (size_t)c->Nap * 4,
+                             (size_t)c->Na * 4, (size_t)c->Ne, hipMemcpyDeviceToDevice, s));
   if (P) {
     HIP_TRY(hipMemcpy2DAsync(P, (size_t)c->Ne * 4, c->P, (size_t)c->Nep * 4, (size_t)c->Ne * 4,
                              (size_t)c->Ne, hipMemcpyDeviceToDevice, s));

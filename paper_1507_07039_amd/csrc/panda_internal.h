@@ -33,6 +33,30 @@ struct Rule {
 
 typedef unsigned short bf16_t;           // raw bits of a bfloat16
 
+// An FP32 matrix (rows x K, products contract over K) given as bf16 planes,
+// plane q at p + q * stride, leading term first: two planes x = hi + lo to
+// 2^-17, three planes x = hi + mid + lo exactly.  A plane is stored K-tile by
+// K-tile, [K / KT][rows][KT] with KT = plane_kt(planes), the K-tile depth of
+// the products: the direct-to-LDS loads of a tile then read whole cache lines
+// (row-major, a K-tile of 16 took 32 bytes of each row, 32 lines per load
+// instruction instead of 8, and the loads bound the C update).
+struct Planes {
+  bf16_t* p;
+  int64_t stride;
+  int64_t rows;
+};
+__host__ __device__ constexpr int plane_kt(int planes) { return planes == 2 ? 32 : 16; }
+template <int KT>
+__host__ __device__ constexpr int64_t plane_index(int64_t rows, int64_t r, int64_t k) {
+  return (k / KT * rows + r) * KT + k % KT;
+}
+// Entry (r, k) of a matrix given as three planes, exactly (both sums are).
+__device__ __forceinline__ float join_planes(const Planes& P, int64_t r, int64_t k) {
+  const bf16_t* p = P.p + plane_index<plane_kt(3)>(P.rows, r, k);
+  auto f = [](bf16_t b) { return __builtin_bit_cast(float, (unsigned)b << 16); };
+  return f(p[0]) + (f(p[P.stride]) + f(p[2 * P.stride]));
+}
+
 constexpr int kThreads = 256;            // threads per block (4 waves of 64)
 constexpr int64_t kMaxStreamKBlocks = 1024;
 constexpr int kColChunks = 64;           // row chunks of the column-norm kernel
@@ -64,11 +88,14 @@ inline int64_t packed_floats(int64_t Nap) {
 // nx / ny are the FP64 squared norms of the rows of X / columns of Y.
 // part: rect_partial_floats() floats of split-tile scratch.
 int64_t rect_tiles(int64_t Mp, int64_t Np);
-int64_t rect_tiles_b3(int64_t Mp, int64_t Np);  // tiles of the split-BF16 A + W product
-// h partial slots of the split-BF16 A + W product: one per tile and fix-up
-// block part (slots of tiles the fix-up never splits stay zero)
-int64_t rect_hpart_slots_b3(int64_t Mp, int64_t Np);
+// h partial slots of the A + W product: one per tile and fix-up block part
+// (slots of tiles the fix-up never splits stay zero)
+int64_t avail_hpart_slots(int64_t Mp, int64_t Np);
 size_t rect_partial_floats();
+// K up to which a product of three planes stays in one accumulator (see
+// BlockGemmB3P::kFolds), and the A product's scratch for longer ones.
+constexpr int64_t kFoldK = 1024;
+size_t rect_fold_floats(int64_t Kp, int np);
 
 // Out[i][j] = T(X, Y)_ij for i < M, j < N.  yd (optional): Y is square with
 // its diagonal held apart in this FP64 vector (and zero in Y).
@@ -87,19 +114,23 @@ hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const floa
                        hipStream_t s);
 
 // A = T(W, C) fused with the W update of Eq. 2 and per-tile h partials (Eq. 7).
-hipError_t launch_avail_wupdate(const float* Wold, const float* C, const double* dC,
-                                const float* R, float* Wnew, int64_t ld, int64_t Nep, int64_t Nap,
-                                int64_t Ne, int64_t Na, const double* nWrow, const double* nC,
-                                Rule rule, double* hpart, float* part, const int32_t* gate,
-                                hipStream_t s, bool packed = false);
+// (C is symmetric: its row n is the column n the product needs; it is split
+// into planes as it is read.)  With three planes the old W is read from them
+// (Wold unused) and Wnew may be R itself; fold holds rect_fold_floats().
+hipError_t launch_avail_wupdate(const Planes& Wr, int np, const float* Wold, const float* C,
+                                const double* dC, const float* R, float* Wnew, int64_t ld,
+                                int64_t Nep, int64_t Nap, int64_t Ne, int64_t Na,
+                                const double* nWrow, const double* nC, Rule rule, double* hpart,
+                                float* part, float* fold, const int32_t* gate, hipStream_t s,
+                                bool packed);
 
 // C update (Eq. 5) on the upper tiles of T(W^T, W) with mirror writes and
 // per-row partial sums for the sigma of Eq. 6 (and |C_.j|^2).  order holds
 // the upper tiles (I | J << 16) in launch order, see coreg_order_fill.
-hipError_t launch_coreg_update(const float* W, int64_t ldw, int64_t Nep, float* C, int64_t ldc,
-                               int64_t Nap, int64_t Na, const double* nWcol, Rule rule,
-                               double2* cstat, double* csq, const uint32_t* order,
-                               const int32_t* gate, hipStream_t s, bool packed = false);
+hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Nep, float* C,
+                               int64_t ldc, int64_t Nap, int64_t Na, const double* nWcol,
+                               Rule rule, double2* cstat, double* csq, const uint32_t* order,
+                               const int32_t* gate, hipStream_t s, bool packed);
 int64_t coreg_slots(int64_t Nap);
 // Upper tiles of the C product (Nap / 128 per side) and their launch order:
 // group x group super-tiles, so the tiles running together on one XCD share
@@ -112,74 +143,40 @@ void coreg_order_fill(int64_t Nap, int group, uint32_t* out);
 constexpr int kCoregGroup = PANDA_COREG_GROUP;
 
 // P update, split over K: partial products of W W^T on upper tiles.
-hipError_t launch_coop_partial(const float* W, int64_t ldw, int64_t Nep, int64_t Nap, int splits,
+hipError_t launch_coop_partial(const Planes& Wr, int np, int64_t Nep, int64_t Nap, int splits,
                                float* part, const int32_t* gate, hipStream_t s);
 // K chunks of the partial products, for about `blocks` blocks in all (at
-// T=700, G=18000 the FP32 products run best at 1024, the split-BF16 ones at
-// 512: their partial sums then cost the finalise more than they save).
+// T=700, G=18000 the split-BF16 products run best at 512: more partial sums
+// cost the finalise more than they save; the FP32 form takes 1024, whose
+// shorter sums also round less).
 int coop_splits(int64_t Nep, int64_t Nap, int64_t blocks);
 
-// Split-BF16 forms of the same products.  Operands are K-contiguous hi/lo
-// planes: P (diagonal zero), W row-major, W^T (gene-major); C stays FP32.
-hipError_t launch_resp_b3(const bf16_t* Ph, const bf16_t* Pl, int64_t ldp, const double* dP,
-                          const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt, int64_t Nep,
-                          int64_t Nap, int64_t Ne, int64_t Na, const float* W, int64_t ldw,
-                          const double* nP, const double* nWc, float* R, float* part,
-                          const int32_t* gate, hipStream_t s);
-// A = T(W, C) + W update with X = the W planes and Y = the FP32 C itself
-// (symmetric; split into hi/lo while staged).
-hipError_t launch_avail_wupdate_b3(const bf16_t* Wh, const bf16_t* Wl, const float* Wold,
-                                   const float* C, const double* dC, const float* R, float* Wnew,
-                                   int64_t ld, int64_t Nep, int64_t Nap, int64_t Ne, int64_t Na,
-                                   const double* nWrow, const double* nC, Rule rule,
-                                   double* hpart, float* part, const int32_t* gate,
-                                   hipStream_t s, bool packed = false);
-hipError_t launch_coreg_update_b3(const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt, int64_t Nep,
-                                  float* C, int64_t ldc, int64_t Nap, int64_t Na,
-                                  const double* nWcol, Rule rule, double2* cstat, double* csq,
-                                  const uint32_t* order, const int32_t* gate, hipStream_t s,
-                                  bool packed = false);
 // R = T(P, W) (Eq. 3) on 128 x 128 tiles (next_r_tiles of them), alone or
 // inside the C update's launch: that launch runs the C tiles and the R tiles
 // of the order coreg_next_r_order_fill builds, so the next iteration's R is
 // ready when the C update ends (P, its diagonal dP and norms nP, and W's
 // planes and column norms must be the new ones).  Both compute R the same
-// way, bit for bit.  W, R: leading dimension ldw; P's planes Nep x Nep.
+// way, bit for bit.  W, R: leading dimension ldw (R may be W itself: an entry
+// of W is read by the thread that stores R there).
 int64_t next_r_row_tiles(int64_t Nep);
 int64_t next_r_tiles(int64_t Nep, int64_t Nap);
 void coreg_next_r_order_fill(int64_t Nep, int64_t Nap, const uint32_t* corder, uint32_t* out);
-// FP32 form: P is read k-major and needs next_r_p_slack(Nep) floats of
-// readable memory after its Nep x Nep entries.
-int64_t next_r_p_slack(int64_t Nep);
-hipError_t launch_resp_tiles(const float* P, int64_t ldp, const double* dP, int64_t Nap,
-                             int64_t Ne, int64_t Na, const float* W, int64_t ldw,
-                             const double* nP, const double* nWc, float* R, const int32_t* gate,
-                             hipStream_t s);
-hipError_t launch_coreg_update_next_r(const float* W, int64_t ldw, int64_t Nep, float* C,
-                                      int64_t ldc, int64_t Nap, int64_t Na, const double* nWcol,
-                                      Rule rule, double2* cstat, double* csq,
+hipError_t launch_resp_tiles(const Planes& Pp, const Planes& Wt, int np, int64_t ldp,
+                             const double* dP, int64_t Nap, int64_t Ne, int64_t Na,
+                             const float* W, int64_t ldw, const double* nP, const double* nWc,
+                             float* R, const int32_t* gate, hipStream_t s);
+hipError_t launch_coreg_update_next_r(const Planes& Wt, int np, int64_t Nep,
+                                      float* C, int64_t ldc, int64_t Nap, int64_t Na,
+                                      const double* nWcol, Rule rule, double2* cstat, double* csq,
                                       const uint32_t* order_r, const int32_t* gate, hipStream_t s,
-                                      bool packed, const float* P, const double* dP,
-                                      const double* nP, int64_t Ne, float* R);
-hipError_t launch_resp_tiles_b3(const bf16_t* Ph, const bf16_t* Pl, int64_t ldp, const double* dP,
-                                const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt, int64_t Nap,
-                                int64_t Ne, int64_t Na, const float* W, int64_t ldw,
-                                const double* nP, const double* nWc, float* R,
-                                const int32_t* gate, hipStream_t s);
-hipError_t launch_coreg_update_next_r_b3(const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt,
-                                         int64_t Nep, float* C, int64_t ldc, int64_t Nap,
-                                         int64_t Na, const double* nWcol, Rule rule,
-                                         double2* cstat, double* csq, const uint32_t* order_r,
-                                         const int32_t* gate, hipStream_t s, bool packed,
-                                         const bf16_t* Ph, const bf16_t* Pl, const double* dP,
-                                         const double* nP, const float* W, int64_t ldw,
-                                         int64_t Ne, float* R);
-hipError_t launch_coop_partial_b3(const bf16_t* Wh, const bf16_t* Wl, int64_t ldw, int64_t Nep,
-                                  int64_t Nap, int splits, float* part, const int32_t* gate,
-                                  hipStream_t s);
-// hi/lo planes of W (Ne x Na, leading dimension ldw) row-major (ld ldw) and
-// hi/lo planes of an n x n matrix with its diagonal left zero.
-hipError_t launch_split_offdiag(const float* M, int64_t n, int64_t ld, bf16_t* Mh, bf16_t* Ml,
+                                      bool packed, const Planes& Pp, const double* dP,
+                                      const double* nP, const float* W, int64_t ldw, int64_t Ne,
+                                      float* R);
+// out[r][k] of the matrix that three planes hold (rows x cols, leading dimension ldo).
+hipError_t launch_join_planes(const Planes& P, int64_t rows, int64_t cols, float* out, int64_t ldo,
+                              hipStream_t s);
+// The np planes of an n x n matrix with its diagonal left zero.
+hipError_t launch_split_offdiag(const float* M, int64_t n, int64_t ld, Planes out, int np,
                                 hipStream_t s);
 
 // Packed C (see packed_tile).  pack: the upper tiles of the n x n symmetric
@@ -204,7 +201,7 @@ hipError_t launch_finish_h(const double* hpart, int64_t n, int64_t count, DevSta
                            Rule rule, hipStream_t s);
 hipError_t launch_coop_finalize(const float* part, int splits, int64_t Nep, const double* nWrow,
                                 float* P, int64_t ldp, int64_t Ne, Rule rule, float* Tside,
-                                bf16_t* Ph, bf16_t* Pl, const int32_t* gate, hipStream_t s);
+                                Planes Pp, int np, const int32_t* gate, hipStream_t s);
 // part: kDiagBoth, or kDiagP / kDiagC for P's rows (dP, nP: they need only
 // the new P) or C's rows (dC, nC: they need the C update's row sums) alone.
 constexpr int kDiagBoth = 0, kDiagP = 1, kDiagC = 2;
@@ -228,12 +225,12 @@ hipError_t launch_state_set(DevState* st, int32_t t, int32_t active, int32_t run
                             hipStream_t s);
 // Squared norms of the rows / columns of a rows x cols matrix with leading
 // Row and column squared norms of W (padded Nep x ldw, real Ne x Na) in one
-// pass over it, plus its bf16 planes (row-major and gene-major, leading
-// dimension ldt) when Wh is given.  scr holds w_norm_scratch_doubles().
+// pass over it, plus its np bf16 planes (of W, Wr, and of W^T, Wt).  scr holds
+// w_norm_scratch_doubles().
 size_t w_norm_scratch_doubles(int64_t Nep, int64_t Nap);
 hipError_t launch_w_norms(const float* W, int64_t Ne, int64_t Na, int64_t ldw, int64_t Nep,
-                          double* nr, double* nc, double* scr, bf16_t* Wh, bf16_t* Wl, bf16_t* Wth,
-                          bf16_t* Wtl, int64_t ldt, const int32_t* gate, hipStream_t s);
+                          double* nr, double* nc, double* scr, Planes Wr, Planes Wt, int np,
+                          const int32_t* gate, hipStream_t s);
 // dimension ld.  The column version needs kColChunks * cols doubles of scratch.
 hipError_t launch_row_sqnorms(const float* M, int64_t rows, int64_t cols, int64_t ld, double* out,
                               const int32_t* gate, hipStream_t s);

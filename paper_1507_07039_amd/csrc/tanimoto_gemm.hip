@@ -5,10 +5,12 @@
 //   C update                    Eq. 5 on upper tiles of T(W^T, W), mirrored,
 //                               with the per-row sums for the sigma of Eq. 6
 //   W W^T partial products      first half of the P update (Eq. 5), split-K
-// FP32 form: v_mfma_f32_32x32x2f32 on FP32 operands.  Split-BF16 form: the
-// same products as hi*hi + hi*lo + lo*hi on v_mfma_f32_32x32x16_bf16 with an
-// FP32 accumulator; the diagonals of P and C (which grow like exp(2 alpha t),
-// Eq. 6) are kept out of the bf16 operands and added back in FP64 in the
+// The iteration's products run on bf16 planes of their operands
+// (v_mfma_f32_32x32x16_bf16, FP32 accumulator): two planes and three products
+// in the split-BF16 form, three exact planes and six products in the FP32
+// form.  The stand-alone Tfunction and the correlations use
+// v_mfma_f32_32x32x2f32.  The diagonals of P and C (which grow like exp(2
+// alpha t), Eq. 6) are kept out of the operands and added back in FP64 in the
 // epilogue (P_ii W_ij in R, W_ij C_jj in A).  Norms, denominators and h stay
 // FP64 in both forms.
 #include "epilogues.h"
@@ -19,12 +21,10 @@ namespace {
 using namespace gemm;
 
 // R = T(P, W) (Eq. 3) on 128 x 128 tiles of the symmetric product's block,
-// the same K = N_e as the C update: X = P (split-BF16: P's planes with rows
-// past N_e clamped; FP32: P read k-major, rows past N_e read into slack),
-// Y = W^T (its planes) or W; rows past N_e are never stored.  Both forms
-// compute the next iteration's R inside the C update's launch, as soon as P,
-// its diagonal and W's norms (and planes) are new: its tiles fill the
-// launch's last wave of C tiles.
+// the same K = N_e as the C update: X = P's planes (rows past N_e clamped), Y
+// = W^T's planes; rows past N_e are never stored.  The next iteration's R is
+// computed inside the C update's launch, as soon as P, its diagonal and W's
+// norms and planes are new: its tiles fill the launch's last wave of C tiles.
 template <class G>
 struct NextR {
   typename G::Ops ops;
@@ -40,20 +40,35 @@ constexpr int kNextRRun = 16;
 // The product of the tile, then the update in its epilogue (two blocks per
 // CU, so one block's epilogue overlaps the other's products).  With NR the
 // order also holds R tiles (kNextRTile).
-template <class G, bool SIGT, bool PK, bool NR>
+// LK: K past kFoldK (three planes), folded through LDS behind the stages.
+template <class G, bool SIGT, bool LK>
+constexpr int coreg_kernel_bytes() {
+  constexpr int main = G::MAIN_BYTES + (LK ? G::BM * G::BN * 4 : 0);
+  return main > coreg_smem_bytes<G, SIGT>() ? main : coreg_smem_bytes<G, SIGT>();
+}
+template <bool LK, class G>
+__device__ __forceinline__ void run_lk(G& g, const typename G::Ops& ops, int64_t m0, int64_t n0,
+                                       int64_t kbeg, int64_t kend, char* smem) {
+  if constexpr (LK)
+    g.template run_long<G::kFoldQ>(ops, m0, n0, kbeg, kend, smem, nullptr);
+  else
+    g.run(ops, m0, n0, kbeg, kend, smem);
+}
+
+template <class G, bool SIGT, bool PK, bool NR, bool LK>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_coreg_update(
     typename G::Ops ops, int64_t Kp, float* __restrict__ C, int64_t ldc, int64_t Na,
     const double* __restrict__ ncol, double alpha, double2* __restrict__ cstat,
     double* __restrict__ csq, int64_t ldstat, const uint32_t* __restrict__ order,
     const int32_t* gate, NextR<G> nr) {
   if (gate && *gate == 0) return;
-  __shared__ __align__(16) char smem[coreg_smem_bytes<G, SIGT>()];
+  __shared__ __align__(16) char smem[coreg_kernel_bytes<G, SIGT, LK>()];
   const uint32_t ij = order[xcd_tile(blockIdx.x, gridDim.x)];
   if constexpr (NR) {
     if (ij & kNextRTile) {
       const int64_t m0 = (int64_t)(ij & 0xffff) * kCB, n0 = (int64_t)((ij >> 16) & 0x7fff) * kCB;
       G g;
-      g.run(nr.ops, m0, n0, 0, Kp, smem);
+      run_lk<LK>(g, nr.ops, m0, n0, 0, Kp, smem);
       store_t_tile_xd<kNextRRun>(g, smem, nr.epi, m0, n0);
       return;
     }
@@ -62,21 +77,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int64_t m0 = I * kCB, n0 = J * kCB;
   const double nval = coreg_norm_load(ncol, I, J, Na);
   G g;
-  g.run(ops, m0, n0, 0, Kp, smem);
+  run_lk<LK>(g, ops, m0, n0, 0, Kp, smem);
   coreg_epilogue<SIGT, PK>(g, smem, I, J, C, ldc, Na, nval, alpha, cstat, csq, ldstat);
 }
 
 // R alone on the same tiles (same arithmetic, so R is the same bit for bit
 // whichever launch computed it): block b is tile (b % nRT, b / nRT).
-template <class G>
+template <class G, bool LK>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_resp_tiles(
     NextR<G> nr, int64_t Kp, int64_t nRT, const int32_t* gate) {
   if (gate && *gate == 0) return;
-  __shared__ __align__(16) char smem[G::MAIN_BYTES];
+  __shared__ __align__(16) char smem[G::MAIN_BYTES + (LK ? G::BM * G::BN * 4 : 0)];
   const int64_t b = xcd_tile(blockIdx.x, gridDim.x);
   const int64_t m0 = (b % nRT) * kCB, n0 = (b / nRT) * kCB;
   G g;
-  g.run(nr.ops, m0, n0, 0, Kp, smem);
+  run_lk<LK>(g, nr.ops, m0, n0, 0, Kp, smem);
   store_t_tile_xd<kNextRRun>(g, smem, nr.epi, m0, n0);
 }
 
@@ -98,14 +113,14 @@ __global__ __launch_bounds__(kThreads) void k_corr_sym(typename G::Ops ops, int6
 // P update, first half: each block writes the partial product of one upper
 // tile over one K chunk.
 
-template <class G>
+template <class G, bool LK>
 __global__ __launch_bounds__(kThreads) void k_coop_partial(typename G::Ops ops, int64_t Nep,
                                                            int64_t nU, int64_t chunk, int64_t Nap,
                                                            float* __restrict__ part,
                                                            const int32_t* gate) {
   if (gate && *gate == 0) return;
   static_assert(G::BM == kPB && G::BN == kPB, "square tiles");
-  __shared__ __align__(16) char smem[G::MAIN_BYTES];
+  __shared__ __align__(16) char smem[G::MAIN_BYTES + (LK ? G::BM * G::BN * 4 : 0)];
   const int64_t idx = xcd_tile(blockIdx.x, gridDim.x);
   const int64_t u = idx % nU, s = idx / nU;
   int64_t I, J;
@@ -115,7 +130,7 @@ __global__ __launch_bounds__(kThreads) void k_coop_partial(typename G::Ops ops, 
   if (kb > Nap) kb = Nap;
   if (ke > Nap) ke = Nap;
   G g;
-  g.run(ops, m0, n0, kb, ke, smem);
+  run_lk<LK>(g, ops, m0, n0, kb, ke, smem);
   float* ps = part + s * Nep * Nep;
   g.for_each([&](int r, int c, float v) { ps[(m0 + r) * Nep + n0 + c] = v; });
 }
@@ -125,12 +140,19 @@ __global__ __launch_bounds__(kThreads) void k_coop_partial(typename G::Ops ops, 
 // ---------------------------------------------------------------- launch --
 
 int64_t rect_tiles(int64_t Mp, int64_t Np) { return (Mp / RectF32::BM) * (Np / RectF32::BN); }
-int64_t rect_tiles_b3(int64_t Mp, int64_t Np) {
-  return ((Mp + RectB3D::BM - 1) / RectB3D::BM) * (Np / RectB3D::BN);
+template <int NP>
+constexpr bool kOneAvailGrid = Tiles<NP>::Rect::BM == Tiles<2>::Rect::BM &&
+                               Tiles<NP>::Rect::BN == Tiles<2>::Rect::BN &&
+                               Tiles<NP>::RectP::BM == Tiles<2>::Rect::BM &&
+                               Tiles<NP>::RectP::BN == Tiles<2>::Rect::BN;
+static_assert(kOneAvailGrid<2> && kOneAvailGrid<3>, "one slot layout for both forms and layouts");
+int64_t avail_hpart_slots(int64_t Mp, int64_t Np) {
+  using G = Tiles<2>::Rect;
+  return (Mp + G::BM - 1) / G::BM * (Np / G::BN) * kFixParts<G>;
 }
-static_assert(kFixParts<RectB3D> == kFixParts<RectB3DP>, "one slot layout for both C layouts");
-int64_t rect_hpart_slots_b3(int64_t Mp, int64_t Np) {
-  return rect_tiles_b3(Mp, Np) * kFixParts<RectB3D>;
+size_t rect_fold_floats(int64_t Kp, int np) {
+  using G = Tiles<3>::Rect;
+  return np == 3 && Kp > kFoldK ? (size_t)kFoldBlocks * G::BM * G::BN : 0;
 }
 size_t rect_partial_floats() {
   return (size_t)2 * (size_t)kMaxStreamKBlocks * RectF32::BM * RectF32::BN;
@@ -168,38 +190,31 @@ hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const floa
   return launch_rect<RectF32>(OpsF32{P, ldp, W, ldw}, Nep, Nap, Nep, epi, part, gate, s);
 }
 
-hipError_t launch_resp_b3(const bf16_t* Ph, const bf16_t* Pl, int64_t ldp, const double* dP,
-                          const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt, int64_t Nep,
-                          int64_t Nap, int64_t Ne, int64_t Na, const float* W, int64_t ldw,
-                          const double* nP, const double* nWc, float* R, float* part,
-                          const int32_t* gate, hipStream_t s) {
-  EpiStoreT epi{R, ldw, Ne, Na, nP, nWc, dP, W, ldw};
-  return launch_rect<RectB3>(OpsB3{Ph, Pl, ldp, Wth, Wtl, ldwt}, Nep, Nap, Nep, epi, part, gate, s);
+template <int NP, class Epi>
+static hipError_t avail_np(const Planes& Wr, const float* C, int64_t ld, int64_t Nep, int64_t Nap,
+                           const Epi& epi, float* part, float* fold, const int32_t* gate,
+                           hipStream_t s, bool packed) {
+  using T = Tiles<NP>;
+  const int64_t Mp = round_up(Nep, T::Rect::BM);
+  if (packed)
+    return launch_rect<typename T::RectP>(OpsB3FP{Wr, C, Nep}, Mp, Nap, Nap, epi, part, gate, s, fold);
+  return launch_rect<typename T::Rect>(OpsB3F{Wr, C, ld, Nep}, Mp, Nap, Nap, epi, part, gate, s, fold);
 }
 
-hipError_t launch_avail_wupdate(const float* Wold, const float* C, const double* dC,
-                                const float* R, float* Wnew, int64_t ld, int64_t Nep, int64_t Nap,
-                                int64_t Ne, int64_t Na, const double* nWrow, const double* nC,
-                                Rule rule, double* hpart, float* part, const int32_t* gate,
-                                hipStream_t s, bool packed) {
-  EpiWUpdate epi{Wold, R, Wnew, ld, Ne, Na, nWrow, nC, dC, rule.alpha, rule.h_undamped, hpart, 0.0};
-  if (packed)
-    return launch_rect<RectF32P>(OpsF32P{Wold, ld, C}, Nep, Nap, Nap, epi, part, gate, s);
-  return launch_rect<RectF32>(OpsF32{Wold, ld, C, ld}, Nep, Nap, Nap, epi, part, gate, s);
-}
-
-hipError_t launch_avail_wupdate_b3(const bf16_t* Wh, const bf16_t* Wl, const float* Wold,
-                                   const float* C, const double* dC, const float* R, float* Wnew,
-                                   int64_t ld, int64_t Nep, int64_t Nap, int64_t Ne, int64_t Na,
-                                   const double* nWrow, const double* nC, Rule rule,
-                                   double* hpart, float* part, const int32_t* gate,
-                                   hipStream_t s, bool packed) {
-  EpiWUpdate epi{Wold, R, Wnew, ld, Ne, Na, nWrow, nC, dC, rule.alpha, rule.h_undamped, hpart, 0.0};
-  // C is symmetric: its row n is the column n the product needs
-  const int64_t Mp = (Nep + RectB3D::BM - 1) / RectB3D::BM * RectB3D::BM;
-  if (packed)
-    return launch_rect<RectB3DP>(OpsB3FP{Wh, Wl, ld, C, Nep}, Mp, Nap, Nap, epi, part, gate, s);
-  return launch_rect<RectB3D>(OpsB3F{Wh, Wl, ld, C, ld, Nep}, Mp, Nap, Nap, epi, part, gate, s);
+hipError_t launch_avail_wupdate(const Planes& Wr, int np, const float* Wold, const float* C,
+                                const double* dC, const float* R, float* Wnew, int64_t ld,
+                                int64_t Nep, int64_t Nap, int64_t Ne, int64_t Na,
+                                const double* nWrow, const double* nC, Rule rule, double* hpart,
+                                float* part, float* fold, const int32_t* gate, hipStream_t s,
+                                bool packed) {
+  if (np == 2) {
+    const EpiWUpdate epi{Wold, R,  Wnew,       ld,              Ne,    Na, nWrow,
+                         nC,   dC, rule.alpha, rule.h_undamped, hpart, 0.0};
+    return avail_np<2>(Wr, C, ld, Nep, Nap, epi, part, nullptr, gate, s, packed);
+  }
+  const EpiWUpdateT<true> epi{nullptr, R,  Wnew,       ld,              Ne,    Na,  nWrow,
+                              nC,      dC, rule.alpha, rule.h_undamped, hpart, 0.0, Wr};
+  return avail_np<3>(Wr, C, ld, Nep, Nap, epi, part, fold, gate, s, packed);
 }
 
 int64_t coreg_slots(int64_t Nap) { return Nap / kCB; }
@@ -221,13 +236,24 @@ static hipError_t coreg_launch_pk(const typename G::Ops& ops, int64_t Nep, float
                                   double2* cstat, double* csq, const uint32_t* order,
                                   const int32_t* gate, hipStream_t s, const NextR<G>& nr,
                                   int64_t extra) {
-  const unsigned nb = (unsigned)(coreg_tiles(Nap) + extra);
+  const dim3 nb((unsigned)(coreg_tiles(Nap) + extra));
+  auto go = [&](auto* fn) {
+    fn<<<nb, dim3(kThreads), 0, s>>>(ops, Nep, C, ldc, Na, nWcol, rule.alpha, cstat, csq, Nap, order,
+                                     gate, nr);
+  };
+  if constexpr (folds_k<G>::value) {
+    if (Nep > kFoldK) {
+      if (rule.sigma_from_T)
+        go(k_coreg_update<G, true, PK, NR, true>);
+      else
+        go(k_coreg_update<G, false, PK, NR, true>);
+      return hipGetLastError();
+    }
+  }
   if (rule.sigma_from_T)
-    k_coreg_update<G, true, PK, NR><<<dim3(nb), dim3(kThreads), 0, s>>>(
-        ops, Nep, C, ldc, Na, nWcol, rule.alpha, cstat, csq, Nap, order, gate, nr);
+    go(k_coreg_update<G, true, PK, NR, false>);
   else
-    k_coreg_update<G, false, PK, NR><<<dim3(nb), dim3(kThreads), 0, s>>>(
-        ops, Nep, C, ldc, Na, nWcol, rule.alpha, cstat, csq, Nap, order, gate, nr);
+    go(k_coreg_update<G, false, PK, NR, false>);
   return hipGetLastError();
 }
 
@@ -243,24 +269,17 @@ static hipError_t coreg_launch(const typename G::Ops& ops, int64_t Nep, float* C
                                                 csq, order, gate, s, nr, extra);
 }
 
-hipError_t launch_coreg_update(const float* W, int64_t ldw, int64_t Nep, float* C, int64_t ldc,
-                               int64_t Nap, int64_t Na, const double* nWcol, Rule rule,
-                               double2* cstat, double* csq, const uint32_t* order,
+hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Nep, float* C,
+                               int64_t ldc, int64_t Nap, int64_t Na, const double* nWcol,
+                               Rule rule, double2* cstat, double* csq, const uint32_t* order,
                                const int32_t* gate, hipStream_t s, bool packed) {
-  // X = W^T (gene m, tf k) = W[k][m]; Y = W (tf k, gene n) = W[k][n].
-  return coreg_launch<SymF32>(OpsF32{W, ldw, W, ldw}, Nep, C, ldc, Nap, Na, nWcol, rule, cstat,
-                              csq, order, gate, s, packed);
-}
-
-hipError_t launch_coreg_update_b3(const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt, int64_t Nep,
-                                  float* C, int64_t ldc, int64_t Nap, int64_t Na,
-                                  const double* nWcol, Rule rule, double2* cstat, double* csq,
-                                  const uint32_t* order, const int32_t* gate, hipStream_t s,
-                                  bool packed) {
   // X = Yt = W^T stored gene-major: row m of W^T is column m of W.  Only the
   // FP32 C is written; the next A product splits it while staging.
-  return coreg_launch<SymB3>(OpsB3{Wth, Wtl, ldwt, Wth, Wtl, ldwt}, Nep, C, ldc, Nap, Na, nWcol,
-                             rule, cstat, csq, order, gate, s, packed);
+  const OpsB3 ops{Wt, Wt};
+  return np == 2 ? coreg_launch<Tiles<2>::Sym>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq,
+                                               order, gate, s, packed)
+                 : coreg_launch<Tiles<3>::Sym>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq,
+                                               order, gate, s, packed);
 }
 
 int64_t next_r_row_tiles(int64_t Nep) { return (Nep + kCB - 1) / kCB; }
@@ -283,77 +302,58 @@ void coreg_next_r_order_fill(int64_t Nep, int64_t Nap, const uint32_t* corder, u
   }
 }
 
-// FP32 form: X = P read k-major (P[k][i] = P[i][k]); the rows of the last
-// row tile past N_e read past row N_e - 1 into the slack P is allocated with
-// (next_r_p_slack floats), and their outputs are never stored.
-static NextR<SymF32> next_r_args_f32(const float* P, int64_t ldp, const double* dP,
-                                     const double* nP, const float* W, int64_t ldw, int64_t Ne,
-                                     int64_t Na, const double* nWc, float* R) {
-  NextR<SymF32> nr;
-  nr.ops = OpsF32{P, ldp, W, ldw};
+template <class G>
+static NextR<G> next_r_args(const Planes& Pp, const double* dP, const double* nP,
+                            const Planes& Wt, const float* W, int64_t ldw, int64_t Ne,
+                            int64_t Na, const double* nWc, float* R) {
+  NextR<G> nr;
+  nr.ops = OpsB3{Pp, Wt, Pp.rows};  // P has N_e (padded) rows
   nr.epi = EpiStoreT{R, ldw, Ne, Na, nP, nWc, dP, W, ldw};
   return nr;
 }
-int64_t next_r_p_slack(int64_t Nep) { return next_r_row_tiles(Nep) * kCB - Nep; }
 
-hipError_t launch_resp_tiles(const float* P, int64_t ldp, const double* dP, int64_t Nap,
-                             int64_t Ne, int64_t Na, const float* W, int64_t ldw,
-                             const double* nP, const double* nWc, float* R, const int32_t* gate,
-                             hipStream_t s) {
-  if (ldp % SymF32::BK || Nap % kCB) return hipErrorInvalidValue;
-  k_resp_tiles<SymF32><<<dim3((unsigned)next_r_tiles(ldp, Nap)), dim3(kThreads), 0, s>>>(
-      next_r_args_f32(P, ldp, dP, nP, W, ldw, Ne, Na, nWc, R), ldp, next_r_row_tiles(ldp), gate);
+template <class G, bool LK>
+static hipError_t resp_tiles_launch(const NextR<G>& nr, int64_t ldp, int64_t Nap,
+                                    const int32_t* gate, hipStream_t s) {
+  k_resp_tiles<G, LK><<<dim3((unsigned)next_r_tiles(ldp, Nap)), dim3(kThreads), 0, s>>>(
+      nr, ldp, next_r_row_tiles(ldp), gate);
   return hipGetLastError();
 }
 
-hipError_t launch_coreg_update_next_r(const float* W, int64_t ldw, int64_t Nep, float* C,
-                                      int64_t ldc, int64_t Nap, int64_t Na, const double* nWcol,
-                                      Rule rule, double2* cstat, double* csq,
-                                      const uint32_t* order_r, const int32_t* gate, hipStream_t s,
-                                      bool packed, const float* P, const double* dP,
-                                      const double* nP, int64_t Ne, float* R) {
-  if (Nep % SymF32::BK || Nap % kCB) return hipErrorInvalidValue;
-  return coreg_launch<SymF32, true>(
-      OpsF32{W, ldw, W, ldw}, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq, order_r, gate, s,
-      packed, next_r_args_f32(P, Nep, dP, nP, W, ldw, Ne, Na, nWcol, R), next_r_tiles(Nep, Nap));
-}
-
-static NextR<SymB3> next_r_args(const bf16_t* Ph, const bf16_t* Pl, int64_t ldp, const double* dP,
-                                const double* nP, const bf16_t* Wth, const bf16_t* Wtl,
-                                int64_t ldwt, const float* W, int64_t ldw, int64_t Ne, int64_t Na,
-                                const double* nWc, float* R) {
-  NextR<SymB3> nr;
-  nr.ops = OpsB3{Ph, Pl, ldp, Wth, Wtl, ldwt, ldp};  // P has ldp (= N_e padded) rows
-  nr.epi = EpiStoreT{R, ldw, Ne, Na, nP, nWc, dP, W, ldw};
-  return nr;
-}
-
-hipError_t launch_resp_tiles_b3(const bf16_t* Ph, const bf16_t* Pl, int64_t ldp, const double* dP,
-                                const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt, int64_t Nap,
-                                int64_t Ne, int64_t Na, const float* W, int64_t ldw,
-                                const double* nP, const double* nWc, float* R,
-                                const int32_t* gate, hipStream_t s) {
+hipError_t launch_resp_tiles(const Planes& Pp, const Planes& Wt, int np, int64_t ldp,
+                             const double* dP, int64_t Nap, int64_t Ne, int64_t Na,
+                             const float* W, int64_t ldw, const double* nP, const double* nWc,
+                             float* R, const int32_t* gate, hipStream_t s) {
   if (ldp % SymB3::BK || Nap % kCB) return hipErrorInvalidValue;
-  const int64_t nRT = next_r_row_tiles(ldp);
-  k_resp_tiles<SymB3><<<dim3((unsigned)next_r_tiles(ldp, Nap)), dim3(kThreads), 0, s>>>(
-      next_r_args(Ph, Pl, ldp, dP, nP, Wth, Wtl, ldwt, W, ldw, Ne, Na, nWc, R), ldp, nRT, gate);
-  return hipGetLastError();
+  using G2 = Tiles<2>::Sym;
+  using G3 = Tiles<3>::Sym;
+  if (np == 2)
+    return resp_tiles_launch<G2, false>(next_r_args<G2>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWc, R),
+                                        ldp, Nap, gate, s);
+  const NextR<G3> nr = next_r_args<G3>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWc, R);
+  return ldp > kFoldK ? resp_tiles_launch<G3, true>(nr, ldp, Nap, gate, s)
+                      : resp_tiles_launch<G3, false>(nr, ldp, Nap, gate, s);
 }
 
-hipError_t launch_coreg_update_next_r_b3(const bf16_t* Wth, const bf16_t* Wtl, int64_t ldwt,
-                                         int64_t Nep, float* C, int64_t ldc, int64_t Nap,
-                                         int64_t Na, const double* nWcol, Rule rule,
-                                         double2* cstat, double* csq, const uint32_t* order_r,
-                                         const int32_t* gate, hipStream_t s, bool packed,
-                                         const bf16_t* Ph, const bf16_t* Pl, const double* dP,
-                                         const double* nP, const float* W, int64_t ldw,
-                                         int64_t Ne, float* R) {
+hipError_t launch_coreg_update_next_r(const Planes& Wt, int np, int64_t Nep,
+                                      float* C, int64_t ldc, int64_t Nap, int64_t Na,
+                                      const double* nWcol, Rule rule, double2* cstat, double* csq,
+                                      const uint32_t* order_r, const int32_t* gate, hipStream_t s,
+                                      bool packed, const Planes& Pp, const double* dP,
+                                      const double* nP, const float* W, int64_t ldw, int64_t Ne,
+                                      float* R) {
   if (Nep % SymB3::BK || Nap % kCB) return hipErrorInvalidValue;
-  return coreg_launch<SymB3, true>(
-      OpsB3{Wth, Wtl, ldwt, Wth, Wtl, ldwt}, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq,
-      order_r, gate, s, packed,
-      next_r_args(Ph, Pl, Nep, dP, nP, Wth, Wtl, ldwt, W, ldw, Ne, Na, nWcol, R),
-      next_r_tiles(Nep, Nap));
+  using G2 = Tiles<2>::Sym;
+  using G3 = Tiles<3>::Sym;
+  const OpsB3 ops{Wt, Wt};
+  const int64_t extra = next_r_tiles(Nep, Nap);
+  if (np == 2)
+    return coreg_launch<G2, true>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq, order_r, gate,
+                                  s, packed,
+                                  next_r_args<G2>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWcol, R), extra);
+  return coreg_launch<G3, true>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq, order_r, gate, s,
+                                packed, next_r_args<G3>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWcol, R),
+                                extra);
 }
 
 int coop_splits(int64_t Nep, int64_t Nap, int64_t blocks) {
@@ -369,20 +369,14 @@ static int64_t coop_chunk(int64_t Nap, int splits) {
   return round_up((Nap + splits - 1) / splits, CoopF32::BK);
 }
 
-hipError_t launch_coop_partial(const float* W, int64_t ldw, int64_t Nep, int64_t Nap, int splits,
+hipError_t launch_coop_partial(const Planes& Wr, int np, int64_t Nep, int64_t Nap, int splits,
                                float* part, const int32_t* gate, hipStream_t s) {
-  const int64_t nT = Nep / kPB, nU = nT * (nT + 1) / 2;
-  k_coop_partial<CoopF32><<<dim3((unsigned)(nU * splits)), dim3(kThreads), 0, s>>>(
-      OpsF32{W, ldw, W, ldw}, Nep, nU, coop_chunk(Nap, splits), Nap, part, gate);
-  return hipGetLastError();
-}
-
-hipError_t launch_coop_partial_b3(const bf16_t* Wh, const bf16_t* Wl, int64_t ldw, int64_t Nep,
-                                  int64_t Nap, int splits, float* part, const int32_t* gate,
-                                  hipStream_t s) {
-  const int64_t nT = Nep / kPB, nU = nT * (nT + 1) / 2;
-  k_coop_partial<CoopB3P><<<dim3((unsigned)(nU * splits)), dim3(kThreads), 0, s>>>(
-      OpsB3{Wh, Wl, ldw, Wh, Wl, ldw}, Nep, nU, coop_chunk(Nap, splits), Nap, part, gate);
+  const int64_t nT = Nep / kPB, nU = nT * (nT + 1) / 2, chunk = coop_chunk(Nap, splits);
+  auto* fn = np == 2          ? k_coop_partial<Tiles<2>::Coop, false>
+             : chunk > kFoldK ? k_coop_partial<Tiles<3>::Coop, true>
+                              : k_coop_partial<Tiles<3>::Coop, false>;
+  fn<<<dim3((unsigned)(nU * splits)), dim3(kThreads), 0, s>>>(OpsB3{Wr, Wr}, Nep, nU, chunk, Nap,
+                                                              part, gate);
   return hipGetLastError();
 }
 

@@ -27,10 +27,37 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 __device__ __forceinline__ bf16_t to_bf16(float x) {
   return __builtin_bit_cast(bf16_t, (__bf16)x);
 }
-// hi = bf16(x), lo = bf16(x - hi), both rounded to nearest even.
-__device__ __forceinline__ void split_bf16(float x, bf16_t& hi, bf16_t& lo) {
-  hi = to_bf16(x);
-  lo = to_bf16(x - (float)__builtin_bit_cast(__bf16, hi));
+// The bf16 planes of x.  Two: hi = RNE(x), lo = RNE(x - hi).  Three: x = hi +
+// mid + lo exactly (hi truncated, so that no finite x overflows; mid rounded;
+// lo holds the 8 bits that are left); an infinity or NaN is its hi alone, so
+// that x is their sum for every x (join_planes).
+template <int NP>
+__device__ __forceinline__ void split_planes(float x, bf16_t (&o)[3]) {
+  if constexpr (NP == 2) {
+    o[0] = to_bf16(x);
+    o[1] = to_bf16(x - (float)__builtin_bit_cast(__bf16, o[0]));
+  } else {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+    o[0] = (bf16_t)((u >> 16) | ((u & 0x7fffffffu) > 0x7f800000u ? 0x40u : 0u));
+    const float r = fin ? x - __builtin_bit_cast(float, u & 0xffff0000u) : 0.0f;
+    o[1] = to_bf16(r);
+    o[2] = (bf16_t)(__builtin_bit_cast(unsigned, r - (float)__builtin_bit_cast(__bf16, o[1])) >> 16);
+  }
+}
+
+// Entry (r, k) of a matrix's np planes.
+__device__ __forceinline__ void put_planes(const Planes& P, int np, int64_t r, int64_t k, float x) {
+  bf16_t o[3];
+  int64_t at;
+  if (np == 2) {
+    split_planes<2>(x, o);
+    at = plane_index<plane_kt(2)>(P.rows, r, k);
+  } else {
+    split_planes<3>(x, o);
+    at = plane_index<plane_kt(3)>(P.rows, r, k);
+  }
+  for (int q = 0; q < np; ++q) P.p[q * P.stride + at] = o[q];
 }
 
 // h = (1 / count) * sum of the n per-tile partials (Eq. 7); advance t, flip
@@ -71,11 +98,11 @@ __device__ __forceinline__ void finish_h(const double* __restrict__ hpart, int64
 // P update, second half (Eq. 5), entry e of the row-major Ne x Ne matrix:
 // for i < j sum the split-K partial products, form T(W_i., W_j.) with the
 // row norms of the new W and write the damped value at (i, j) and (j, i)
-// (and the hi/lo planes, and the fresh similarity when Tside is set).
+// (and its np planes, and the fresh similarity when Tside is set).
 __device__ __forceinline__ void coop_finalize_entry(
     int64_t e, const float* __restrict__ part, int splits, int64_t Nep,
     const double* __restrict__ nW, float* __restrict__ P, int64_t ldp, int64_t Ne, double alpha,
-    float* __restrict__ Tside, bf16_t* __restrict__ Ph, bf16_t* __restrict__ Pl) {
+    float* __restrict__ Tside, Planes Pp, int np) {
   if (e >= Ne * Ne) return;
   const int64_t i = e / Ne, j = e % Ne;
   if (i >= j) return;
@@ -98,11 +125,9 @@ __device__ __forceinline__ void coop_finalize_entry(
   const float v = (float)((1.0 - alpha) * (double)P[i * ldp + j] + alpha * tv);
   P[i * ldp + j] = v;
   P[j * ldp + i] = v;
-  if (Ph) {
-    bf16_t h, l;
-    split_bf16(v, h, l);
-    Ph[i * ldp + j] = Ph[j * ldp + i] = h;
-    Pl[i * ldp + j] = Pl[j * ldp + i] = l;
+  if (np) {
+    put_planes(Pp, np, i, j, v);
+    put_planes(Pp, np, j, i, v);
   }
   if (Tside) {
     Tside[i * ldp + j] = (float)tv;

@@ -9,7 +9,7 @@ namespace panda {
 namespace {
 
 using upd::block_sum;
-using upd::split_bf16;
+using upd::split_planes;
 constexpr int kRT = upd::kUT;  // threads per block for the kernels in this file
 
 __global__ __launch_bounds__(kRT) void k_finish_h(const double* __restrict__ hpart, int64_t n,
@@ -22,10 +22,10 @@ __global__ __launch_bounds__(kRT) void k_finish_h(const double* __restrict__ hpa
 __global__ __launch_bounds__(kRT) void k_coop_finalize(
     const float* __restrict__ part, int splits, int64_t Nep, const double* __restrict__ nW,
     float* __restrict__ P, int64_t ldp, int64_t Ne, double alpha, float* __restrict__ Tside,
-    bf16_t* __restrict__ Ph, bf16_t* __restrict__ Pl, const int32_t* gate) {
+    Planes Pp, int np, const int32_t* gate) {
   if (*gate == 0) return;
   upd::coop_finalize_entry((int64_t)blockIdx.x * kRT + threadIdx.x, part, splits, Nep, nW, P, ldp,
-                           Ne, alpha, Tside, Ph, Pl);
+                           Ne, alpha, Tside, Pp, np);
 }
 
 // Eq. 6 for both networks.  Blocks [0, Ne): row i of P; remaining blocks:
@@ -159,24 +159,26 @@ __global__ __launch_bounds__(kRT) void k_pearson_z(const float* __restrict__ E, 
   }
 }
 
-// ---- split-BF16 operand planes ----------------------------------------------
+// ---- bf16 operand planes ----------------------------------------------------
 // Planes of P without its diagonal (which lives in its FP64 vector).
 __global__ __launch_bounds__(kRT) void k_split_offdiag(const float* __restrict__ M, int64_t n,
-                                                       int64_t ld, bf16_t* __restrict__ Mh,
-                                                       bf16_t* __restrict__ Ml) {
+                                                       int64_t ld, Planes out, int np) {
   const int64_t tot = n * n;
   for (int64_t e = (int64_t)blockIdx.x * kRT + threadIdx.x; e < tot; e += (int64_t)gridDim.x * kRT) {
     const int64_t i = e / n, j = e % n;
-    bf16_t h = 0, l = 0;
-    if (i != j) split_bf16(M[i * ld + j], h, l);
-    Mh[i * ld + j] = h;
-    Ml[i * ld + j] = l;
+    upd::put_planes(out, np, i, j, i != j ? M[i * ld + j] : 0.0f);
   }
+}
+
+__global__ __launch_bounds__(kRT) void k_join_planes(Planes P, int64_t cols,
+                                                     float* __restrict__ out, int64_t ldo) {
+  const int64_t r = blockIdx.y, k = (int64_t)blockIdx.x * kRT + threadIdx.x;
+  if (k < cols) out[r * ldo + k] = join_planes(P, r, k);
 }
 
 // ---- squared norms --------------------------------------------------------
 // Squared norms of the rows and columns of W in one pass (Eq. 9 needs
-// |W_i.|^2 and |W_.j|^2), and with SHADOW also its bf16 hi/lo planes,
+// |W_i.|^2 and |W_.j|^2), and with NP > 0 also its NP bf16 planes,
 // row-major and gene-major.  Block (bx, by) takes the 64 x 64 tile at rows
 // 64 by, columns 64 bx and writes FP64 partial sums: rowpart[bx][r] over its
 // 64 columns, colpart[by][c] over its 64 rows; k_w_norms_sum adds them up in
@@ -186,15 +188,12 @@ __global__ __launch_bounds__(kRT) void k_split_offdiag(const float* __restrict__
 // the quad of lanes.  The planes are written whole tiles at a time from the
 // staged tile, 8 entries (16 bytes) per store; entries past Ne x Na are zero
 // in the tile, so the padding of the planes stays zero.
-template <bool SHADOW>
+template <int NP>
 __global__ __launch_bounds__(kRT) void k_w_norms(const float* __restrict__ W, int64_t Ne,
                                                  int64_t Na, int64_t ldw, int64_t Nep,
                                                  double* __restrict__ rowpart,
                                                  double* __restrict__ colpart,
-                                                 bf16_t* __restrict__ Wh, bf16_t* __restrict__ Wl,
-                                                 bf16_t* __restrict__ Wth,
-                                                 bf16_t* __restrict__ Wtl, int64_t ldt,
-                                                 const int32_t* gate) {
+                                                 Planes Wr, Planes Wt, const int32_t* gate) {
   __shared__ float tile[64][65];
   __shared__ double cred[4][64];
   if (gate && *gate == 0) return;
@@ -233,31 +232,37 @@ __global__ __launch_bounds__(kRT) void k_w_norms(const float* __restrict__ W, in
   if (ty == 0)
     colpart[(int64_t)blockIdx.y * gridDim.x * 64 + c0 + tx] =
         ((cred[0][tx] + cred[1][tx]) + cred[2][tx]) + cred[3][tx];
-  if constexpr (SHADOW) {
-    // thread t: line t / 8 (+ 32 in the second pass), entries 8 (t % 8) .. +7
-    const int q = threadIdx.x & 7;
+  if constexpr (NP > 0) {
+    // 64 lines x 8 chunks of 8 entries (16 bytes), in the planes' own order:
+    // a K-tile of the planes holds CT chunks of each line, line after line, so
+    // consecutive threads write consecutive bytes
+    constexpr int KT = plane_kt(NP), CT = KT / 8;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-      const int line = (int)(threadIdx.x >> 3) + 32 * pass;
-      unsigned rh[4], rl[4], th[4], tl[4];
+      const int id = (int)threadIdx.x + kRT * pass;
+      const int line = (id / CT) % 64, q = id % CT + CT * (id / (64 * CT));
+      unsigned r[3][4], t[3][4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        bf16_t h0, l0, h1, l1;
-        split_bf16(tile[line][8 * q + 2 * e], h0, l0);  // row line, along the columns
-        split_bf16(tile[line][8 * q + 2 * e + 1], h1, l1);
-        rh[e] = (unsigned)h0 | ((unsigned)h1 << 16);
-        rl[e] = (unsigned)l0 | ((unsigned)l1 << 16);
-        split_bf16(tile[8 * q + 2 * e][line], h0, l0);  // column line, along the rows
-        split_bf16(tile[8 * q + 2 * e + 1][line], h1, l1);
-        th[e] = (unsigned)h0 | ((unsigned)h1 << 16);
-        tl[e] = (unsigned)l0 | ((unsigned)l1 << 16);
+        bf16_t a[3], b[3];
+        split_planes<NP>(tile[line][8 * q + 2 * e], a);  // row line, along the columns
+        split_planes<NP>(tile[line][8 * q + 2 * e + 1], b);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) r[p][e] = (unsigned)a[p] | ((unsigned)b[p] << 16);
+        split_planes<NP>(tile[8 * q + 2 * e][line], a);  // column line, along the rows
+        split_planes<NP>(tile[8 * q + 2 * e + 1][line], b);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) t[p][e] = (unsigned)a[p] | ((unsigned)b[p] << 16);
       }
-      const int64_t ro = (r0 + line) * ldw + c0 + 8 * q;  // rows < Nep, columns < ldw
-      const int64_t to = (c0 + line) * ldt + r0 + 8 * q;  // columns < ldw, rows < ldt
-      *reinterpret_cast<uint4*>(Wh + ro) = make_uint4(rh[0], rh[1], rh[2], rh[3]);
-      *reinterpret_cast<uint4*>(Wl + ro) = make_uint4(rl[0], rl[1], rl[2], rl[3]);
-      *reinterpret_cast<uint4*>(Wth + to) = make_uint4(th[0], th[1], th[2], th[3]);
-      *reinterpret_cast<uint4*>(Wtl + to) = make_uint4(tl[0], tl[1], tl[2], tl[3]);
+      const int64_t ro = plane_index<KT>(Wr.rows, r0 + line, c0 + 8 * q);
+      const int64_t to = plane_index<KT>(Wt.rows, c0 + line, r0 + 8 * q);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        *reinterpret_cast<uint4*>(Wr.p + p * Wr.stride + ro) =
+            make_uint4(r[p][0], r[p][1], r[p][2], r[p][3]);
+        *reinterpret_cast<uint4*>(Wt.p + p * Wt.stride + to) =
+            make_uint4(t[p][0], t[p][1], t[p][2], t[p][3]);
+      }
     }
   }
 }
@@ -669,16 +674,23 @@ hipError_t launch_finish_h(const double* hpart, int64_t n, int64_t count, DevSta
 
 hipError_t launch_coop_finalize(const float* part, int splits, int64_t Nep, const double* nWrow,
                                 float* P, int64_t ldp, int64_t Ne, Rule rule, float* Tside,
-                                bf16_t* Ph, bf16_t* Pl, const int32_t* gate, hipStream_t s) {
+                                Planes Pp, int np, const int32_t* gate, hipStream_t s) {
   const int64_t n = Ne * Ne;
   k_coop_finalize<<<dim3((unsigned)((n + kRT - 1) / kRT)), kRT, 0, s>>>(
-      part, splits, Nep, nWrow, P, ldp, Ne, rule.alpha, Tside, Ph, Pl, gate);
+      part, splits, Nep, nWrow, P, ldp, Ne, rule.alpha, Tside, Pp, np, gate);
   return hipGetLastError();
 }
 
-hipError_t launch_split_offdiag(const float* M, int64_t n, int64_t ld, bf16_t* Mh, bf16_t* Ml,
+hipError_t launch_split_offdiag(const float* M, int64_t n, int64_t ld, Planes out, int np,
                                 hipStream_t s) {
-  k_split_offdiag<<<grid_for(n * n, 8192), kRT, 0, s>>>(M, n, ld, Mh, Ml);
+  k_split_offdiag<<<grid_for(n * n, 8192), kRT, 0, s>>>(M, n, ld, out, np);
+  return hipGetLastError();
+}
+
+hipError_t launch_join_planes(const Planes& P, int64_t rows, int64_t cols, float* out, int64_t ldo,
+                              hipStream_t s) {
+  k_join_planes<<<dim3((unsigned)((cols + kRT - 1) / kRT), (unsigned)rows), kRT, 0, s>>>(P, cols,
+                                                                                         out, ldo);
   return hipGetLastError();
 }
 
@@ -742,20 +754,16 @@ size_t w_norm_scratch_doubles(int64_t Nep, int64_t Nap) {
 }
 
 hipError_t launch_w_norms(const float* W, int64_t Ne, int64_t Na, int64_t ldw, int64_t Nep,
-                          double* nr, double* nc, double* scr, bf16_t* Wh, bf16_t* Wl, bf16_t* Wth,
-                          bf16_t* Wtl, int64_t ldt, const int32_t* gate, hipStream_t s) {
+                          double* nr, double* nc, double* scr, Planes Wr, Planes Wt, int np,
+                          const int32_t* gate, hipStream_t s) {
   const int64_t Nap = ldw;
   if (Nep % 64 || Nap % 64 || Ne > Nep || Na > Nap) return hipErrorInvalidValue;
-  if (Wh && (ldt < Nep || ldt % 8)) return hipErrorInvalidValue;  // 16-byte plane stores
+  if (np && (Wr.rows != Nep || Wt.rows != Nap)) return hipErrorInvalidValue;
   double* rowpart = scr;
   double* colpart = scr + (Nap / 64) * Nep;
   const dim3 grid((unsigned)(Nap / 64), (unsigned)(Nep / 64));
-  if (Wh)
-    k_w_norms<true><<<grid, kRT, 0, s>>>(W, Ne, Na, ldw, Nep, rowpart, colpart, Wh, Wl, Wth, Wtl,
-                                         ldt, gate);
-  else
-    k_w_norms<false><<<grid, kRT, 0, s>>>(W, Ne, Na, ldw, Nep, rowpart, colpart, nullptr, nullptr,
-                                          nullptr, nullptr, ldt, gate);
+  auto* fn = np == 0 ? k_w_norms<0> : np == 2 ? k_w_norms<2> : k_w_norms<3>;
+  fn<<<grid, kRT, 0, s>>>(W, Ne, Na, ldw, Nep, rowpart, colpart, Wr, Wt, gate);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t nb = Nep + (Nap + kRT - 1) / kRT;

@@ -14,6 +14,8 @@ namespace {
 
 struct FeatLayout {
   float* S;  // Nep x Nap: A0, then S = (R0 + A0) / 2
+  float* R;  // Nep x Nap: R0, then S - W0
+  float* part;  // split tiles of the two products
   double *dr, *dc, *omP, *omC, *tmpP, *yP, *a, *zP, *b, *tmpC, *yC, *d, *zC, *c;
   double *LinvP, *LinvC, *mom, *zsW, *zsS, *zsD;
   VecRefHost* vref;
@@ -27,6 +29,8 @@ size_t feat_layout(int64_t Ne, int64_t Na, char* base, FeatLayout* L) {
   Carver cv{base};
   FeatLayout l;
   l.S = cv.take<float>((size_t)Nep * Nap);
+  l.R = cv.take<float>((size_t)Nep * Nap);
+  l.part = cv.take<float>(rect_partial_floats());
   l.dr = cv.take<double>((size_t)Ne);
   l.dc = cv.take<double>((size_t)Na);
   double** sixNe[] = {&l.omP, &l.tmpP, &l.yP, &l.a, &l.zP, &l.c};
@@ -68,19 +72,19 @@ panda_status panda_ws_features(panda_ctx* c, const float* omegaP, const float* o
   FeatLayout L;
   feat_layout(Ne, Na, static_cast<char*>(workspace), &L);
   hipStream_t s = c->stream;
-  c->r_next = false;  // R serves as scratch below
-  const float* W0 = c->W[c->executed & 1];
+  float* W0 = nullptr;
+  PANDA_TRY(ctx_current_w(c, &W0));
   // one-step similarities R0 = T(P0, W0) (into R) and A0 = T(W0, C0) (into S)
-  HIP_TRY(launch_resp(c->P, Nep, c->dP, W0, Nap, Nep, Nap, Ne, Na, c->nP, c->nWc, c->R,
-                      c->skpart, nullptr, s));
+  HIP_TRY(launch_resp(c->P, Nep, c->dP, W0, Nap, Nep, Nap, Ne, Na, c->nP, c->nWc, L.R, L.part,
+                      nullptr, s));
   HIP_TRY(launch_tanimoto_store(W0, Nap, c->C, Nap, Nep, Nap, Nap, Ne, Na, c->nWr, c->nC, L.S,
-                                Nap, c->skpart, nullptr, s, c->dC));
-  HIP_TRY(launch_half_sum(c->R, L.S, Ne, Na, Nap, s));
+                                Nap, L.part, nullptr, s, c->dC));
+  HIP_TRY(launch_half_sum(L.R, L.S, Ne, Na, Nap, s));
   // statistics of W0, S and S - W0 (tau)
   HIP_TRY(launch_zscore_stats(W0, Ne, Na, Nap, L.zsW, s));
   HIP_TRY(launch_zscore_stats(L.S, Ne, Na, Nap, L.zsS, s));
-  HIP_TRY(launch_ws_affine(L.S, Nap, W0, Nap, Ne, Na, 1.0, -1.0, c->R, Nap, s));
-  HIP_TRY(launch_zscore_stats(c->R, Ne, Na, Nap, L.zsD, s));
+  HIP_TRY(launch_ws_affine(L.S, Nap, W0, Nap, Ne, Na, 1.0, -1.0, L.R, Nap, s));
+  HIP_TRY(launch_zscore_stats(L.R, Ne, Na, Nap, L.zsD, s));
   // degrees and the two sketch bases
   HIP_TRY(launch_degrees(W0, Ne, Na, Nap, L.dr, L.dc, s));
   // the sketches use the whole P0 and C0: their diagonals go back in for now
@@ -192,26 +196,18 @@ panda_status panda_ws_init(panda_ctx* c, const float* Wpred, int32_t t0) {
   HIP_TRY(hipMemcpy2DAsync(c->W[0], (size_t)Nap * 4, Wpred, (size_t)Na * 4, (size_t)Na * 4,
                            (size_t)Ne, hipMemcpyDeviceToDevice, s));
   float* W = c->W[0];
-  HIP_TRY(launch_w_norms(W, Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wh, c->Wl, c->Wth,
-                         c->Wtl, Nep, nullptr, s));
+  HIP_TRY(launch_w_norms(W, Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt, c->np,
+                         nullptr, s));
   HIP_TRY(launch_state_set(c->st, t0, 1, 1, s));
   const int32_t* run_pc = &c->st->run_pc;
   // off-diagonals: the update rule of Eq. 5 with alpha = 1 gives T itself
   Rule r1 = c->rule;
   r1.alpha = 1.0;
-  if (c->b3)
-    HIP_TRY(launch_coop_partial_b3(c->Wh, c->Wl, Nap, Nep, Nap, c->splits, c->ppart, run_pc, s));
-  else
-    HIP_TRY(launch_coop_partial(W, Nap, Nep, Nap, c->splits, c->ppart, run_pc, s));
-  HIP_TRY(launch_coop_finalize(c->ppart, c->splits, Nep, c->nWr, c->P, Nep, Ne, r1,
-                               c->rule.sigma_from_T ? c->Tside : nullptr, c->Ph, c->Pl, run_pc, s));
-  if (c->b3)
-    HIP_TRY(launch_coreg_update_b3(c->Wth, c->Wtl, Nep, Nep, c->C, Nap, Nap, Na,
-                                   c->nWc, r1, c->cstat, c->csq, c->corder, run_pc, s,
-                                   c->packed));
-  else
-    HIP_TRY(launch_coreg_update(W, Nap, Nep, c->C, Nap, Nap, Na, c->nWc, r1, c->cstat, c->csq,
-                                c->corder, run_pc, s, c->packed));
+  HIP_TRY(launch_coop_partial(c->Wr, c->np, Nep, Nap, c->splits, c->ppart, run_pc, s));
+  HIP_TRY(launch_coop_finalize(c->ppart, c->splits, c->Nep, c->nWr, c->P, Nep, Ne, r1,
+                               c->rule.sigma_from_T ? c->Tside : nullptr, c->Pp, c->np, run_pc, s));
+  HIP_TRY(launch_coreg_update(c->Wt, c->np, Nep, c->C, Nap, Nap, Na, c->nWc, r1, c->cstat,
+                              c->csq, c->corder, run_pc, s, c->packed));
   // diagonals: t0 steps of Eq. 6 in closed form with sigma of the rebuilt rows
   const double a = c->rule.alpha;
   double g = 0.0;

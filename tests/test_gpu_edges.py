@@ -123,3 +123,73 @@ def test_tanimoto_split_k(torch, pd, M, K, N):
     want = dot / np.sqrt(den)
     bound = 2 * K * U * (np.abs(X) @ np.abs(Y)) / np.sqrt(den) + 4 * U * np.abs(want) + 1e-30
     assert np.all(np.abs(got - want) <= bound)
+
+
+# ------------------------------------ FP32 products on three bf16 planes --
+def prep(oracle, seed, Ne, Na):
+    W0, P0, C0 = I.priors(seed, Ne, Na, 0.1, 0.05, 40, 6)
+    return tuple(f32r(oracle.normalize(M)) for M in (W0, P0, C0))
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    from oracle import oracle as O
+    return O
+
+
+# one K-tile of N_e and of N_a; either side of a padded row tile; K past one
+# and two folds of the A product (1008 genes each); N_e past one fold
+# (1024 TFs: the C update, R and W W^T fold in LDS); both layouts of C
+@pytest.mark.parametrize("Ne,Na", [(3, 130), (64, 128), (65, 129), (70, 1100), (257, 2200),
+                                   (1100, 260)])
+@pytest.mark.parametrize("packed", [0, 1])
+def test_fp32_planes_run(torch, pd, oracle, Ne, Na, packed):
+    """Three iterations against the FP64 oracle: W and the off-diagonals of P
+    and C to 1e-4, their diagonals to 1e-5 of their size (the plain form's
+    targets); the stored state resumes bit for bit."""
+    W, P, C = prep(oracle, Ne + Na, Ne, Na)
+    o = pd.default_options(tol=0.0, packed_c=packed)
+    g = pd.run(cuda(torch, W), cuda(torch, P), cuda(torch, C), tol=0.0, max_iter=3, opts=o)
+    ref = oracle.run(W, P, C, oracle.Options(tol=0.0, max_iter=3))
+    assert np.abs(host(g.W) - ref.W).max() <= 1e-4
+    for got, want in ((host(g.P), ref.P), (host(g.C), ref.C)):
+        d = np.diag(want)
+        assert np.abs(np.diag(got) - d).max() <= 1e-5 * np.abs(d).max()
+        off = ~np.eye(want.shape[0], dtype=bool)
+        assert np.abs(got - want)[off].max() <= 1e-4
+    # W comes back from its planes exactly: two iterations, store, load, one more
+    a = pd.run(cuda(torch, W), cuda(torch, P), cuda(torch, C), tol=0.0, max_iter=2, opts=o)
+    c = pd.Context(Ne, Na, o)
+    c.load(a.W, a.P, a.C, t=2)
+    c.iterate()
+    Wb, Pb, Cb, _, _ = c.state()
+    assert torch.equal(Wb, g.W) and torch.equal(Pb, g.P) and torch.equal(Cb, g.C)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), 3.4e38])
+def test_fp32_planes_extreme_entry(torch, pd, oracle, bad):
+    """One extreme entry of W: the entry itself keeps its infinity, T is 0
+    wherever its denominator is not positive, and no other entry is lost."""
+    Ne, Na = 40, 200
+    W, P, C = prep(oracle, 3, Ne, Na)
+    W[4, 7] = np.float32(bad)
+
+    def T(X, Y):
+        with np.errstate(all="ignore"):
+            dot = X @ Y
+            den = (X ** 2).sum(1)[:, None] + (Y ** 2).sum(0)[None, :] - np.abs(dot)
+            return np.where(den > 0, dot / np.sqrt(den), 0.0)
+
+    g = pd.run(cuda(torch, W), cuda(torch, P), cuda(torch, C), tol=0.0, max_iter=1,
+               opts=pd.default_options(tol=0.0))
+    with np.errstate(all="ignore"):
+        want = 0.9 * W + 0.05 * (T(P, W) + T(W, C))
+    got = host(g.W)
+    if np.isinf(bad):
+        assert got[4, 7] == bad
+    else:
+        assert abs(got[4, 7] - 0.9 * W[4, 7]) <= 0.06 * W[4, 7]
+    rest = np.ones((Ne, Na), bool)
+    rest[4, :] = rest[:, 7] = False
+    assert np.abs(got - want)[rest].max() <= 1e-4
+    assert np.isfinite(got[rest]).all()
