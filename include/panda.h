@@ -75,7 +75,9 @@ typedef enum {
  *                      of the split operands and their terms added in FP64.
  *                      C stays FP32 (split while it is staged for the
  *                      products); the extra workspace is the hi/lo planes of
- *                      W (two layouts) and P, about 4 * Ne * Na * 2 bytes. */
+ *                      W (two layouts) and P, about 4 * Ne * Na * 2 bytes.
+ * Networks of a few hundred nodes a side, whose iterations wait for launches
+ * rather than matrix cores, take the same FP32 kernels in both forms. */
 enum { PANDA_PREC_FP32 = 0, PANDA_PREC_BF16X3 = 1 };
 
 /* Scope of the z-score of Sec. II-A (the paper says only that each network

@@ -48,6 +48,8 @@ struct panda_batch {
   std::vector<int64_t> h_flat[5];
   FlatList flat[5];
   bool b3;  // split-BF16 products
+  bool small;  // every network in the small kernels (under the default tiles)
+  SmallDims mx;  // largest network
   int32_t* ctr;
   DevState* d_states;
   DevState* h_states;  // pinned
@@ -190,33 +192,7 @@ panda_status upload_insts(panda_batch* b) {
   for (int32_t i = 0; i < b->n; ++i) {
     const panda_ctx& c = b->ctx[(size_t)i];
     BInst& d = b->h_inst[(size_t)i];
-    d.Ne = c.Ne;
-    d.Na = c.Na;
-    d.Nep = c.Nep;
-    d.Nap = c.Nap;
-    d.W[0] = c.W[0];
-    d.W[1] = c.W[1];
-    d.R = c.R;
-    d.P = c.P;
-    d.C = c.C;
-    d.Tside = c.Tside;
-    d.ppart = c.ppart;
-    d.dP = c.dP;
-    d.dC = c.dC;
-    d.nP = c.nP;
-    d.nC = c.nC;
-    d.nWr = c.nWr;
-    d.nWc = c.nWc;
-    d.colscr = c.colscr;
-    d.hpart = c.hpart;
-    d.cstat = c.cstat;
-    d.csq = c.csq;
-    d.corder = c.corder;
-    d.st = c.st;
-    d.Wr = c.Wr;
-    d.Wt = c.Wt;
-    d.Pp = c.Pp;
-    d.np = c.np;
+    d = inst_of(&c);
     d.nh = (c.Nep / bm) * (c.Nap / bn);
     d.chunk = chunk;
     d.splits = (c.Nap + chunk - 1) / chunk;
@@ -270,6 +246,13 @@ panda_status launch_phase(panda_batch* b, int phase, hipStream_t s) {
 // One iteration of every network: R, A + W, h, norms, P, C, diagonals.
 // Only kernel launches, so the sequence can be captured in a graph.
 panda_status enqueue_batch_iteration(panda_batch* b, hipStream_t s) {
+  if (b->small) {
+    const SmallRule rule = small_rule_of(&b->ctx[0]);
+    HIP_TRY(launch_small_avail(b->d_inst, BInst{}, b->n, b->mx, rule, s));
+    HIP_TRY(launch_small_update(b->d_inst, BInst{}, b->n, b->mx, rule, kSmallStep, s));
+    HIP_TRY(launch_small_finish(b->d_inst, BInst{}, b->n, b->mx, rule, kSmallStep, s));
+    return PANDA_OK;
+  }
   HIP_TRY(launch_batch_reset(b->ctr, kCtrCount, s));
   PANDA_TRY(launch_phase(b, kBTResp, s));
   PANDA_TRY(launch_phase(b, kBTAvail, s));
@@ -321,7 +304,20 @@ panda_status gather_states(panda_batch* b) {
   return PANDA_OK;
 }
 
+// Small networks leave the grouped kernels for the small ones unless the
+// caller chose (or tuned) tiles of the grouped ones.
+constexpr int kMaxGridY = 65535;
 panda_status apply_tiles(panda_batch* b) {
+  bool small = b->n <= kMaxGridY;
+  for (int l = 0; l < kNumLists; ++l) small = small && b->tiles[l] == 0;
+  b->mx = SmallDims{0, 0};
+  for (const auto& c : b->ctx) {
+    small = small && small_net(c.Ne, c.Na);
+    b->mx.Ne = std::max(b->mx.Ne, c.Ne);
+    b->mx.Na = std::max(b->mx.Na, c.Na);
+  }
+  for (auto& c : b->ctx) PANDA_TRY(ctx_set_small(&c, small));
+  b->small = small;
   for (int l = 0; l < kNumLists; ++l) PANDA_TRY(build_list(b, l));
   PANDA_TRY(upload_insts(b));
   drop_graph(b);

@@ -17,7 +17,8 @@ struct BInst {
   float* C;
   float* Tside;
   float* ppart;
-  double* dP;  // diagonals of P and C (FP64; zero in the matrices)
+  double* dP;  // diagonals of P and C (FP64; zero in the matrices); in the small
+               // kernels P's is at dP + (t & 1) * Nep
   double* dC;
   double* nP;
   double* nC;

@@ -7,7 +7,7 @@
 
 #include <stdio.h>
 
-#include "panda_internal.h"
+#include "small_internal.h"
 
 namespace panda {
 
@@ -90,7 +90,7 @@ struct panda_ctx {
   float* ppart;   // split-K partial products of W W^T
   float* skpart;  // stream-K partial tiles (single-network schedule only)
   float* fold;    // running sums of the A product over long K (FP32 form, else null)
-  double* dP;     // diagonal of P (FP64; P holds zero there)
+  double* dP;     // diagonal of P (FP64; P holds zero there; see diag_p_of)
   double* dC;     // diagonal of C
   double* nP;     // |P_i.|^2
   double* nC;     // |C_.j|^2
@@ -103,6 +103,7 @@ struct panda_ctx {
   double* zs;
   uint32_t* corder;  // launch order of the upper C tiles
   uint32_t* corder_r;  // the same with the R tiles of the next iteration (not in a batch)
+  bool small;       // iterates in the small kernels (small_internal.h)
   bool w_in_place;  // W and R share a buffer (FP32 form of a single network)
   bool r_next;  // R holds T(P, W) of the current state (computed by the last C update)
   panda::DevState* st;
@@ -112,6 +113,7 @@ struct panda_ctx {
   panda::DevState* host;  // pinned
   panda::DevState* snap;  // pinned, two slots: states copied ahead (run_loaded)
   hipEvent_t snap_ev[2];
+  panda::DevState* snap_to;  // slot that the iteration being enqueued fills itself (small), or null
   int splits;
   int64_t nh;
   int32_t t0;
@@ -137,6 +139,18 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
 panda_status ctx_setup(panda_ctx* c, int64_t Ne, int64_t Na, const panda_options& o,
                        const LayoutSpec& spec, char* base, hipStream_t stream);
 void ctx_free(panda_ctx* c);
+// P's diagonal at iteration t: the small kernels alternate between two vectors.
+inline double* diag_p_of(const panda_ctx* c, int32_t t) {
+  return c->dP + (c->small && (t & 1) ? c->Nep : 0);
+}
+// Rules and descriptor of a network for the small and grouped kernels.
+SmallRule small_rule_of(const panda_ctx* c);
+BInst inst_of(const panda_ctx* c);
+// The same for the small kernels of one network, step k since the load (k < 0:
+// outside a step, after -k - 1 of them).
+BInst small_inst_of(const panda_ctx* c, int64_t k);
+// Into (or out of) the small kernels: a loaded state is carried over.
+panda_status ctx_set_small(panda_ctx* c, bool small);
 // The current W of a loaded context as an FP32 matrix (leading dimension
 // Nap), for callers between iterations; R, which may share its buffer, is
 // computed again by the next iteration.

@@ -85,7 +85,8 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   Carver cv{base};
   const size_t nw = (size_t)Nep * (size_t)Nap;
   // bf16 planes of the operands: two, or three for the FP32 form
-  const int np = precision == PANDA_PREC_BF16X3 ? 2 : spec.batched ? 0 : 3;
+  const bool sm = small_net(Ne, Na);
+  const int np = sm && !spec.batched ? 0 : precision == PANDA_PREC_BF16X3 ? 2 : spec.batched ? 0 : 3;
   const bool in_place = np == 3;  // one buffer for W and R
   float* w0 = cv.take<float>(nw);
   float* w1 = in_place ? w0 : cv.take<float>(nw);
@@ -103,22 +104,23 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   const size_t nsk = spec.batched ? 0 : rect_partial_floats();
   float* sk = cv.take<float>(in_place ? std::max(nsk, (3 * nw + 1) / 2) : nsk);
   if (spec.batched) sk = nullptr;
-  double* dp = cv.take<double>((size_t)Nep);
+  double* dp = cv.take<double>((size_t)Nep * (sm ? 2 : 1));
   double* dc = cv.take<double>((size_t)Nap);
   double* np_ = cv.take<double>((size_t)Nep);
   double* nc = cv.take<double>((size_t)Nap);
   double* nwr = cv.take<double>((size_t)Nep);
   double* nwc = cv.take<double>((size_t)Nap);
   double* scr = cv.take<double>(w_norm_scratch_doubles(Nep, Nap));
-  const int64_t nh = spec.hpart_tiles;
+  const int64_t nh = sm ? std::max(spec.hpart_tiles, small_h_slots(Ne, Na)) : spec.hpart_tiles;
   double* hp = cv.take<double>((size_t)nh);
-  double2* cs = cv.take<double2>((size_t)coreg_slots(Nap) * Nap);
-  double* cq = cv.take<double>((size_t)coreg_slots(Nap) * Nap);
+  const int64_t nslots = sm ? std::max(coreg_slots(Nap), small_tiles(Na)) : coreg_slots(Nap);
+  double2* cs = cv.take<double2>((size_t)nslots * Nap);
+  double* cq = cv.take<double>((size_t)nslots * Nap);
   // z-score scratch, large enough for an identity prior of either side in any scope
   const int64_t nid = Nep > Nap ? Nep : Nap;
   double* zs = cv.take<double>(zscore_scratch_doubles(nid, nid, PANDA_ZSCORE_ROWCOL));
   uint32_t* co = cv.take<uint32_t>((size_t)coreg_tiles(Nap));
-  DevState* st = cv.take<DevState>(1);
+  DevState* st = cv.take<DevState>(2);  // the second: the small kernels' next state
   uint32_t* cor = !spec.batched
                       ? cv.take<uint32_t>((size_t)(coreg_tiles(Nap) + next_r_tiles(Nep, Nap)))
                       : nullptr;
@@ -155,6 +157,7 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
     c->zs = zs;
     c->corder = co;
     c->corder_r = cor;
+    c->small = sm && !spec.batched;
     c->w_in_place = in_place;
     c->r_next = false;
     c->st = st;
@@ -270,11 +273,53 @@ panda_status zscore(float* M, int64_t rows, int64_t cols, int64_t ld, int32_t mo
   return PANDA_OK;
 }
 
+SmallRule small_rule_of(const panda_ctx* c) {
+  return SmallRule{c->rule, c->rule.sigma_from_T, c->packed ? 1 : 0};
+}
+
+BInst inst_of(const panda_ctx* c) {
+  BInst d{};
+  d.Ne = c->Ne;
+  d.Na = c->Na;
+  d.Nep = c->Nep;
+  d.Nap = c->Nap;
+  d.W[0] = c->W[0];
+  d.W[1] = c->W[1];
+  d.R = c->R;
+  d.P = c->P;
+  d.C = c->C;
+  d.Tside = c->Tside;
+  d.ppart = c->ppart;
+  d.dP = c->dP;
+  d.dC = c->dC;
+  d.nP = c->nP;
+  d.nC = c->nC;
+  d.nWr = c->nWr;
+  d.nWc = c->nWc;
+  d.colscr = c->colscr;
+  d.hpart = c->hpart;
+  d.cstat = c->cstat;
+  d.csq = c->csq;
+  d.corder = c->corder;
+  d.st = c->st;
+  d.Wr = c->Wr;
+  d.Wt = c->Wt;
+  d.Pp = c->Pp;
+  d.np = c->np;
+  return d;
+}
+
+BInst small_inst_of(const panda_ctx* c, int64_t k) {
+  BInst d = inst_of(c);
+  const int64_t at = k >= 0 ? k : -k - 1;
+  d.W[0] = c->W[at & 1];
+  d.W[1] = c->W[(k >= 0 ? at + 1 : at) & 1];
+  return d;
+}
+
 }  // namespace panda
 
 namespace {
-
-// z-score of a strided matrix using `scratch`; synchronises the stream.
 
 // Phase boundary marker: records event `p` of the current pending
 // iteration when timing is on.
@@ -318,6 +363,22 @@ panda_status enqueue_iteration(panda_ctx* c) {
   const int32_t* active = &c->st->active;
   const int32_t* run_pc = &c->st->run_pc;
   PANDA_TRY(mark(c, PANDA_PHASE_R));
+  if (c->small) {  // three launches: the P phases are empty, R belongs to the last
+    const BInst d = small_inst_of(c, k);
+    const SmallDims mx{c->Ne, c->Na};
+    const SmallRule rule = small_rule_of(c);
+    PANDA_TRY(mark(c, PANDA_PHASE_AW));
+    HIP_TRY(launch_small_avail(nullptr, d, 1, mx, rule, s));
+    for (int p : {PANDA_PHASE_H, PANDA_PHASE_PPART, PANDA_PHASE_PFIN, PANDA_PHASE_C})
+      PANDA_TRY(mark(c, p));
+    HIP_TRY(launch_small_update(nullptr, d, 1, mx, rule, kSmallStep, s));
+    PANDA_TRY(mark(c, PANDA_PHASE_DIAG));
+    HIP_TRY(launch_small_finish(nullptr, d, 1, mx, rule, kSmallStep, s, c->snap_to));
+    PANDA_TRY(mark(c, PANDA_NPHASE));
+    if (c->timing) c->npend += 1;
+    c->enqueued += 1;
+    return PANDA_OK;
+  }
   // Eq. 3: R = T(P, W), K = N_e (computed by the last C update unless the
   // state is new)
   if (!c->r_next)
@@ -381,6 +442,29 @@ panda_status copy_in(float* dst, int64_t ldd, const float* src, int64_t rows, in
 
 namespace panda {
 
+panda_status ctx_set_small(panda_ctx* c, bool small) {
+  if (!c->loaded || c->small == small) {
+    c->small = small;
+    return PANDA_OK;
+  }
+  PANDA_TRY(read_state(c));
+  const size_t n = (size_t)c->Nep * sizeof(double);
+  if (c->host->t & 1)  // P's diagonal lies in the second vector in the small kernels
+    HIP_TRY(hipMemcpyAsync(c->dP + (small ? c->Nep : 0), c->dP + (small ? 0 : c->Nep), n,
+                           hipMemcpyDeviceToDevice, c->stream));
+  c->small = small;
+  if (!small && c->np) {  // the planes that the grouped kernels expect (and W's norms again)
+    HIP_TRY(hipMemsetAsync(c->Pp.p, 0, (size_t)c->np * c->Nep * c->Nep * 2, c->stream));
+    HIP_TRY(launch_split_offdiag(c->P, c->Ne, c->Nep, c->Pp, c->np, c->stream));
+    HIP_TRY(launch_w_norms(c->W[c->executed & 1], c->Ne, c->Na, c->Nap, c->Nep, c->nWr, c->nWc,
+                           c->colscr, c->Wr, c->Wt, c->np, nullptr, c->stream));
+  }
+  if (small)  // they expect R of the state they step from
+    HIP_TRY(launch_small_finish(nullptr, small_inst_of(c, -c->executed - 1), 1,
+                                SmallDims{c->Ne, c->Na}, small_rule_of(c), kSmallLoad, c->stream));
+  return PANDA_OK;
+}
+
 panda_status ctx_current_w(panda_ctx* c, float** W) {
   *W = c->W[c->executed & 1];
   if (w_in_planes(c)) {
@@ -408,16 +492,22 @@ panda_status run_loaded(panda_ctx* c) {
   }
   int64_t pending = -1;  // polled iteration whose state copy is awaited
   while (c->enqueued < max_iter) {
-    PANDA_TRY(enqueue_iteration(c));
+    const bool polled = (c->enqueued + 1) % poll == 0 && c->enqueued + 1 < max_iter;
+    c->snap_to = c->small && polled ? &c->snap[(c->enqueued + 1) & 1] : nullptr;
+    const panda_status st = enqueue_iteration(c);
+    const bool copied = c->snap_to != nullptr;
+    c->snap_to = nullptr;
+    PANDA_TRY(st);
     const int64_t k = c->enqueued;
     if (pending >= 0) {
       HIP_TRY(hipEventSynchronize(c->snap_ev[pending & 1]));
       if (!c->snap[pending & 1].active) break;
       pending = -1;
     }
-    if (k % poll == 0 && k < max_iter) {
-      HIP_TRY(hipMemcpyAsync(&c->snap[k & 1], c->st, sizeof(DevState), hipMemcpyDeviceToHost,
-                             c->stream));
+    if (polled) {
+      if (!copied)
+        HIP_TRY(hipMemcpyAsync(&c->snap[k & 1], c->st, sizeof(DevState), hipMemcpyDeviceToHost,
+                               c->stream));
       HIP_TRY(hipEventRecord(c->snap_ev[k & 1], c->stream));
       pending = k;
     }
@@ -759,7 +849,7 @@ panda_status panda_ctx_load(panda_ctx* c, const float* W, const float* P, const 
   else
     HIP_TRY(launch_col_sqnorms(c->C, Na, Na, Nap, c->nC, c->colscr, nullptr, s));
   // the diagonals of P and C move to their FP64 vectors (zero in the matrices)
-  HIP_TRY(launch_take_diag(c->P, Ne, Nep, c->dP, s));
+  HIP_TRY(launch_take_diag(c->P, Ne, Nep, diag_p_of(c, t), s));
   if (c->packed)
     HIP_TRY(launch_take_diag_packed(c->C, Na, c->dC, s));
   else
@@ -769,14 +859,22 @@ panda_status panda_ctx_load(panda_ctx* c, const float* W, const float* P, const 
     HIP_TRY(hipMemsetAsync(c->Pp.p, 0, (size_t)c->np * Nep * Nep * 2, s));
     HIP_TRY(launch_split_offdiag(c->P, Ne, Nep, c->Pp, c->np, s));
   }
+  HIP_TRY(launch_state_init(c->st, t, s));
   // norms (and planes) of W exactly as an iteration computes them, so a
   // stored state resumes bit for bit
-  HIP_TRY(launch_w_norms(c->W[0], Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt, c->np,
-                         nullptr, s));
+  if (c->small) {
+    const BInst d = small_inst_of(c, -1);
+    const SmallDims mx{Ne, Na};
+    const SmallRule rule = small_rule_of(c);
+    HIP_TRY(launch_small_update(nullptr, d, 1, mx, rule, kSmallLoad, s));
+    HIP_TRY(launch_small_finish(nullptr, d, 1, mx, rule, kSmallLoad, s));
+  } else {
+    HIP_TRY(launch_w_norms(c->W[0], Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt,
+                           c->np, nullptr, s));
+  }
   PANDA_TRY(ctx_fill_order(c));
   // h partial slots the A + W product never writes add zeros
   HIP_TRY(hipMemsetAsync(c->hpart, 0, (size_t)c->nh * sizeof(double), s));
-  HIP_TRY(launch_state_init(c->st, t, s));
   c->r_next = false;
   c->t0 = t;
   c->executed = 0;
@@ -816,7 +914,7 @@ panda_status panda_ctx_store(panda_ctx* c, float* W, float* P, float* C, double*
   if (P) {
     HIP_TRY(hipMemcpy2DAsync(P, (size_t)c->Ne * 4, c->P, (size_t)c->Nep * 4, (size_t)c->Ne * 4,
                              (size_t)c->Ne, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(launch_put_diag(P, c->Ne, c->Ne, c->dP, s));
+    HIP_TRY(launch_put_diag(P, c->Ne, c->Ne, diag_p_of(c, c->host->t), s));
   }
   if (C) {
     if (c->packed)

@@ -16,7 +16,7 @@ struct DevState {
   int32_t run_pc;  // 1 when the current iteration updates P and C: gates Eq. 5-6
   int32_t conv;    // 1 once h < tol
   int32_t wsel;    // index (0/1) of the buffer holding the current W; flipped with t
-  int32_t pad;
+  int32_t stepped; // small kernels: whether the last launched iteration advanced t
 };
 
 // Scalars of the update rules.

@@ -653,7 +653,7 @@ __global__ void k_state_init(DevState* st, int32_t t0) {
     st->run_pc = 0;
     st->conv = 0;
     st->wsel = 0;
-    st->pad = 0;
+    st->stepped = 0;
   }
 }
 

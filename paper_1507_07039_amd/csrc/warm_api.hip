@@ -72,10 +72,11 @@ panda_status panda_ws_features(panda_ctx* c, const float* omegaP, const float* o
   FeatLayout L;
   feat_layout(Ne, Na, static_cast<char*>(workspace), &L);
   hipStream_t s = c->stream;
+  double* const dP = diag_p_of(c, c->host->t);
   float* W0 = nullptr;
   PANDA_TRY(ctx_current_w(c, &W0));
   // one-step similarities R0 = T(P0, W0) (into R) and A0 = T(W0, C0) (into S)
-  HIP_TRY(launch_resp(c->P, Nep, c->dP, W0, Nap, Nep, Nap, Ne, Na, c->nP, c->nWc, L.R, L.part,
+  HIP_TRY(launch_resp(c->P, Nep, dP, W0, Nap, Nep, Nap, Ne, Na, c->nP, c->nWc, L.R, L.part,
                       nullptr, s));
   HIP_TRY(launch_tanimoto_store(W0, Nap, c->C, Nap, Nep, Nap, Nap, Ne, Na, c->nWr, c->nC, L.S,
                                 Nap, L.part, nullptr, s, c->dC));
@@ -89,7 +90,7 @@ panda_status panda_ws_features(panda_ctx* c, const float* omegaP, const float* o
   HIP_TRY(launch_degrees(W0, Ne, Na, Nap, L.dr, L.dc, s));
   // the sketches use the whole P0 and C0: their diagonals go back in for now
   // (the vectors hold the FP32 values taken out at load, so this is exact)
-  HIP_TRY(launch_put_diag(c->P, Ne, Nep, c->dP, s));
+  HIP_TRY(launch_put_diag(c->P, Ne, Nep, dP, s));
   HIP_TRY(launch_put_diag(c->C, Na, Nap, c->dC, s));
   HIP_TRY(launch_widen6(omegaP, Ne, L.omP, s));
   HIP_TRY(launch_widen6(omegaC, Na, L.omC, s));
@@ -101,7 +102,7 @@ panda_status panda_ws_features(panda_ctx* c, const float* omegaP, const float* o
   HIP_TRY(launch_cholqr(L.yC, Na, kSketchPivotRel, L.LinvC, L.d, s));
   HIP_TRY(launch_skinny(c->C, Na, Na, Nap, L.d, L.zC, s));          // C0 d
   HIP_TRY(launch_skinny(W0, Ne, Na, Nap, L.zC, L.c, s));            // c = W0 C0 d
-  HIP_TRY(launch_take_diag(c->P, Ne, Nep, c->dP, s));
+  HIP_TRY(launch_take_diag(c->P, Ne, Nep, dP, s));
   HIP_TRY(launch_take_diag(c->C, Na, Nap, c->dC, s));
   // moments of the 26 vectors, then the statistics of the 16 features
   VecRefHost refs[kNumVec];
@@ -196,28 +197,44 @@ panda_status panda_ws_init(panda_ctx* c, const float* Wpred, int32_t t0) {
   HIP_TRY(hipMemcpy2DAsync(c->W[0], (size_t)Nap * 4, Wpred, (size_t)Na * 4, (size_t)Na * 4,
                            (size_t)Ne, hipMemcpyDeviceToDevice, s));
   float* W = c->W[0];
-  HIP_TRY(launch_w_norms(W, Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt, c->np,
-                         nullptr, s));
+  double* const dP = diag_p_of(c, t0);  // the priors' diagonal moves to t0's vector
+  if (dP != diag_p_of(c, c->host->t))
+    HIP_TRY(hipMemcpyAsync(dP, diag_p_of(c, c->host->t), (size_t)Nep * sizeof(double),
+                           hipMemcpyDeviceToDevice, s));
+  if (!c->small)
+    HIP_TRY(launch_w_norms(W, Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt, c->np,
+                           nullptr, s));
   HIP_TRY(launch_state_set(c->st, t0, 1, 1, s));
   const int32_t* run_pc = &c->st->run_pc;
   // off-diagonals: the update rule of Eq. 5 with alpha = 1 gives T itself
   Rule r1 = c->rule;
   r1.alpha = 1.0;
-  HIP_TRY(launch_coop_partial(c->Wr, c->np, Nep, Nap, c->splits, c->ppart, run_pc, s));
-  HIP_TRY(launch_coop_finalize(c->ppart, c->splits, c->Nep, c->nWr, c->P, Nep, Ne, r1,
-                               c->rule.sigma_from_T ? c->Tside : nullptr, c->Pp, c->np, run_pc, s));
-  HIP_TRY(launch_coreg_update(c->Wt, c->np, Nep, c->C, Nap, Nap, Na, c->nWc, r1, c->cstat,
-                              c->csq, c->corder, run_pc, s, c->packed));
+  const BInst inst = small_inst_of(c, -1);
+  const SmallDims mx{Ne, Na};
+  SmallRule sr = small_rule_of(c);
+  sr.r.alpha = 1.0;
+  if (c->small) {
+    HIP_TRY(launch_small_update(nullptr, inst, 1, mx, sr, kSmallForce, s));
+  } else {
+    HIP_TRY(launch_coop_partial(c->Wr, c->np, Nep, Nap, c->splits, c->ppart, run_pc, s));
+    HIP_TRY(launch_coop_finalize(c->ppart, c->splits, c->Nep, c->nWr, c->P, Nep, Ne, r1,
+                                 c->rule.sigma_from_T ? c->Tside : nullptr, c->Pp, c->np, run_pc, s));
+    HIP_TRY(launch_coreg_update(c->Wt, c->np, Nep, c->C, Nap, Nap, Na, c->nWc, r1, c->cstat, c->csq,
+                                c->corder, run_pc, s, c->packed));
+  }
   // diagonals: t0 steps of Eq. 6 in closed form with sigma of the rebuilt rows
   const double a = c->rule.alpha;
   double g = 0.0;
   for (int32_t tau = 1; tau <= t0; ++tau) g += pow(1.0 - a, (double)(t0 - tau)) * exp(2.0 * a * tau);
   const double keep = pow(1.0 - a, (double)t0);
-  HIP_TRY(launch_diagonals_schedule(c->P, Nep, c->dP, Ne,
+  HIP_TRY(launch_diagonals_schedule(c->P, Nep, dP, Ne,
                                     c->rule.sigma_from_T ? c->Tside : nullptr, c->nP, c->dC, Nap,
                                     Na, c->cstat, c->rule.sigma_from_T ? c->csq : nullptr,
-                                    coreg_slots(Nap), c->nC, c->rule, keep, g, c->st, s));
+                                    c->small ? small_tiles(Na) : coreg_slots(Nap), c->nC, c->rule,
+                                    keep, g, c->st, s));
   HIP_TRY(launch_state_set(c->st, t0, 1, 0, s));
+  if (c->small)
+    HIP_TRY(launch_small_finish(nullptr, inst, 1, mx, small_rule_of(c), kSmallLoad, s));
   HIP_TRY(hipStreamSynchronize(s));
   c->t0 = t0;
   c->executed = 0;

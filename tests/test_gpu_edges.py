@@ -191,5 +191,76 @@ def test_fp32_planes_extreme_entry(torch, pd, oracle, bad):
         assert abs(got[4, 7] - 0.9 * W[4, 7]) <= 0.06 * W[4, 7]
     rest = np.ones((Ne, Na), bool)
     rest[4, :] = rest[:, 7] = False
-    assert np.abs(got - want)[rest].max() <= 1e-4
     assert np.isfinite(got[rest]).all()
+    assert np.abs(got[rest] - want[rest]).max() <= 1e-4
+
+
+# --------------------------------------------------------- small networks --
+# one entry a side (no spread), below, at and past one 32 x 32 tile, ragged
+# in both, taller than wide, and the sizes either side of the rule that sends
+# a network to the tiled kernels (N_e N_a (N_e + N_a) = 9e8, N_a = 2048)
+@pytest.mark.parametrize("Ne,Na", [(1, 2), (2, 3), (31, 33), (32, 32), (33, 31), (64, 300),
+                                   (150, 90), (40, 2048), (40, 2049)])
+@pytest.mark.parametrize("kw", [{}, {"packed_c": 1}, {"precision": 1},
+                                {"sigma_from_T": 1, "sigma_ddof": 1, "n_own": 1},
+                                {"h_undamped": 1, "diag_alpha": 0, "update_last": 1}])
+def test_small_kernels(torch, pd, oracle, Ne, Na, kw):
+    """Four iterations one at a time against the FP64 oracle (targets of the
+    plain form), a resume bit for bit, and a batch of the network with a
+    smaller one beside it."""
+    rng = np.random.default_rng(Ne * 3 + Na)
+    W, P, C = (f32r(M) for M in (rng.normal(size=(Ne, Na)), I.random_symmetric(Ne, Ne),
+                                 I.random_symmetric(Na + 1, Na)))
+    ro = {k: v for k, v in kw.items() if k not in ("packed_c", "precision")}
+    # the split form's own bound where the network does not take these kernels
+    tol = 1e-4 if Na <= 2048 or kw.get("precision", 0) == 0 else 1e-3
+    o = pd.default_options(tol=0.0, **kw)
+    c = pd.Context(Ne, Na, o)
+    c.load(cuda(torch, W), cuda(torch, P), cuda(torch, C))
+    ref, mid = (W, P, C), None
+    for t in range(1, 5):
+        Wo, Po, Co, ho, _ = oracle.step(*ref, t, oracle.Options(tol=0.0, **ro))
+        ref = (Wo, Po, Co)
+        h, tt = c.iterate()
+        assert tt == t and abs(h - ho) <= 10 * tol * ho + 1e-9
+        if t == 2:
+            mid = c.state()
+    g = c.state()
+    assert np.abs(host(g[0]) - ref[0]).max() <= tol
+    for got, want in ((host(g[1]), ref[1]), (host(g[2]), ref[2])):
+        d, off = np.diag(want), ~np.eye(want.shape[0], dtype=bool)
+        assert np.all(np.abs(np.diag(got) - d) <= 1e-5 * np.maximum(1.0, np.abs(d)))
+        assert not off.any() or np.abs(got - want)[off].max() <= tol
+    r = pd.Context(Ne, Na, o)
+    r.load(*mid[:3], t=2)
+    for _ in range(2):
+        r.iterate()
+    assert all(torch.equal(x, y) for x, y in zip(r.state()[:3], g[:3]))
+    if kw.get("packed_c"):
+        return
+    b = pd.Batch([(Ne, Na), (5, 9)], o)
+    b.load(0, cuda(torch, W), cuda(torch, P), cuda(torch, C))
+    b.load(1, *(cuda(torch, M) for M in (rng.normal(size=(5, 9)), I.random_symmetric(2, 5),
+                                         I.random_symmetric(3, 9))))
+    b.iterate(4, graph=True)
+    assert np.abs(host(b.state(0)[0]) - ref[0]).max() <= tol
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_small_batch_changes_tiles(torch, pd, oracle, precision):
+    """A loaded batch moved to the grouped kernels (other tiles) and back
+    between iterations goes on from the same state."""
+    nets = [prep(oracle, s, 40 + s, 90 + s) for s in (1, 2)]
+    b = pd.Batch([n[0].shape for n in nets], pd.default_options(tol=0.0, precision=precision))
+    for i, n in enumerate(nets):
+        b.load(i, *(cuda(torch, M) for M in n))
+    refs = [list(n) for n in nets]
+    for t, tiles in enumerate(([0, 0, 0, 0], [0, 0, 1, 0], [0, 0, 1, 0], [0, 0, 0, 0]), 1):
+        b.tiles = tiles
+        b.iterate(1, graph=t % 2 == 0)
+        for i in range(2):
+            refs[i] = list(oracle.step(*refs[i], t, oracle.Options(tol=0.0))[:3])
+            got = [host(x) for x in b.state(i)[:3]]
+            assert np.abs(got[0] - refs[i][0]).max() <= 1e-4
+            d = np.diag(refs[i][1])
+            assert np.abs(np.diag(got[1]) - d).max() <= 1e-5 * np.abs(d).max()
