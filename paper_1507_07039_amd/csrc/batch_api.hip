@@ -297,6 +297,7 @@ panda_status capture_graph(panda_batch* b) {
 }
 
 panda_status gather_states(panda_batch* b) {
+  for (auto& c : b->ctx) c.fresh = false;
   HIP_TRY(launch_batch_gather(b->d_inst, b->n, b->d_states, b->stream));
   HIP_TRY(hipMemcpyAsync(b->h_states, b->d_states, (size_t)b->n * sizeof(DevState),
                          hipMemcpyDeviceToHost, b->stream));

@@ -7,6 +7,7 @@
 
 #include <stdio.h>
 
+#include "load_internal.h"
 #include "small_internal.h"
 
 namespace panda {
@@ -100,7 +101,6 @@ struct panda_ctx {
   double* hpart;
   double2* cstat;
   double* csq;
-  double* zs;
   uint32_t* corder;  // launch order of the upper C tiles
   uint32_t* corder_r;  // the same with the R tiles of the next iteration (not in a batch)
   bool small;       // iterates in the small kernels (small_internal.h)
@@ -120,6 +120,7 @@ struct panda_ctx {
   int64_t executed;  // iterations known to have run since load
   int64_t enqueued;  // iterations enqueued since load
   bool loaded;
+  bool fresh;  // host holds the state of everything enqueued
   // phase timing
   bool timing;
   int npend;
@@ -155,7 +156,9 @@ panda_status ctx_set_small(panda_ctx* c, bool small);
 // Nap), for callers between iterations; R, which may share its buffer, is
 // computed again by the next iteration.
 panda_status ctx_current_w(panda_ctx* c, float** W);
-// Launch-order table of the upper C tiles (synchronises the context's stream).
+// panda_ctx_load without its wait for the copies out of W, P and C.
+panda_status ctx_load(panda_ctx* c, const float* W, const float* P, const float* C, int32_t t);
+// Launch-order tables of the upper C tiles, enqueued on the context's stream.
 panda_status ctx_fill_order(panda_ctx* c);
 
 }  // namespace panda

@@ -204,7 +204,7 @@ panda_status panda_null(const float* W0, const float* P0, const float* C0, int64
     }
     panda_ctx* c = nullptr;
     PANDA_TRY(panda_ctx_create(Ne, Na, &o, L.ctx, ctx_bytes, s, &c));
-    panda_status st = panda_ctx_load(c, W0, Pk, Ck, 0);
+    panda_status st = ctx_load(c, W0, Pk, Ck, 0);
     if (st == PANDA_OK) st = run_loaded(c);
     int32_t t = 0;
     if (st == PANDA_OK) st = panda_ctx_store(c, L.W, nullptr, nullptr, nullptr, &t);

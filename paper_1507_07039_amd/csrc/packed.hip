@@ -12,7 +12,6 @@ namespace {
 
 constexpr int kNT = 256;                          // threads per block
 constexpr int kTileF = (int)(kPT * kPT);          // floats per tile
-constexpr int kPerThread = kTileF / kNT;          // entries per thread and tile
 constexpr int kLdsLd = (int)kPT + 1;              // staged tile row length
 
 // (a, b), a <= b, of packed tile u.
@@ -22,22 +21,6 @@ __device__ __forceinline__ void tile_of(int64_t u, int64_t& a, int64_t& b) {
   while ((j + 1) * (j + 2) / 2 <= u) ++j;
   b = j;
   a = u - j * (j + 1) / 2;
-}
-
-// One block per upper tile; consecutive threads take consecutive entries of
-// a tile row, so the source rows are read along their length.
-__global__ __launch_bounds__(kNT) void k_pack_sym(const float* __restrict__ src, int64_t n,
-                                                  int64_t lds, float* __restrict__ dst) {
-  int64_t a, b;
-  tile_of(blockIdx.x, a, b);
-  float* t = dst + (int64_t)blockIdx.x * kTileF;
-  for (int q = 0; q < kPerThread; ++q) {
-    const int e = threadIdx.x + q * kNT, r = e / (int)kPT, c = e % (int)kPT;
-    const int64_t gi = a * kPT + r, gj = b * kPT + c;
-    float v = 0.0f;
-    if (gi < n && gj < n) v = gi <= gj ? src[gi * lds + gj] : src[gj * lds + gi];
-    t[e] = v;
-  }
 }
 
 // The tile is staged in LDS so that both its own rows and its mirror image
@@ -90,48 +73,54 @@ __global__ __launch_bounds__(kNT) void k_unpack_sym(const float* __restrict__ sr
   }
 }
 
-__global__ __launch_bounds__(kNT) void k_identity_packed(float* __restrict__ dst, int64_t n,
-                                                         float dval, float oval) {
-  int64_t a, b;
-  tile_of(blockIdx.x, a, b);
-  float* t = dst + (int64_t)blockIdx.x * kTileF;
-  for (int q = 0; q < kPerThread; ++q) {
-    const int e = threadIdx.x + q * kNT, r = e / (int)kPT, c = e % (int)kPT;
-    const int64_t gi = a * kPT + r, gj = b * kPT + c;
-    t[e] = (gi < n && gj < n) ? (gi == gj ? dval : oval) : 0.0f;
-  }
-}
-
-__global__ __launch_bounds__(kNT) void k_take_diag_packed(float* __restrict__ C, int64_t n,
-                                                          double* __restrict__ d) {
-  const int64_t i = (int64_t)blockIdx.x * kNT + threadIdx.x;
-  if (i >= n) return;
-  const int64_t blk = i / kPT, r = i % kPT;
-  float* p = C + packed_tile(blk, blk) * kTileF + r * (kPT + 1);
-  d[i] = (double)*p;
-  *p = 0.0f;
-}
-
-// Column sums of squares of every upper tile (a, b): column c of the tile
-// is part of column b kPT + c of C (slot a); for a < b, row r of the tile is
-// the mirror image's column a kPT + r (slot b).  Every column of C gets one
-// slot value from each block of rows.
-__global__ __launch_bounds__(kNT) void k_packed_sq_part(const float* __restrict__ C,
-                                                        int64_t Nap, double* __restrict__ slots) {
+// One block per upper tile (a, b): the source rows are read along their
+// length (16 bytes per lane where they allow), the tile stored without its
+// diagonal, and its sums of squares taken from LDS: column c of the tile is
+// part of column b kPT + c of C (slot a); for a < b, row r is the mirror
+// image's column a kPT + r (slot b).  Every column of C gets one slot value
+// from each block of rows.
+__global__ __launch_bounds__(kNT) void k_load_packed(const float* __restrict__ src, int64_t n,
+                                                     int64_t Nap, float dval, float oval,
+                                                     float* __restrict__ dst,
+                                                     double* __restrict__ diag,
+                                                     double* __restrict__ slots) {
   __shared__ float ts[kPT * kLdsLd];
   int64_t a, b;
   tile_of(blockIdx.x, a, b);
-  const fv4* t = reinterpret_cast<const fv4*>(C + (int64_t)blockIdx.x * kTileF);
+  float* t = dst + (int64_t)blockIdx.x * kTileF;
+  const bool al = src && (reinterpret_cast<uintptr_t>(src) & 15) == 0 && n % 4 == 0;
   fv4 v4[kPerThread4];
-#pragma unroll
-  for (int q = 0; q < kPerThread4; ++q) v4[q] = t[threadIdx.x + q * kNT];
 #pragma unroll
   for (int q = 0; q < kPerThread4; ++q) {
     const int e = threadIdx.x + q * kNT, r = e / kC4, c = (e % kC4) * 4;
-    ts[r * kLdsLd + c] = v4[q].x;
-    ts[r * kLdsLd + c + 1] = v4[q].y;
-    ts[r * kLdsLd + c + 2] = v4[q].z;
-    ts[r * kLdsLd + c + 3] = v4[q].w;
+    const int64_t gi = a * kPT + r, gj = b * kPT + c;
+    if (al && a < b && gi < n && gj + 3 < n) {
+      v4[q] = __builtin_nontemporal_load(reinterpret_cast<const fv4*>(src + gi * n + gj));
+      continue;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t j = gj + k;
+      const bool in = gi < n && j < n;
+      if (!src)
+        v4[q][k] = !in ? 0.0f : gi == j ? dval : oval;
+      else
+        v4[q][k] = !in ? 0.0f : gi <= j ? src[gi * n + j] : src[j * n + gi];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kPerThread4; ++q) {
+    const int e = threadIdx.x + q * kNT, r = e / kC4, c = (e % kC4) * 4;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      ts[r * kLdsLd + c + k] = v4[q][k];
+      if (a == b && r == c + k) {
+        const int64_t gi = a * kPT + r;
+        if (gi < n) diag[gi] = (double)v4[q][k];
+        v4[q][k] = 0.0f;
+      }
+    }
+    *reinterpret_cast<fv4*>(t + 4 * e) = v4[q];
   }
   __syncthreads();
   // threads 0-127: column th of the tile (rows in order); 128-255: row th -
@@ -154,12 +143,13 @@ __global__ __launch_bounds__(kNT) void k_packed_sq_part(const float* __restrict_
   }
 }
 
-__global__ __launch_bounds__(kNT) void k_packed_sq_sum(const double* __restrict__ slots,
-                                                       int64_t Nap, int64_t nT,
-                                                       double* __restrict__ out) {
+__global__ __launch_bounds__(kNT) void k_sum_slots(const double* __restrict__ slots,
+                                                   int64_t Nap, int64_t nT,
+                                                   double* __restrict__ out) {
   const int64_t j = (int64_t)blockIdx.x * kNT + threadIdx.x;
   if (j >= Nap) return;
   double s = 0.0;
+#pragma unroll 8
   for (int64_t k = 0; k < nT; ++k) s += slots[k * Nap + j];
   out[j] = s;
 }
@@ -171,13 +161,6 @@ unsigned tiles_of(int64_t Nap) {
 
 }  // namespace
 
-hipError_t launch_pack_sym(const float* src, int64_t n, int64_t lds, float* dst, int64_t Nap,
-                           hipStream_t s) {
-  if (Nap % kPT || n > Nap) return hipErrorInvalidValue;
-  k_pack_sym<<<dim3(tiles_of(Nap)), kNT, 0, s>>>(src, n, lds, dst);
-  return hipGetLastError();
-}
-
 hipError_t launch_unpack_sym(const float* src, int64_t n, int64_t Nap, float* dst, int64_t ldd,
                              hipStream_t s) {
   if (Nap % kPT || n > Nap) return hipErrorInvalidValue;
@@ -185,27 +168,20 @@ hipError_t launch_unpack_sym(const float* src, int64_t n, int64_t Nap, float* ds
   return hipGetLastError();
 }
 
-hipError_t launch_identity_packed(float* dst, int64_t n, int64_t Nap, double dval, double oval,
-                                  hipStream_t s) {
+hipError_t launch_sum_slots(const double* slots, int64_t Nap, int64_t nslots, double* out,
+                            hipStream_t s) {
+  k_sum_slots<<<dim3((unsigned)((Nap + kNT - 1) / kNT)), kNT, 0, s>>>(slots, Nap, nslots, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_load_packed(const float* src, int64_t n, int64_t Nap, float dval, float oval,
+                              float* dst, double* diag, double* slots, double* norms,
+                              hipStream_t s) {
   if (Nap % kPT || n > Nap) return hipErrorInvalidValue;
-  k_identity_packed<<<dim3(tiles_of(Nap)), kNT, 0, s>>>(dst, n, (float)dval, (float)oval);
-  return hipGetLastError();
-}
-
-hipError_t launch_take_diag_packed(float* C, int64_t n, double* d, hipStream_t s) {
-  k_take_diag_packed<<<dim3((unsigned)((n + kNT - 1) / kNT)), kNT, 0, s>>>(C, n, d);
-  return hipGetLastError();
-}
-
-hipError_t launch_col_sqnorms_packed(const float* C, int64_t Nap, double* slots, double* out,
-                                     hipStream_t s) {
-  if (Nap % kPT) return hipErrorInvalidValue;
-  k_packed_sq_part<<<dim3(tiles_of(Nap)), kNT, 0, s>>>(C, Nap, slots);
+  k_load_packed<<<dim3(tiles_of(Nap)), kNT, 0, s>>>(src, n, Nap, dval, oval, dst, diag, slots);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_packed_sq_sum<<<dim3((unsigned)((Nap + kNT - 1) / kNT)), kNT, 0, s>>>(slots, Nap, Nap / kPT,
-                                                                          out);
-  return hipGetLastError();
+  return launch_sum_slots(slots, Nap, Nap / kPT, norms, s);
 }
 
 }  // namespace panda

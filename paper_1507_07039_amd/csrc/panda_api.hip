@@ -116,9 +116,6 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   const int64_t nslots = sm ? std::max(coreg_slots(Nap), small_tiles(Na)) : coreg_slots(Nap);
   double2* cs = cv.take<double2>((size_t)nslots * Nap);
   double* cq = cv.take<double>((size_t)nslots * Nap);
-  // z-score scratch, large enough for an identity prior of either side in any scope
-  const int64_t nid = Nep > Nap ? Nep : Nap;
-  double* zs = cv.take<double>(zscore_scratch_doubles(nid, nid, PANDA_ZSCORE_ROWCOL));
   uint32_t* co = cv.take<uint32_t>((size_t)coreg_tiles(Nap));
   DevState* st = cv.take<DevState>(2);  // the second: the small kernels' next state
   uint32_t* cor = !spec.batched
@@ -154,7 +151,6 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
     c->nh = avail_hpart_slots(c->Nep, c->Nap);  // h partials of the A + W product
     c->cstat = cs;
     c->csq = cq;
-    c->zs = zs;
     c->corder = co;
     c->corder_r = cor;
     c->small = sm && !spec.batched;
@@ -185,19 +181,7 @@ panda_status ctx_setup(panda_ctx* c, int64_t Ne, int64_t Na, const panda_options
 }
 
 panda_status ctx_fill_order(panda_ctx* c) {
-  // host table, copied before it goes away
-  std::vector<uint32_t> order((size_t)coreg_tiles(c->Nap));
-  coreg_order_fill(c->Nap, kCoregGroup, order.data());
-  HIP_TRY(hipMemcpyAsync(c->corder, order.data(), order.size() * sizeof(uint32_t),
-                         hipMemcpyHostToDevice, c->stream));
-  std::vector<uint32_t> order_r;
-  if (c->corder_r) {
-    order_r.resize(order.size() + (size_t)next_r_tiles(c->Nep, c->Nap));
-    coreg_next_r_order_fill(c->Nep, c->Nap, order.data(), order_r.data());
-    HIP_TRY(hipMemcpyAsync(c->corder_r, order_r.data(), order_r.size() * sizeof(uint32_t),
-                           hipMemcpyHostToDevice, c->stream));
-  }
-  HIP_TRY(hipStreamSynchronize(c->stream));
+  HIP_TRY(launch_order(c->Nep, c->Nap, kCoregGroup, c->corder, c->corder_r, c->stream));
   return PANDA_OK;
 }
 
@@ -347,6 +331,7 @@ panda_status read_state(panda_ctx* c) {
   HIP_TRY(hipMemcpyAsync(c->host, c->st, sizeof(DevState), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->executed = c->host->t - c->t0;
+  c->fresh = true;
   return collect_times(c);
 }
 
@@ -355,6 +340,7 @@ panda_status read_state(panda_ctx* c) {
 // iterations past convergence are skipped on the device, so the executed
 // ones are always a prefix of the enqueued ones.
 panda_status enqueue_iteration(panda_ctx* c) {
+  c->fresh = false;
   if (c->timing && c->npend == kMaxPending) PANDA_TRY(read_state(c));
   const int64_t k = c->enqueued;
   float* Wold = c->W[k & 1];
@@ -431,13 +417,6 @@ bool w_in_planes(const panda_ctx* c) {
   return c->w_in_place && c->r_next && (!c->host->conv || c->rule.update_last);
 }
 
-panda_status copy_in(float* dst, int64_t ldd, const float* src, int64_t rows, int64_t cols,
-                     hipStream_t s) {
-  HIP_TRY(hipMemcpy2DAsync(dst, (size_t)ldd * 4, src, (size_t)cols * 4, (size_t)cols * 4,
-                           (size_t)rows, hipMemcpyDeviceToDevice, s));
-  return PANDA_OK;
-}
-
 }  // namespace
 
 namespace panda {
@@ -474,8 +453,73 @@ panda_status ctx_current_w(panda_ctx* c, float** W) {
   return PANDA_OK;
 }
 
-// Enqueue ahead and read h back every poll_every iterations; iterations
-// enqueued past convergence are no-ops on the device.
+panda_status ctx_load(panda_ctx* c, const float* W, const float* P, const float* C,
+                      int32_t t) {
+  if (!c || !W || t < 0) return fail(PANDA_ERR_ARG, "ctx_load: bad arguments%s");
+  hipStream_t s = c->stream;
+  const int64_t Ne = c->Ne, Na = c->Na, Nep = c->Nep, Nap = c->Nap;
+  // an absent prior is the z-scored identity
+  auto prior = [&](const float* src, int64_t n, PriorSrc* p) {
+    double dv = 0.0, ov = 0.0;
+    if (!src && !identity_zscore(n, c->opt.zscore_mode, c->opt.sigma_ddof, &dv, &ov)) return false;
+    *p = PriorSrc{src, (float)dv, (float)ov};
+    return true;
+  };
+  LoadArgs a{};
+  if (!prior(P, Ne, &a.Psrc) || !prior(C, Na, &a.Csrc))
+    return fail(PANDA_ERR_DEGENERATE, "identity prior of order 1 has std 0%s");
+  a.Wsrc = W;
+  a.Ne = Ne;
+  a.Na = Na;
+  a.Nep = Nep;
+  a.Nap = Nap;
+  a.W = c->W[0];
+  a.W1 = c->w_in_place ? nullptr : c->W[1];
+  a.P = c->P;
+  a.C = c->packed ? nullptr : c->C;
+  a.dP = diag_p_of(c, t);
+  a.dC = c->dC;
+  a.nP = c->nP;
+  a.nC = c->nC;
+  a.nWr = c->nWr;
+  a.nWc = c->nWc;
+  a.hpart = c->hpart;  // partials the A + W product never writes add zeros
+  a.nh = c->nh;
+  a.slots = c->csq;
+  a.crows = small_net(Ne, Na) ? kSmallTile : kPT;
+  a.Pp = c->Pp;
+  a.np = c->np;
+  a.t = t;
+  a.st = c->st;
+  HIP_TRY(launch_load(a, s));
+  if (c->packed)
+    HIP_TRY(launch_load_packed(C, Na, Nap, a.Csrc.dval, a.Csrc.oval, c->C, c->dC, c->csq, c->nC, s));
+  // norms (and planes) of W exactly as an iteration computes them, so a
+  // stored state resumes bit for bit
+  if (c->small) {
+    const BInst d = small_inst_of(c, -1);
+    const SmallDims mx{Ne, Na};
+    const SmallRule rule = small_rule_of(c);
+    HIP_TRY(launch_small_update(nullptr, d, 1, mx, rule, kSmallLoad, s));
+    HIP_TRY(launch_small_finish(nullptr, d, 1, mx, rule, kSmallLoad, s));
+  } else {
+    HIP_TRY(launch_w_norms(c->W[0], Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt,
+                           c->np, nullptr, s));
+    PANDA_TRY(ctx_fill_order(c));
+  }
+  c->r_next = false;
+  c->t0 = t;
+  c->executed = 0;
+  c->enqueued = 0;
+  c->host->h = 0.0;
+  c->host->t = t;
+  c->host->active = 1;
+  c->host->conv = 0;
+  c->loaded = true;
+  c->fresh = false;
+  return PANDA_OK;
+}
+
 // Iterate to convergence or max_iter.  The host never makes the device wait
 // for it: the state after a polled iteration is copied to a pinned slot (with
 // an event) as soon as that iteration is enqueued, and the host looks at it
@@ -501,7 +545,15 @@ panda_status run_loaded(panda_ctx* c) {
     const int64_t k = c->enqueued;
     if (pending >= 0) {
       HIP_TRY(hipEventSynchronize(c->snap_ev[pending & 1]));
-      if (!c->snap[pending & 1].active) break;
+      if (!c->snap[pending & 1].active) {
+        // the state of the converging iteration is the final one: what is
+        // queued behind it does nothing
+        if (c->timing) break;
+        *c->host = c->snap[pending & 1];
+        c->executed = c->enqueued = c->host->t - c->t0;
+        c->fresh = true;
+        return PANDA_OK;
+      }
       pending = -1;
     }
     if (polled) {
@@ -620,6 +672,13 @@ panda_status panda_normalize_ex(float* M, int64_t rows, int64_t cols, int32_t zs
 }
 
 namespace {
+panda_status copy_in(float* dst, int64_t ldd, const float* src, int64_t rows, int64_t cols,
+                     hipStream_t s) {
+  HIP_TRY(hipMemcpy2DAsync(dst, (size_t)ldd * 4, src, (size_t)cols * 4, (size_t)cols * 4,
+                           (size_t)rows, hipMemcpyDeviceToDevice, s));
+  return PANDA_OK;
+}
+
 struct TaniLayout {
   float *Xp, *Yp, *Op, *part;
   double *nx, *ny, *scr;
@@ -804,86 +863,10 @@ void panda_ctx_destroy(panda_ctx* c) {
 
 panda_status panda_ctx_load(panda_ctx* c, const float* W, const float* P, const float* C,
                             int32_t t) {
-  if (!c || !W || t < 0) return fail(PANDA_ERR_ARG, "ctx_load: bad arguments%s");
-  hipStream_t s = c->stream;
-  const int64_t Ne = c->Ne, Na = c->Na, Nep = c->Nep, Nap = c->Nap;
-  HIP_TRY(hipMemsetAsync(c->W[0], 0, (size_t)Nep * Nap * 4, s));
-  if (!c->w_in_place) HIP_TRY(hipMemsetAsync(c->W[1], 0, (size_t)Nep * Nap * 4, s));
-  HIP_TRY(hipMemsetAsync(c->P, 0, (size_t)Nep * Nep * 4, s));
-  if (!c->packed) HIP_TRY(hipMemsetAsync(c->C, 0, (size_t)Nap * Nap * 4, s));
-  HIP_TRY(hipMemsetAsync(c->Tside, 0, (size_t)Nep * Nep * 4, s));
-  panda_status st = copy_in(c->W[0], Nap, W, Ne, Na, s);
-  if (st != PANDA_OK) return st;
-  if (P) {
-    st = copy_in(c->P, Nep, P, Ne, Ne, s);
-  } else {
-    HIP_TRY(launch_fill_identity(c->P, Ne, Nep, s));
-    st = zscore(c->P, Ne, Ne, Nep, c->opt.zscore_mode, c->opt.sigma_ddof, c->zs, s);
-  }
-  if (st != PANDA_OK) return st;
-  if (c->packed) {
-    // the upper tiles of C (every stored entry is written: no clearing)
-    if (C) {
-      HIP_TRY(launch_pack_sym(C, Na, Na, c->C, Nap, s));
-    } else {
-      double dv, ov;
-      if (!identity_zscore(Na, c->opt.zscore_mode, c->opt.sigma_ddof, &dv, &ov))
-        return fail(PANDA_ERR_DEGENERATE, "identity C of order 1 has std 0%s");
-      HIP_TRY(launch_identity_packed(c->C, Na, Nap, dv, ov, s));
-    }
-  } else if (C) {
-    st = copy_in(c->C, Nap, C, Na, Na, s);
-  } else {
-    HIP_TRY(launch_fill_identity(c->C, Na, Nap, s));
-    st = zscore(c->C, Na, Na, Nap, c->opt.zscore_mode, c->opt.sigma_ddof, c->zs, s);
-  }
-  if (st != PANDA_OK) return st;
-  // squared norms of the loaded state (later iterations produce their own)
-  HIP_TRY(hipMemsetAsync(c->nP, 0, (size_t)Nep * 8, s));
-  HIP_TRY(hipMemsetAsync(c->nWr, 0, (size_t)Nep * 8, s));
-  HIP_TRY(hipMemsetAsync(c->nC, 0, (size_t)Nap * 8, s));
-  HIP_TRY(hipMemsetAsync(c->nWc, 0, (size_t)Nap * 8, s));
-  HIP_TRY(launch_row_sqnorms(c->P, Ne, Ne, Nep, c->nP, nullptr, s));
-  if (c->packed)
-    HIP_TRY(launch_col_sqnorms_packed(c->C, Nap, c->csq, c->nC, s));
-  else
-    HIP_TRY(launch_col_sqnorms(c->C, Na, Na, Nap, c->nC, c->colscr, nullptr, s));
-  // the diagonals of P and C move to their FP64 vectors (zero in the matrices)
-  HIP_TRY(launch_take_diag(c->P, Ne, Nep, diag_p_of(c, t), s));
-  if (c->packed)
-    HIP_TRY(launch_take_diag_packed(c->C, Na, c->dC, s));
-  else
-    HIP_TRY(launch_take_diag(c->C, Na, Nap, c->dC, s));
-  if (c->np) {
-    // planes of the loaded P; its padding and diagonal stay zero
-    HIP_TRY(hipMemsetAsync(c->Pp.p, 0, (size_t)c->np * Nep * Nep * 2, s));
-    HIP_TRY(launch_split_offdiag(c->P, Ne, Nep, c->Pp, c->np, s));
-  }
-  HIP_TRY(launch_state_init(c->st, t, s));
-  // norms (and planes) of W exactly as an iteration computes them, so a
-  // stored state resumes bit for bit
-  if (c->small) {
-    const BInst d = small_inst_of(c, -1);
-    const SmallDims mx{Ne, Na};
-    const SmallRule rule = small_rule_of(c);
-    HIP_TRY(launch_small_update(nullptr, d, 1, mx, rule, kSmallLoad, s));
-    HIP_TRY(launch_small_finish(nullptr, d, 1, mx, rule, kSmallLoad, s));
-  } else {
-    HIP_TRY(launch_w_norms(c->W[0], Ne, Na, Nap, Nep, c->nWr, c->nWc, c->colscr, c->Wr, c->Wt,
-                           c->np, nullptr, s));
-  }
-  PANDA_TRY(ctx_fill_order(c));
-  // h partial slots the A + W product never writes add zeros
-  HIP_TRY(hipMemsetAsync(c->hpart, 0, (size_t)c->nh * sizeof(double), s));
-  c->r_next = false;
-  c->t0 = t;
-  c->executed = 0;
-  c->enqueued = 0;
-  c->host->h = 0.0;
-  c->host->t = t;
-  c->host->active = 1;
-  c->host->conv = 0;
-  c->loaded = true;
+  PANDA_TRY(ctx_load(c, W, P, C, t));
+  // the caller may free or reuse its buffers, which need not belong to the
+  // context's stream
+  HIP_TRY(hipStreamSynchronize(c->stream));
   return PANDA_OK;
 }
 
@@ -903,26 +886,25 @@ panda_status panda_iterate(panda_ctx* c, double* h, int32_t* t) {
 
 panda_status panda_ctx_store(panda_ctx* c, float* W, float* P, float* C, double* h, int32_t* t) {
   if (!c || !c->loaded) return fail(PANDA_ERR_ARG, "ctx_store: context not loaded%s");
-  panda_status st = read_state(c);
-  if (st != PANDA_OK) return st;
-  hipStream_t s = c->stream;
-  if (W && w_in_planes(c))
-    HIP_TRY(launch_join_planes(c->Wr, c->Ne, c->Na, W, c->Na, s));
-  else if (W)
-    HIP_TRY(hipMemcpy2DAsync(W, (size_t)c->Na * 4, c->W[c->executed & 1], (size_t)c->Nap * 4,
-                             (size_t)c->Na * 4, (size_t)c->Ne, hipMemcpyDeviceToDevice, s));
-  if (P) {
-    HIP_TRY(hipMemcpy2DAsync(P, (size_t)c->Ne * 4, c->P, (size_t)c->Nep * 4, (size_t)c->Ne * 4,
-                             (size_t)c->Ne, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(launch_put_diag(P, c->Ne, c->Ne, diag_p_of(c, c->host->t), s));
-  }
-  if (C) {
-    if (c->packed)
-      HIP_TRY(launch_unpack_sym(c->C, c->Na, c->Nap, C, c->Na, s));
-    else
-      HIP_TRY(hipMemcpy2DAsync(C, (size_t)c->Na * 4, c->C, (size_t)c->Nap * 4, (size_t)c->Na * 4,
-                               (size_t)c->Na, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(launch_put_diag(C, c->Na, c->Na, c->dC, s));
+  if (!c->fresh) PANDA_TRY(read_state(c));
+  StoreArgs a{};
+  a.Wbuf = w_in_planes(c) ? nullptr : c->W[c->executed & 1];
+  a.Wr = c->Wr;
+  a.P = c->P;
+  a.C = c->C;
+  a.dP = diag_p_of(c, c->host->t);
+  a.dC = c->dC;
+  a.Ne = c->Ne;
+  a.Na = c->Na;
+  a.Nep = c->Nep;
+  a.Nap = c->Nap;
+  a.W = W;
+  a.Pout = P;
+  a.Cout = c->packed ? nullptr : C;
+  HIP_TRY(launch_store(a, c->stream));
+  if (C && c->packed) {
+    HIP_TRY(launch_unpack_sym(c->C, c->Na, c->Nap, C, c->Na, c->stream));
+    HIP_TRY(launch_put_diag(C, c->Na, c->Na, c->dC, c->stream));
   }
   if (h) *h = c->host->h;
   if (t) *t = c->host->t;
@@ -945,7 +927,7 @@ panda_status panda_run(const float* W0, const float* P0, const float* C0, int64_
   panda_ctx* c = nullptr;
   panda_status st = panda_ctx_create(Ne, Na, &o, workspace, ws_bytes, stream, &c);
   if (st != PANDA_OK) return st;
-  st = panda_ctx_load(c, W0, P0, C0, 0);
+  st = ctx_load(c, W0, P0, C0, 0);
   if (st == PANDA_OK) st = run_loaded(c);
   if (st == PANDA_OK) st = panda_ctx_store(c, W, P, C, h, iters);
   if (st == PANDA_OK && c->host->active) st = PANDA_NOT_CONVERGED;

@@ -126,17 +126,17 @@ hipError_t launch_avail_wupdate(const Planes& Wr, int np, const float* Wold, con
 
 // C update (Eq. 5) on the upper tiles of T(W^T, W) with mirror writes and
 // per-row partial sums for the sigma of Eq. 6 (and |C_.j|^2).  order holds
-// the upper tiles (I | J << 16) in launch order, see coreg_order_fill.
+// the upper tiles (I | J << 16) in launch order, see launch_order.
 hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Nep, float* C,
                                int64_t ldc, int64_t Nap, int64_t Na, const double* nWcol,
                                Rule rule, double2* cstat, double* csq, const uint32_t* order,
                                const int32_t* gate, hipStream_t s, bool packed);
 int64_t coreg_slots(int64_t Nap);
 // Upper tiles of the C product (Nap / 128 per side) and their launch order:
-// group x group super-tiles, so the tiles running together on one XCD share
-// 2 * group operand strips in its L2.
+// group x group super-tiles (column of super-tiles by column, downwards, a
+// super-tile's tiles column by column), so the tiles running together on one
+// XCD share 2 * group operand strips in its L2.
 int64_t coreg_tiles(int64_t Nap);
-void coreg_order_fill(int64_t Nap, int group, uint32_t* out);
 #ifndef PANDA_COREG_GROUP
 #define PANDA_COREG_GROUP 6
 #endif
@@ -153,14 +153,19 @@ int coop_splits(int64_t Nep, int64_t Nap, int64_t blocks);
 
 // R = T(P, W) (Eq. 3) on 128 x 128 tiles (next_r_tiles of them), alone or
 // inside the C update's launch: that launch runs the C tiles and the R tiles
-// of the order coreg_next_r_order_fill builds, so the next iteration's R is
-// ready when the C update ends (P, its diagonal dP and norms nP, and W's
+// of order_r, so the next iteration's R is ready when the C update ends (P, its diagonal dP and norms nP, and W's
 // planes and column norms must be the new ones).  Both compute R the same
 // way, bit for bit.  W, R: leading dimension ldw (R may be W itself: an entry
 // of W is read by the thread that stores R there).
 int64_t next_r_row_tiles(int64_t Nep);
 int64_t next_r_tiles(int64_t Nep, int64_t Nap);
-void coreg_next_r_order_fill(int64_t Nep, int64_t Nap, const uint32_t* corder, uint32_t* out);
+// An entry of order_r with this bit set is R tile (entry & 0xffff, (entry >>
+// 16) & 0x7fff) (row tile of P, column tile of W); the others are C tiles (I,
+// J) = (entry & 0xffff, entry >> 16).  Each XCD's share of the launch (the
+// ranges xcd_tile maps block indices to) takes its share of the C tiles in
+// their order, then its share of the R tiles, column tile by column tile (R
+// tiles of one column share W's strip): they fill the end of its work.
+constexpr uint32_t kNextRTile = 0x80000000u;
 hipError_t launch_resp_tiles(const Planes& Pp, const Planes& Wt, int np, int64_t ldp,
                              const double* dP, int64_t Nap, int64_t Ne, int64_t Na,
                              const float* W, int64_t ldw, const double* nP, const double* nWc,
@@ -179,22 +184,20 @@ hipError_t launch_join_planes(const Planes& P, int64_t rows, int64_t cols, float
 hipError_t launch_split_offdiag(const float* M, int64_t n, int64_t ld, Planes out, int np,
                                 hipStream_t s);
 
-// Packed C (see packed_tile).  pack: the upper tiles of the n x n symmetric
-// matrix src (leading dimension lds; the upper triangle is read, and
-// mirrored inside diagonal tiles), zero past n.  unpack: the full n x n
-// matrix into dst (leading dimension ldd).  identity: dval on the diagonal,
-// oval off it (within n), zero past n.  take_diag: the diagonal moves to d
-// and reads zero.  col_sqnorms: out[j] = sum_i C[i][j]^2 (j < Nap, FP64),
-// through slots (nT x Nap doubles, nT = Nap / kPT).
-hipError_t launch_pack_sym(const float* src, int64_t n, int64_t lds, float* dst, int64_t Nap,
-                           hipStream_t s);
+// Packed C (see packed_tile).  load: the upper tiles of the n x n symmetric
+// matrix src (row length n; its upper triangle is read, and mirrored inside
+// diagonal tiles; the identity dval / oval where null), zero past n and on the
+// diagonal, which goes to diag; norms[j] = sum_i C[i][j]^2 with the diagonal
+// (j < Nap, FP64), through slots (nT x Nap doubles, nT = Nap / kPT).  unpack:
+// the full n x n matrix into dst (leading dimension ldd).  sum_slots: out[j] =
+// sum_k slots[k][j], j < Nap.
 hipError_t launch_unpack_sym(const float* src, int64_t n, int64_t Nap, float* dst, int64_t ldd,
                              hipStream_t s);
-hipError_t launch_identity_packed(float* dst, int64_t n, int64_t Nap, double dval, double oval,
-                                  hipStream_t s);
-hipError_t launch_take_diag_packed(float* C, int64_t n, double* d, hipStream_t s);
-hipError_t launch_col_sqnorms_packed(const float* C, int64_t Nap, double* slots, double* out,
-                                     hipStream_t s);
+hipError_t launch_sum_slots(const double* slots, int64_t Nap, int64_t nslots, double* out,
+                            hipStream_t s);
+hipError_t launch_load_packed(const float* src, int64_t n, int64_t Nap, float dval, float oval,
+                              float* dst, double* diag, double* slots, double* norms,
+                              hipStream_t s);
 
 // Rest of the iteration: h, P finalisation, both diagonals, norm vectors.
 hipError_t launch_finish_h(const double* hpart, int64_t n, int64_t count, DevState* st,
@@ -262,7 +265,6 @@ hipError_t launch_zscore_rc_apply(float* M, int64_t rows, int64_t cols, int64_t 
 // Skipped on the device where the moments refuse the matrix.
 hipError_t launch_zscore_apply(float* M, int64_t rows, int64_t cols, int64_t ld,
                                const double* scratch, hipStream_t s);
-hipError_t launch_fill_identity(float* M, int64_t n, int64_t ld, hipStream_t s);
 // Pearson correlation of the G rows of E (G x S, leading dimension lde):
 // row statistics, then the centred rows scaled to unit norm, stored
 // sample-major as Zt (Sp x Gp, zero-padded; Gp a multiple of 128, Sp of 16);
@@ -272,6 +274,5 @@ hipError_t launch_pearson_z(const float* E, int64_t G, int64_t S, int64_t lde, d
 hipError_t launch_corr(const float* Zt, int64_t Gp, int64_t Sp, int64_t G, float* C, int64_t ldc,
                        hipStream_t s);
 
-hipError_t launch_state_init(DevState* st, int32_t t0, hipStream_t s);
 
 }  // namespace panda

@@ -30,10 +30,6 @@ struct NextR {
   typename G::Ops ops;
   EpiStoreT epi;
 };
-// An entry of the tile order with this bit set is R tile (entry & 0xffff,
-// (entry >> 16) & 0x7fff) (row tile of P, column tile of W); the others are
-// C tiles (I, J) = (entry & 0xffff, entry >> 16).
-constexpr uint32_t kNextRTile = 0x80000000u;
 // R's epilogue: W entries of runs of 16 rows of a column loaded together.
 constexpr int kNextRRun = 16;
 
@@ -220,16 +216,6 @@ hipError_t launch_avail_wupdate(const Planes& Wr, int np, const float* Wold, con
 int64_t coreg_slots(int64_t Nap) { return Nap / kCB; }
 int64_t coreg_tiles(int64_t Nap) { return (Nap / kCB) * (Nap / kCB + 1) / 2; }
 
-void coreg_order_fill(int64_t Nap, int group, uint32_t* out) {
-  const int64_t nT = Nap / kCB, nG = (nT + group - 1) / group;
-  int64_t k = 0;
-  for (int64_t bj = 0; bj < nG; ++bj)
-    for (int64_t bi = 0; bi <= bj; ++bi)
-      for (int64_t J = bj * group; J < (bj + 1) * group && J < nT; ++J)
-        for (int64_t I = bi * group; I < (bi + 1) * group && I <= J; ++I)
-          out[k++] = (uint32_t)(I | (J << 16));
-}
-
 template <class G, bool PK, bool NR>
 static hipError_t coreg_launch_pk(const typename G::Ops& ops, int64_t Nep, float* C, int64_t ldc,
                                   int64_t Nap, int64_t Na, const double* nWcol, Rule rule,
@@ -284,23 +270,6 @@ hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Nep, float* C,
 
 int64_t next_r_row_tiles(int64_t Nep) { return (Nep + kCB - 1) / kCB; }
 int64_t next_r_tiles(int64_t Nep, int64_t Nap) { return next_r_row_tiles(Nep) * (Nap / kCB); }
-
-void coreg_next_r_order_fill(int64_t Nep, int64_t Nap, const uint32_t* corder, uint32_t* out) {
-  // each XCD's share of the launch (the ranges xcd_tile maps block indices
-  // to) takes its share of the C tiles in their order, then its share of the
-  // R tiles, column tile by column tile (R tiles of one column share W's
-  // strip): the R tiles fill the end of every XCD's work
-  const int64_t nC = coreg_tiles(Nap), nRT = next_r_row_tiles(Nep), nR = next_r_tiles(Nep, Nap);
-  const int64_t n = nC + nR;
-  int64_t ci = 0, ri = 0, pos = 0;
-  for (int64_t x = 0; x < 8; ++x) {
-    const int64_t size = n / 8 + (x < n % 8 ? 1 : 0);
-    const int64_t nr = nR / 8 + (x < nR % 8 ? 1 : 0);
-    for (int64_t k = 0; k < size - nr; ++k) out[pos++] = corder[ci++];
-    for (int64_t k = 0; k < nr; ++k, ++ri)
-      out[pos++] = kNextRTile | (uint32_t)(ri % nRT) | ((uint32_t)(ri / nRT) << 16);
-  }
-}
 
 template <class G>
 static NextR<G> next_r_args(const Planes& Pp, const double* dP, const double* nP,

@@ -627,33 +627,12 @@ __global__ __launch_bounds__(kRT) void k_zs_flags_clear(double* flags) {
   if (threadIdx.x < 8) flags[threadIdx.x] = 0.0;
 }
 
-__global__ __launch_bounds__(kRT) void k_fill_identity(float* __restrict__ M, int64_t n,
-                                                       int64_t ld) {
-  const int64_t tot = n * n;
-  for (int64_t e = (int64_t)blockIdx.x * kRT + threadIdx.x; e < tot; e += (int64_t)gridDim.x * kRT) {
-    const int64_t i = e / n, j = e % n;
-    M[i * ld + j] = (i == j) ? 1.0f : 0.0f;
-  }
-}
-
 __global__ void k_state_set(DevState* st, int32_t t, int32_t active, int32_t run_pc) {
   if (threadIdx.x == 0) {
     st->t = t;
     st->wsel = 0;
     st->active = active;
     st->run_pc = run_pc;
-  }
-}
-
-__global__ void k_state_init(DevState* st, int32_t t0) {
-  if (threadIdx.x == 0) {
-    st->h = 0.0;
-    st->t = t0;
-    st->active = 1;
-    st->run_pc = 0;
-    st->conv = 0;
-    st->wsel = 0;
-    st->stepped = 0;
   }
 }
 
@@ -865,16 +844,6 @@ hipError_t launch_zscore_apply(float* M, int64_t rows, int64_t cols, int64_t ld,
   auto* fn = p.vec ? (p.large ? k_zs_apply<true, 8> : k_zs_apply<true, 1>)
                    : (p.large ? k_zs_apply<false, 8> : k_zs_apply<false, 1>);
   fn<<<dim3(nb), kRT, 0, s>>>(M, p.rows, p.cols, p.ld, p.per_row, scratch);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_identity(float* M, int64_t n, int64_t ld, hipStream_t s) {
-  k_fill_identity<<<grid_for(n * n, 4096), kRT, 0, s>>>(M, n, ld);
-  return hipGetLastError();
-}
-
-hipError_t launch_state_init(DevState* st, int32_t t0, hipStream_t s) {
-  k_state_init<<<1, 64, 0, s>>>(st, t0);
   return hipGetLastError();
 }
 

@@ -236,6 +236,7 @@ panda_status panda_ws_init(panda_ctx* c, const float* Wpred, int32_t t0) {
   if (c->small)
     HIP_TRY(launch_small_finish(nullptr, inst, 1, mx, small_rule_of(c), kSmallLoad, s));
   HIP_TRY(hipStreamSynchronize(s));
+  c->fresh = false;
   c->t0 = t0;
   c->executed = 0;
   c->enqueued = 0;

@@ -264,3 +264,42 @@ def test_small_batch_changes_tiles(torch, pd, oracle, precision):
             assert np.abs(got[0] - refs[i][0]).max() <= 1e-4
             d = np.diag(refs[i][1])
             assert np.abs(np.diag(got[1]) - d).max() <= 1e-5 * np.abs(d).max()
+
+
+# ---------------------------------------------------------------- load, store --
+# one tile; odd rows off 16-byte alignment; rows of 1024 columns and either
+# side; more than one chunk of rows; past the small kernels
+@pytest.mark.parametrize("Ne,Na", [(2, 3), (33, 130), (64, 1024), (20, 1025), (130, 2300)])
+@pytest.mark.parametrize("kw", [{}, {"packed_c": 1}, {"precision": 1}])
+@pytest.mark.parametrize("off", [0, 1])
+def test_load_store_roundtrip(torch, pd, Ne, Na, kw, off):
+    """A loaded state comes back bit for bit (matrices off alignment too), the
+    identity as the rounded z-score of the identity."""
+    rng = np.random.default_rng(Ne * 3 + Na)
+
+    def put(a):
+        buf = torch.zeros(a.size + off, device="cuda")
+        t = buf[off:].view(a.shape)
+        t.copy_(torch.from_numpy(np.asarray(a, np.float32)))
+        return t
+
+    def sym(n):
+        a = rng.normal(size=(n, n))
+        return a + a.T
+
+    def identity(n):
+        e = np.eye(n)
+        return ((e - e.mean()) / e.std()).astype(np.float32)
+
+    W, P, C = put(rng.normal(size=(Ne, Na))), put(sym(Ne)), put(sym(Na))
+    ctx = pd.Context(Ne, Na, pd.default_options(**kw))
+    ctx.load(W, P, C)
+    out = [put(np.zeros(t.shape)) for t in (W, P, C)]
+    ctx.store(*out)
+    for a, b in zip(out, (W, P, C)):
+        assert torch.equal(a, b)
+    ctx.load(W)
+    ctx.store(*out)
+    assert torch.equal(out[0], W)
+    for a, n in zip(out[1:], (Ne, Na)):
+        assert np.abs(host(a) - identity(n)).max() <= 2 * U * np.abs(identity(n)).max()
