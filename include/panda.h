@@ -62,12 +62,11 @@ typedef enum {
 
 /* Arithmetic of the similarity products (norms, denominators, h and the
  * diagonal rule are FP64 in both forms; the state W, P, C is FP32):
- *   PANDA_PREC_FP32    products of the whole FP32 operands, FP32 accumulation.
- *                      A single network forms them on bf16 matrix cores from
- *                      three bf16 terms per operand that add up to it exactly
- *                      (six products; the ones left out are below the
- *                      rounding of the accumulation); a batch on FP32 matrix
- *                      cores.
+ *   PANDA_PREC_FP32    products of the whole FP32 operands, FP32 accumulation,
+ *                      formed on bf16 matrix cores from three bf16 terms per
+ *                      operand that add up to it exactly (six products; the
+ *                      ones left out are below the rounding of the
+ *                      accumulation).
  *   PANDA_PREC_BF16X3  every operand split as x = hi + lo (bf16, round to
  *                      nearest even) and each product formed as
  *                      hi*hi + hi*lo + lo*hi on bf16 matrix cores with FP32
@@ -156,7 +155,7 @@ panda_status panda_normalize_ex(float* M, int64_t rows, int64_t cols, int32_t zs
 
 /* Similarity matrix of Eq. 1 in the matrix form of Sec. II-C (the paper's
  * Tfunction): Out[i][j] = T(row i of X, column j of Y) for X (M x K) and
- * Y (K x N); Out is M x N.  FP32 MFMA products, FP64 norms and denominator,
+ * Y (K x N); Out is M x N.  Products as PANDA_PREC_FP32's, FP64 norms and denominator,
  * T := 0 where the denominator is 0 (both vectors zero).  M, K, N >= 1.
  * Needs panda_tanimoto_workspace_bytes(M, K, N) bytes of workspace. */
 size_t panda_tanimoto_workspace_bytes(int64_t M, int64_t K, int64_t N);
@@ -168,7 +167,7 @@ panda_status panda_tanimoto(const float* X, const float* Y, int64_t M, int64_t K
  * leading dimension lde >= S, device memory); C is G x G with leading
  * dimension ldc >= G (device memory, written; E is not modified; columns past
  * G of each row are left alone).  Row means and centred sums of squares in
- * FP64; the correlations as one FP32 MFMA product of the centred rows scaled
+ * FP64; the correlations as one product (PANDA_PREC_FP32's) of the centred rows scaled
  * to unit norm, computed on the upper triangle of 128 x 128 tiles and
  * mirrored, so C is exactly symmetric.  C[i][i] = 1, and a constant row gets
  * correlation 0 with every other row.  G >= 1, S >= 2.  Needs

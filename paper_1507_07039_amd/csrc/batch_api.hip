@@ -48,6 +48,7 @@ struct panda_batch {
   std::vector<int64_t> h_flat[5];
   FlatList flat[5];
   bool b3;  // split-BF16 products
+  bool long_k;  // R and the C update sum over more than kFoldK of k somewhere
   bool small;  // every network in the small kernels (under the default tiles)
   SmallDims mx;  // largest network
   int32_t* ctr;
@@ -101,16 +102,14 @@ size_t batch_layout(int32_t n, const int64_t* Ne, const int64_t* Na, int32_t pre
 
 // Items and cost per item of network c in grouped product `phase`.
 void phase_items(const panda_ctx& c, int phase, int choice, int64_t* count, int64_t* cost) {
-  int64_t bm, bn;
+  const bool b3 = c.np != 0;
   switch (phase) {
     case kBTResp:
-      rect_tile_shape(choice, &bm, &bn);
-      *count = (c.Nep / bm) * (c.Nap / bn);
+      *count = rect_items(choice, b3, c.Nep, c.Nap);
       *cost = c.Nep + 64;
       return;
     case kBTAvail:
-      rect_tile_shape(choice, &bm, &bn);
-      *count = (c.Nep / bm) * (c.Nap / bn);
+      *count = rect_items(choice, b3, c.Nep, c.Nap);
       *cost = c.Nap + 64;
       return;
     case kBTCoop: {
@@ -174,7 +173,7 @@ panda_status build_list(panda_batch* b, int phase) {
   wl.nseg = n;
   wl.ctr = b->ctr + (int64_t)phase * kNumXcd * kCtrStride;
   L.wl = wl;
-  L.nb = batch_grid(phase, b->tiles[phase], b->rule.sigma_from_T != 0, b->b3);
+  L.nb = batch_grid(phase, b->tiles[phase], b->b3, b->long_k, b->rule);
   HIP_TRY(hipMemcpyAsync(L.d_seg_inst, L.seg_inst.data(), (size_t)n * sizeof(int32_t),
                          hipMemcpyHostToDevice, b->stream));
   HIP_TRY(hipMemcpyAsync(L.d_seg_first, L.seg_first.data(), ((size_t)n + 1) * sizeof(int64_t),
@@ -185,15 +184,13 @@ panda_status build_list(panda_batch* b, int phase) {
 
 // Device descriptors of all networks for the current tile choices.
 panda_status upload_insts(panda_batch* b) {
-  int64_t bm, bn;
-  rect_tile_shape(b->tiles[kBTAvail], &bm, &bn);
   const int64_t chunk = coop_chunk_of(b->tiles[kBTCoop]);
   b->h_inst.resize((size_t)b->n);
   for (int32_t i = 0; i < b->n; ++i) {
     const panda_ctx& c = b->ctx[(size_t)i];
     BInst& d = b->h_inst[(size_t)i];
     d = inst_of(&c);
-    d.nh = (c.Nep / bm) * (c.Nap / bn);
+    d.nh = rect_items(b->tiles[kBTAvail], b->b3, c.Nep, c.Nap);
     d.chunk = chunk;
     d.splits = (c.Nap + chunk - 1) / chunk;
   }
@@ -229,17 +226,8 @@ panda_status build_flat(panda_batch* b) {
 
 panda_status launch_phase(panda_batch* b, int phase, hipStream_t s) {
   const auto& L = b->lists[phase];
-  switch (phase) {
-    case kBTResp:
-      HIP_TRY(launch_batch_resp(b->tiles[phase], b->b3, b->d_inst, L.wl, L.nb, s));
-      break;
-    case kBTAvail:
-      HIP_TRY(launch_batch_avail(b->tiles[phase], b->b3, b->d_inst, L.wl, b->rule, L.nb, s));
-      break;
-    case kBTCoop: HIP_TRY(launch_batch_coop_partial(b->b3, b->d_inst, L.wl, L.nb, s)); break;
-    default:
-      HIP_TRY(launch_batch_coreg(b->tiles[phase], b->b3, b->d_inst, L.wl, b->rule, L.nb, s));
-  }
+  HIP_TRY(launch_batch_product(phase, b->tiles[phase], b->b3, b->long_k, b->d_inst, L.wl, b->rule,
+                               L.nb, s));
   return PANDA_OK;
 }
 
@@ -312,9 +300,11 @@ panda_status apply_tiles(panda_batch* b) {
   bool small = b->n <= kMaxGridY;
   for (int l = 0; l < kNumLists; ++l) small = small && b->tiles[l] == 0;
   b->mx = SmallDims{0, 0};
+  b->long_k = false;
   for (const auto& c : b->ctx) {
     small = small && small_net(c.Ne, c.Na);
     b->mx.Ne = std::max(b->mx.Ne, c.Ne);
+    b->long_k = b->long_k || c.Nep > kFoldK;
     b->mx.Na = std::max(b->mx.Na, c.Na);
   }
   for (auto& c : b->ctx) PANDA_TRY(ctx_set_small(&c, small));

@@ -20,24 +20,29 @@ namespace {
 
 using namespace gemm;
 
-// Candidate tilings (index = autotuner choice).
-using RectT0 = BlockGemm<64, 128, 1, 4, true, false, 16>;
-using RectT1 = BlockGemm<64, 64, 2, 2, true, false, 16>;
-using RectT2 = BlockGemm<64, 128, 2, 2, true, false, 16>;
-using SymT0 = BlockGemm<128, 128, 2, 2, false, false, 16>;
-using SymT1 = BlockGemm<128, 128, 2, 2, false, false, 32>;
-using SymT2 = BlockGemm<128, 128, 1, 4, false, false, 16>;
-using CoopT = BlockGemm<64, 64, 2, 2, true, true, 32>;
+// Candidate tilings of the FP32 form (index = autotuner choice); LK: sums over
+// more than kFoldK of k.
+template <bool LK>
+using RectT0 = BlockGemmF3<128, 128, 2, 2, true, false, LK>;
+template <bool LK>
+using RectT1 = BlockGemmF3<64, 64, 1, 2, true, false, LK>;
+template <bool LK>
+using RectT2 = BlockGemmF3<64, 128, 1, 2, true, false, LK>;
+template <bool LK>
+using SymT0 = BlockGemmF3<128, 128, 2, 2, false, false, LK>;
+template <bool LK>
+using SymT1 = BlockGemmF3<128, 128, 4, 1, false, false, LK>;
+template <bool LK>
+using SymT2 = BlockGemmF3<128, 128, 1, 4, false, false, LK>;
+using CoopT = BlockGemmF3<64, 64, 1, 2, true, true, true>;
 constexpr int64_t kCoopChunks[4] = {512, 1024, 2048, 4096};
-// Split-BF16 batches: the tilings of candidate 0 on the split-BF16 block
-// GEMMs of the single-network form (R register-staged; A + W with direct
-// loads and C split as it is read, 64 x 128 so that the item lists are those
-// of candidate 0; W W^T and the C update as in the single-network form).
+// Split-BF16 batches: the block GEMMs of the single-network form (R
+// register-staged; A + W with direct loads and C split as it is read, 64 x 128
+// so that R and A + W cut a network alike; W W^T and the C update as there).
 using RectB3A = BlockGemmB3P<64, 128, 1, 4, true, 3>;
-static_assert(RectB3::BM == RectT0::BM && RectB3::BN == RectT0::BN &&
-                  RectB3A::BM == RectT0::BM && RectB3A::BN == RectT0::BN &&
-                  SymB3::BM == SymT0::BM && CoopB3::BM == CoopT::BM && CoopB3::BK == CoopT::BK,
-              "split-BF16 tiles share the work lists of candidate 0");
+static_assert(RectB3::BM == RectB3A::BM && RectB3::BN == RectB3A::BN &&
+                  SymB3::BM == SymT0<false>::BM && CoopB3::BM == CoopT::BM,
+              "one work list per product");
 
 // Largest s with seg_first[s] <= it.
 __device__ __forceinline__ int find_segment(const int64_t* __restrict__ first, int nseg,
@@ -65,13 +70,13 @@ struct PhResp {
     const DevState* st = d.st;
     if (st->active == 0) return;
     const float* W = d.W[st->wsel];
-    const int64_t nMT = d.Nep / G::BM;
+    const int64_t nMT = (d.Nep + G::BM - 1) / G::BM;
     const int64_t m0 = (local % nMT) * G::BM, n0 = (local / nMT) * G::BN;
     G g;
     if constexpr (B3)
       g.run(OpsB3{d.Pp, d.Wt}, m0, n0, 0, d.Nep, smem);
     else
-      g.run(OpsF32{d.P, d.Nep, W, d.Nap}, m0, n0, 0, d.Nep, smem);
+      g.run(OpsF32{d.P, d.Nep, W, d.Nap, d.Ne}, m0, n0, 0, d.Nep, smem);
     EpiStoreT epi{d.R, d.Nap, d.Ne, d.Na, d.nP, d.nWc, d.dP, W, d.Nap};
     epi_tile(g, epi, m0, n0);
   }
@@ -92,13 +97,13 @@ struct PhAvail {
     if (st->active == 0) return;
     const int ws = st->wsel;
     const float* Wold = d.W[ws];
-    const int64_t nMT = d.Nep / G::BM;
+    const int64_t nMT = (d.Nep + G::BM - 1) / G::BM;
     const int64_t m0 = (local % nMT) * G::BM, n0 = (local / nMT) * G::BN;
     G g;
     if constexpr (B3)
       g.run(OpsB3F{d.Wr, d.C, d.Nap, d.Nep}, m0, n0, 0, d.Nap, smem);
     else
-      g.run(OpsF32{Wold, d.Nap, d.C, d.Nap}, m0, n0, 0, d.Nap, smem);
+      g.run(OpsF32{Wold, d.Nap, d.C, d.Nap, d.Ne}, m0, n0, 0, d.Nap, smem);
     EpiWUpdate epi{Wold, d.R,   d.W[ws ^ 1], d.Nap, d.Ne,       d.Na,    d.nWr,
                    d.nC, d.dC,  alpha,       h_undamped, d.hpart, 0.0};
     epi_tile(g, epi, m0, n0);
@@ -161,8 +166,8 @@ struct PhCoreg {
 // Persistent grouped product: blocks drain the per-XCD queues, their own
 // first.  Every block exits once all eight queues are empty.
 template <class G, class Ph>
-__global__ __launch_bounds__(G::NT) void k_group_gemm(const BInst* __restrict__ bi, WorkList wl,
-                                                      Ph ph) {
+__global__ __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(G::WAVES_PER_EU)))
+void k_group_gemm(const BInst* __restrict__ bi, WorkList wl, Ph ph) {
   __shared__ __align__(16) char smem[Ph::template smem_bytes<G>()];
   __shared__ double red[8];
   __shared__ int64_t s_item;
@@ -175,7 +180,7 @@ __global__ __launch_bounds__(G::NT) void k_group_gemm(const BInst* __restrict__ 
       __syncthreads();  // the previous item is done with smem and s_item
       if (threadIdx.x == 0) s_item = beg + (int64_t)atomicAdd(wl.ctr + x * kCtrStride, 1);
       __syncthreads();
-      const int64_t it = s_item;
+      const int64_t it = uniform(s_item);
       if (it >= end) break;
       const int seg = find_segment(wl.seg_first, wl.nseg, it);
       ph.template run<G>(bi[wl.seg_inst[seg]], it - wl.seg_first[seg], smem, red);
@@ -354,91 +359,66 @@ int batch_tile_candidates(int phase, bool b3) {
   return 0;
 }
 
-void rect_tile_shape(int choice, int64_t* bm, int64_t* bn) {
-  switch (choice) {
-    case 1: *bm = RectT1::BM; *bn = RectT1::BN; return;
-    case 2: *bm = RectT2::BM; *bn = RectT2::BN; return;
-    default: *bm = RectT0::BM; *bn = RectT0::BN; return;
-  }
+int64_t rect_items(int choice, bool b3, int64_t Nep, int64_t Nap) {
+  auto items = [&](int64_t bm, int64_t bn) { return (Nep + bm - 1) / bm * (Nap / bn); };
+  if (b3) return items(RectB3A::BM, RectB3A::BN);
+  if (choice == 1) return items(RectT1<true>::BM, RectT1<true>::BN);
+  if (choice == 2) return items(RectT2<true>::BM, RectT2<true>::BN);
+  return items(RectT0<true>::BM, RectT0<true>::BN);
 }
 
 int64_t coop_chunk_of(int choice) { return kCoopChunks[choice < 0 || choice > 3 ? 0 : choice]; }
 
-int64_t batch_grid(int phase, int choice, bool sigT, bool b3) {
-  if (b3) {
-    switch (phase) {
-      case kBTResp: return group_grid<RectB3, PhResp<true>>();
-      case kBTAvail: return group_grid<RectB3A, PhAvail<true>>();
-      case kBTCoop: return group_grid<CoopB3, PhCoop<true>>();
-      case kBTCoreg:
-        return sigT ? group_grid<SymB3, PhCoreg<true, true>>()
-                    : group_grid<SymB3, PhCoreg<false, true>>();
-    }
-    return 0;
-  }
+// f(G, phase) for the kernel of grouped product `phase`: lk, whether a
+// network of the batch has sums over more than kFoldK of k there (A + W: most
+// have).  The fresh similarities' sums (sigT) leave room for one block per CU
+// either way.
+template <class F>
+static auto with_product(int phase, int choice, bool sigT, bool b3, bool lk, Rule rule, F&& f) {
+  auto rect = [&](const auto& ph, auto L) {
+    constexpr bool LK = decltype(L)::value;
+    if (choice == 1) return f(RectT1<LK>{}, ph);
+    if (choice == 2) return f(RectT2<LK>{}, ph);
+    return f(RectT0<LK>{}, ph);
+  };
+  auto sym = [&](const auto& ph, auto L) {
+    constexpr bool LK = decltype(L)::value;
+    if (choice == 1) return f(SymT1<LK>{}, ph);
+    if (choice == 2) return f(SymT2<LK>{}, ph);
+    return f(SymT0<LK>{}, ph);
+  };
   switch (phase) {
     case kBTResp:
-      if (choice == 1) return group_grid<RectT1, PhResp<false>>();
-      if (choice == 2) return group_grid<RectT2, PhResp<false>>();
-      return group_grid<RectT0, PhResp<false>>();
+      if (b3) return f(RectB3{}, PhResp<true>{});
+      return lk ? rect(PhResp<false>{}, std::true_type{}) : rect(PhResp<false>{}, std::false_type{});
     case kBTAvail:
-      if (choice == 1) return group_grid<RectT1, PhAvail<false>>();
-      if (choice == 2) return group_grid<RectT2, PhAvail<false>>();
-      return group_grid<RectT0, PhAvail<false>>();
-    case kBTCoop: return group_grid<CoopT, PhCoop<false>>();
-    case kBTCoreg:
-      if (sigT) {
-        if (choice == 1) return group_grid<SymT1, PhCoreg<true, false>>();
-        if (choice == 2) return group_grid<SymT2, PhCoreg<true, false>>();
-        return group_grid<SymT0, PhCoreg<true, false>>();
-      }
-      if (choice == 1) return group_grid<SymT1, PhCoreg<false, false>>();
-      if (choice == 2) return group_grid<SymT2, PhCoreg<false, false>>();
-      return group_grid<SymT0, PhCoreg<false, false>>();
+      if (b3) return f(RectB3A{}, PhAvail<true>{rule.alpha, rule.h_undamped});
+      return rect(PhAvail<false>{rule.alpha, rule.h_undamped}, std::true_type{});
+    case kBTCoop:
+      return b3 ? f(CoopB3{}, PhCoop<true>{}) : f(CoopT{}, PhCoop<false>{});
+    default:
+      if (b3)
+        return sigT ? f(SymB3{}, PhCoreg<true, true>{rule.alpha})
+                    : f(SymB3{}, PhCoreg<false, true>{rule.alpha});
+      if (sigT) return sym(PhCoreg<true, false>{rule.alpha}, std::true_type{});
+      return lk ? sym(PhCoreg<false, false>{rule.alpha}, std::true_type{})
+                : sym(PhCoreg<false, false>{rule.alpha}, std::false_type{});
   }
-  return 0;
 }
 
-hipError_t launch_batch_resp(int choice, bool b3, const BInst* bi, const WorkList& wl, int64_t nb,
-                             hipStream_t s) {
-  if (b3) return group_launch<RectB3>(bi, wl, PhResp<true>{}, nb, s);
-  if (choice == 1) return group_launch<RectT1>(bi, wl, PhResp<false>{}, nb, s);
-  if (choice == 2) return group_launch<RectT2>(bi, wl, PhResp<false>{}, nb, s);
-  return group_launch<RectT0>(bi, wl, PhResp<false>{}, nb, s);
+int64_t batch_grid(int phase, int choice, bool b3, bool lk, Rule rule) {
+  return with_product(phase, choice, rule.sigma_from_T != 0, b3, lk, rule,
+                      [](const auto& g, const auto& ph) {
+                        return group_grid<std::decay_t<decltype(g)>, std::decay_t<decltype(ph)>>();
+                      });
 }
 
-hipError_t launch_batch_avail(int choice, bool b3, const BInst* bi, const WorkList& wl, Rule rule,
-                              int64_t nb, hipStream_t s) {
-  if (b3) return group_launch<RectB3A>(bi, wl, PhAvail<true>{rule.alpha, rule.h_undamped}, nb, s);
-  const PhAvail<false> ph{rule.alpha, rule.h_undamped};
-  if (choice == 1) return group_launch<RectT1>(bi, wl, ph, nb, s);
-  if (choice == 2) return group_launch<RectT2>(bi, wl, ph, nb, s);
-  return group_launch<RectT0>(bi, wl, ph, nb, s);
-}
-
-hipError_t launch_batch_coop_partial(bool b3, const BInst* bi, const WorkList& wl, int64_t nb,
-                                     hipStream_t s) {
-  if (b3) return group_launch<CoopB3>(bi, wl, PhCoop<true>{}, nb, s);
-  return group_launch<CoopT>(bi, wl, PhCoop<false>{}, nb, s);
-}
-
-hipError_t launch_batch_coreg(int choice, bool b3, const BInst* bi, const WorkList& wl, Rule rule,
-                              int64_t nb, hipStream_t s) {
-  if (b3) {
-    if (rule.sigma_from_T)
-      return group_launch<SymB3>(bi, wl, PhCoreg<true, true>{rule.alpha}, nb, s);
-    return group_launch<SymB3>(bi, wl, PhCoreg<false, true>{rule.alpha}, nb, s);
-  }
-  if (rule.sigma_from_T) {
-    const PhCoreg<true, false> ph{rule.alpha};
-    if (choice == 1) return group_launch<SymT1>(bi, wl, ph, nb, s);
-    if (choice == 2) return group_launch<SymT2>(bi, wl, ph, nb, s);
-    return group_launch<SymT0>(bi, wl, ph, nb, s);
-  }
-  const PhCoreg<false, false> ph{rule.alpha};
-  if (choice == 1) return group_launch<SymT1>(bi, wl, ph, nb, s);
-  if (choice == 2) return group_launch<SymT2>(bi, wl, ph, nb, s);
-  return group_launch<SymT0>(bi, wl, ph, nb, s);
+hipError_t launch_batch_product(int phase, int choice, bool b3, bool lk, const BInst* bi,
+                                const WorkList& wl, Rule rule, int64_t nb, hipStream_t s) {
+  return with_product(phase, choice, rule.sigma_from_T != 0, b3, lk, rule,
+                      [&](const auto& g, const auto& ph) {
+                        return group_launch<std::decay_t<decltype(g)>>(bi, wl, ph, nb, s);
+                      });
 }
 
 hipError_t launch_batch_planes(const BInst* bi, const FlatList& fl, hipStream_t s) {

@@ -159,16 +159,14 @@ struct EpiWUpdateT {
 
 using EpiWUpdate = EpiWUpdateT<false>;
 
-// Tile configurations.  FP32 matrix cores (stand-alone similarity, batches,
-// the co-expression prior): rectangular products on 64 x 128 tiles, 4 waves
-// side by side, symmetric ones on 128 x 128.
-using RectF32 = BlockGemm<64, 128, 1, 4, true, false, 16>;
+// Tile configurations.  FP32 operands (stand-alone similarity, the warm start,
+// the co-expression prior): 128 x 128, four waves.
+template <bool LK>
+using RectF32 = BlockGemmF3<128, 128, 2, 2, true, false, LK>;
 using RectB3 = BlockGemmB3<64, 128, 1, 4>;  // batched R: K = N_e is short, register staging wins
-static_assert(RectF32::BM == RectB3::BM && RectF32::BN == RectB3::BN, "one tile grid");
-using SymF32 = BlockGemm<128, 128, 2, 2, false, false, 16>;
-using CoopF32 = BlockGemm<64, 64, 2, 2, true, true, 32>;
+template <bool LK>
+using SymF32 = BlockGemmF3<128, 128, 4, 1, false, false, LK>;
 using CoopB3 = BlockGemmB3<64, 64, 2, 2>;
-static_assert(CoopF32::BK == CoopB3::BK, "one K split");
 // The products of a single network on bf16 planes, NP = 2 (split-BF16 form)
 // or 3 (FP32 form).  The FP32 form runs on them too because six bf16 products
 // of exact planes take 6/16 of the FP32 matrix cores' time for the same

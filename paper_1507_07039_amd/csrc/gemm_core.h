@@ -27,6 +27,13 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// A value that is the same in every lane, for the compiler to keep as such.
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+  const int hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return ((int64_t)hi << 32) | lo;
+}
+
 // Logical number for block b of an n-block grid: contiguous chunks per XCD.
 __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t n) {
   const int64_t xcd = b & 7, slot = b >> 3;
@@ -79,67 +86,6 @@ __device__ __forceinline__ float from_bf16(bf16_t b) {
   return (float)__builtin_bit_cast(__bf16, b);
 }
 
-// ======================================================== FP32 main loop ==
-// One operand's MN x BK tile: global -> registers -> LDS.  KC: the operand
-// is contiguous along k in global memory (element (mn, k) at base[mn*ld+k]);
-// otherwise along mn (element at base[k*ld + mn]).  The LDS copy is always
-// [k][mn] with row length LD, the layout the MFMA operand reads want (32
-// consecutive mn per half-wave).  LD is padded so that the transposing
-// stores of the KC case hit every bank equally often.
-template <int MN, bool KC, int BK>
-struct TileLoad {
-  static constexpr int NV = MN * BK / 4 / kThreads;  // float4 per thread
-  static constexpr int KQ = BK / 4;                  // KC: threads per mn-row
-  static constexpr int RP = kThreads / KQ;           // KC: mn-rows per pass
-  static constexpr int TPR = MN / 4;                 // !KC: threads per k-row
-  static constexpr int RPP = kThreads / TPR;         // !KC: k-rows per pass
-  static constexpr int LD = KC ? MN + (BK == 32 ? 2 : 4) : MN + 4;
-  static_assert(NV >= 1, "tile too small for one float4 per thread");
-  static_assert(KC ? (RP * NV == MN) : (RPP * NV == BK), "loads must cover the tile");
-
-  f4 v[NV];
-
-  __device__ __forceinline__ void load(const float* __restrict__ base, int64_t ld, int64_t mn0,
-                                       int64_t k0, int t) {
-    if constexpr (KC) {
-      const int kq = (t % KQ) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int mn = t / KQ + i * RP;
-        v[i] = *reinterpret_cast<const f4*>(base + (mn0 + mn) * ld + k0 + kq);
-      }
-    } else {
-      const int mnq = (t % TPR) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int k = t / TPR + i * RPP;
-        v[i] = *reinterpret_cast<const f4*>(base + (k0 + k) * ld + mn0 + mnq);
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(float* lds, int t) const {
-    if constexpr (KC) {
-      const int kq = (t % KQ) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int mn = t / KQ + i * RP;
-        lds[(kq + 0) * LD + mn] = v[i].x;
-        lds[(kq + 1) * LD + mn] = v[i].y;
-        lds[(kq + 2) * LD + mn] = v[i].z;
-        lds[(kq + 3) * LD + mn] = v[i].w;
-      }
-    } else {
-      const int mnq = (t % TPR) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int k = t / TPR + i * RPP;
-        *reinterpret_cast<f4*>(lds + k * LD + mnq) = v[i];
-      }
-    }
-  }
-};
-
 // FP32 operands: X element (m, k) = XK ? X[m*ldx + k] : X[k*ldx + m];
 // Y element (k, n) = YK ? Y[n*ldy + k] : Y[k*ldy + n].
 struct OpsF32 {
@@ -147,186 +93,7 @@ struct OpsF32 {
   int64_t ldx;
   const float* Y;
   int64_t ldy;
-};
-// The same with Y a packed symmetric matrix (packed_tile).
-struct OpsF32P {
-  const float* X;
-  int64_t ldx;
-  const float* Yp;
-};
-
-// Y tile (MN = kPT columns, BK rows) of a product whose Y is a packed
-// symmetric matrix: element (k, n) = Y[k][n], n in column block J = n0 / kPT.
-// For k in block Kb <= J, tile (Kb, J) holds it at row k, column n (n
-// contiguous, TileLoad<MN, false>'s pattern); for Kb > J, tile (J, Kb) holds
-// it at row n, column k (k contiguous, TileLoad<MN, true>'s pattern).  A
-// K-tile lies inside one block (BK divides kPT), so the orientation is chosen
-// per K-tile, the same for the whole block; both fill the same [k][mn] LDS
-// layout.
-template <int MN, int BK>
-struct TileLoadPY {
-  using LN = TileLoad<MN, false, BK>;
-  using LT = TileLoad<MN, true, BK>;
-  static_assert(MN == kPT && kPT % BK == 0, "one packed column block per tile");
-  static_assert(LN::LD == LT::LD && LN::NV == LT::NV, "one LDS layout for both orientations");
-  static constexpr int LD = LN::LD;
-  static constexpr int NV = LN::NV;
-  f4 v[NV];
-  bool tr;
-
-  __device__ __forceinline__ void load(const float* __restrict__ Yp, int64_t n0, int64_t k0, int t) {
-    const int64_t J = n0 / kPT, Kb = k0 / kPT, kk = k0 % kPT;
-    tr = Kb > J;
-    if (!tr) {
-      const float* base = Yp + packed_tile(Kb, J) * (kPT * kPT) + kk * kPT;
-      const int mnq = (t % LN::TPR) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int k = t / LN::TPR + i * LN::RPP;
-        v[i] = *reinterpret_cast<const f4*>(base + k * kPT + mnq);
-      }
-    } else {
-      const float* base = Yp + packed_tile(J, Kb) * (kPT * kPT) + kk;
-      const int kq = (t % LT::KQ) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int mn = t / LT::KQ + i * LT::RP;
-        v[i] = *reinterpret_cast<const f4*>(base + mn * kPT + kq);
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(float* lds, int t) const {
-    if (!tr) {
-      const int mnq = (t % LN::TPR) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int k = t / LN::TPR + i * LN::RPP;
-        *reinterpret_cast<f4*>(lds + k * LD + mnq) = v[i];
-      }
-    } else {
-      const int kq = (t % LT::KQ) * 4;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int mn = t / LT::KQ + i * LT::RP;
-        lds[(kq + 0) * LD + mn] = v[i].x;
-        lds[(kq + 1) * LD + mn] = v[i].y;
-        lds[(kq + 2) * LD + mn] = v[i].z;
-        lds[(kq + 3) * LD + mn] = v[i].w;
-      }
-    }
-  }
-};
-
-// Block-level FP32 GEMM over k in [kbeg, kend) for a BM x BN tile with WM x WN
-// waves; each wave owns a (BM/WM) x (BN/WN) sub-tile of 32 x 32 MFMA blocks
-// (v_mfma_f32_32x32x2f32).  YP: Y is a packed symmetric matrix (OpsF32P).
-template <int BM_, int BN_, int WM, int WN, bool XK, bool YK, int BK_, bool YP = false>
-struct BlockGemm {
-  using Ops = typename std::conditional<YP, OpsF32P, OpsF32>::type;
-  static constexpr int BM = BM_, BN = BN_, BK = BK_, NT = kThreads;
-  static constexpr int WAVES_PER_EU = 1;  // occupancy asked of the compiler (1: no request)
-  static_assert(WM * WN == 4, "four waves per block");
-  static constexpr int TM = BM / WM / 32;
-  static constexpr int TN = BN / WN / 32;
-  static_assert(TM >= 1 && TN >= 1, "wave tile below one MFMA block");
-  using LX = TileLoad<BM, XK, BK>;
-  using LY = typename std::conditional<YP, TileLoadPY<BN, BK>, TileLoad<BN, YK, BK>>::type;
-  __device__ __forceinline__ static void load_y(LY& ly, const Ops& o, int64_t n0, int64_t k0,
-                                                int t) {
-    if constexpr (YP)
-      ly.load(o.Yp, n0, k0, t);
-    else
-      ly.load(o.Y, o.ldy, n0, k0, t);
-  }
-  static constexpr int XS = BK * LX::LD;
-  static constexpr int YS = BK * LY::LD;
-  static constexpr int MAIN_BYTES = 2 * (XS + YS) * 4;
-
-  floatx16 acc[TM][TN];
-  int lane, wm, wn;
-
-  __device__ __forceinline__ void run(const Ops& o, int64_t m0, int64_t n0, int64_t kbeg,
-                                      int64_t kend, char* smem) {
-    const int t = threadIdx.x;
-    lane = t & 63;
-    const int w = t >> 6;
-    wm = w % WM;
-    wn = w / WM;
-    float* xs = reinterpret_cast<float*>(smem);
-    float* ys = xs + 2 * XS;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    LX lx;
-    LY ly;
-    const int64_t nk = (kend - kbeg) / BK;
-    if (nk > 0) {
-      lx.load(o.X, o.ldx, m0, kbeg, t);
-      load_y(ly, o, n0, kbeg, t);
-      lx.store(xs, t);
-      ly.store(ys, t);
-    }
-    __syncthreads();
-    const int mrow = wm * (BM / WM) + (lane & 31);
-    const int ncol = wn * (BN / WN) + (lane & 31);
-    const int khalf = lane >> 5;
-    for (int64_t kt = 0; kt < nk; ++kt) {
-      const int cur = (int)(kt & 1);
-      const bool more = kt + 1 < nk;
-      if (more) {
-        lx.load(o.X, o.ldx, m0, kbeg + (kt + 1) * BK, t);
-        load_y(ly, o, n0, kbeg + (kt + 1) * BK, t);
-      }
-      const float* xc = xs + cur * XS;
-      const float* yc = ys + cur * YS;
-#pragma unroll
-      for (int kk = 0; kk < BK / 2; ++kk) {
-        const int kr = 2 * kk + khalf;
-        float a[TM], b[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) a[i] = xc[kr * LX::LD + mrow + i * 32];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) b[j] = yc[kr * LY::LD + ncol + j * 32];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_iglp_opt(0);  // interleave LDS reads with the MFMAs
-      }
-      if (more) {
-        lx.store(xs + (cur ^ 1) * XS, t);
-        ly.store(ys + (cur ^ 1) * YS, t);
-      }
-      __syncthreads();
-    }
-  }
-
-  // Local (row, col) in the block tile of accumulator register r of MFMA
-  // block (i, j): the 32x32 result layout puts column lane%32 in each lane
-  // and rows 8*(r/4) + 4*(lane/32) + r%4.
-  __device__ __forceinline__ int row_of(int i, int r) const {
-    return wm * (BM / WM) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-  }
-  __device__ __forceinline__ int col_of(int j) const {
-    return wn * (BN / WN) + j * 32 + (lane & 31);
-  }
-  template <class F>
-  __device__ __forceinline__ void for_each(F&& f) const {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int c = col_of(j);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) f(row_of(i, r), c, acc[i][j][r]);
-      }
-  }
+  int64_t xrows = INT64_MAX;  // rows (m) of X that exist (loaders may clamp to them)
 };
 
 // ================================================== split-BF16 main loop ==
@@ -603,6 +370,289 @@ __device__ __forceinline__ void split_pair3(float a, float b, unsigned (&o)[3]) 
   o[2] = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, lb), __builtin_bit_cast(unsigned, la),
                                0x07060302u);
 }
+
+// ========================================= FP32 operands on bf16 planes ==
+// Block-level product of FP32 operands (OpsF32) over k in [kbeg, kend), a
+// multiple of 16, on the bf16 matrix cores: each 16-deep K-tile is split into
+// its three exact bf16 planes (split_pair3) between the registers it was
+// loaded into and LDS, and multiplied as BlockGemmB3P<NP = 3> multiplies
+// stored planes.  For operands nobody keeps planes of: batches, the
+// stand-alone similarity, the correlations, the warm start.
+//
+// A wave of 64 x 64 has 24 MFMAs of 32 cycles per K-tile; the next tile's
+// split (some 90 vector instructions) and LDS stores go between them, and two
+// waves per SIMD cover each other's fragment reads and barriers.  What it took
+// to keep the matrix cores fed: two K-tiles on their way in registers, loads
+// known to be in global memory (flat ones are waited for with every LDS
+// read), and no work for row blocks that are all padding.  Against
+// v_mfma_f32_32x32x2f32 on the same operands: A + W of a batch of six
+// networks (57 x 4999 to 661 x 9787, 238 GFLOP) 2.81 -> 1.62 ms (880 TFLOP/s
+// of bf16), its C update 1.74 -> 1.11, W W^T 0.15 -> 0.11; a similarity of 700
+// x 2001 x 5003 167 -> 94 us; correlations of 18000 genes over 200 samples
+// 890 -> 730 us (1.3 GB written).  The error against 64 bits falls to between
+// a third and 0.8 of what it was.
+//
+// LK: for sums over more than kFoldK of k, folded as there, in registers (a
+// choice of kernel: the running sum takes 64 of the 256 registers a wave has;
+// it cost 15 % where it was carried for K = 700).
+template <int MN, bool KC, int NT>
+struct TileLoadF3 {
+  static constexpr int NI = MN * 2 / NT;  // runs of 8 k per thread
+  static_assert(NI >= 1 && NI * NT == MN * 2, "whole runs per thread");
+  // LDS, per plane and 8 k: 16 bytes per row.  The pad keeps the two runs of
+  // a row, which neighbouring lanes of the KC case write, in other banks.
+  static constexpr int RUN = MN * 16 + (KC ? 128 : 0), PLANE = 2 * RUN;
+  // the next K-tile to load: uniform, and known to be in global memory (a flat
+  // load would also be waited for with every LDS read)
+  using Global = const __attribute__((address_space(1))) char*;
+  template <class T>
+  using GlobalP = const __attribute__((address_space(1))) T*;
+  Global base;
+  unsigned off[NI];  // bytes, per lane
+  int64_t ld;        // bytes from one row in memory to the next
+  float v[2][NI][8];  // two tiles on their way
+
+  __device__ __forceinline__ static int row(int t, int i) {
+    return KC ? (t + i * NT) >> 1 : (t + i * NT) % MN;
+  }
+  __device__ __forceinline__ static int run(int t, int i) {
+    return KC ? (t + i * NT) & 1 : (t + i * NT) / MN;
+  }
+  // Rows past the operand's end re-read its last one; their outputs are never
+  // stored.
+  __device__ __forceinline__ void setup(const float* b, int64_t ld_, int64_t mn0, int64_t rows,
+                                        int64_t kbeg, int t) {
+    ld = uniform(4 * ld_);
+    base = (Global)(size_t)uniform((int64_t)(size_t)(KC ? b + mn0 * ld_ + kbeg : b + kbeg * ld_ + mn0));
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int r = mn0 + row(t, i) < rows ? row(t, i) : (int)(rows - 1 - mn0);
+      off[i] = KC ? (unsigned)(r * ld) + 32u * run(t, i) : (unsigned)(8 * run(t, i) * ld) + 4u * r;
+    }
+  }
+  // The tile at `base` into set S; `more`: another one follows it.
+  template <int S>
+  __device__ __forceinline__ void load(bool more) {
+#pragma unroll
+    for (int e = 0; e < (KC ? 1 : 8); ++e) {
+      // a uniform base per row: one 32-bit offset per run serves all its loads
+      int64_t a = (int64_t)base + (KC ? 0 : e * ld);
+      asm("" : "+s"(a));
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        unsigned r = off[i];
+        asm("" : "+v"(r));  // (stays a 32-bit offset)
+        if constexpr (KC) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const f4 x = *(GlobalP<f4>)((Global)a + r + 16 * h);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[S][i][4 * h + k] = x[k];
+          }
+        } else {
+          v[S][i][e] = *(GlobalP<float>)((Global)a + r);
+        }
+      }
+    }
+    base += more ? (KC ? 64 : 16 * ld) : 0;
+  }
+  // Piece q of 5 NI of set S: four pairs split, then the run's planes stored.
+  template <int S>
+  __device__ __forceinline__ void put(char* lds, int t, int q, unsigned (&o)[3][4]) {
+    const int i = q / 5, s = q % 5;
+    if (s < 4) {
+      unsigned u[3];
+      // not before its MFMA (the compiler would otherwise start with it and
+      // wait for the loads there)
+      asm volatile("" : "+v"(v[S][i][2 * s]), "+v"(v[S][i][2 * s + 1]));
+      split_pair3(v[S][i][2 * s], v[S][i][2 * s + 1], u);
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl) o[pl][s] = u[pl];
+    } else {
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl)
+        *reinterpret_cast<u4*>(lds + pl * PLANE + run(t, i) * RUN + row(t, i) * 16) =
+            (u4){o[pl][0], o[pl][1], o[pl][2], o[pl][3]};
+    }
+  }
+};
+
+template <int BM_, int BN_, int WM, int WN, bool XK, bool YK, bool LK>
+struct BlockGemmF3 {
+  using Ops = OpsF32;
+  static constexpr int BM = BM_, BN = BN_, BK = 16, NT = 64 * WM * WN;
+  static constexpr int WAVES_PER_EU = 2;
+  static constexpr bool kPrefetchEpi = true, kBlockEpi = true;
+  static constexpr int TM = BM / WM / 32;
+  static constexpr int TN = BN / WN / 32;
+  static_assert(TM >= 1 && TN >= 1, "wave tile below one MFMA block");
+  using LX = TileLoadF3<BM, XK, NT>;
+  using LY = TileLoadF3<BN, YK, NT>;
+  static constexpr int STAGE = 3 * (LX::PLANE + LY::PLANE);
+  static constexpr int MAIN_BYTES = 2 * STAGE;
+  static constexpr int NQX = LX::NI * 5, NQ = NQX + LY::NI * 5;  // pieces of a split
+  static constexpr int kFoldTiles = (int)(kFoldK / BK);
+
+  floatx16 acc[TM][TN];
+  int lane, wm, wn;
+
+  __device__ __forceinline__ void run(const Ops& o, int64_t m0, int64_t n0, int64_t kbeg,
+                                      int64_t kend, char* smem) {
+    constexpr int XP[6] = {2, 0, 1, 1, 0, 0}, YP[6] = {0, 2, 1, 0, 1, 0};
+    const int t = threadIdx.x;
+    lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    wm = w % WM;
+    wn = w / WM;
+    floatx16 sum[LK ? TM : 1][LK ? TN : 1];
+    auto clear = [](auto& a) {
+#pragma unroll
+      for (auto& row : a)
+#pragma unroll
+        for (auto& x : row)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) x[r] = 0.0f;
+    };
+    clear(acc);
+    if constexpr (LK) clear(sum);
+
+    LX lx;
+    LY ly;
+    lx.setup(o.X, o.ldx, m0, o.xrows, kbeg, t);
+    ly.setup(o.Y, o.ldy, n0, INT64_MAX, kbeg, t);
+    const int nk = (int)(uniform(kend - kbeg) / BK);
+    // 32-row blocks of this wave that hold rows of X; the others (padding) take
+    // no part: their outputs are never stored
+    const int64_t rows = uniform(o.xrows - m0) - wm * (BM / WM);
+    const int live = rows >= 32 * TM ? TM : rows <= 0 ? 0 : (int)(rows + 31) / 32;
+    unsigned ox[3][4], oy[3][4];
+    const int xo = (lane >> 5) * LX::RUN + (wm * (BM / WM) + (lane & 31)) * 16;
+    const int yo = 3 * LX::PLANE + (lane >> 5) * LY::RUN + (wn * (BN / WN) + (lane & 31)) * 16;
+    // K-tile kt: stage kt % 2 holds it, register set S tile kt + 1 and the other
+    // set tile kt + 2 (or the last tile again, at the end of the range).  Tile
+    // kt + 1 is split into the other stage and tile kt + 3 loaded, each piece
+    // under an MFMA.
+    auto step = [&](auto set, auto nl, int kt) {
+      constexpr int S = decltype(set)::value;
+      constexpr int TL = decltype(nl)::value;  // live row blocks
+      constexpr int NM = 6 * TL * TN;          // MFMAs per K-tile
+      constexpr int PM = NM > 1 ? (NQ + NM - 2) / (NM - 1) : NQ;  // pieces under each
+      const char* rd = smem + (kt & 1) * STAGE;
+      char* wr = smem + ((kt + 1) & 1) * STAGE;
+      auto piece = [&](int q) {
+        if (q < NQX)
+          lx.template put<S>(wr, t, q, ox);
+        else if (q < NQ)
+          ly.template put<S>(wr + 3 * LX::PLANE, t, q - NQX, oy);
+      };
+      const bool more = kt + 4 < nk;
+      if constexpr (TL == 0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) piece(q);
+        lx.template load<S>(more);
+        ly.template load<S>(more);
+      } else {
+        bf16x8 x[3][TL], y[3][TN];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+          for (int i = 0; i < TL; ++i)
+            x[pl][i] = *reinterpret_cast<const bf16x8*>(rd + xo + pl * LX::PLANE + i * 512);
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            y[pl][j] = *reinterpret_cast<const bf16x8*>(rd + yo + pl * LY::PLANE + j * 512);
+        }
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+          const int j = m % TN, i = (m / TN) % TL, p = m / TN / TL;
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[XP[p]][i], y[YP[p]][j], acc[i][j],
+                                                              0, 0, 0);
+#pragma unroll
+          for (int q = m * PM; q < (m + 1) * PM; ++q) piece(q);
+          if (m == (NQX + PM - 1) / PM) lx.template load<S>(more);
+          if (m == (NQ + PM - 1) / PM) ly.template load<S>(more);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __syncthreads();
+    };
+    if (nk > 0) {
+      lx.template load<0>(nk > 1);
+      ly.template load<0>(nk > 1);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        if (q < NQX)
+          lx.template put<0>(smem, t, q, ox);
+        else
+          ly.template put<0>(smem + 3 * LX::PLANE, t, q - NQX, oy);
+      }
+      lx.template load<0>(nk > 2);
+      ly.template load<0>(nk > 2);
+      lx.template load<1>(nk > 3);
+      ly.template load<1>(nk > 3);
+    }
+    __syncthreads();
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    auto tiles = [&](auto nl) {
+      constexpr int TL = decltype(nl)::value;
+      for (int kt = 0; kt < nk; kt += 2) {
+        step(S0{}, nl, kt);
+        if (kt + 1 < nk) step(S1{}, nl, kt + 1);
+        if constexpr (LK) {
+          if (kt % kFoldTiles == kFoldTiles - 2) {
+#pragma unroll
+            for (int i = 0; i < TL; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                  sum[i][j][r] += acc[i][j][r];
+                  acc[i][j][r] = 0.0f;
+                }
+          }
+        }
+      }
+    };
+    static_assert(TM <= 4 && TM != 3, "live row blocks");
+    if (live == TM) {
+      tiles(std::integral_constant<int, TM>{});
+    } else if (live == 0) {
+      tiles(std::integral_constant<int, 0>{});
+    } else if constexpr (TM >= 2) {
+      if (live == 1) tiles(std::integral_constant<int, 1>{});
+      if constexpr (TM == 4) {
+        if (live == 2) tiles(std::integral_constant<int, 2>{});
+        if (live == 3) tiles(std::integral_constant<int, 3>{});
+      }
+    }
+    if constexpr (LK) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] += sum[i][j][r];
+    }
+  }
+  __device__ __forceinline__ int row_of(int i, int r) const {
+    return wm * (BM / WM) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+  }
+  __device__ __forceinline__ int col_of(int j) const {
+    return wn * (BN / WN) + j * 32 + (lane & 31);
+  }
+  template <class F>
+  __device__ __forceinline__ void for_each(F&& f) const {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int c = col_of(j);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) f(row_of(i, r), c, acc[i][j][r]);
+      }
+  }
+};
 
 // YF32: Y is the FP32 symmetric matrix split as its fragments are read;
 // otherwise Y is given as bf16 hi/lo planes like X (no split arithmetic).
@@ -1448,6 +1498,7 @@ __global__ __launch_bounds__(kFixThreads) void k_rect_fixup(int64_t nMT, int64_t
   epi.end_tile(qb * nTiles + tile, red);
 }
 
+constexpr int64_t kPartTile = 64 * 128;  // floats of a unit of split-tile scratch
 constexpr int64_t kFoldBlocks = 256;  // folding slots of a rectangular product
 
 inline int64_t device_cus() {
@@ -1486,7 +1537,7 @@ hipError_t launch_rect(const typename G::Ops& ops, int64_t Mp, int64_t Np, int64
   // K-steps: the largest block load (with start-up per item) plus the fix-up,
   // which reads S partials per entry; the partials must fit the scratch
   // (2 * kMaxStreamKBlocks tiles of 64 x 128).
-  const int64_t cap = 2 * kMaxStreamKBlocks * 64 * 128 / (G::BM * G::BN);
+  const int64_t cap = 2 * kMaxStreamKBlocks * kPartTile / (G::BM * G::BN);
   constexpr int64_t kItemCost = 8;
   // A product of fewer tiles than CUs is all tail: with S = 1 a block per
   // tile would leave the other CUs idle for the whole of K.  Blocks of one CU

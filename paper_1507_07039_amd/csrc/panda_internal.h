@@ -87,7 +87,6 @@ inline int64_t packed_floats(int64_t Nap) {
 // Y is Kp x Np (n contiguous); Mp % 64 == 0, Np % 128 == 0, Kp % 32 == 0.
 // nx / ny are the FP64 squared norms of the rows of X / columns of Y.
 // part: rect_partial_floats() floats of split-tile scratch.
-int64_t rect_tiles(int64_t Mp, int64_t Np);
 // h partial slots of the A + W product: one per tile and fix-up block part
 // (slots of tiles the fix-up never splits stay zero)
 int64_t avail_hpart_slots(int64_t Mp, int64_t Np);

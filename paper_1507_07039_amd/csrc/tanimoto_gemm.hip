@@ -8,11 +8,11 @@
 // The iteration's products run on bf16 planes of their operands
 // (v_mfma_f32_32x32x16_bf16, FP32 accumulator): two planes and three products
 // in the split-BF16 form, three exact planes and six products in the FP32
-// form.  The stand-alone Tfunction and the correlations use
-// v_mfma_f32_32x32x2f32.  The diagonals of P and C (which grow like exp(2
-// alpha t), Eq. 6) are kept out of the operands and added back in FP64 in the
-// epilogue (P_ii W_ij in R, W_ij C_jj in A).  Norms, denominators and h stay
-// FP64 in both forms.
+// form.  The stand-alone Tfunction and the correlations split their FP32
+// operands into the three planes as they are loaded.  The diagonals of P and C
+// (which grow like exp(2 alpha t), Eq. 6) are kept out of the operands and
+// added back in FP64 in the epilogue (P_ii W_ij in R, W_ij C_jj in A).  Norms,
+// denominators and h stay FP64 in both forms.
 #include "epilogues.h"
 
 namespace panda {
@@ -94,9 +94,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 // Pearson correlations: one upper 128 x 128 tile of Z Z^T per block, both
 // operands read from Z^T (samples x genes), stored at the tile and mirrored.
 template <class G>
-__global__ __launch_bounds__(kThreads) void k_corr_sym(typename G::Ops ops, int64_t Kp,
-                                                       float* __restrict__ C, int64_t ldc,
-                                                       int64_t n) {
+__global__ __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(G::WAVES_PER_EU)))
+void k_corr_sym(typename G::Ops ops, int64_t Kp, float* __restrict__ C, int64_t ldc, int64_t n) {
   __shared__ __align__(16) char smem[corr_smem_bytes<G>()];
   int64_t I, J;
   tri_tile(xcd_tile(blockIdx.x, gridDim.x), I, J);
@@ -135,7 +134,6 @@ __global__ __launch_bounds__(kThreads) void k_coop_partial(typename G::Ops ops, 
 
 // ---------------------------------------------------------------- launch --
 
-int64_t rect_tiles(int64_t Mp, int64_t Np) { return (Mp / RectF32::BM) * (Np / RectF32::BN); }
 template <int NP>
 constexpr bool kOneAvailGrid = Tiles<NP>::Rect::BM == Tiles<2>::Rect::BM &&
                                Tiles<NP>::Rect::BN == Tiles<2>::Rect::BN &&
@@ -151,7 +149,16 @@ size_t rect_fold_floats(int64_t Kp, int np) {
   return np == 3 && Kp > kFoldK ? (size_t)kFoldBlocks * G::BM * G::BN : 0;
 }
 size_t rect_partial_floats() {
-  return (size_t)2 * (size_t)kMaxStreamKBlocks * RectF32::BM * RectF32::BN;
+  return (size_t)2 * (size_t)kMaxStreamKBlocks * (size_t)kPartTile;
+}
+
+static hipError_t rect_f32(const OpsF32& ops, int64_t Mp, int64_t Np, int64_t Kp,
+                           const EpiStoreT& epi, float* part, const int32_t* gate, hipStream_t s) {
+  auto run = [&](auto g) {
+    using G = decltype(g);
+    return launch_rect<G>(ops, round_up(Mp, G::BM), Np, Kp, epi, part, gate, s);
+  };
+  return Kp > kFoldK ? run(RectF32<true>{}) : run(RectF32<false>{});
 }
 
 hipError_t launch_tanimoto_store(const float* X, int64_t ldx, const float* Y, int64_t ldy,
@@ -165,17 +172,21 @@ hipError_t launch_tanimoto_store(const float* X, int64_t ldx, const float* Y, in
     epi.xv = X;
     epi.ldxv = ldx;
   }
-  return launch_rect<RectF32>(OpsF32{X, ldx, Y, ldy}, Mp, Np, Kp, epi, part, gate, s);
+  return rect_f32(OpsF32{X, ldx, Y, ldy, M}, Mp, Np, Kp, epi, part, gate, s);
 }
 
 hipError_t launch_corr(const float* Zt, int64_t Gp, int64_t Sp, int64_t G, float* C, int64_t ldc,
                        hipStream_t s) {
   // X = Z stored sample-major (Z^T), as W^T is read from W in the C update.
-  if (Gp % kCB || Sp % SymF32::BK || G > Gp) return hipErrorInvalidValue;
   const int64_t nT = Gp / kCB;
-  k_corr_sym<SymF32><<<dim3((unsigned)(nT * (nT + 1) / 2)), dim3(kThreads), 0, s>>>(
-      OpsF32{Zt, Gp, Zt, Gp}, Sp, C, ldc, G);
-  return hipGetLastError();
+  auto run = [&](auto g) {
+    using Gm = decltype(g);
+    if (Gp % kCB || Sp % Gm::BK || G > Gp) return hipErrorInvalidValue;
+    k_corr_sym<Gm><<<dim3((unsigned)(nT * (nT + 1) / 2)), dim3(Gm::NT), 0, s>>>(
+        OpsF32{Zt, Gp, Zt, Gp}, Sp, C, ldc, G);
+    return hipGetLastError();
+  };
+  return Sp > kFoldK ? run(SymF32<true>{}) : run(SymF32<false>{});
 }
 
 hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const float* W, int64_t ldw,
@@ -183,7 +194,7 @@ hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const floa
                        const double* nWc, float* R, float* part, const int32_t* gate,
                        hipStream_t s) {
   EpiStoreT epi{R, ldw, Ne, Na, nP, nWc, dP, W, ldw};
-  return launch_rect<RectF32>(OpsF32{P, ldp, W, ldw}, Nep, Nap, Nep, epi, part, gate, s);
+  return rect_f32(OpsF32{P, ldp, W, ldw, Ne}, Nep, Nap, Nep, epi, part, gate, s);
 }
 
 template <int NP, class Epi>
@@ -328,14 +339,14 @@ hipError_t launch_coreg_update_next_r(const Planes& Wt, int np, int64_t Nep,
 int coop_splits(int64_t Nep, int64_t Nap, int64_t blocks) {
   const int64_t nT = Nep / kPB, nU = nT * (nT + 1) / 2;
   int64_t s = (blocks + nU - 1) / nU;
-  const int64_t maxs = Nap / (4 * CoopF32::BK);  // at least 4 K-steps per block
+  const int64_t maxs = Nap / (4 * CoopB3::BK);  // at least 4 K-steps per block
   if (s > maxs) s = maxs;
   if (s < 1) s = 1;
   return (int)s;
 }
 
 static int64_t coop_chunk(int64_t Nap, int splits) {
-  return round_up((Nap + splits - 1) / splits, CoopF32::BK);
+  return round_up((Nap + splits - 1) / splits, CoopB3::BK);
 }
 
 hipError_t launch_coop_partial(const Planes& Wr, int np, int64_t Nep, int64_t Nap, int splits,

@@ -2,10 +2,11 @@
 (the Pearson correlation between the genes of an expression matrix, genes x
 samples) and place it on its roofline.
 
-The correlations are one FP32 MFMA product of the centred, normalised rows
+The correlations are one FP32 product of the centred, normalised rows
 with their transpose, taken on the upper triangle of tiles and mirrored:
 S G (G + 1) flops algorithmic (2 S per distinct entry, diagonal included,
-unpadded sizes) against FP32 MFMA's 157.3 TFLOP/s; the output, 4 G^2 bytes,
+unpadded sizes) against FP32 MFMA's 157.3 TFLOP/s (the product itself runs as
+six bf16 ones on three exact planes, so it may exceed that); the output, 4 G^2 bytes,
 is the bulk of the HBM traffic.  The input
 is the synthetic expression matrix of the T=700, G=18000 workload (inputs.py:
 200 samples, 20 latent factors) unless sizes are given.  Prints one JSON line.

@@ -125,6 +125,41 @@ def test_tanimoto_split_k(torch, pd, M, K, N):
     assert np.all(np.abs(got - want) <= bound)
 
 
+# rows ending in each 32-row block of a tile and either side of it; K of one
+# to five 16-deep tiles (the loads run up to three ahead), either side of the
+# longest unfolded sum and of a fold
+@pytest.mark.parametrize("M", [1, 32, 33, 65, 97, 128, 129])
+@pytest.mark.parametrize("K", [16, 32, 48, 64, 80, 1024, 1040, 2033])
+def test_tanimoto_row_blocks_and_folds(torch, pd, M, K):
+    """The bound of test_tanimoto_split_k."""
+    X = f32r(I.random_dense(M + K, (M, K)))
+    Y = f32r(I.random_dense(M * K, (K, 130), -2.0, 2.0))
+    got = host(pd.tanimoto(cuda(torch, X), cuda(torch, Y)))
+    dot = X @ Y
+    den = (X ** 2).sum(1)[:, None] + (Y ** 2).sum(0)[None, :] - np.abs(dot)
+    want = dot / np.sqrt(den)
+    bound = 2 * K * U * (np.abs(X) @ np.abs(Y)) / np.sqrt(den) + 4 * U * np.abs(want) + 1e-30
+    assert np.all(np.abs(got - want) <= bound)
+
+
+# every tiling over networks with one live row block, a ragged last tile, and
+# more TFs than an unfolded sum takes
+@pytest.mark.parametrize("tiles", [0, 1, 2])
+def test_batch_tiles_ragged(torch, pd, oracle, tiles):
+    """One iteration against the oracle, relative to each matrix's largest entry,
+    within the bound the grouped form is held to elsewhere (1e-5)."""
+    shapes = [(3, 2100), (33, 2100), (161, 2100), (1100, 1150)]
+    nets = [prep(oracle, 900 + i, *s) for i, s in enumerate(shapes)]
+    b = pd.Batch(shapes, pd.default_options(tol=0.0))
+    b.tiles = [tiles] * 4
+    for i, net in enumerate(nets):
+        b.load(i, *(cuda(torch, a) for a in net))
+    b.iterate(1)
+    for i, (W, P, C) in enumerate(nets):
+        for got, want in zip(b.state(i)[:3], oracle.step(W, P, C, 1)[:3]):
+            assert np.abs(host(got) - want).max() <= 1e-5 * np.abs(want).max()
+
+
 # ------------------------------------ FP32 products on three bf16 planes --
 def prep(oracle, seed, Ne, Na):
     W0, P0, C0 = I.priors(seed, Ne, Na, 0.1, 0.05, 40, 6)
