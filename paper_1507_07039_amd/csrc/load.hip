@@ -159,6 +159,52 @@ __global__ __launch_bounds__(kLT) void k_load(LoadArgs a) {
   if (k < a.nh) a.hpart[k] = 0.0;
 }
 
+// Blocks [0, Mp): a row of X each, padded, with its squared norm; then (chunk
+// of rows, 1024 columns) of Y, padded, with the columns' partial sums of
+// squares.
+__global__ __launch_bounds__(kLT) void k_pack_xy(PackArgs a) {
+  __shared__ double red[4];
+  constexpr int U = 8;
+  const int64_t b = blockIdx.x;
+  if (b < a.Mp) {
+    const bool al = aligned16(a.X, a.K);
+    double q = 0.0;
+    for (int64_t c = 4 * threadIdx.x; c < a.Kp; c += 4 * kLT) {
+      f4 v = {0.f, 0.f, 0.f, 0.f};
+      if (b < a.M && c < a.K) v = row4(a.X + b * a.K, c, a.K, al);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q += (double)v[e] * (double)v[e];
+      *reinterpret_cast<f4*>(a.Xp + b * a.Kp + c) = v;
+    }
+    const double tot = upd::block_sum(q, red);
+    if (threadIdx.x == 0) a.nx[b] = tot;
+    return;
+  }
+  const int64_t strips = c_strips(a.Np), k = (b - a.Mp) / strips;
+  const int64_t c = 4 * kLT * ((b - a.Mp) % strips) + 4 * threadIdx.x;
+  if (c >= a.Np) return;
+  const int64_t i0 = k * a.rows, i1 = i0 + a.rows < a.Kp ? i0 + a.rows : a.Kp;
+  const bool al = aligned16(a.Y, a.N);
+  double q[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t r0 = i0; r0 < i1; r0 += U) {
+    f4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u] = f4{0.f, 0.f, 0.f, 0.f};
+      if (r0 + u < i1 && r0 + u < a.K && c < a.N) v[u] = row4(a.Y + (r0 + u) * a.N, c, a.N, al);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (r0 + u >= i1) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q[e] += (double)v[u][e] * (double)v[u][e];
+      *reinterpret_cast<f4*>(a.Yp + (r0 + u) * a.Np + c) = v[u];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) a.slots[k * a.Np + c + e] = q[e];
+}
+
 __global__ __launch_bounds__(kLT) void k_store(StoreArgs a) {
   int64_t b = blockIdx.x;
   if (a.W) {
@@ -258,6 +304,14 @@ hipError_t launch_load(const LoadArgs& a, hipStream_t s) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !a.C) return e;
   return launch_sum_slots(a.slots, a.Nap, nq, a.nC, s);
+}
+
+hipError_t launch_pack_xy(const PackArgs& a, hipStream_t s) {
+  const int64_t nq = (a.Kp + a.rows - 1) / a.rows, nb = a.Mp + c_strips(a.Np) * nq;
+  k_pack_xy<<<dim3((unsigned)nb), kLT, 0, s>>>(a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_sum_slots(a.slots, a.Np, nq, a.ny, s);
 }
 
 hipError_t launch_store(const StoreArgs& a, hipStream_t s) {

@@ -672,15 +672,8 @@ panda_status panda_normalize_ex(float* M, int64_t rows, int64_t cols, int32_t zs
 }
 
 namespace {
-panda_status copy_in(float* dst, int64_t ldd, const float* src, int64_t rows, int64_t cols,
-                     hipStream_t s) {
-  HIP_TRY(hipMemcpy2DAsync(dst, (size_t)ldd * 4, src, (size_t)cols * 4, (size_t)cols * 4,
-                           (size_t)rows, hipMemcpyDeviceToDevice, s));
-  return PANDA_OK;
-}
-
 struct TaniLayout {
-  float *Xp, *Yp, *Op, *part;
+  float *Xp, *Yp, *part;
   double *nx, *ny, *scr;
 };
 static size_t tanimoto_layout(int64_t M, int64_t K, int64_t N, char* base, TaniLayout* L) {
@@ -688,12 +681,11 @@ static size_t tanimoto_layout(int64_t M, int64_t K, int64_t N, char* base, TaniL
   Carver cv{base};
   float* xp = cv.take<float>((size_t)Mp * Kp);
   float* yp = cv.take<float>((size_t)Kp * Np);
-  float* op = cv.take<float>((size_t)Mp * Np);
   float* pt = cv.take<float>(rect_partial_floats());
   double* nx = cv.take<double>((size_t)Mp);
   double* ny = cv.take<double>((size_t)Np);
   double* sc = cv.take<double>((size_t)kColChunks * (size_t)Np);
-  if (L) *L = TaniLayout{xp, yp, op, pt, nx, ny, sc};
+  if (L) *L = TaniLayout{xp, yp, pt, nx, ny, sc};
   return cv.off;
 }
 }  // namespace
@@ -714,18 +706,11 @@ panda_status panda_tanimoto(const float* X, const float* Y, int64_t M, int64_t K
   const int64_t Mp = round_up(M, kPadE), Kp = round_up(K, kPadK), Np = round_up(N, kPadA);
   TaniLayout L;
   tanimoto_layout(M, K, N, static_cast<char*>(workspace), &L);
-  HIP_TRY(hipMemsetAsync(L.Xp, 0, (size_t)Mp * Kp * 4, s));
-  HIP_TRY(hipMemsetAsync(L.Yp, 0, (size_t)Kp * Np * 4, s));
-  panda_status st = copy_in(L.Xp, Kp, X, M, K, s);
-  if (st != PANDA_OK) return st;
-  st = copy_in(L.Yp, Np, Y, K, N, s);
-  if (st != PANDA_OK) return st;
-  HIP_TRY(launch_row_sqnorms(L.Xp, Mp, Kp, Kp, L.nx, nullptr, s));
-  HIP_TRY(launch_col_sqnorms(L.Yp, Kp, Np, Np, L.ny, L.scr, nullptr, s));
-  HIP_TRY(launch_tanimoto_store(L.Xp, Kp, L.Yp, Np, Mp, Np, Kp, M, N, L.nx, L.ny, L.Op, Np, L.part,
+  PackArgs a{X, Y, M, K, N, Mp, Kp, Np, L.Xp, L.Yp, L.nx, L.ny, L.scr, 0};
+  a.rows = std::max<int64_t>(32, round_up((Kp + kColChunks - 1) / kColChunks, 8));
+  HIP_TRY(launch_pack_xy(a, s));
+  HIP_TRY(launch_tanimoto_store(L.Xp, Kp, L.Yp, Np, Mp, Np, Kp, M, N, L.nx, L.ny, Out, N, L.part,
                                 nullptr, s));
-  HIP_TRY(hipMemcpy2DAsync(Out, (size_t)N * 4, L.Op, (size_t)Np * 4, (size_t)N * 4, (size_t)M,
-                           hipMemcpyDeviceToDevice, s));
   return PANDA_OK;
 }
 

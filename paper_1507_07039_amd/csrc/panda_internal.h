@@ -233,12 +233,6 @@ size_t w_norm_scratch_doubles(int64_t Nep, int64_t Nap);
 hipError_t launch_w_norms(const float* W, int64_t Ne, int64_t Na, int64_t ldw, int64_t Nep,
                           double* nr, double* nc, double* scr, Planes Wr, Planes Wt, int np,
                           const int32_t* gate, hipStream_t s);
-// dimension ld.  The column version needs kColChunks * cols doubles of scratch.
-hipError_t launch_row_sqnorms(const float* M, int64_t rows, int64_t cols, int64_t ld, double* out,
-                              const int32_t* gate, hipStream_t s);
-hipError_t launch_col_sqnorms(const float* M, int64_t rows, int64_t cols, int64_t ld, double* out,
-                              double* scratch, const int32_t* gate, hipStream_t s);
-
 // Z-score (Sec. II-A) on a strided matrix; scratch holds kZsScratch doubles:
 // the moments (mean, std, non-finite flag) at kZsBlocks, the blocks' moments
 // (3 doubles each) from kZsPart on.

@@ -302,40 +302,6 @@ __global__ __launch_bounds__(kRT) void k_w_norms_sum(const double* __restrict__ 
   nc[c] = s;
 }
 
-__global__ __launch_bounds__(kRT) void k_row_sqnorms(const float* __restrict__ M, int64_t cols,
-                                                     int64_t ld, double* __restrict__ out,
-                                                     const int32_t* gate) {
-  __shared__ double red[4];
-  if (gate && *gate == 0) return;
-  const double tot = upd::row_sqnorm(M + (int64_t)blockIdx.x * ld, cols, red);
-  if (threadIdx.x == 0) out[blockIdx.x] = tot;
-}
-
-// Column sums of squares over row chunk blockIdx.y, into scratch[chunk][col].
-__global__ __launch_bounds__(kRT) void k_col_sqnorms_part(const float* __restrict__ M,
-                                                          int64_t rows, int64_t cols, int64_t ld,
-                                                          int64_t chunk, double* __restrict__ scr,
-                                                          const int32_t* gate) {
-  if (gate && *gate == 0) return;
-  const int64_t j = (int64_t)blockIdx.x * kRT + threadIdx.x;
-  if (j >= cols) return;
-  const int64_t r0 = (int64_t)blockIdx.y * chunk;
-  const int64_t r1 = r0 + chunk < rows ? r0 + chunk : rows;
-  scr[(int64_t)blockIdx.y * cols + j] = upd::col_sqnorm_part(M, ld, j, r0, r1);
-}
-
-__global__ __launch_bounds__(kRT) void k_col_sqnorms_sum(const double* __restrict__ scr,
-                                                         int64_t cols, int nchunks,
-                                                         double* __restrict__ out,
-                                                         const int32_t* gate) {
-  if (gate && *gate == 0) return;
-  const int64_t j = (int64_t)blockIdx.x * kRT + threadIdx.x;
-  if (j >= cols) return;
-  double s = 0.0;
-  for (int c = 0; c < nchunks; ++c) s += scr[(int64_t)c * cols + j];
-  out[j] = s;
-}
-
 // ---- z-score --------------------------------------------------------------
 // Moments of a set of entries: count, mean, sum of squared deviations from
 // that mean.  Two sets merge without cancellation (Chan, Golub & LeVeque,
@@ -747,25 +713,6 @@ hipError_t launch_w_norms(const float* W, int64_t Ne, int64_t Na, int64_t ldw, i
   if (e != hipSuccess) return e;
   const int64_t nb = Nep + (Nap + kRT - 1) / kRT;
   k_w_norms_sum<<<dim3((unsigned)nb), kRT, 0, s>>>(rowpart, colpart, Nep, Nap, nr, nc, gate);
-  return hipGetLastError();
-}
-
-hipError_t launch_row_sqnorms(const float* M, int64_t rows, int64_t cols, int64_t ld, double* out,
-                              const int32_t* gate, hipStream_t s) {
-  k_row_sqnorms<<<dim3((unsigned)rows), kRT, 0, s>>>(M, cols, ld, out, gate);
-  return hipGetLastError();
-}
-
-hipError_t launch_col_sqnorms(const float* M, int64_t rows, int64_t cols, int64_t ld, double* out,
-                              double* scratch, const int32_t* gate, hipStream_t s) {
-  const int nch = upd::col_chunks(rows);
-  const int64_t chunk = (rows + nch - 1) / nch;
-  const unsigned gx = (unsigned)((cols + kRT - 1) / kRT);
-  k_col_sqnorms_part<<<dim3(gx, (unsigned)nch), kRT, 0, s>>>(M, rows, cols, ld, chunk, scratch,
-                                                             gate);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_col_sqnorms_sum<<<dim3(gx), kRT, 0, s>>>(scratch, cols, nch, out, gate);
   return hipGetLastError();
 }
 

@@ -142,6 +142,28 @@ def test_tanimoto_row_blocks_and_folds(torch, pd, M, K):
     assert np.all(np.abs(got - want) <= bound)
 
 
+# operands off 16-byte alignment; rows of 1024 columns and either side, chunks
+# of 32 rows of Y
+@pytest.mark.parametrize("M,K,N", [(5, 33, 1023), (5, 32, 1024), (64, 4, 1025), (3, 2100, 8)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_tanimoto_packing(torch, pd, M, K, N, off):
+    """The bound of test_tanimoto_split_k."""
+    def put(a):
+        buf = torch.zeros(a.size + off, device="cuda")
+        t = buf[off:].view(a.shape)
+        t.copy_(torch.from_numpy(a.astype(np.float32)))
+        return t
+
+    X = f32r(I.random_dense(M + K, (M, K)))
+    Y = f32r(I.random_dense(N + K, (K, N), -2.0, 2.0))
+    got = host(pd.tanimoto(put(X), put(Y)))
+    dot = X @ Y
+    den = (X ** 2).sum(1)[:, None] + (Y ** 2).sum(0)[None, :] - np.abs(dot)
+    want = dot / np.sqrt(den)
+    bound = 2 * K * U * (np.abs(X) @ np.abs(Y)) / np.sqrt(den) + 4 * U * np.abs(want) + 1e-30
+    assert np.all(np.abs(got - want) <= bound)
+
+
 # every tiling over networks with one live row block, a ragged last tile, and
 # more TFs than an unfolded sum takes
 @pytest.mark.parametrize("tiles", [0, 1, 2])
