@@ -397,71 +397,127 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Sums over the wave of N values per lane (N = 3 * 2^h), in lanes: each of the
+// first h steps adds one half of the values across lanes and keeps it, so
+// N + 3 (6 - h) exchanges serve all N.  Lane l ends with the sums of values
+// [at, at + 3), at = wave_sums_at<N>(l).
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&v)[N], int lane) {
+  int n = N;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    if (n % 2 == 0 && n > 3) {
+      n /= 2;
+      const bool up = (lane & off) != 0;
+#pragma unroll
+      for (int k = 0; k < N / 2; ++k) {
+        if (k >= n) break;
+        const double keep = up ? v[k + n] : v[k], send = up ? v[k] : v[k + n];
+        v[k] = keep + __shfl_xor(send, off);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[k] += __shfl_xor(v[k], off);
+    }
+  }
+}
+template <int N>
+__device__ __forceinline__ int wave_sums_at(int lane) {
+  int at = 0, n = N;
+  for (int off = 32; off >= 1 && n > 3; off >>= 1) {
+    n /= 2;
+    if (lane & off) at += n;
+  }
+  return at;
+}
+
+// Sums over a block of NW waves of N values per thread; red holds NW x N
+// doubles and ends with the sums in red[0][..], for every thread.
+template <int N, int NW>
+__device__ __forceinline__ void block_sums(double (&v)[N], double (*red)[N]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  wave_sums<N>(v, lane);
+  const int at = wave_sums_at<N>(lane);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) red[wave][at + k] = v[k];  // (equal sums from equal lanes)
+  __syncthreads();
+  if (threadIdx.x < N) {
+    double s = red[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += red[w][threadIdx.x];
+    red[0][threadIdx.x] = s;
+  }
+  __syncthreads();
+}
+
 // Y = M X (rows x 6, FP64) for M rows x cols (FP32, leading dimension ld) and
-// X cols x 6 (FP64).  A block covers 16 rows (4 per wave) and walks the
-// columns in chunks of 256 staged in LDS.
-constexpr int kSkRows = 16;
+// X cols x 6 (FP64).  Bound by reading M where it is large, by latency where
+// it is small: a block takes RB rows and its threads walk the columns side by
+// side, RB entries of M and a row of X (which L2 holds) at a time, two columns
+// in flight.  4000 x 4000 (64 MB): 21 us; 200 rows of 200 or 4000: 5; 57 on
+// average over both as 16 rows a block, a wave to four.
+template <int RB>
 __global__ __launch_bounds__(kT) void k_skinny(const float* __restrict__ M, int64_t rows,
                                                int64_t cols, int64_t ld,
                                                const double* __restrict__ X,
                                                double* __restrict__ Y) {
-  __shared__ double xs[kT][kSk];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t r0 = (int64_t)blockIdx.x * kSkRows + wave * (kSkRows / kWaves);
-  double acc[kSkRows / kWaves][kSk];
+  __shared__ double red[kWaves][RB * kSk];
+  const int64_t r0 = (int64_t)blockIdx.x * RB;
+  double acc[RB * kSk];
 #pragma unroll
-  for (int q = 0; q < kSkRows / kWaves; ++q)
+  for (int k = 0; k < RB * kSk; ++k) acc[k] = 0.0;
+#pragma unroll 2
+  for (int64_t c = threadIdx.x; c < cols; c += kT) {
+    double x[kSk];
 #pragma unroll
-    for (int k = 0; k < kSk; ++k) acc[q][k] = 0.0;
-  for (int64_t c0 = 0; c0 < cols; c0 += kT) {
-    __syncthreads();
-    {
-      const int64_t c = c0 + threadIdx.x;
+    for (int k = 0; k < kSk; ++k) x[k] = X[c * kSk + k];
+    float m[RB];
 #pragma unroll
-      for (int k = 0; k < kSk; ++k) xs[threadIdx.x][k] = c < cols ? X[c * kSk + k] : 0.0;
+    for (int q = 0; q < RB; ++q) {
+      const int64_t r = r0 + q < rows ? r0 + q : rows - 1;
+      m[q] = M[r * ld + c];
     }
-    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < kSkRows / kWaves; ++q) {
-      const int64_t r = r0 + q;
-      if (r >= rows) continue;
-      for (int j = lane; j < kT; j += 64) {
-        const int64_t c = c0 + j;
-        if (c >= cols) break;
-        const double v = (double)M[r * ld + c];
+    for (int q = 0; q < RB; ++q)
 #pragma unroll
-        for (int k = 0; k < kSk; ++k) acc[q][k] += v * xs[j][k];
-      }
-    }
+      for (int k = 0; k < kSk; ++k) acc[q * kSk + k] += (double)m[q] * x[k];
   }
-#pragma unroll
-  for (int q = 0; q < kSkRows / kWaves; ++q) {
-    const int64_t r = r0 + q;
-#pragma unroll
-    for (int k = 0; k < kSk; ++k) {
-      const double s = wave_sum(acc[q][k]);
-      if (lane == 0 && r < rows) Y[r * kSk + k] = s;
-    }
-  }
+  block_sums<RB * kSk, kWaves>(acc, red);
+  if (threadIdx.x < RB * kSk && r0 + threadIdx.x / kSk < rows)
+    Y[r0 * kSk + threadIdx.x] = red[0][threadIdx.x];
 }
 
-// out[j][k] = sum_i M[i][j] z[i][k] (M rows x cols), one thread per column.
+// out[j][k] = sum_i M[i][j] z[i][k] (M rows x cols).  A block takes 32 columns,
+// eight threads sharing one: a thread per column was one serial chain of
+// `rows` loads.  200 x 4000: 50 -> 6 us.
+constexpr int kColG = 8, kColC = kT / kColG;
 __global__ __launch_bounds__(kT) void k_colskinny(const float* __restrict__ M, int64_t rows,
                                                   int64_t cols, int64_t ld,
                                                   const double* __restrict__ z,
                                                   double* __restrict__ out) {
-  const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (j >= cols) return;
+  __shared__ double red[kColG][kColC][kSk];
+  const int cl = threadIdx.x % kColC, g = threadIdx.x / kColC;
+  const int64_t j = (int64_t)blockIdx.x * kColC + cl, jj = j < cols ? j : cols - 1;
   double acc[kSk];
 #pragma unroll
   for (int k = 0; k < kSk; ++k) acc[k] = 0.0;
-  for (int64_t i = 0; i < rows; ++i) {
-    const double v = (double)M[i * ld + j];
+#pragma unroll 4
+  for (int64_t i = g; i < rows; i += kColG) {
+    const double v = (double)M[i * ld + jj];
 #pragma unroll
     for (int k = 0; k < kSk; ++k) acc[k] += v * z[i * kSk + k];
   }
 #pragma unroll
-  for (int k = 0; k < kSk; ++k) out[j * kSk + k] = acc[k];
+  for (int k = 0; k < kSk; ++k) red[g][cl][k] = acc[k];
+  __syncthreads();
+  if (threadIdx.x < kColC * kSk) {
+    const int c = threadIdx.x / kSk, k = threadIdx.x % kSk;
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < kColG; ++q) s += red[q][c][k];
+    const int64_t jo = (int64_t)blockIdx.x * kColC + c;
+    if (jo < cols) out[jo * kSk + k] = s;
+  }
 }
 
 __device__ __forceinline__ double bsum(double v, double* red) {
@@ -475,19 +531,31 @@ __device__ __forceinline__ double bsum(double v, double* red) {
 // Cholesky QR of Y (n x 6): G = Y^T Y (one block), L L^T = G with the pivot
 // rule (stop at L_kk^2 <= rel * max diag G), Q = Y L^-T on the first k
 // columns, zero after.
-__global__ __launch_bounds__(kT) void k_cholqr_factor(const double* __restrict__ Y, int64_t n,
-                                                      double rel, double* __restrict__ Linv) {
-  __shared__ double red[4];
-  __shared__ double G[kSk][kSk];
-  for (int a = 0; a < kSk; ++a)
-    for (int b = 0; b <= a; ++b) {
-      double s = 0.0;
-      for (int64_t i = threadIdx.x; i < n; i += kT) s += Y[i * kSk + a] * Y[i * kSk + b];
-      const double t = bsum(s, red);
-      if (threadIdx.x == 0) G[a][b] = G[b][a] = t;
-    }
-  __syncthreads();
+constexpr int kChT = 1024;
+__global__ __launch_bounds__(kChT) void k_cholqr_factor(const double* __restrict__ Y, int64_t n,
+                                                        double rel, double* __restrict__ Linv) {
+  // the 21 products of the lower triangle in one pass (a pass each took 45 us
+  // at n = 4000, this one 20); the last three are the filler block_sums wants
+  constexpr int N = 24;
+  __shared__ double red[kChT / 64][N];
+  double v[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) v[k] = 0.0;
+  for (int64_t i = threadIdx.x; i < n; i += kChT) {
+    double y[kSk];
+#pragma unroll
+    for (int k = 0; k < kSk; ++k) y[k] = Y[i * kSk + k];
+    int q = 0;
+#pragma unroll
+    for (int a = 0; a < kSk; ++a)
+#pragma unroll
+      for (int b = 0; b <= a; ++b) v[q++] += y[a] * y[b];
+  }
+  block_sums<N, kChT / 64>(v, red);
   if (threadIdx.x != 0) return;
+  double G[kSk][kSk];
+  for (int a = 0, q = 0; a < kSk; ++a)
+    for (int b = 0; b <= a; ++b) G[a][b] = G[b][a] = red[0][q++];
   double L[kSk][kSk] = {};
   double mx = 0.0;
   for (int a = 0; a < kSk; ++a) mx = G[a][a] > mx ? G[a][a] : mx;
@@ -543,8 +611,8 @@ __global__ __launch_bounds__(kT) void k_widen6(const float* __restrict__ in, int
   if (i < rows * kSk) out[i] = (double)in[i];
 }
 
-// Row sums (blocks [0, rows)) and column sums (threads of the remaining
-// blocks) of M (FP64 results).
+// Row sums (blocks [0, rows)) and column sums (the remaining blocks, as
+// k_colskinny's) of M (FP64 results).  200 x 4000: 47 -> 6 us.
 __global__ __launch_bounds__(kT) void k_degrees(const float* __restrict__ M, int64_t rows,
                                                 int64_t cols, int64_t ld, double* __restrict__ dr,
                                                 double* __restrict__ dc) {
@@ -557,11 +625,19 @@ __global__ __launch_bounds__(kT) void k_degrees(const float* __restrict__ M, int
     if (threadIdx.x == 0) dr[i] = t;
     return;
   }
-  const int64_t j = ((int64_t)blockIdx.x - rows) * kT + threadIdx.x;
-  if (j >= cols) return;
+  __shared__ double part[kColG][kColC];
+  const int cl = threadIdx.x % kColC, g = threadIdx.x / kColC;
+  const int64_t j = ((int64_t)blockIdx.x - rows) * kColC + cl, jj = j < cols ? j : cols - 1;
   double s = 0.0;
-  for (int64_t i = 0; i < rows; ++i) s += (double)M[i * ld + j];
-  dc[j] = s;
+#pragma unroll 4
+  for (int64_t i = g; i < rows; i += kColG) s += (double)M[i * ld + jj];
+  part[g][cl] = s;
+  __syncthreads();
+  if (g == 0 && j < cols) {
+#pragma unroll
+    for (int q = 1; q < kColG; ++q) s += part[q][cl];
+    dc[j] = s;
+  }
 }
 
 // Population mean and variance (two passes, FP64) of column `col` of an
@@ -716,31 +792,31 @@ hipError_t launch_ws_affine(const float* A, int64_t lda, const float* B, int64_t
 
 hipError_t launch_ws_sketch(const float* M, int64_t n, int64_t ld, const double* X, double* tmp,
                             double* Y, hipStream_t s) {
-  const unsigned nb = (unsigned)((n + kSkRows - 1) / kSkRows);
-  k_skinny<<<dim3(nb), dim3(kT), 0, s>>>(M, n, n, ld, X, tmp);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_skinny<<<dim3(nb), dim3(kT), 0, s>>>(M, n, n, ld, tmp, Y);
-  return hipGetLastError();
+  const hipError_t e = launch_skinny(M, n, n, ld, X, tmp, s);
+  return e != hipSuccess ? e : launch_skinny(M, n, n, ld, tmp, Y, s);
 }
 
+// Eight rows per block once that fills the CUs; X is read once per block, so
+// fewer cost more of L2 (4000 rows two at a time: 30 us; 200 by eights: 8).
 hipError_t launch_skinny(const float* M, int64_t rows, int64_t cols, int64_t ld, const double* X,
                          double* Y, hipStream_t s) {
-  k_skinny<<<dim3((unsigned)((rows + kSkRows - 1) / kSkRows)), dim3(kT), 0, s>>>(M, rows, cols,
-                                                                                 ld, X, Y);
+  if (rows >= 2048)
+    k_skinny<8><<<dim3((unsigned)((rows + 7) / 8)), dim3(kT), 0, s>>>(M, rows, cols, ld, X, Y);
+  else
+    k_skinny<2><<<dim3((unsigned)((rows + 1) / 2)), dim3(kT), 0, s>>>(M, rows, cols, ld, X, Y);
   return hipGetLastError();
 }
 
 hipError_t launch_colskinny(const float* M, int64_t rows, int64_t cols, int64_t ld,
                             const double* z, double* out, hipStream_t s) {
-  k_colskinny<<<dim3((unsigned)((cols + kT - 1) / kT)), dim3(kT), 0, s>>>(M, rows, cols, ld, z,
-                                                                          out);
+  k_colskinny<<<dim3((unsigned)((cols + kColC - 1) / kColC)), dim3(kT), 0, s>>>(M, rows, cols, ld,
+                                                                               z, out);
   return hipGetLastError();
 }
 
 hipError_t launch_cholqr(const double* Y, int64_t n, double rel, double* Linv, double* Q,
                          hipStream_t s) {
-  k_cholqr_factor<<<1, kT, 0, s>>>(Y, n, rel, Linv);
+  k_cholqr_factor<<<1, kChT, 0, s>>>(Y, n, rel, Linv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_cholqr_apply<<<dim3((unsigned)((n + kT - 1) / kT)), dim3(kT), 0, s>>>(Y, n, Linv, Q);
@@ -754,7 +830,7 @@ hipError_t launch_widen6(const float* in, int64_t rows, double* out, hipStream_t
 
 hipError_t launch_degrees(const float* M, int64_t rows, int64_t cols, int64_t ld, double* dr,
                           double* dc, hipStream_t s) {
-  const unsigned nb = (unsigned)(rows + (cols + kT - 1) / kT);
+  const unsigned nb = (unsigned)(rows + (cols + kColC - 1) / kColC);
   k_degrees<<<dim3(nb), dim3(kT), 0, s>>>(M, rows, cols, ld, dr, dc);
   return hipGetLastError();
 }
