@@ -16,7 +16,11 @@ constexpr int kOffB2 = kOffW2 + kMlpHidden * kMlpHidden;
 constexpr int kOffW3 = kOffB2 + kMlpHidden;
 constexpr int kOffB3 = kOffW3 + kMlpHidden;
 constexpr int kMlpParams = kOffB3 + 1;  // 5313
-constexpr int64_t kMlpGradBlocks = 512;  // blocks of the gradient kernel (4 slots each)
+// Blocks of the gradient kernel (4 slots each): one per CU, as many as run at
+// once (registers and LDS).  With 512 the second half of 65536 edges waited to
+// set up its weights again, and wrote as many partial gradients again: 44 +
+// 13 us (gradient and reduction) against 31 + 7.
+constexpr int64_t kMlpGradBlocks = 256;
 constexpr double kSketchPivotRel = 1e-10;
 
 // Per-wave partial gradients of a batch of n edges.

@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kT) void k_mlp_grad(const float* __restrict__ p,
 // slots is one serial chain of up to 2048 of them.  Here 32 threads share a
 // parameter (slots g, g + 32, ... each, eight loads in flight) and their sums
 // are added in order from LDS; the block after the last takes the loss.
-// 65536 edges (2048 slots, 43 MB): 590 -> 13 us.
+// 65536 edges: 590 -> 13 us with 2048 slots (43 MB), 7 with 1024.
 constexpr int kRedT = 1024, kRedC = 32, kRedG = kRedT / kRedC;
 __global__ __launch_bounds__(kRedT) void k_mlp_reduce(const float* __restrict__ part, int64_t slots,
                                                       const double* __restrict__ lpart, int64_t n,
@@ -756,7 +756,10 @@ int64_t mlp_grad_slots(int64_t n) {
 hipError_t launch_mlp_forward(const float* p, const float* F, int64_t n, float* y, hipStream_t s) {
   const int64_t chunks = (n + 31) / 32;
   int64_t blocks = (chunks + kWaves - 1) / kWaves;
-  if (blocks > 4096) blocks = 4096;
+  // as many as run at once: a block's weights cost more to set up than its
+  // chunks to compute (402804 edges: 51 us as 3147 blocks of a chunk per wave,
+  // 16 as these)
+  if (blocks > 512) blocks = 512;
   if (blocks < 1) blocks = 1;
   k_mlp_forward<<<dim3((unsigned)blocks), dim3(kT), 0, s>>>(p, F, n, y);
   return hipGetLastError();
