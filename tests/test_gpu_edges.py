@@ -360,3 +360,22 @@ def test_load_store_roundtrip(torch, pd, Ne, Na, kw, off):
     assert torch.equal(out[0], W)
     for a, n in zip(out[1:], (Ne, Na)):
         assert np.abs(host(a) - identity(n)).max() <= 2 * U * np.abs(identity(n)).max()
+
+
+# ----------------------------------------------------------------- correlations --
+# one tile and its edges, two tiles; rows of C on 16 bytes, off them by the
+# leading dimension, and by the base
+@pytest.mark.parametrize("G", [1, 3, 127, 128, 130, 259])
+@pytest.mark.parametrize("pad,off", [(0, 0), (1, 0), (4, 0), (4, 1)])
+def test_pearson_stores(torch, pd, G, pad, off):
+    """Against numpy's corrcoef within the bound of the other sizes (1e-5);
+    exactly symmetric; nothing outside the G x G result is written."""
+    E = np.random.default_rng(G).normal(size=(G, 33)).astype(np.float32)
+    ldc = -(-G // 4) * 4 + pad
+    buf = torch.full((G * ldc + off,), 7.0, device="cuda")
+    C = buf[off:].view(G, ldc)
+    pd.pearson_noalloc(cuda(torch, E), C, ldc)
+    got = host(C)
+    assert np.abs(got[:, :G] - np.atleast_2d(np.corrcoef(E.astype(np.float64)))).max() <= 1e-5
+    assert np.array_equal(got[:, :G], got[:, :G].T) and np.all(np.diag(got) == 1.0)
+    assert np.all(got[:, G:] == 7.0) and np.all(host(buf[:off]) == 7.0)
