@@ -186,13 +186,15 @@ panda_status ctx_fill_order(panda_ctx* c) {
 }
 
 void ctx_free(panda_ctx* c) {
-  if (c->host) (void)hipHostFree(c->host);
-  c->host = nullptr;
   if (c->snap) {
+    // an iteration queued behind the converged one may still write it
+    (void)hipStreamSynchronize(c->stream);
     (void)hipHostFree(c->snap);
     for (hipEvent_t& e : c->snap_ev) (void)hipEventDestroy(e);
   }
   c->snap = nullptr;
+  if (c->host) (void)hipHostFree(c->host);
+  c->host = nullptr;
   if (c->ev[0][0])
     for (int i = 0; i < kMaxPending; ++i)
       for (int p = 0; p <= PANDA_NPHASE; ++p) (void)hipEventDestroy(c->ev[i][p]);
