@@ -335,7 +335,12 @@ def main():
         per, total, phases = time_iterations(torch, panda, W, P, C, args.steps, args.warmup,
                                              precision)
         ms = {k: (v[0] / v[1] if v[1] else None) for k, v in phases.items()}
-        rates = {k: flops[k] / (ms[k] * 1e-3) / 1e12 for k in flops if ms.get(k)}
+        # the next iteration's R is computed inside the C update's launch
+        # (after warm-up the R phase holds only its timing events)
+        if ms.get("C") is not None:
+            ms["C+R"] = ms.pop("C") + (ms.pop("R", None) or 0.0)
+        work = dict(flops, **{"C+R": flops["C"] + flops["R"]})
+        rates = {k: work[k] / (ms[k] * 1e-3) / 1e12 for k in work if ms.get(k)}
         return per, ms, rates
 
     traffic = recorded_traffic()
@@ -375,13 +380,6 @@ def main():
     if not args.plain_only:
         log("timing iterations (split-BF16 form)")
         per3, ms3, rates3 = measure(1)
-        # this form computes the next iteration's R inside the C update's
-        # launch (after warm-up the R phase holds only its timing events)
-        if ms3.get("C") is not None:
-            ms3["C+R"] = ms3.pop("C") + (ms3.pop("R", None) or 0.0)
-            rates3.pop("R", None)
-            rates3.pop("C", None)
-            rates3["C+R"] = (flops["C"] + flops["R"]) / (ms3["C+R"] * 1e-3) / 1e12
         # executed bf16 flops: three products per FP32-equivalent product
         bf_rate = 3.0 * rates3["A+W"]
         result["chosen_form"] = {
