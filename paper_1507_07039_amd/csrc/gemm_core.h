@@ -683,6 +683,14 @@ struct BlockGemmB3P {
   // G=18000: 1.1e-7) is below that of v_mfma_f32_32x32x2f32 (5.8e-7).
   static constexpr bool kFolds = NP == 3;
   static constexpr int kFoldTiles = (int)(kFoldK / BK_) / 3 * 3;
+  // k of the first run of a range of `k`: what is summed before the first fold
+  // (all of it where no fold follows).  The pipelined loop stops five K-tiles
+  // before the end of its range and folds only inside it, so a shorter rest
+  // stays in the accumulator; every layout of Y cuts a range in the same places.
+  static __host__ __device__ constexpr int64_t fold_run(int64_t k) {
+    return k < (int64_t)(kFoldTiles + 5) * BK_ ? k : (int64_t)kFoldTiles * BK_;
+  }
+  static_assert(!kFolds || (kFoldTiles + 5) * BK_ > kFoldK, "no fold where there is no scratch");
   static_assert(!YP || (YF32 && BN_ == (int)kPT && kPT % BK_ == 0 && (BK_ == 32 || BK_ == 16)),
                 "packed Y: FP32 rows of one packed column block, K-tiles inside a block");
   // one block per CU (its stages fill most of the LDS): the epilogue has
@@ -1087,15 +1095,15 @@ struct BlockGemmB3P {
     if constexpr (!YP) {
       run<LQ>(o, m0, n0, kbeg, kend, smem, slot);
     } else {
-      constexpr int64_t kSeg = (int64_t)kFoldTiles * BK;
-      for (int64_t k = kbeg;; k += kSeg) {
-        const bool last = k + kSeg >= kend;
-        run(o, m0, n0, k, last ? kend : k + kSeg, smem);
-        if (last) {
+      for (int64_t k = kbeg;;) {
+        const int64_t n = fold_run(kend - k);
+        run(o, m0, n0, k, k + n, smem);
+        if (k + n >= kend) {
           if (k != kbeg) unfold<LQ>(smem, slot);
           return;
         }
         fold<LQ>(smem, slot, k == kbeg);
+        k += n;
       }
     }
   }
@@ -1531,6 +1539,7 @@ hipError_t launch_rect(const typename G::Ops& ops, int64_t Mp, int64_t Np, int64
   static const int64_t cus = device_cus();
   // blocks with a folding slot of their own
   if (folds_k<G>::value && resident > kFoldBlocks) resident = kFoldBlocks;
+  if (folds_k<G>::value && Kp > kFoldK && !fold) return hipErrorInvalidValue;
   const int64_t nMT = Mp / G::BM, nNT = Np / G::BN;
   const int64_t nTiles = nMT * nNT, U = Kp / G::BK;
   // K-chunks per tail tile: the smallest S with the least cost, counted in
