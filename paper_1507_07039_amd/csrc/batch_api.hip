@@ -11,19 +11,21 @@
 
 using namespace panda;
 
-namespace {
+namespace panda {
 
-constexpr int kNumLists = kBTNum;  // one work list per grouped product
-constexpr int64_t kCtrCount = (int64_t)kNumLists * kNumXcd * kCtrStride;
-constexpr int kMaxBatch = 1 << 16;
-
-// Buffers of network i sized for every tile candidate: the smallest A + W
-// tile (64 x 64) and the smallest W W^T chunk.
 LayoutSpec batch_spec(int64_t Ne, int64_t Na) {
   const int64_t Nep = round_up(Ne, kPadE), Nap = round_up(Na, kPadA);
   const int64_t c0 = coop_chunk_of(0);
   return LayoutSpec{true, (Nep / 64) * (Nap / 64), (Nap + c0 - 1) / c0};
 }
+
+}  // namespace panda
+
+namespace {
+
+constexpr int kNumLists = kBTNum;  // one work list per grouped product
+constexpr int64_t kCtrCount = (int64_t)kNumLists * kNumXcd * kCtrStride;
+constexpr int kMaxBatch = 1 << 16;
 
 }  // namespace
 

@@ -72,6 +72,9 @@ struct LayoutSpec {
   bool packed_c = false; // C as its upper tiles (packed_tile)
 };
 LayoutSpec single_spec(int64_t Ne, int64_t Na, bool packed_c, int32_t precision);
+// A network of a batch, sized for every tile candidate: the smallest A + W tile
+// (64 x 64) and the smallest W W^T chunk.
+LayoutSpec batch_spec(int64_t Ne, int64_t Na);
 
 }  // namespace panda
 

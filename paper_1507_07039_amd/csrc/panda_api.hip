@@ -148,7 +148,7 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
     c->colscr = scr;
     c->splits = splits;
     c->hpart = hp;
-    c->nh = avail_hpart_slots(c->Nep, c->Nap);  // h partials of the A + W product
+    c->nh = spec.hpart_tiles;  // h partials that the tiled A + W products may add up
     c->cstat = cs;
     c->csq = cq;
     c->corder = co;

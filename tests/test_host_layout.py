@@ -38,3 +38,14 @@ def test_folding_scratch_wherever_the_product_folds(layout):
     for k, run, scratch in layout("fold"):
         assert 0 < run <= k
         assert run == k or scratch > 0, (k, run, scratch)
+
+
+def test_loads_clear_only_the_h_partials(layout):
+    """A load clears every h partial of its network, and no more than the room
+    carved for them (in a batch that is the grouped kernels' count, not the
+    single network's)."""
+    lines = layout("hpart")
+    assert {(prec, batched) for _, _, prec, batched, _, _ in lines} == {(0, 0), (0, 1), (1, 0), (1, 1)}
+    for line in lines:
+        cleared, room = line[4:]
+        assert 0 < cleared <= room, line
