@@ -69,3 +69,207 @@ def test_packed_equals_full_whole_k(torch, pd, Na):
     W, P, C = W.double(), P.double(), C.double()
     want = 0.9 * W + 0.05 * (t64(torch, P, W) + t64(torch, W, C))
     assert (out[1][0].double() - want).abs().max() <= 1e-5 * want.abs().max()
+
+
+# ------------------------------------------------ iterations past the small rule --
+ALPHA = 0.1
+
+
+def tiled(pd, Ne, Na):
+    """Whether a network of this size iterates in the tiled kernels: asked of
+    the library, so that a change of its rule cannot empty these tests."""
+    import ctypes as ct
+    f = pd.load_library()._ZN5panda9small_netEll
+    f.restype, f.argtypes = ct.c_bool, [ct.c_int64, ct.c_int64]
+    return not f(Ne, Na)
+
+
+def damp64(torch, M, T, n, t, kw):
+    """Eq. 5 off the diagonal, Eq. 6 on it, with the readings kw."""
+    d, k = M.diagonal().clone(), M.shape[0]
+    M = (1 - ALPHA) * M + ALPHA * T
+    S = (T if kw.get("sigma_from_T") else M).clone()
+    S.fill_diagonal_(0.0)
+    m = max(k - 1, 1)
+    q = (S - (S.sum(1) / m)[:, None]).square()
+    q.fill_diagonal_(0.0)
+    dof = k - 1 - kw.get("sigma_ddof", 0)
+    sd = (q.sum(1) / dof).sqrt() if dof >= 1 else torch.zeros_like(d)
+    mult = k if kw.get("n_own") else n
+    f = ALPHA if kw.get("diag_alpha", 1) else 1.0
+    M.diagonal().copy_((1 - ALPHA) * d + f * mult * sd * np.exp(2 * ALPHA * t))
+    return M
+
+
+def step64(torch, W, P, C, t, kw):
+    """One iteration in 64 bits: (W, P, C, h)."""
+    Ne, Na = W.shape
+    pred = 0.5 * (t64(torch, P, W) + t64(torch, W, C))
+    new = (1 - ALPHA) * W + ALPHA * pred
+    h = ((pred if kw.get("h_undamped") else new) - W).abs().mean().item()
+    return (new, damp64(torch, P, t64(torch, new, new.T.contiguous()), Na, t, kw),
+            damp64(torch, C, t64(torch, new.T.contiguous(), new), Ne, t, kw), h)
+
+
+def close(got, want, tol):
+    """Off the diagonal to tol of the largest entry there (or of 1), the
+    diagonal of a square matrix to 0.1 tol of each entry's size."""
+    got = got.double()
+    if got.shape[0] == got.shape[1]:
+        g, w = got.diagonal(), want.diagonal()
+        assert ((g - w).abs() <= 0.1 * tol * w.abs().clamp_min(1.0)).all()
+        got, want = got.clone(), want.clone()
+        got.fill_diagonal_(0.0)
+        want.fill_diagonal_(0.0)
+        assert (got == got.T).all()
+    assert (got - want).abs().max() <= tol * max(1.0, want.abs().max().item())
+
+
+# one tile row and one past it; either side of a padded row tile; more TFs than
+# an unfolded sum takes (the C update and R fold in LDS); so many that the
+# partials of W W^T fold as well
+SIZES = [(3, 2100), (64, 2176), (65, 2060), (129, 2100), (257, 2200), (1100, 2100), (2900, 2300)]
+
+
+@pytest.mark.parametrize("Ne,Na", SIZES)
+@pytest.mark.parametrize("packed", [0, 1])
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("kw", [{}, {"sigma_from_T": 1, "sigma_ddof": 1, "n_own": 1},
+                                {"h_undamped": 1, "diag_alpha": 0, "update_last": 1}])
+def test_tiled_steps(torch, pd, Ne, Na, packed, precision, kw):
+    """Three iterations one at a time against 64 bits, each from the library's
+    own state before it, then a resume of the stored state bit for bit.
+
+    FP32 form: |dT| <= 2 K u sum |x y| / sqrt(den), which for these normal
+    entries is below 1e-4 of T's largest; it enters W, P and C damped by 0.1 (or
+    0.05).  Split form: 2^-16 sum |x y| / sqrt(den) is below 1e-3 on W, damped
+    like it on P and C (the targets of both forms elsewhere)."""
+    assert tiled(pd, Ne, Na)
+    tol = 1e-3 if precision else 1e-4
+    o = pd.default_options(tol=0.0, packed_c=packed, precision=precision, **kw)
+    c = pd.Context(Ne, Na, o)
+    c.load(*gpu_net(torch, Ne + Na, Ne, Na))
+    mid = None
+    for t in range(1, 4):
+        before = c.state()[:3]
+        h, tt = c.iterate()
+        want = step64(torch, *(M.double() for M in before), t, kw)
+        after = c.state()[:3]
+        assert tt == t and abs(h - want[3]) <= 0.1 * tol * want[3]
+        for g, w in zip(after, want):
+            close(g, w, tol)
+        if t == 2:
+            mid = after
+    r = pd.Context(Ne, Na, o)
+    r.load(*mid, t=2)
+    r.iterate()
+    assert all(torch.equal(a, b) for a, b in zip(r.state()[:3], after))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_grouped_batch_steps(torch, pd, precision):
+    """The grouped kernels over ragged networks past the small rule, the bounds
+    of test_tiled_steps."""
+    shapes = [(3, 2100), (64, 2176), (130, 2300), (1100, 2100)]
+    assert all(tiled(pd, *s) for s in shapes)
+    tol = 1e-3 if precision else 1e-4
+    b = pd.Batch(shapes, pd.default_options(tol=0.0, precision=precision))
+    for i, s in enumerate(shapes):
+        b.load(i, *gpu_net(torch, 7 + i, *s))
+    for t in range(1, 4):
+        before = [b.state(i)[:3] for i in range(len(shapes))]
+        b.iterate(1, graph=t > 1)
+        for i, net in enumerate(before):
+            for g, w in zip(b.state(i)[:3], step64(torch, *(M.double() for M in net), t, {})):
+                close(g, w, tol)
+
+
+@pytest.mark.parametrize("where", ["W", "C", "P"])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan"), 3.4e38])
+@pytest.mark.parametrize("packed", [0, 1])
+def test_tiled_extreme_entry(torch, pd, where, bad, packed):
+    """One extreme entry of a prior: W keeps its infinity (or NaN), T is 0
+    where its denominator is not positive, and no entry whose sums do not
+    hold the extreme one is lost."""
+    Ne, Na = 40, 2100
+    assert tiled(pd, Ne, Na)
+    net = dict(zip("WPC", gpu_net(torch, 3, Ne, Na)))
+    i, j = (4, 7)
+    net[where][i, j] = bad
+    if where != "W":
+        net[where][j, i] = bad
+    c = pd.Context(Ne, Na, pd.default_options(tol=0.0, packed_c=packed))
+    c.load(*(net[k] for k in "WPC"))
+    c.iterate()
+    got = c.state()[0].double()
+    d = {k: M.double() for k, M in net.items()}
+    rest = torch.ones(Ne, Na, dtype=torch.bool, device="cuda")
+    if where == "W":
+        rest[i, :] = rest[:, j] = False
+    elif where == "P":
+        rest[i, :] = rest[j, :] = False
+    else:
+        rest[:, i] = rest[:, j] = False
+    want = 0.9 * d["W"] + 0.05 * (t64(torch, d["P"], d["W"]) + t64(torch, d["W"], d["C"]))
+    assert torch.isfinite(got[rest]).all()
+    assert (got[rest] - want[rest]).abs().max() <= 1e-4
+    if where == "W":
+        g = got[i, j].item()
+        assert g == bad or (g != g and bad != bad) or abs(g - 0.9 * bad) <= 0.06 * abs(bad)
+    else:  # W itself is finite: so is every T of it (or 0)
+        assert torch.isfinite(got).all()
+
+
+# ------------------------------------------------------- warm start, tiled context --
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("steps", [0, 2])
+def test_tiled_features(torch, pd, precision, steps):
+    """Features of a tiled context just loaded and after iterations (where the
+    FP32 form holds R in W's buffer) equal the oracle's on its stored state
+    within 1e-4 (z-scored O(1) values; the one-step similarity in FP32), and
+    the run goes on bit for bit as one left alone."""
+    from oracle import warmstart as WS
+    Ne, Na = 70, 2100
+    assert tiled(pd, Ne, Na)
+    o = pd.default_options(tol=0.0, precision=precision)
+    a, b = pd.Context(Ne, Na, o), pd.Context(Ne, Na, o)
+    for c in (a, b):
+        c.load(*gpu_net(torch, 11, Ne, Na))
+        for _ in range(steps):
+            c.iterate()
+    Op, Oc = I.sketch_matrices(5, Ne, Na)
+    F, tau = a.features(*(torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda()
+                          for x in (Op, Oc)))
+    W, P, C = (host(M) for M in b.state()[:3])
+    want = WS.features(W, P, C, Op.astype(np.float32).astype(np.float64),
+                       Oc.astype(np.float32).astype(np.float64))
+    assert np.abs(host(F) - want).max() <= 1e-4
+    S = WS.one_step(W, P, C)
+    assert abs(tau - WS.target_scale(W, S)) <= 1e-5 * WS.target_scale(W, S)
+    assert all(torch.equal(x, y) for x, y in zip(a.state()[:3], b.state()[:3]))
+    for _ in range(2):
+        assert a.iterate() == b.iterate()
+    assert all(torch.equal(x, y) for x, y in zip(a.state()[:3], b.state()[:3]))
+
+
+@pytest.mark.parametrize("precision,packed", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_tiled_warm_state(torch, pd, precision, packed):
+    """The warm state of a tiled context against the oracle's, and two
+    iterations from it against 64 bits (the bounds of test_tiled_steps)."""
+    from oracle import warmstart as WS
+    Ne, Na, t0 = 70, 2100, 6
+    assert tiled(pd, Ne, Na)
+    tol = 1e-3 if precision else 1e-4
+    W, P, C = gpu_net(torch, 12, Ne, Na)
+    Wp = W + 0.05 * torch.randn(W.shape, generator=torch.Generator(device="cuda").manual_seed(1),
+                                device="cuda")
+    c = pd.Context(Ne, Na, pd.default_options(tol=0.0, precision=precision, packed_c=packed))
+    c.load(W, P, C)
+    c.ws_init(Wp, t0)
+    for g, w in zip(c.state()[:3], WS.warm_state(*(host(M) for M in (Wp, P, C)), t0)):
+        close(g, torch.from_numpy(w).cuda(), tol)
+    for t in (t0 + 1, t0 + 2):
+        before = c.state()[:3]
+        assert c.iterate()[1] == t
+        for g, w in zip(c.state()[:3], step64(torch, *(M.double() for M in before), t, {})):
+            close(g, w, tol)
