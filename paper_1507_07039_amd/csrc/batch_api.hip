@@ -19,6 +19,41 @@ LayoutSpec batch_spec(int64_t Ne, int64_t Na) {
   return LayoutSpec{true, (Nep / 64) * (Nap / 64), (Nap + c0 - 1) / c0};
 }
 
+// Estimates of an iteration's time in both sets of kernels, fitted to 74
+// batches of equal networks (20 x 100 to 100 x 2000 and 2000 x 100, 2 to 1000
+// of them, both forms; the small kernels' within 8 %, the grouped ones' within
+// 20 %).  One network leaves the chip idle, and there the small kernels win at
+// every size that small_net takes; many fill it, and then their 32 x 32 tiles run
+// at a third of the grouped kernels' rate.  us an iteration, small / grouped
+// FP32 / grouped split-BF16:
+//   20 of 125 x 125   37 /  150 / 139     2 of 100 x 2000   133 / 285 / 184
+//   16 of 40 x 400    57 /  172 / 128     8 of 100 x 2000   469 / 377 / 239
+//   400 of 40 x 400  974 /  628 / 656    32 of 100 x 2000  1890 / 616 / 629
+//   8 of 500 x 500   171 /  291 / 200   100 of 500 x 500   1953 / 1153 / 1293
+// At the line the two differ by 8 % at most over those batches; the margin
+// leaves doubtful ones to the grouped kernels.
+bool small_batch(int32_t n, const int64_t* Ne, const int64_t* Na, int32_t precision) {
+  const bool b3 = precision == PANDA_PREC_BF16X3;
+  auto tri = [](double t) { return t * (t + 1) / 2; };
+  double small = 22, grouped = b3 ? 105 : 120, mxE = 0, mxA = 0;
+  for (int32_t i = 0; i < n; ++i) {
+    // blocks of one tile each: a fixed part and one for its K
+    const double e = (double)Ne[i], a = (double)Na[i];
+    const double te = (double)small_tiles(Ne[i]), ta = (double)small_tiles(Na[i]);
+    small += te * ta * (0.019 + 3.6e-5 * (e + a)) + tri(ta) * (0.014 + 1.3e-5 * e) +
+             tri(te) * (0.0114 + 0.9e-5 * a);
+    // (us per 1e9) products of K = N_a and N_e, then (per 1e6) C, P, W
+    const double E = (double)round_up(Ne[i], kPadE), A = (double)round_up(Na[i], kPadA);
+    grouped += (b3 ? 1.8e-9 : 4.5e-9) * E * A * A + (b3 ? 1.8e-9 : 0.0) * E * E * A +
+               (b3 ? 1.7e-6 : 1e-6) * A * A + (b3 ? 12e-6 : 8e-6) * E * E +
+               (b3 ? 21e-6 : 19e-6) * E * A;
+    mxE = std::max(mxE, e);
+    mxA = std::max(mxA, a);
+  }
+  grouped += b3 ? 0.04 * mxE + 0.02 * mxA : 0.12 * mxE + 0.07 * mxA;  // their longest K
+  return small < 0.96 * grouped;
+}
+
 }  // namespace panda
 
 namespace {
@@ -302,8 +337,9 @@ panda_status gather_states(panda_batch* b) {
   return PANDA_OK;
 }
 
-// Small networks leave the grouped kernels for the small ones unless the
-// caller chose (or tuned) tiles of the grouped ones.
+// Small networks leave the grouped kernels for the small ones where those are
+// faster (small_batch), unless the caller chose (or tuned) tiles of the grouped
+// ones.
 constexpr int kMaxGridY = 65535;
 panda_status apply_tiles(panda_batch* b) {
   bool small = b->n <= kMaxGridY;
@@ -315,6 +351,14 @@ panda_status apply_tiles(panda_batch* b) {
     b->mx.Ne = std::max(b->mx.Ne, c.Ne);
     b->long_k = b->long_k || c.Nep > kFoldK;
     b->mx.Na = std::max(b->mx.Na, c.Na);
+  }
+  if (small) {
+    std::vector<int64_t> Ne, Na;
+    for (const auto& c : b->ctx) {
+      Ne.push_back(c.Ne);
+      Na.push_back(c.Na);
+    }
+    small = small_batch(b->n, Ne.data(), Na.data(), b->opt.precision);
   }
   for (auto& c : b->ctx) PANDA_TRY(ctx_set_small(&c, small));
   b->small = small;

@@ -75,6 +75,9 @@ LayoutSpec single_spec(int64_t Ne, int64_t Na, bool packed_c, int32_t precision)
 // A network of a batch, sized for every tile candidate: the smallest A + W tile
 // (64 x 64) and the smallest W W^T chunk.
 LayoutSpec batch_spec(int64_t Ne, int64_t Na);
+// Whether a batch of n networks, all of them small (small_net), runs faster in
+// the small kernels than in the grouped ones.
+bool small_batch(int32_t n, const int64_t* Ne, const int64_t* Na, int32_t precision);
 
 }  // namespace panda
 

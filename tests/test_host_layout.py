@@ -24,8 +24,8 @@ def layout(tmp_path_factory):
          "-Wl,-rpath," + PKG], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
 
-    def lines(mode):
-        r = subprocess.run([exe, mode], capture_output=True, text=True, timeout=60)
+    def lines(mode, *args):
+        r = subprocess.run([exe, mode] + [str(a) for a in args], capture_output=True, text=True, timeout=60)
         assert r.returncode == 0, r.stderr
         return [[int(x) for x in line.split()] for line in r.stdout.splitlines()]
     return lines
@@ -49,3 +49,19 @@ def test_loads_clear_only_the_h_partials(layout):
     for line in lines:
         cleared, room = line[4:]
         assert 0 < cleared <= room, line
+
+
+# us an iteration measured in the small and in the grouped kernels, FP32 and
+# split form, where they differ by more than an eighth
+@pytest.mark.parametrize("n,Ne,Na,small,fp32,split", [
+    (20, 125, 125, 37, 150, 139), (400, 125, 125, 311, 416, 471), (16, 250, 250, 81, 212, 171),
+    (8, 354, 354, 104, 239, 173), (100, 354, 354, 927, 667, 730), (2, 500, 500, 64, 240, 172),
+    (8, 500, 500, 171, 291, 200), (32, 500, 500, 609, 419, 443), (100, 500, 500, 1953, 1153, 1293),
+    (2, 700, 700, 119, 303, 194), (16, 700, 700, 737, 557, 503), (16, 40, 400, 57, 172, 128),
+    (200, 40, 400, 478, 367, 365), (400, 40, 400, 974, 628, 656), (2, 100, 2000, 133, 285, 184),
+    (8, 100, 2000, 469, 376, 239), (32, 100, 2000, 1890, 616, 629), (8, 30, 1000, 94, 200, 155),
+    (64, 30, 1000, 635, 334, 332), (64, 64, 1024, 823, 374, 362), (300, 65, 130, 234, 339, 368),
+    (8, 2000, 100, 409, 663, 680), (4, 1000, 300, 148, 322, 233)])
+def test_batches_take_the_faster_kernels(layout, n, Ne, Na, small, fp32, split):
+    for precision, grouped in ((0, fp32), (1, split)):
+        assert layout("batch", n, Ne, Na, precision) == [[int(small < grouped)]], (precision, grouped)
