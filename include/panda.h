@@ -326,11 +326,15 @@ void panda_batch_destroy(panda_batch* b);
  * panda_batch_tile_candidates(phase) gives how many exist for an FP32 batch
  * (choice in [0, count); a split-BF16 batch accepts only choice 0 for R, A + W
  * and the C update).  set_tiles validates every entry and rebuilds the work lists
- * (synchronises the stream).  autotune times every candidate of every phase
- * on the batch's own shapes (reps timed launches each, best time wins) and
- * keeps the fastest; it overwrites the whole state, so it must precede
- * panda_batch_load (loaded networks are marked unloaded).  Timing does not
- * depend on the values, so the state is zero while it runs. */
+ * (synchronises the stream).  A batch of small networks whose choices are all 0
+ * runs in kernels of its own, without these products, where they are expected
+ * to be faster.  autotune times every candidate of every phase on the batch's
+ * own shapes (reps timed launches each, best time wins) and keeps the fastest;
+ * where those other kernels can run the batch it times whole iterations of both
+ * and keeps the faster (all choices 0 if it is they).  It overwrites the whole
+ * state, so it must precede panda_batch_load (loaded networks are marked
+ * unloaded).  Timing does not depend on the values, so the state is zero while
+ * it runs. */
 enum {
   PANDA_BATCH_TILE_R = 0,     /* R = T(P, W) tile                    */
   PANDA_BATCH_TILE_AW = 1,    /* A = T(W, C) + W update tile         */

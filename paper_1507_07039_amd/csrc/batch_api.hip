@@ -87,6 +87,8 @@ struct panda_batch {
   bool b3;  // split-BF16 products
   bool long_k;  // R and the C update sum over more than kFoldK of k somewhere
   bool small;  // every network in the small kernels (under the default tiles)
+  // how that was settled under the default tiles: by the rule, or by the autotuner
+  enum Choice { kByRule, kTunedSmall, kTunedGrouped } choice;
   SmallDims mx;  // largest network
   int32_t* ctr;
   DevState* d_states;
@@ -337,35 +339,70 @@ panda_status gather_states(panda_batch* b) {
   return PANDA_OK;
 }
 
-// Small networks leave the grouped kernels for the small ones where those are
-// faster (small_batch), unless the caller chose (or tuned) tiles of the grouped
-// ones.
+// Whether the batch can run in the small kernels (its tile choices aside).
 constexpr int kMaxGridY = 65535;
-panda_status apply_tiles(panda_batch* b) {
+bool can_be_small(const panda_batch* b) {
   bool small = b->n <= kMaxGridY;
+  for (const auto& c : b->ctx) small = small && small_net(c.Ne, c.Na);
+  return small;
+}
+
+// Small networks leave the grouped kernels for the small ones where those are
+// faster (by the autotuner's timing, else by small_batch), unless the caller
+// chose (or tuned) tiles of the grouped ones.
+panda_status apply_tiles(panda_batch* b) {
+  bool small = can_be_small(b) && b->choice != panda_batch::kTunedGrouped;
   for (int l = 0; l < kNumLists; ++l) small = small && b->tiles[l] == 0;
   b->mx = SmallDims{0, 0};
   b->long_k = false;
+  std::vector<int64_t> Ne, Na;
   for (const auto& c : b->ctx) {
-    small = small && small_net(c.Ne, c.Na);
     b->mx.Ne = std::max(b->mx.Ne, c.Ne);
     b->long_k = b->long_k || c.Nep > kFoldK;
     b->mx.Na = std::max(b->mx.Na, c.Na);
+    Ne.push_back(c.Ne);
+    Na.push_back(c.Na);
   }
-  if (small) {
-    std::vector<int64_t> Ne, Na;
-    for (const auto& c : b->ctx) {
-      Ne.push_back(c.Ne);
-      Na.push_back(c.Na);
-    }
+  if (small && b->choice == panda_batch::kByRule)
     small = small_batch(b->n, Ne.data(), Na.data(), b->opt.precision);
-  }
   for (auto& c : b->ctx) PANDA_TRY(ctx_set_small(&c, small));
   b->small = small;
   for (int l = 0; l < kNumLists; ++l) PANDA_TRY(build_list(b, l));
   PANDA_TRY(upload_insts(b));
   drop_graph(b);
   return PANDA_OK;
+}
+
+// Fewest milliseconds of `reps` whole iterations (each the mean of four in a
+// row) in the small or the grouped kernels, from a zero state: with a tol of 0
+// nothing converges and every step does its work.
+panda_status time_iterations(panda_batch* b, bool small, int32_t reps, hipEvent_t e0, hipEvent_t e1,
+                             float* best) {
+  constexpr int kRow = 4;
+  const Rule rule = b->rule, rule0 = b->ctx[0].rule;
+  const bool was = b->small;
+  b->small = small;
+  b->rule.tol = b->ctx[0].rule.tol = 0.0;
+  panda_status st = PANDA_OK;
+  auto hip = [&](hipError_t e) {
+    if (e != hipSuccess && st == PANDA_OK) st = hip_fail(e, "batch_autotune");
+    return e == hipSuccess;
+  };
+  hip(launch_batch_gates(b->d_inst, b->n, 1, 1, b->stream));
+  *best = 1e30f;
+  for (int r = 0; r <= reps && st == PANDA_OK; ++r) {  // r = 0 warms up
+    if (!hip(hipEventRecord(e0, b->stream))) break;
+    for (int k = 0; k < kRow && st == PANDA_OK; ++k) st = enqueue_batch_iteration(b, b->stream);
+    float ms = 0.0f;
+    if (st != PANDA_OK || !hip(hipEventRecord(e1, b->stream)) || !hip(hipEventSynchronize(e1)) ||
+        !hip(hipEventElapsedTime(&ms, e0, e1)))
+      break;
+    if (r > 0) *best = std::min(*best, ms / kRow);
+  }
+  b->rule = rule;
+  b->ctx[0].rule = rule0;
+  b->small = was;
+  return st;
 }
 
 panda_status check_shapes(int32_t n, const int64_t* Ne, const int64_t* Na) {
@@ -455,6 +492,7 @@ panda_status panda_batch_set_tiles(panda_batch* b, const int32_t* choice) {
     if (choice[l] < 0 || choice[l] >= batch_tile_candidates(l, b->b3))
       return fail(PANDA_ERR_ARG, "batch_set_tiles: choice out of range%s");
   for (int l = 0; l < kNumLists; ++l) b->tiles[l] = choice[l];
+  b->choice = panda_batch::kByRule;
   return apply_tiles(b);
 }
 
@@ -506,6 +544,20 @@ panda_status panda_batch_autotune(panda_batch* b, int32_t reps, float* best_ms) 
     }
     b->tiles[phase] = bestc;
     if (best_ms) best_ms[phase] = best;
+  }
+  // the grouped kernels with the best tiles against the small ones, over whole
+  // iterations (how a small batch divides into phases differs between them)
+  b->choice = panda_batch::kTunedGrouped;
+  if (st == PANDA_OK && can_be_small(b)) {
+    float grouped = 0.0f, small = 0.0f;
+    for (int l = 0; l < kNumLists && st == PANDA_OK; ++l) st = build_list(b, l);
+    if (st == PANDA_OK) st = upload_insts(b);
+    if (st == PANDA_OK) st = time_iterations(b, false, reps, e0, e1, &grouped);
+    if (st == PANDA_OK) st = time_iterations(b, true, reps, e0, e1, &small);
+    if (st == PANDA_OK && small < grouped) {
+      b->choice = panda_batch::kTunedSmall;
+      for (int l = 0; l < kNumLists; ++l) b->tiles[l] = 0;
+    }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

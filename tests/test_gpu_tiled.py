@@ -273,3 +273,31 @@ def test_tiled_warm_state(torch, pd, precision, packed):
         assert c.iterate()[1] == t
         for g, w in zip(c.state()[:3], step64(torch, *(M.double() for M in before), t, {})):
             close(g, w, tol)
+
+
+# two networks that the small kernels run three to four times faster, and a
+# batch that they run three times slower
+@pytest.mark.parametrize("n,Ne,Na,small", [(2, 500, 500, True), (32, 100, 2000, False)])
+def test_autotune_keeps_the_faster_kernels(torch, pd, n, Ne, Na, small):
+    """A tuned batch goes on in whichever kernels are faster: bit for bit as one
+    that takes the small ones by rule, or one given the tuned tiles."""
+    shapes = [(Ne, Na)] * n
+    net = gpu_net(torch, 5, Ne, Na)
+    tuned, given = (pd.Batch(shapes, pd.default_options(tol=0.0)) for _ in range(2))
+    best = tuned.autotune(reps=2)
+    assert all(v > 0 for v in best.values())
+    with pytest.raises(pd.PandaError):
+        tuned.iterate(1)
+    if small:
+        assert tuned.tiles == [0, 0, 0, 0]
+    else:
+        given.tiles = tuned.tiles
+    for b in (tuned, given):
+        for i in range(n):
+            b.load(i, *net)
+        b.iterate(2, graph=True)
+    assert all(torch.equal(x, y) for x, y in zip(tuned.state(n - 1)[:3], given.state(n - 1)[:3]))
+    want = [M.double() for M in net]
+    for t in (1, 2):
+        want = step64(torch, *want[:3], t, {})
+    assert (tuned.state(0)[0].double() - want[0]).abs().max() <= 1e-4
