@@ -64,9 +64,10 @@ typedef enum {
  * diagonal rule are FP64 in both forms; the state W, P, C is FP32):
  *   PANDA_PREC_FP32    products of the whole FP32 operands, FP32 accumulation,
  *                      formed on bf16 matrix cores from three bf16 terms per
- *                      operand that add up to it exactly (six products; the
- *                      ones left out are below the rounding of the
- *                      accumulation).
+ *                      operand that add up to it (six products; the ones
+ *                      left out, 2^-22 of a term at most, average out below
+ *                      the rounding of the accumulation).  Sums of at most
+ *                      eight terms are formed term by term in FP64.
  *   PANDA_PREC_BF16X3  every operand split as x = hi + lo (bf16, round to
  *                      nearest even) and each product formed as
  *                      hi*hi + hi*lo + lo*hi on bf16 matrix cores with FP32

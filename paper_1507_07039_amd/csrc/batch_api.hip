@@ -85,7 +85,8 @@ struct panda_batch {
   std::vector<int64_t> h_flat[5];
   FlatList flat[5];
   bool b3;  // split-BF16 products
-  bool long_k;  // R and the C update sum over more than kFoldK of k somewhere
+  int ks;   // how the products sum: any K, where a network has a short one; else
+            // folded, where R and the C update sum over more than kFoldK somewhere
   bool small;  // every network in the small kernels (under the default tiles)
   // how that was settled under the default tiles: by the rule, or by the autotuner
   enum Choice { kByRule, kTunedSmall, kTunedGrouped } choice;
@@ -212,7 +213,7 @@ panda_status build_list(panda_batch* b, int phase) {
   wl.nseg = n;
   wl.ctr = b->ctr + (int64_t)phase * kNumXcd * kCtrStride;
   L.wl = wl;
-  L.nb = batch_grid(phase, b->tiles[phase], b->b3, b->long_k, b->rule);
+  L.nb = batch_grid(phase, b->tiles[phase], b->b3, b->ks, b->rule);
   HIP_TRY(hipMemcpyAsync(L.d_seg_inst, L.seg_inst.data(), (size_t)n * sizeof(int32_t),
                          hipMemcpyHostToDevice, b->stream));
   HIP_TRY(hipMemcpyAsync(L.d_seg_first, L.seg_first.data(), ((size_t)n + 1) * sizeof(int64_t),
@@ -265,7 +266,7 @@ panda_status build_flat(panda_batch* b) {
 
 panda_status launch_phase(panda_batch* b, int phase, hipStream_t s) {
   const auto& L = b->lists[phase];
-  HIP_TRY(launch_batch_product(phase, b->tiles[phase], b->b3, b->long_k, b->d_inst, L.wl, b->rule,
+  HIP_TRY(launch_batch_product(phase, b->tiles[phase], b->b3, b->ks, b->d_inst, L.wl, b->rule,
                                L.nb, s));
   return PANDA_OK;
 }
@@ -354,11 +355,12 @@ panda_status apply_tiles(panda_batch* b) {
   bool small = can_be_small(b) && b->choice != panda_batch::kTunedGrouped;
   for (int l = 0; l < kNumLists; ++l) small = small && b->tiles[l] == 0;
   b->mx = SmallDims{0, 0};
-  b->long_k = false;
+  b->ks = kSumOnce;
   std::vector<int64_t> Ne, Na;
   for (const auto& c : b->ctx) {
     b->mx.Ne = std::max(b->mx.Ne, c.Ne);
-    b->long_k = b->long_k || c.Nep > kFoldK;
+    const int ks = std::min(c.Ne, c.Na) <= kShortK ? kSumAny : c.Nep > kFoldK ? kSumFolded : kSumOnce;
+    b->ks = std::max(b->ks, ks);
     b->mx.Na = std::max(b->mx.Na, c.Na);
     Ne.push_back(c.Ne);
     Na.push_back(c.Na);

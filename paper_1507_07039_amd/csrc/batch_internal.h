@@ -69,10 +69,10 @@ enum BatchTile { kBTResp = 0, kBTAvail = 1, kBTCoop = 2, kBTCoreg = 3, kBTNum = 
 int batch_tile_candidates(int phase, bool b3 = false);
 int64_t rect_items(int choice, bool b3, int64_t Nep, int64_t Nap);  // R and A + W tiles
 int64_t coop_chunk_of(int choice);                           // K chunk of W W^T
-// Persistent grid of a grouped product with candidate `choice`; lk: whether a
-// network's sums in it run over more than kFoldK of k.
-int64_t batch_grid(int phase, int choice, bool b3, bool lk, Rule rule);
-hipError_t launch_batch_product(int phase, int choice, bool b3, bool lk, const BInst* bi,
+// Persistent grid of a grouped product with candidate `choice`; ks: how the
+// batch's networks need their sums taken (KSum).
+int64_t batch_grid(int phase, int choice, bool b3, int ks, Rule rule);
+hipError_t launch_batch_product(int phase, int choice, bool b3, int ks, const BInst* bi,
                                 const WorkList& wl, Rule rule, int64_t nb, hipStream_t s);
 // bf16 planes of the new W (split-BF16 batches): (Nep / 64) x (Nap / 64)
 // blocks per network.

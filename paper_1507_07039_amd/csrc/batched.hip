@@ -20,28 +20,29 @@ namespace {
 
 using namespace gemm;
 
-// Candidate tilings of the FP32 form (index = autotuner choice); LK: sums over
-// more than kFoldK of k.
-template <bool LK>
-using RectT0 = BlockGemmF3<128, 128, 2, 2, true, false, LK>;
-template <bool LK>
-using RectT1 = BlockGemmF3<64, 64, 1, 2, true, false, LK>;
-template <bool LK>
-using RectT2 = BlockGemmF3<64, 128, 1, 2, true, false, LK>;
-template <bool LK>
-using SymT0 = BlockGemmF3<128, 128, 2, 2, false, false, LK>;
-template <bool LK>
-using SymT1 = BlockGemmF3<128, 128, 4, 1, false, false, LK>;
-template <bool LK>
-using SymT2 = BlockGemmF3<128, 128, 1, 4, false, false, LK>;
-using CoopT = BlockGemmF3<64, 64, 1, 2, true, true, true>;
+// Candidate tilings of the FP32 form (index = autotuner choice) and how they
+// sum over K (KSum).
+template <int KS>
+using RectT0 = BlockGemmF3<128, 128, 2, 2, true, false, KS>;
+template <int KS>
+using RectT1 = BlockGemmF3<64, 64, 1, 2, true, false, KS>;
+template <int KS>
+using RectT2 = BlockGemmF3<64, 128, 1, 2, true, false, KS>;
+template <int KS>
+using SymT0 = BlockGemmF3<128, 128, 2, 2, false, false, KS>;
+template <int KS>
+using SymT1 = BlockGemmF3<128, 128, 4, 1, false, false, KS>;
+template <int KS>
+using SymT2 = BlockGemmF3<128, 128, 1, 4, false, false, KS>;
+template <int KS>
+using CoopT = BlockGemmF3<64, 64, 1, 2, true, true, KS>;
 constexpr int64_t kCoopChunks[4] = {512, 1024, 2048, 4096};
 // Split-BF16 batches: the block GEMMs of the single-network form (R
 // register-staged; A + W with direct loads and C split as it is read, 64 x 128
 // so that R and A + W cut a network alike; W W^T and the C update as there).
 using RectB3A = BlockGemmB3P<64, 128, 1, 4, true, 3>;
 static_assert(RectB3::BM == RectB3A::BM && RectB3::BN == RectB3A::BN &&
-                  SymB3::BM == SymT0<false>::BM && CoopB3::BM == CoopT::BM,
+                  SymB3::BM == SymT0<kSumOnce>::BM && CoopB3::BM == CoopT<kSumOnce>::BM,
               "one work list per product");
 
 // Largest s with seg_first[s] <= it.
@@ -76,7 +77,7 @@ struct PhResp {
     if constexpr (B3)
       g.run(OpsB3{d.Pp, d.Wt}, m0, n0, 0, d.Nep, smem);
     else
-      g.run(OpsF32{d.P, d.Nep, W, d.Nap, d.Ne}, m0, n0, 0, d.Nep, smem);
+      g.run(OpsF32{d.P, d.Nep, W, d.Nap, d.Ne, d.Ne}, m0, n0, 0, d.Nep, smem);
     EpiStoreT epi{d.R, d.Nap, d.Ne, d.Na, d.nP, d.nWc, d.dP, W, d.Nap};
     epi_tile(g, epi, m0, n0);
   }
@@ -103,7 +104,7 @@ struct PhAvail {
     if constexpr (B3)
       g.run(OpsB3F{d.Wr, d.C, d.Nap, d.Nep}, m0, n0, 0, d.Nap, smem);
     else
-      g.run(OpsF32{Wold, d.Nap, d.C, d.Nap, d.Ne}, m0, n0, 0, d.Nap, smem);
+      g.run(OpsF32{Wold, d.Nap, d.C, d.Nap, d.Ne, d.Na}, m0, n0, 0, d.Nap, smem);
     EpiWUpdate epi{Wold, d.R,   d.W[ws ^ 1], d.Nap, d.Ne,       d.Na,    d.nWr,
                    d.nC, d.dC,  alpha,       h_undamped, d.hpart, 0.0};
     epi_tile(g, epi, m0, n0);
@@ -133,7 +134,7 @@ struct PhCoop {
     if constexpr (B3)
       g.run(OpsB3{d.Wr, d.Wr}, m0, n0, kb, ke, smem);
     else
-      g.run(OpsF32{W, d.Nap, W, d.Nap}, m0, n0, kb, ke, smem);
+      g.run(OpsF32{W, d.Nap, W, d.Nap, INT64_MAX, d.Na}, m0, n0, kb, ke, smem);
     float* ps = d.ppart + sp * d.Nep * d.Nep;
     g.for_each([&](int r, int c, float v) { ps[(m0 + r) * d.Nep + n0 + c] = v; });
   }
@@ -158,7 +159,7 @@ struct PhCoreg {
     if constexpr (B3)
       g.run(OpsB3{d.Wt, d.Wt}, I * kCB, J * kCB, 0, d.Nep, smem);
     else
-      g.run(OpsF32{W, d.Nap, W, d.Nap}, I * kCB, J * kCB, 0, d.Nep, smem);
+      g.run(OpsF32{W, d.Nap, W, d.Nap, INT64_MAX, d.Ne}, I * kCB, J * kCB, 0, d.Nep, smem);
     coreg_epilogue<SIGT, false>(g, smem, I, J, d.C, d.Nap, d.Na, nval, alpha, d.cstat, d.csq, d.Nap);
   }
 };
@@ -362,60 +363,71 @@ int batch_tile_candidates(int phase, bool b3) {
 int64_t rect_items(int choice, bool b3, int64_t Nep, int64_t Nap) {
   auto items = [&](int64_t bm, int64_t bn) { return (Nep + bm - 1) / bm * (Nap / bn); };
   if (b3) return items(RectB3A::BM, RectB3A::BN);
-  if (choice == 1) return items(RectT1<true>::BM, RectT1<true>::BN);
-  if (choice == 2) return items(RectT2<true>::BM, RectT2<true>::BN);
-  return items(RectT0<true>::BM, RectT0<true>::BN);
+  if (choice == 1) return items(RectT1<kSumOnce>::BM, RectT1<kSumOnce>::BN);
+  if (choice == 2) return items(RectT2<kSumOnce>::BM, RectT2<kSumOnce>::BN);
+  return items(RectT0<kSumOnce>::BM, RectT0<kSumOnce>::BN);
 }
 
 int64_t coop_chunk_of(int choice) { return kCoopChunks[choice < 0 || choice > 3 ? 0 : choice]; }
 
-// f(G, phase) for the kernel of grouped product `phase`: lk, whether a
-// network of the batch has sums over more than kFoldK of k there (A + W: most
-// have).  The fresh similarities' sums (sigT) leave room for one block per CU
-// either way.
+// f(G, phase) for the kernel of grouped product `phase`; ks: how the batch's
+// sums over N_e must be taken (A + W and W W^T fold over N_a in any case, as
+// most networks need it there).  The fresh similarities' sums (sigT) leave room
+// for one block per CU either way.
 template <class F>
-static auto with_product(int phase, int choice, bool sigT, bool b3, bool lk, Rule rule, F&& f) {
-  auto rect = [&](const auto& ph, auto L) {
-    constexpr bool LK = decltype(L)::value;
-    if (choice == 1) return f(RectT1<LK>{}, ph);
-    if (choice == 2) return f(RectT2<LK>{}, ph);
-    return f(RectT0<LK>{}, ph);
+static auto with_product(int phase, int choice, bool sigT, bool b3, int ks, Rule rule, F&& f) {
+  auto rect = [&](const auto& ph, auto k) {
+    constexpr int KS = decltype(k)::value;
+    if (choice == 1) return f(RectT1<KS>{}, ph);
+    if (choice == 2) return f(RectT2<KS>{}, ph);
+    return f(RectT0<KS>{}, ph);
   };
-  auto sym = [&](const auto& ph, auto L) {
-    constexpr bool LK = decltype(L)::value;
-    if (choice == 1) return f(SymT1<LK>{}, ph);
-    if (choice == 2) return f(SymT2<LK>{}, ph);
-    return f(SymT0<LK>{}, ph);
+  auto sym = [&](const auto& ph, auto k) {
+    constexpr int KS = decltype(k)::value;
+    if (choice == 1) return f(SymT1<KS>{}, ph);
+    if (choice == 2) return f(SymT2<KS>{}, ph);
+    return f(SymT0<KS>{}, ph);
   };
+  constexpr std::integral_constant<int, kSumOnce> once;
+  constexpr std::integral_constant<int, kSumFolded> folded;
+  constexpr std::integral_constant<int, kSumAny> any;
   switch (phase) {
-    case kBTResp:
+    case kBTResp: {
       if (b3) return f(RectB3{}, PhResp<true>{});
-      return lk ? rect(PhResp<false>{}, std::true_type{}) : rect(PhResp<false>{}, std::false_type{});
-    case kBTAvail:
+      const PhResp<false> ph{};
+      return ks == kSumAny ? rect(ph, any) : ks == kSumFolded ? rect(ph, folded) : rect(ph, once);
+    }
+    case kBTAvail: {
       if (b3) return f(RectB3A{}, PhAvail<true>{rule.alpha, rule.h_undamped});
-      return rect(PhAvail<false>{rule.alpha, rule.h_undamped}, std::true_type{});
+      const PhAvail<false> ph{rule.alpha, rule.h_undamped};
+      return ks == kSumAny ? rect(ph, any) : rect(ph, folded);
+    }
     case kBTCoop:
-      return b3 ? f(CoopB3{}, PhCoop<true>{}) : f(CoopT{}, PhCoop<false>{});
-    default:
+      if (b3) return f(CoopB3{}, PhCoop<true>{});
+      return ks == kSumAny ? f(CoopT<kSumAny>{}, PhCoop<false>{})
+                           : f(CoopT<kSumFolded>{}, PhCoop<false>{});
+    default: {
       if (b3)
         return sigT ? f(SymB3{}, PhCoreg<true, true>{rule.alpha})
                     : f(SymB3{}, PhCoreg<false, true>{rule.alpha});
-      if (sigT) return sym(PhCoreg<true, false>{rule.alpha}, std::true_type{});
-      return lk ? sym(PhCoreg<false, false>{rule.alpha}, std::true_type{})
-                : sym(PhCoreg<false, false>{rule.alpha}, std::false_type{});
+      const PhCoreg<true, false> fresh{rule.alpha};
+      if (sigT) return ks == kSumAny ? sym(fresh, any) : sym(fresh, folded);
+      const PhCoreg<false, false> ph{rule.alpha};
+      return ks == kSumAny ? sym(ph, any) : ks == kSumFolded ? sym(ph, folded) : sym(ph, once);
+    }
   }
 }
 
-int64_t batch_grid(int phase, int choice, bool b3, bool lk, Rule rule) {
-  return with_product(phase, choice, rule.sigma_from_T != 0, b3, lk, rule,
+int64_t batch_grid(int phase, int choice, bool b3, int ks, Rule rule) {
+  return with_product(phase, choice, rule.sigma_from_T != 0, b3, ks, rule,
                       [](const auto& g, const auto& ph) {
                         return group_grid<std::decay_t<decltype(g)>, std::decay_t<decltype(ph)>>();
                       });
 }
 
-hipError_t launch_batch_product(int phase, int choice, bool b3, bool lk, const BInst* bi,
+hipError_t launch_batch_product(int phase, int choice, bool b3, int ks, const BInst* bi,
                                 const WorkList& wl, Rule rule, int64_t nb, hipStream_t s) {
-  return with_product(phase, choice, rule.sigma_from_T != 0, b3, lk, rule,
+  return with_product(phase, choice, rule.sigma_from_T != 0, b3, ks, rule,
                       [&](const auto& g, const auto& ph) {
                         return group_launch<std::decay_t<decltype(g)>>(bi, wl, ph, nb, s);
                       });

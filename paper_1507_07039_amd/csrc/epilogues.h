@@ -161,11 +161,11 @@ using EpiWUpdate = EpiWUpdateT<false>;
 
 // Tile configurations.  FP32 operands (stand-alone similarity, the warm start,
 // the co-expression prior): 128 x 128, four waves.
-template <bool LK>
-using RectF32 = BlockGemmF3<128, 128, 2, 2, true, false, LK>;
+template <int KS>
+using RectF32 = BlockGemmF3<128, 128, 2, 2, true, false, KS>;
 using RectB3 = BlockGemmB3<64, 128, 1, 4>;  // batched R: K = N_e is short, register staging wins
-template <bool LK>
-using SymF32 = BlockGemmF3<128, 128, 4, 1, false, false, LK>;
+template <int KS>
+using SymF32 = BlockGemmF3<128, 128, 4, 1, false, false, KS>;
 using CoopB3 = BlockGemmB3<64, 64, 2, 2>;
 // The products of a single network on bf16 planes, NP = 2 (split-BF16 form)
 // or 3 (FP32 form).  The FP32 form runs on them too because six bf16 products

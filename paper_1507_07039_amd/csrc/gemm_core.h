@@ -94,7 +94,48 @@ struct OpsF32 {
   const float* Y;
   int64_t ldy;
   int64_t xrows = INT64_MAX;  // rows (m) of X that exist (loaders may clamp to them)
+  int64_t K = INT64_MAX;      // length of the contraction without its padding
 };
+
+// Entries of block GEMM g summed over kn <= kShortK terms in FP64.  fill(xs, ys)
+// puts the terms of the tile's rows and columns in LDS, kShortK doubles each.
+// Bound by the FP64 FMAs and the epilogue.  A similarity of 5000 x 8 x 5000 takes
+// 134 us (105 on planes, 151 on FP32 matrix cores), 5000 x 3 x 5000 114 (107, 150),
+// correlations of 18000 genes over 5 samples 322 (305, 383).
+constexpr int kShortLd = (int)kShortK + 1;  // columns read lane by lane: in other banks
+template <class G, class Fill>
+__device__ __forceinline__ void short_product(G& g, int kn, char* smem, Fill&& fill) {
+  double* xs = reinterpret_cast<double*>(smem);
+  double* ys = xs + G::BM * kShortLd;
+  static_assert((G::BM + G::BN) * kShortLd * 8 <= G::MAIN_BYTES, "within the stages");
+  __syncthreads();
+  fill(xs, ys);
+  __syncthreads();
+  double y[G::TN][kShortK];
+#pragma unroll
+  for (int j = 0; j < G::TN; ++j)
+#pragma unroll
+    for (int k = 0; k < (int)kShortK; ++k) y[j][k] = ys[g.col_of(j) * kShortLd + k];
+#pragma unroll
+  for (int i = 0; i < G::TM; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const double* x = xs + g.row_of(i, r) * kShortLd;
+      double s[G::TN];
+#pragma unroll
+      for (int j = 0; j < G::TN; ++j) s[j] = 0.0;
+#pragma unroll
+      for (int k = 0; k < (int)kShortK; ++k) {
+        if (k >= kn) break;
+        const double xk = x[k];
+#pragma unroll
+        for (int j = 0; j < G::TN; ++j) s[j] += xk * y[j][k];
+      }
+#pragma unroll
+      for (int j = 0; j < G::TN; ++j) g.acc[i][j][r] = (float)s[j];
+    }
+  __syncthreads();
+}
 
 // ================================================== split-BF16 main loop ==
 // Both operands are stored as bf16 planes (see Planes; X[m][k] and Yt[n][k], Yt
@@ -104,9 +145,9 @@ struct OpsF32 {
 //   and the rounding of lo bound the relative error of each product term by
 //   about 2^-16.
 //   Three planes (x = hi + mid + lo exactly, 8 bits each, see split_pair3):
-//   the six products down to 2^-16 of the leading one; the dropped ones are
-//   2^-23 of a term at most (2^-25 on average, of either sign), below the
-//   rounding of an FP32 accumulation.
+//   the six products down to 2^-16 of the leading one; the dropped ones add up
+//   to 2^-22 of a term at most (of either sign), which sums of more than
+//   kShortK terms average out below what an FP32 accumulation rounds away.
 struct OpsB3 {
   Planes X;
   Planes Y;
@@ -392,9 +433,9 @@ __device__ __forceinline__ void split_pair3(float a, float b, unsigned (&o)[3]) 
 // 890 -> 760 us (1.3 GB written).  The error against 64 bits falls to between
 // a third and 0.8 of what it was.
 //
-// LK: for sums over more than kFoldK of k, folded as there, in registers (a
-// choice of kernel: the running sum takes 64 of the 256 registers a wave has;
-// it cost 15 % where it was carried for K = 700).
+// KS: how K is summed (KSum).  Folded as there, but in registers (a choice of
+// kernel: the running sum takes 64 of the 256 registers a wave has; it cost
+// 15 % where it was carried for K = 700).
 template <int MN, bool KC, int NT>
 struct TileLoadF3 {
   static constexpr int NI = MN * 2 / NT;  // runs of 8 k per thread
@@ -477,8 +518,9 @@ struct TileLoadF3 {
   }
 };
 
-template <int BM_, int BN_, int WM, int WN, bool XK, bool YK, bool LK>
+template <int BM_, int BN_, int WM, int WN, bool XK, bool YK, int KS>
 struct BlockGemmF3 {
+  static constexpr bool LK = KS == kSumFolded || KS == kSumAny;
   using Ops = OpsF32;
   static constexpr int BM = BM_, BN = BN_, BK = 16, NT = 64 * WM * WN;
   static constexpr int WAVES_PER_EU = 2;
@@ -504,6 +546,12 @@ struct BlockGemmF3 {
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     wm = w % WM;
     wn = w / WM;
+    if constexpr (KS == kSumAny || KS == kSumShort) {
+      if (KS == kSumShort || o.K <= kShortK) {
+        run_short(o, m0, n0, kbeg, kend, smem);
+        return;
+      }
+    }
     floatx16 sum[LK ? TM : 1][LK ? TN : 1];
     auto clear = [](auto& a) {
 #pragma unroll
@@ -634,6 +682,24 @@ struct BlockGemmF3 {
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] += sum[i][j][r];
     }
+  }
+  // Terms of one operand (rows rows, ld floats apart along k or across it) in LDS.
+  template <bool KC, int MN>
+  __device__ __forceinline__ static void put_terms(double* s, const float* p, int64_t ld, int64_t mn0,
+                                                   int64_t rows, int64_t kbeg, int64_t kn) {
+    for (int e = threadIdx.x; e < MN * (int)kShortK; e += NT) {
+      const int k = KC ? e % (int)kShortK : e / MN, q = KC ? e / (int)kShortK : e % MN;
+      const int64_t mn = mn0 + q < rows ? mn0 + q : rows - 1;
+      s[q * kShortLd + k] = k < kn ? (double)(KC ? p[mn * ld + kbeg + k] : p[(kbeg + k) * ld + mn]) : 0.0;
+    }
+  }
+  __device__ __forceinline__ void run_short(const Ops& o, int64_t m0, int64_t n0, int64_t kbeg,
+                                            int64_t kend, char* smem) {
+    const int64_t kn = (kend < o.K ? kend : o.K) - kbeg;  // (none in a later chunk of K)
+    short_product(*this, kn > 0 ? (int)kn : 0, smem, [&](double* xs, double* ys) {
+      put_terms<XK, BM>(xs, o.X, o.ldx, m0, o.xrows, kbeg, kn);
+      put_terms<YK, BN>(ys, o.Y, o.ldy, n0, INT64_MAX, kbeg, kn);
+    });
   }
   __device__ __forceinline__ int row_of(int i, int r) const {
     return wm * (BM / WM) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
@@ -1106,6 +1172,31 @@ struct BlockGemmB3P {
         k += n;
       }
     }
+  }
+
+  // The product over a short K (three planes of both operands; the planes are
+  // zero past it).
+  __device__ __forceinline__ void run_short(const Ops& o, int64_t m0, int64_t n0, int64_t K,
+                                            char* smem) {
+    static_assert(NP == 3 && !YF32 && KT >= kShortK, "whole operands, one K-tile");
+    lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    wm = w % WM;
+    wn = w / WM;
+    auto terms = [](double* s, const Planes& P, int64_t row) {
+      const bf16_t* p = P.p + plane_index<KT>(P.rows, row, 0);
+      const bf16x8 hi = *reinterpret_cast<const bf16x8*>(p);
+      const bf16x8 mid = *reinterpret_cast<const bf16x8*>(p + P.stride);
+      const bf16x8 lo = *reinterpret_cast<const bf16x8*>(p + 2 * P.stride);
+#pragma unroll
+      for (int k = 0; k < (int)kShortK; ++k)
+        s[k] = (double)(float)hi[k] + ((double)(float)mid[k] + (double)(float)lo[k]);
+    };
+    short_product(*this, (int)K, smem, [&](double* xs, double* ys) {
+      for (int q = threadIdx.x; q < BM; q += NT)
+        terms(xs + q * kShortLd, o.X, m0 + q < o.mrows ? m0 + q : o.mrows - 1);
+      for (int q = threadIdx.x; q < BN; q += NT) terms(ys + q * kShortLd, o.Y, n0 + q);
+    });
   }
 
   // LQ >= 0: fold a long K (see run_long).

@@ -711,7 +711,7 @@ panda_status panda_tanimoto(const float* X, const float* Y, int64_t M, int64_t K
   PackArgs a{X, Y, M, K, N, Mp, Kp, Np, L.Xp, L.Yp, L.nx, L.ny, L.scr, 0};
   a.rows = std::max<int64_t>(32, round_up((Kp + kColChunks - 1) / kColChunks, 8));
   HIP_TRY(launch_pack_xy(a, s));
-  HIP_TRY(launch_tanimoto_store(L.Xp, Kp, L.Yp, Np, Mp, Np, Kp, M, N, L.nx, L.ny, Out, N, L.part,
+  HIP_TRY(launch_tanimoto_store(L.Xp, Kp, L.Yp, Np, Mp, Np, Kp, M, N, K, L.nx, L.ny, Out, N, L.part,
                                 nullptr, s));
   return PANDA_OK;
 }
@@ -750,7 +750,7 @@ panda_status pearson_enqueue(const float* E, int64_t G, int64_t S, int64_t lde, 
   PearsonLayout L;
   pearson_layout(G, S, base, &L);
   HIP_TRY(launch_pearson_z(E, G, S, lde, L.stat, L.Zt, Gp, Sp, s));
-  HIP_TRY(launch_corr(L.Zt, Gp, Sp, G, C, ldc, s));
+  HIP_TRY(launch_corr(L.Zt, Gp, Sp, S, G, C, ldc, s));
   return PANDA_OK;
 }
 

@@ -94,12 +94,24 @@ size_t rect_partial_floats();
 // K up to which a product of three planes stays in one accumulator (see
 // BlockGemmB3P::kFolds), and the A product's scratch for longer ones.
 constexpr int64_t kFoldK = 1024;
+// K up to which the products of the FP32 form are summed term by term in FP64
+// from the whole operands.  What three planes leave out (mid * lo, lo * mid,
+// lo * lo: 2^-22 of a term at most) is lost in a longer sum, but not in one or
+// a few terms.  Error of a similarity in units of 2^-24 sum |x y| / sqrt(den),
+// rms (largest of 3.6e6), on planes / on FP32 matrix cores: K = 1 0.98 (7.3) /
+// 0.69 (2.4), K = 3 0.66 (5.7) / 0.62 (4.2), K = 5 0.53 (5.0) / 0.59 (4.5), K = 8
+// 0.43 (4.2) / 0.56 (4.7), and below the cores' from there on.
+constexpr int64_t kShortK = 8;
+// How a product of FP32 operands sums over K: in one accumulator; folded where
+// K is past kFoldK; that, but term by term where K is at most kShortK (of a
+// batch's networks some may have a short one); all of it term by term.
+enum KSum { kSumOnce = 0, kSumFolded = 1, kSumAny = 2, kSumShort = 3 };
 size_t rect_fold_floats(int64_t Kp, int np);
 
-// Out[i][j] = T(X, Y)_ij for i < M, j < N.  yd (optional): Y is square with
+// Out[i][j] = T(X, Y)_ij for i < M, j < N, over K (zeros from there to Kp).  yd (optional): Y is square with
 // its diagonal held apart in this FP64 vector (and zero in Y).
 hipError_t launch_tanimoto_store(const float* X, int64_t ldx, const float* Y, int64_t ldy,
-                                 int64_t Mp, int64_t Np, int64_t Kp, int64_t M, int64_t N,
+                                 int64_t Mp, int64_t Np, int64_t Kp, int64_t M, int64_t N, int64_t K,
                                  const double* nx, const double* ny, float* Out, int64_t ldo,
                                  float* part, const int32_t* gate, hipStream_t s,
                                  const double* yd = nullptr);
@@ -126,7 +138,7 @@ hipError_t launch_avail_wupdate(const Planes& Wr, int np, const float* Wold, con
 // C update (Eq. 5) on the upper tiles of T(W^T, W) with mirror writes and
 // per-row partial sums for the sigma of Eq. 6 (and |C_.j|^2).  order holds
 // the upper tiles (I | J << 16) in launch order, see launch_order.
-hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Nep, float* C,
+hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Ne, int64_t Nep, float* C,
                                int64_t ldc, int64_t Nap, int64_t Na, const double* nWcol,
                                Rule rule, double2* cstat, double* csq, const uint32_t* order,
                                const int32_t* gate, hipStream_t s, bool packed);
@@ -264,8 +276,8 @@ hipError_t launch_zscore_apply(float* M, int64_t rows, int64_t cols, int64_t ld,
 // then C = Z Z^T on the upper 128 x 128 tiles, mirrored, 1 on the diagonal.
 hipError_t launch_pearson_z(const float* E, int64_t G, int64_t S, int64_t lde, double2* stat,
                             float* Zt, int64_t Gp, int64_t Sp, hipStream_t s);
-hipError_t launch_corr(const float* Zt, int64_t Gp, int64_t Sp, int64_t G, float* C, int64_t ldc,
-                       hipStream_t s);
+hipError_t launch_corr(const float* Zt, int64_t Gp, int64_t Sp, int64_t S, int64_t G, float* C,
+                       int64_t ldc, hipStream_t s);
 
 
 }  // namespace panda

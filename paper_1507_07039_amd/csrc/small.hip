@@ -524,8 +524,9 @@ __global__ __launch_bounds__(kNT, 4) void k_small_finish(const BInst* __restrict
 // 100 x 3000 148 / 103, 40 x 4000 172 / 130 (the small tiles read C at a third
 // of its bandwidth).  The split-BF16 form takes them as well: its networks
 // of these sizes wait for launches, not for the matrix cores.
+// With few genes every sum over them is short, and takes no planes (kShortK).
 bool small_net(int64_t Ne, int64_t Na) {
-  return Ne <= 2048 && Na <= 2048 && Ne * Na * (Ne + Na) <= 900000000;
+  return Na <= kShortK || (Ne <= 2048 && Na <= 2048 && Ne * Na * (Ne + Na) <= 900000000);
 }
 
 hipError_t launch_small_avail(const BInst* bi, const BInst& one, int n, SmallDims mx,

@@ -36,35 +36,38 @@ constexpr int kNextRRun = 16;
 // The product of the tile, then the update in its epilogue (two blocks per
 // CU, so one block's epilogue overlaps the other's products).  With NR the
 // order also holds R tiles (kNextRTile).
-// LK: K past kFoldK (three planes), folded through LDS behind the stages.
-template <class G, bool SIGT, bool LK>
+// KS (three planes): K past kFoldK is folded through LDS behind the stages
+// (kSumFolded), K of at most kShortK summed term by term (kSumShort).
+template <class G, bool SIGT, int KS>
 constexpr int coreg_kernel_bytes() {
-  constexpr int main = G::MAIN_BYTES + (LK ? G::BM * G::BN * 4 : 0);
+  constexpr int main = G::MAIN_BYTES + (KS == kSumFolded ? G::BM * G::BN * 4 : 0);
   return main > coreg_smem_bytes<G, SIGT>() ? main : coreg_smem_bytes<G, SIGT>();
 }
-template <bool LK, class G>
-__device__ __forceinline__ void run_lk(G& g, const typename G::Ops& ops, int64_t m0, int64_t n0,
-                                       int64_t kbeg, int64_t kend, char* smem) {
-  if constexpr (LK)
+template <int KS, class G>
+__device__ __forceinline__ void run_ks(G& g, const typename G::Ops& ops, int64_t m0, int64_t n0,
+                                       int64_t kbeg, int64_t kend, char* smem, int64_t K = 0) {
+  if constexpr (KS == kSumShort)
+    g.run_short(ops, m0, n0, K, smem);
+  else if constexpr (KS == kSumFolded)
     g.template run_long<G::kFoldQ>(ops, m0, n0, kbeg, kend, smem, nullptr);
   else
     g.run(ops, m0, n0, kbeg, kend, smem);
 }
 
-template <class G, bool SIGT, bool PK, bool NR, bool LK>
+template <class G, bool SIGT, bool PK, bool NR, int KS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_coreg_update(
-    typename G::Ops ops, int64_t Kp, float* __restrict__ C, int64_t ldc, int64_t Na,
+    typename G::Ops ops, int64_t Ne, int64_t Kp, float* __restrict__ C, int64_t ldc, int64_t Na,
     const double* __restrict__ ncol, double alpha, double2* __restrict__ cstat,
     double* __restrict__ csq, int64_t ldstat, const uint32_t* __restrict__ order,
     const int32_t* gate, NextR<G> nr) {
   if (gate && *gate == 0) return;
-  __shared__ __align__(16) char smem[coreg_kernel_bytes<G, SIGT, LK>()];
+  __shared__ __align__(16) char smem[coreg_kernel_bytes<G, SIGT, KS>()];
   const uint32_t ij = order[xcd_tile(blockIdx.x, gridDim.x)];
   if constexpr (NR) {
     if (ij & kNextRTile) {
       const int64_t m0 = (int64_t)(ij & 0xffff) * kCB, n0 = (int64_t)((ij >> 16) & 0x7fff) * kCB;
       G g;
-      run_lk<LK>(g, nr.ops, m0, n0, 0, Kp, smem);
+      run_ks<KS>(g, nr.ops, m0, n0, 0, Kp, smem, nr.epi.M);
       store_t_tile_xd<kNextRRun>(g, smem, nr.epi, m0, n0);
       return;
     }
@@ -73,21 +76,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int64_t m0 = I * kCB, n0 = J * kCB;
   const double nval = coreg_norm_load(ncol, I, J, Na);
   G g;
-  run_lk<LK>(g, ops, m0, n0, 0, Kp, smem);
+  run_ks<KS>(g, ops, m0, n0, 0, Kp, smem, Ne);
   coreg_epilogue<SIGT, PK>(g, smem, I, J, C, ldc, Na, nval, alpha, cstat, csq, ldstat);
 }
 
 // R alone on the same tiles (same arithmetic, so R is the same bit for bit
 // whichever launch computed it): block b is tile (b % nRT, b / nRT).
-template <class G, bool LK>
+template <class G, int KS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_resp_tiles(
     NextR<G> nr, int64_t Kp, int64_t nRT, const int32_t* gate) {
   if (gate && *gate == 0) return;
-  __shared__ __align__(16) char smem[G::MAIN_BYTES + (LK ? G::BM * G::BN * 4 : 0)];
+  __shared__ __align__(16) char smem[G::MAIN_BYTES + (KS == kSumFolded ? G::BM * G::BN * 4 : 0)];
   const int64_t b = xcd_tile(blockIdx.x, gridDim.x);
   const int64_t m0 = (b % nRT) * kCB, n0 = (b / nRT) * kCB;
   G g;
-  run_lk<LK>(g, nr.ops, m0, n0, 0, Kp, smem);
+  run_ks<KS>(g, nr.ops, m0, n0, 0, Kp, smem, nr.epi.M);
   store_t_tile_xd<kNextRRun>(g, smem, nr.epi, m0, n0);
 }
 
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(kThreads) void k_coop_partial(typename G::Ops ops, 
   if (kb > Nap) kb = Nap;
   if (ke > Nap) ke = Nap;
   G g;
-  run_lk<LK>(g, ops, m0, n0, kb, ke, smem);
+  run_ks<LK ? kSumFolded : kSumOnce>(g, ops, m0, n0, kb, ke, smem);
   float* ps = part + s * Nep * Nep;
   g.for_each([&](int r, int c, float v) { ps[(m0 + r) * Nep + n0 + c] = v; });
 }
@@ -158,11 +161,12 @@ static hipError_t rect_f32(const OpsF32& ops, int64_t Mp, int64_t Np, int64_t Kp
     using G = decltype(g);
     return launch_rect<G>(ops, round_up(Mp, G::BM), Np, Kp, epi, part, gate, s);
   };
-  return Kp > kFoldK ? run(RectF32<true>{}) : run(RectF32<false>{});
+  if (ops.K <= kShortK) return run(RectF32<kSumShort>{});
+  return Kp > kFoldK ? run(RectF32<kSumFolded>{}) : run(RectF32<kSumOnce>{});
 }
 
 hipError_t launch_tanimoto_store(const float* X, int64_t ldx, const float* Y, int64_t ldy,
-                                 int64_t Mp, int64_t Np, int64_t Kp, int64_t M, int64_t N,
+                                 int64_t Mp, int64_t Np, int64_t Kp, int64_t M, int64_t N, int64_t K,
                                  const double* nx, const double* ny, float* Out, int64_t ldo,
                                  float* part, const int32_t* gate, hipStream_t s,
                                  const double* yd) {
@@ -172,21 +176,22 @@ hipError_t launch_tanimoto_store(const float* X, int64_t ldx, const float* Y, in
     epi.xv = X;
     epi.ldxv = ldx;
   }
-  return rect_f32(OpsF32{X, ldx, Y, ldy, M}, Mp, Np, Kp, epi, part, gate, s);
+  return rect_f32(OpsF32{X, ldx, Y, ldy, M, K}, Mp, Np, Kp, epi, part, gate, s);
 }
 
-hipError_t launch_corr(const float* Zt, int64_t Gp, int64_t Sp, int64_t G, float* C, int64_t ldc,
-                       hipStream_t s) {
+hipError_t launch_corr(const float* Zt, int64_t Gp, int64_t Sp, int64_t S, int64_t G, float* C,
+                       int64_t ldc, hipStream_t s) {
   // X = Z stored sample-major (Z^T), as W^T is read from W in the C update.
   const int64_t nT = Gp / kCB;
   auto run = [&](auto g) {
     using Gm = decltype(g);
     if (Gp % kCB || Sp % Gm::BK || G > Gp) return hipErrorInvalidValue;
     k_corr_sym<Gm><<<dim3((unsigned)(nT * (nT + 1) / 2)), dim3(Gm::NT), 0, s>>>(
-        OpsF32{Zt, Gp, Zt, Gp}, Sp, C, ldc, G);
+        OpsF32{Zt, Gp, Zt, Gp, Gp, S}, Sp, C, ldc, G);
     return hipGetLastError();
   };
-  return Sp > kFoldK ? run(SymF32<true>{}) : run(SymF32<false>{});
+  if (S <= kShortK) return run(SymF32<kSumShort>{});
+  return Sp > kFoldK ? run(SymF32<kSumFolded>{}) : run(SymF32<kSumOnce>{});
 }
 
 hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const float* W, int64_t ldw,
@@ -194,7 +199,7 @@ hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const floa
                        const double* nWc, float* R, float* part, const int32_t* gate,
                        hipStream_t s) {
   EpiStoreT epi{R, ldw, Ne, Na, nP, nWc, dP, W, ldw};
-  return rect_f32(OpsF32{P, ldp, W, ldw, Ne}, Nep, Nap, Nep, epi, part, gate, s);
+  return rect_f32(OpsF32{P, ldp, W, ldw, Ne, Ne}, Nep, Nap, Nep, epi, part, gate, s);
 }
 
 template <int NP, class Epi>
@@ -228,54 +233,53 @@ int64_t coreg_slots(int64_t Nap) { return Nap / kCB; }
 int64_t coreg_tiles(int64_t Nap) { return (Nap / kCB) * (Nap / kCB + 1) / 2; }
 
 template <class G, bool PK, bool NR>
-static hipError_t coreg_launch_pk(const typename G::Ops& ops, int64_t Nep, float* C, int64_t ldc,
+static hipError_t coreg_launch_pk(const typename G::Ops& ops, int64_t Ne, int64_t Nep, float* C, int64_t ldc,
                                   int64_t Nap, int64_t Na, const double* nWcol, Rule rule,
                                   double2* cstat, double* csq, const uint32_t* order,
                                   const int32_t* gate, hipStream_t s, const NextR<G>& nr,
                                   int64_t extra) {
   const dim3 nb((unsigned)(coreg_tiles(Nap) + extra));
   auto go = [&](auto* fn) {
-    fn<<<nb, dim3(kThreads), 0, s>>>(ops, Nep, C, ldc, Na, nWcol, rule.alpha, cstat, csq, Nap, order,
-                                     gate, nr);
+    fn<<<nb, dim3(kThreads), 0, s>>>(ops, Ne, Nep, C, ldc, Na, nWcol, rule.alpha, cstat, csq, Nap,
+                                     order, gate, nr);
+  };
+  auto with = [&](auto ks) {
+    constexpr int KS = decltype(ks)::value;
+    if (rule.sigma_from_T)
+      go(k_coreg_update<G, true, PK, NR, KS>);
+    else
+      go(k_coreg_update<G, false, PK, NR, KS>);
+    return hipGetLastError();
   };
   if constexpr (folds_k<G>::value) {
-    if (Nep > kFoldK) {
-      if (rule.sigma_from_T)
-        go(k_coreg_update<G, true, PK, NR, true>);
-      else
-        go(k_coreg_update<G, false, PK, NR, true>);
-      return hipGetLastError();
-    }
+    if (Ne <= kShortK) return with(std::integral_constant<int, kSumShort>{});
+    if (Nep > kFoldK) return with(std::integral_constant<int, kSumFolded>{});
   }
-  if (rule.sigma_from_T)
-    go(k_coreg_update<G, true, PK, NR, false>);
-  else
-    go(k_coreg_update<G, false, PK, NR, false>);
-  return hipGetLastError();
+  return with(std::integral_constant<int, kSumOnce>{});
 }
 
 template <class G, bool NR = false>
-static hipError_t coreg_launch(const typename G::Ops& ops, int64_t Nep, float* C, int64_t ldc,
+static hipError_t coreg_launch(const typename G::Ops& ops, int64_t Ne, int64_t Nep, float* C, int64_t ldc,
                                int64_t Nap, int64_t Na, const double* nWcol, Rule rule,
                                double2* cstat, double* csq, const uint32_t* order,
                                const int32_t* gate, hipStream_t s, bool packed,
                                const NextR<G>& nr = NextR<G>{}, int64_t extra = 0) {
-  return packed ? coreg_launch_pk<G, true, NR>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat,
+  return packed ? coreg_launch_pk<G, true, NR>(ops, Ne, Nep, C, ldc, Nap, Na, nWcol, rule, cstat,
                                                csq, order, gate, s, nr, extra)
-                : coreg_launch_pk<G, false, NR>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat,
+                : coreg_launch_pk<G, false, NR>(ops, Ne, Nep, C, ldc, Nap, Na, nWcol, rule, cstat,
                                                 csq, order, gate, s, nr, extra);
 }
 
-hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Nep, float* C,
+hipError_t launch_coreg_update(const Planes& Wt, int np, int64_t Ne, int64_t Nep, float* C,
                                int64_t ldc, int64_t Nap, int64_t Na, const double* nWcol,
                                Rule rule, double2* cstat, double* csq, const uint32_t* order,
                                const int32_t* gate, hipStream_t s, bool packed) {
   // X = Yt = W^T stored gene-major: row m of W^T is column m of W.  Only the
   // FP32 C is written; the next A product splits it while staging.
   const OpsB3 ops{Wt, Wt};
-  return np == 2 ? coreg_launch<Tiles<2>::Sym>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq,
+  return np == 2 ? coreg_launch<Tiles<2>::Sym>(ops, Ne, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq,
                                                order, gate, s, packed)
-                 : coreg_launch<Tiles<3>::Sym>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq,
+                 : coreg_launch<Tiles<3>::Sym>(ops, Ne, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq,
                                                order, gate, s, packed);
 }
 
@@ -292,10 +296,10 @@ static NextR<G> next_r_args(const Planes& Pp, const double* dP, const double* nP
   return nr;
 }
 
-template <class G, bool LK>
+template <class G, int KS>
 static hipError_t resp_tiles_launch(const NextR<G>& nr, int64_t ldp, int64_t Nap,
                                     const int32_t* gate, hipStream_t s) {
-  k_resp_tiles<G, LK><<<dim3((unsigned)next_r_tiles(ldp, Nap)), dim3(kThreads), 0, s>>>(
+  k_resp_tiles<G, KS><<<dim3((unsigned)next_r_tiles(ldp, Nap)), dim3(kThreads), 0, s>>>(
       nr, ldp, next_r_row_tiles(ldp), gate);
   return hipGetLastError();
 }
@@ -308,11 +312,12 @@ hipError_t launch_resp_tiles(const Planes& Pp, const Planes& Wt, int np, int64_t
   using G2 = Tiles<2>::Sym;
   using G3 = Tiles<3>::Sym;
   if (np == 2)
-    return resp_tiles_launch<G2, false>(next_r_args<G2>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWc, R),
+    return resp_tiles_launch<G2, kSumOnce>(next_r_args<G2>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWc, R),
                                         ldp, Nap, gate, s);
   const NextR<G3> nr = next_r_args<G3>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWc, R);
-  return ldp > kFoldK ? resp_tiles_launch<G3, true>(nr, ldp, Nap, gate, s)
-                      : resp_tiles_launch<G3, false>(nr, ldp, Nap, gate, s);
+  if (Ne <= kShortK) return resp_tiles_launch<G3, kSumShort>(nr, ldp, Nap, gate, s);
+  return ldp > kFoldK ? resp_tiles_launch<G3, kSumFolded>(nr, ldp, Nap, gate, s)
+                      : resp_tiles_launch<G3, kSumOnce>(nr, ldp, Nap, gate, s);
 }
 
 hipError_t launch_coreg_update_next_r(const Planes& Wt, int np, int64_t Nep,
@@ -328,10 +333,10 @@ hipError_t launch_coreg_update_next_r(const Planes& Wt, int np, int64_t Nep,
   const OpsB3 ops{Wt, Wt};
   const int64_t extra = next_r_tiles(Nep, Nap);
   if (np == 2)
-    return coreg_launch<G2, true>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq, order_r, gate,
+    return coreg_launch<G2, true>(ops, Ne, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq, order_r, gate,
                                   s, packed,
                                   next_r_args<G2>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWcol, R), extra);
-  return coreg_launch<G3, true>(ops, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq, order_r, gate, s,
+  return coreg_launch<G3, true>(ops, Ne, Nep, C, ldc, Nap, Na, nWcol, rule, cstat, csq, order_r, gate, s,
                                 packed, next_r_args<G3>(Pp, dP, nP, Wt, W, ldw, Ne, Na, nWcol, R),
                                 extra);
 }

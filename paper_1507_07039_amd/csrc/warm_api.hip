@@ -78,7 +78,7 @@ panda_status panda_ws_features(panda_ctx* c, const float* omegaP, const float* o
   // one-step similarities R0 = T(P0, W0) (into R) and A0 = T(W0, C0) (into S)
   HIP_TRY(launch_resp(c->P, Nep, dP, W0, Nap, Nep, Nap, Ne, Na, c->nP, c->nWc, L.R, L.part,
                       nullptr, s));
-  HIP_TRY(launch_tanimoto_store(W0, Nap, c->C, Nap, Nep, Nap, Nap, Ne, Na, c->nWr, c->nC, L.S,
+  HIP_TRY(launch_tanimoto_store(W0, Nap, c->C, Nap, Nep, Nap, Nap, Ne, Na, Na, c->nWr, c->nC, L.S,
                                 Nap, L.part, nullptr, s, c->dC));
   HIP_TRY(launch_half_sum(L.R, L.S, Ne, Na, Nap, s));
   // statistics of W0, S and S - W0 (tau)
@@ -219,7 +219,7 @@ panda_status panda_ws_init(panda_ctx* c, const float* Wpred, int32_t t0) {
     HIP_TRY(launch_coop_partial(c->Wr, c->np, Nep, Nap, c->splits, c->ppart, run_pc, s));
     HIP_TRY(launch_coop_finalize(c->ppart, c->splits, c->Nep, c->nWr, c->P, Nep, Ne, r1,
                                  c->rule.sigma_from_T ? c->Tside : nullptr, c->Pp, c->np, run_pc, s));
-    HIP_TRY(launch_coreg_update(c->Wt, c->np, Nep, c->C, Nap, Nap, Na, c->nWc, r1, c->cstat, c->csq,
+    HIP_TRY(launch_coreg_update(c->Wt, c->np, Ne, Nep, c->C, Nap, Nap, Na, c->nWc, r1, c->cstat, c->csq,
                                 c->corder, run_pc, s, c->packed));
   }
   // diagonals: t0 steps of Eq. 6 in closed form with sigma of the rebuilt rows

@@ -301,3 +301,111 @@ def test_autotune_keeps_the_faster_kernels(torch, pd, n, Ne, Na, small):
     for t in (1, 2):
         want = step64(torch, *want[:3], t, {})
     assert (tuned.state(0)[0].double() - want[0]).abs().max() <= 1e-4
+
+
+# ------------------------------------------------------------- sums of few terms --
+# With the products of a few terms rounded once to FP32, |dT| <= 1.5 u |T| from
+# the product (T moves by at most 1.5 d / sqrt(den) with it, and |dot| <= den)
+# and u |T| from storing T.
+@pytest.mark.parametrize("K", [1, 2, 3, 5, 7, 8])
+@pytest.mark.parametrize("M,N", [(1, 1), (129, 130), (500, 900)])
+def test_tanimoto_few_terms(torch, pd, M, K, N):
+    g = torch.Generator(device="cuda").manual_seed(K * M)
+    X, Y = (torch.randn(s, generator=g, device="cuda") for s in ((M, K), (K, N)))
+    want = t64(torch, X.double(), Y.double())
+    err = (pd.tanimoto(X, Y).double() - want).abs()
+    assert (err <= 2.51 * U * want.abs() + 1e-30).all()
+
+
+@pytest.mark.parametrize("S", [2, 3, 5, 8])
+def test_pearson_few_samples(torch, pd, S):
+    """Two factors and the result each rounded once: 3 u of |c| <= 1."""
+    E = np.random.default_rng(S).normal(size=(300, S)).astype(np.float32)
+    got = host(pd.pearson(torch.from_numpy(E).cuda()))
+    assert np.abs(got - np.corrcoef(E.astype(np.float64))).max() <= 3.01 * U
+    assert np.array_equal(got, got.T)
+
+
+def few_bounds(torch, before, after, what, steps=1):
+    """With alpha = 1 and products rounded `steps` times (once where they are
+    summed in FP64, at each term of an FP32 accumulation): C is T of the new W (the product 1.5 u, its FP32
+    denominator, root and quotient 2.5 u); P is it with an FP64 quotient; W is
+    (A + R) / 2, R stored.  The diagonal of P or C enters A's and R's sums in
+    FP64 after the rounded rest, so there the product's error is 1.5 u of that
+    rest over sqrt(den)."""
+    W, P, C = (M.double() for M in before)
+    W1, P1, C1 = (M.double() for M in after)
+    if "C" in what:
+        T = t64(torch, W1.T.contiguous(), W1)
+        err = (C1 - T).abs()
+        err.fill_diagonal_(0.0)
+        assert (err <= 4.05 * U * T.abs() + 1e-30).all()
+
+    def rounding(X, Y, diagonal=None):
+        """Of a sum of whole products; `diagonal`: their part added in FP64."""
+        dot, mag = X @ Y, X.abs() @ Y.abs()
+        den = (X * X).sum(1)[:, None] + (Y * Y).sum(0)[None, :] - dot.abs()
+        if diagonal is not None:
+            dot, mag = dot - diagonal, mag - diagonal.abs()
+        return 1.5 * U * (dot.abs() if steps == 1 else steps * mag) / den.clamp_min(1e-300).sqrt()
+    if "P" in what:
+        T = t64(torch, W1, W1.T.contiguous())
+        err = (P1 - T).abs()
+        err.fill_diagonal_(0.0)
+        assert (err <= 1.01 * (rounding(W1, W1.T.contiguous()) + U * T.abs()) + 1e-30).all()
+    A, R = t64(torch, W, C), t64(torch, P, W)
+    eA = rounding(W, C, W * C.diagonal()[None, :])
+    eR = rounding(P, W, P.diagonal()[:, None] * W) + U * R.abs()
+    want = 0.5 * (A + R)
+    assert ((W1 - want).abs() <= 1.01 * (0.5 * (eA + eR) + U * want.abs()) + 1e-30).all()
+
+
+def diagonal(torch, M):
+    return torch.diag(M.diagonal().clone()).contiguous()
+
+
+@pytest.mark.parametrize("Ne", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("packed", [0, 1])
+def test_few_factors(torch, pd, Ne, packed):
+    """N_e terms in R and the C update of a tiled network."""
+    Na = 2100
+    assert tiled(pd, Ne, Na)
+    W, P, C = gpu_net(torch, Ne, Ne, Na)
+    before = (W, P, diagonal(torch, C))
+    c = pd.Context(Ne, Na, pd.default_options(tol=0.0, alpha=1.0, packed_c=packed))
+    c.load(*before)
+    c.iterate()
+    few_bounds(torch, before, c.state()[:3], "C")
+
+
+@pytest.mark.parametrize("Na", [1, 3, 8])
+def test_few_genes(torch, pd, Na):
+    """N_a terms in A and the P update, of as many TFs as take the tiled kernels
+    with more genes: whole FP32 products in the small kernels, accumulated in FP32."""
+    Ne = 2100
+    W, P, C = gpu_net(torch, Na, Ne, Na)
+    before = (W, diagonal(torch, P), C)
+    c = pd.Context(Ne, Na, pd.default_options(tol=0.0, alpha=1.0))
+    c.load(*before)
+    c.iterate()
+    few_bounds(torch, before, c.state()[:3], "P", steps=Na)
+
+
+@pytest.mark.parametrize("tiles", [0, 1, 2])
+@pytest.mark.parametrize("sigma_from_T", [0, 1])
+def test_few_terms_in_a_grouped_batch(torch, pd, tiles, sigma_from_T):
+    """The same in the grouped kernels, beside a network of long sums."""
+    shapes = [(1, 2100), (3, 2100), (8, 2300), (2100, 1), (2100, 8), (1100, 2100)]
+    nets = []
+    for i, s in enumerate(shapes):
+        W, P, C = gpu_net(torch, 20 + i, *s)
+        nets.append((W, diagonal(torch, P), C) if s[1] <= 8 else (W, P, diagonal(torch, C)))
+    b = pd.Batch(shapes, pd.default_options(tol=0.0, alpha=1.0, sigma_from_T=sigma_from_T))
+    b.tiles = [tiles] * 4
+    for i, net in enumerate(nets):
+        b.load(i, *net)
+    b.iterate(1)
+    for i, s in enumerate(shapes[:-1]):
+        few_bounds(torch, nets[i], b.state(i)[:3], "P" if s[1] <= 8 else "C")
+    W, P, C = (M.double() for M in nets[-1])
+    assert (b.state(5)[0].double() - 0.5 * (t64(torch, P, W) + t64(torch, W, C))).abs().max() <= 1e-4
