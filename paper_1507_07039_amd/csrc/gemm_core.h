@@ -144,7 +144,7 @@ __device__ __forceinline__ void short_product(G& g, int kn, char* smem, Fill&& f
 //   Two planes (x = hi + lo): hi*hi + hi*lo + lo*hi; the dropped lo*lo term
 //   and the rounding of lo bound the relative error of each product term by
 //   about 2^-16.
-//   Three planes (x = hi + mid + lo exactly, 8 bits each, see split_pair3):
+//   Three planes (x = hi + mid + lo, 8 bits each, see split_pair3):
 //   the six products down to 2^-16 of the leading one; the dropped ones add up
 //   to 2^-22 of a term at most (of either sign), which sums of more than
 //   kShortK terms average out below what an FP32 accumulation rounds away.
@@ -393,10 +393,10 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsign
   l = __builtin_bit_cast(unsigned, __builtin_convertvector((fl2){a - ha, b - hb}, bh2));
 }
 
-// Two floats as three bf16 each, x = hi + mid + lo exactly: hi = the upper 16
-// bits of x (truncated, so that no finite x overflows), mid = RNE(x - hi), lo
-// = x - hi - mid, which has at most 8 significant bits (both differences are
-// exact).
+// Two floats as three bf16 each, x = hi + mid + lo: hi = the upper 16 bits of x
+// (truncated, so that no finite x overflows), mid = RNE(x - hi), lo = x - hi -
+// mid, which has at most 8 significant bits (both differences are exact; below
+// 2^-110 some of those bits lie under the smallest bf16 and are lost).
 __device__ __forceinline__ void split_pair3(float a, float b, unsigned (&o)[3]) {
   typedef float fl2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bh2 __attribute__((ext_vector_type(2)));

@@ -87,8 +87,8 @@ struct panda_ctx {
   panda::Rule rule;
   hipStream_t stream;
   // W, the W being written, and R.  In the FP32 form of a single network the
-  // three are one buffer: the planes hold W exactly, A reads R there and leaves
-  // the new W in its place, and the next R replaces that (see w_in_place)
+  // three are one buffer: the planes hold W (join_planes), A reads R there and
+  // leaves the new W in its place, and the next R replaces that (see w_in_place)
   float* W[2];
   float* R;
   float* P;

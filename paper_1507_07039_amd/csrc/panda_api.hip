@@ -95,12 +95,15 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   float* cc = cv.take<float>(spec.packed_c ? (size_t)packed_floats(Nap) : (size_t)Nap * Nap);
   float* ts = cv.take<float>((size_t)Nep * Nep);
   const int splits = (int)spec.ppart_splits;
-  // Two pairs of the FP32 form share memory: the W W^T partials (from the
-  // partial products to the P finalisation) and the A product's folding
-  // scratch; the A product's split tiles and the planes of W^T, which are
+  // Of the FP32 form's buffers two share memory with others: the W W^T partials
+  // (from the partial products to the P finalisation), then the C update's sums
+  // of squares (to its diagonal; or a load's), then the A product's folding
+  // scratch; the A product's split tiles, then the planes of W^T, which are
   // written after it and last read by the C update before the next one.
+  const int64_t nslots = sm ? std::max(coreg_slots(Nap), small_tiles(Na)) : coreg_slots(Nap);
   const size_t npp = (size_t)splits * Nep * Nep, nfold = rect_fold_floats(Nap, np);
-  float* pp = cv.take<float>(std::max(npp, nfold));
+  const size_t ncsq = (size_t)nslots * Nap;
+  float* pp = cv.take<float>(in_place ? std::max({npp, nfold, 2 * ncsq}) : npp);
   const size_t nsk = spec.batched ? 0 : rect_partial_floats();
   float* sk = cv.take<float>(in_place ? std::max(nsk, (3 * nw + 1) / 2) : nsk);
   if (spec.batched) sk = nullptr;
@@ -113,9 +116,8 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   double* scr = cv.take<double>(w_norm_scratch_doubles(Nep, Nap));
   const int64_t nh = sm ? std::max(spec.hpart_tiles, small_h_slots(Ne, Na)) : spec.hpart_tiles;
   double* hp = cv.take<double>((size_t)nh);
-  const int64_t nslots = sm ? std::max(coreg_slots(Nap), small_tiles(Na)) : coreg_slots(Nap);
-  double2* cs = cv.take<double2>((size_t)nslots * Nap);
-  double* cq = cv.take<double>((size_t)nslots * Nap);
+  double2* cs = cv.take<double2>(ncsq);
+  double* cq = in_place ? reinterpret_cast<double*>(pp) : cv.take<double>(ncsq);
   uint32_t* co = cv.take<uint32_t>((size_t)coreg_tiles(Nap));
   DevState* st = cv.take<DevState>(2);  // the second: the small kernels' next state
   uint32_t* cor = !spec.batched
@@ -123,7 +125,7 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
                       : nullptr;
   Planes wr{nullptr, (int64_t)nw, Nep}, wt{nullptr, (int64_t)nw, Nap}, pl{nullptr, Nep * Nep, Nep};
   if (np) {
-    wr.p = cv.take<bf16_t>(np * nw);  // W
+    wr.p = cv.take<bf16_t>((in_place ? kHeldPlanes : np) * nw);  // W
     wt.p = in_place ? reinterpret_cast<bf16_t*>(sk) : cv.take<bf16_t>(np * nw);  // W^T
     pl.p = cv.take<bf16_t>(np * (size_t)Nep * Nep);  // P, zero diagonal
   }

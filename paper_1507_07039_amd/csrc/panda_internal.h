@@ -35,7 +35,8 @@ typedef unsigned short bf16_t;           // raw bits of a bfloat16
 
 // An FP32 matrix (rows x K, products contract over K) given as bf16 planes,
 // plane q at p + q * stride, leading term first: two planes x = hi + lo to
-// 2^-17, three planes x = hi + mid + lo exactly.  A plane is stored K-tile by
+// 2^-17, three planes x = hi + mid + lo, exactly from 2^-110 up (and at 0); below
+// it to 2^-134, what is left there being finer than the smallest bf16.  A plane is stored K-tile by
 // K-tile, [K / KT][rows][KT] with KT = plane_kt(planes), the K-tile depth of
 // the products: the direct-to-LDS loads of a tile then read whole cache lines
 // (row-major, a K-tile of 16 took 32 bytes of each row, 32 lines per load
@@ -50,11 +51,13 @@ template <int KT>
 __host__ __device__ constexpr int64_t plane_index(int64_t rows, int64_t r, int64_t k) {
   return (k / KT * rows + r) * KT + k % KT;
 }
-// Entry (r, k) of a matrix given as three planes, exactly (both sums are).
+// Where three planes are all that holds a matrix (W of a single network in the
+// FP32 form), a fourth keeps the lower 16 bits of each entry, whose upper 16 are
+// hi: entry (r, k), bit for bit.
+constexpr int kHeldPlanes = 4;
 __device__ __forceinline__ float join_planes(const Planes& P, int64_t r, int64_t k) {
   const bf16_t* p = P.p + plane_index<plane_kt(3)>(P.rows, r, k);
-  auto f = [](bf16_t b) { return __builtin_bit_cast(float, (unsigned)b << 16); };
-  return f(p[0]) + (f(p[P.stride]) + f(p[2 * P.stride]));
+  return __builtin_bit_cast(float, ((unsigned)p[0] << 16) | p[3 * P.stride]);
 }
 
 constexpr int kThreads = 256;            // threads per block (4 waves of 64)
@@ -188,7 +191,7 @@ hipError_t launch_coreg_update_next_r(const Planes& Wt, int np, int64_t Nep,
                                       bool packed, const Planes& Pp, const double* dP,
                                       const double* nP, const float* W, int64_t ldw, int64_t Ne,
                                       float* R);
-// out[r][k] of the matrix that three planes hold (rows x cols, leading dimension ldo).
+// out[r][k] of the matrix that planes hold (join_planes; rows x cols, leading dimension ldo).
 hipError_t launch_join_planes(const Planes& P, int64_t rows, int64_t cols, float* out, int64_t ldo,
                               hipStream_t s);
 // The np planes of an n x n matrix with its diagonal left zero.
@@ -239,7 +242,8 @@ hipError_t launch_state_set(DevState* st, int32_t t, int32_t active, int32_t run
                             hipStream_t s);
 // Squared norms of the rows / columns of a rows x cols matrix with leading
 // Row and column squared norms of W (padded Nep x ldw, real Ne x Na) in one
-// pass over it, plus its np bf16 planes (of W, Wr, and of W^T, Wt).  scr holds
+// pass over it, plus its np bf16 planes (of W, Wr, with the lower bits where np
+// is 3; of W^T, Wt).  scr holds
 // w_norm_scratch_doubles().
 size_t w_norm_scratch_doubles(int64_t Nep, int64_t Nap);
 hipError_t launch_w_norms(const float* W, int64_t Ne, int64_t Na, int64_t ldw, int64_t Nep,

@@ -28,9 +28,9 @@ __device__ __forceinline__ bf16_t to_bf16(float x) {
   return __builtin_bit_cast(bf16_t, (__bf16)x);
 }
 // The bf16 planes of x.  Two: hi = RNE(x), lo = RNE(x - hi).  Three: x = hi +
-// mid + lo exactly (hi truncated, so that no finite x overflows; mid rounded;
-// lo holds the 8 bits that are left); an infinity or NaN is its hi alone, so
-// that x is their sum for every x (join_planes).
+// mid + lo (hi truncated to the upper 16 bits, so that no finite x overflows;
+// mid rounded; lo holds the 8 bits that are left, as far as a bf16 goes); an
+// infinity or NaN is its hi alone.
 template <int NP>
 __device__ __forceinline__ void split_planes(float x, bf16_t (&o)[3]) {
   if constexpr (NP == 2) {

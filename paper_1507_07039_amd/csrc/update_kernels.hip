@@ -241,14 +241,17 @@ __global__ __launch_bounds__(kRT) void k_w_norms(const float* __restrict__ W, in
     for (int pass = 0; pass < 2; ++pass) {
       const int id = (int)threadIdx.x + kRT * pass;
       const int line = (id / CT) % 64, q = id % CT + CT * (id / (64 * CT));
-      unsigned r[3][4], t[3][4];
+      constexpr int NR = NP == 3 ? kHeldPlanes : NP;  // with the lower bits (join_planes)
+      unsigned r[4][4], t[3][4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         bf16_t a[3], b[3];
-        split_planes<NP>(tile[line][8 * q + 2 * e], a);  // row line, along the columns
-        split_planes<NP>(tile[line][8 * q + 2 * e + 1], b);
+        const float x = tile[line][8 * q + 2 * e], y = tile[line][8 * q + 2 * e + 1];
+        split_planes<NP>(x, a);  // row line, along the columns
+        split_planes<NP>(y, b);
 #pragma unroll
         for (int p = 0; p < NP; ++p) r[p][e] = (unsigned)a[p] | ((unsigned)b[p] << 16);
+        r[3][e] = (__builtin_bit_cast(unsigned, x) & 0xffffu) | (__builtin_bit_cast(unsigned, y) << 16);
         split_planes<NP>(tile[8 * q + 2 * e][line], a);  // column line, along the rows
         split_planes<NP>(tile[8 * q + 2 * e + 1][line], b);
 #pragma unroll
@@ -257,12 +260,13 @@ __global__ __launch_bounds__(kRT) void k_w_norms(const float* __restrict__ W, in
       const int64_t ro = plane_index<KT>(Wr.rows, r0 + line, c0 + 8 * q);
       const int64_t to = plane_index<KT>(Wt.rows, c0 + line, r0 + 8 * q);
 #pragma unroll
-      for (int p = 0; p < NP; ++p) {
+      for (int p = 0; p < NR; ++p)
         *reinterpret_cast<uint4*>(Wr.p + p * Wr.stride + ro) =
             make_uint4(r[p][0], r[p][1], r[p][2], r[p][3]);
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
         *reinterpret_cast<uint4*>(Wt.p + p * Wt.stride + to) =
             make_uint4(t[p][0], t[p][1], t[p][2], t[p][3]);
-      }
     }
   }
 }

@@ -409,3 +409,23 @@ def test_few_terms_in_a_grouped_batch(torch, pd, tiles, sigma_from_T):
         few_bounds(torch, nets[i], b.state(i)[:3], "P" if s[1] <= 8 else "C")
     W, P, C = (M.double() for M in nets[-1])
     assert (b.state(5)[0].double() - 0.5 * (t64(torch, P, W) + t64(torch, W, C))).abs().max() <= 1e-4
+
+
+# ------------------------------------------------------------ W held as its planes --
+@pytest.mark.parametrize("packed", [0, 1])
+def test_w_keeps_every_bit(torch, pd, packed):
+    """With P = C = 0 both similarities are 0 and W is damped alone: what comes
+    back is 0.9 W rounded once, bit for bit, down to the subnormals."""
+    Ne, Na = 70, 2100
+    assert tiled(pd, Ne, Na)
+    rng = np.random.default_rng(9)
+    W = (rng.choice([-1.0, 1.0], (Ne, Na)) * rng.uniform(1.0, 2.0, (Ne, Na))
+         * np.exp2(-rng.integers(0, 149, (Ne, Na)))).astype(np.float32)
+    assert ((np.abs(W) < 2.0 ** -126) & (W != 0)).any()
+    c = pd.Context(Ne, Na, pd.default_options(tol=0.0, packed_c=packed))
+    c.load(torch.from_numpy(W).cuda(), torch.zeros(Ne, Ne, device="cuda"),
+           torch.zeros(Na, Na, device="cuda"))
+    c.iterate()
+    got = c.state()[0].cpu().numpy()
+    want = (0.9 * W.astype(np.float64)).astype(np.float32)
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
