@@ -16,11 +16,14 @@ constexpr int kOffB2 = kOffW2 + kMlpHidden * kMlpHidden;
 constexpr int kOffW3 = kOffB2 + kMlpHidden;
 constexpr int kOffB3 = kOffW3 + kMlpHidden;
 constexpr int kMlpParams = kOffB3 + 1;  // 5313
-// Blocks of the gradient kernel (4 slots each): one per CU, as many as run at
-// once (registers and LDS).  With 512 the second half of 65536 edges waited to
-// set up its weights again, and wrote as many partial gradients again: 44 +
-// 13 us (gradient and reduction) against 31 + 7.
-constexpr int64_t kMlpGradBlocks = 256;
+// Partial gradients are FP32 sums over the edges of a wave, 4 slots per group of
+// waves: a slot sums no more edges than 512 groups give it.  One block per CU runs
+// at a time (registers and LDS), so the grid is no larger than that, and a block
+// takes groups in turn, its weights set up once.  65536 edges: 39 + 13 us
+// (gradient and reduction), 44 + 13 with a block per group; with 256 groups 31 +
+// 7, but twice the edges in every FP32 sum.
+constexpr int64_t kMlpGradGroups = 512;
+constexpr int64_t kMlpGradGrid = 256;
 constexpr double kSketchPivotRel = 1e-10;
 
 // Per-wave partial gradients of a batch of n edges.

@@ -151,8 +151,9 @@ __global__ __launch_bounds__(kT) void k_mlp_forward(const float* __restrict__ p,
 }
 
 // Gradient of the mean squared error over a batch of n edges (rows idx[e] of
-// F and target, or e itself when idx is null).  Every wave writes its partial
-// gradient (and loss sum) to its own slot; k_mlp_reduce sums the slots in a
+// F and target, or e itself when idx is null).  The edges are dealt to `groups`
+// groups of four waves, 32 at a time; every wave writes its partial gradient
+// (and loss sum) for each group to that group's slots; k_mlp_reduce sums the slots in a
 // fixed order.  All waves of a block run the same number of chunk rounds
 // (masked past the end) because the LDS transposes need block barriers.
 struct GradShared {
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(kT) void k_mlp_grad(const float* __restrict__ p,
                                                  const float* __restrict__ F, int64_t nrows,
                                                  const float* __restrict__ target,
                                                  const int64_t* __restrict__ idx, int64_t n,
-                                                 float* __restrict__ part,
+                                                 int64_t groups, float* __restrict__ part,
                                                  double* __restrict__ lpart) {
   __shared__ GradShared sm;
   load_params(p, sm.w);
@@ -184,23 +185,6 @@ __global__ __launch_bounds__(kT) void k_mlp_grad(const float* __restrict__ p,
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int e = 0; e < 8; ++e) A3[mb][s][e] = sm.w.W2[kunit(s, h, e)][32 * mb + m];
-  floatx16 g2[2][3], g1[2];  // dW2 | db2 (third block: column 0), dW1 | db1 (column 16)
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) g1[a][r] = 0.0f;
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) g2[a][b][r] = 0.0f;
-  }
-  float gw3[2][16];
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) gw3[b][r] = 0.0f;
-  float gb3 = 0.0f;
-  double loss = 0.0;
   bf16x8 ones, zeros;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -209,109 +193,131 @@ __global__ __launch_bounds__(kT) void k_mlp_grad(const float* __restrict__ p,
   }
   const float inv = 2.0f / (float)n;
   const int64_t chunks = (n + 31) / 32;
-  const int64_t rounds = (chunks + (int64_t)gridDim.x * kWaves - 1) / ((int64_t)gridDim.x * kWaves);
-  for (int64_t rd = 0; rd < rounds; ++rd) {
-    const int64_t c = (rd * gridDim.x + blockIdx.x) * kWaves + wave;
-    const int64_t e = c * 32 + m;
-    int64_t row = e < n ? (idx ? idx[e] : e) : -1;
-    const bool valid = row >= 0 && row < nrows;
-    if (!valid) row = 0;
-    MlpFwd f;
-    f.run(sm.w, op, F, row, valid, lane);
-    const float err = valid ? f.y - target[row] : 0.0f;
-    const float dy = inv * err;
-    if (h == 0) {
-      loss += (double)err * (double)err;
-      gb3 += dy;
+  const int64_t rounds = (chunks + groups * kWaves - 1) / (groups * kWaves);
+#pragma unroll 1
+  for (int64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
+    floatx16 g2[2][3], g1[2];  // dW2 | db2 (third block: column 0), dW1 | db1 (column 16)
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) g1[a][r] = 0.0f;
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) g2[a][b][r] = 0.0f;
     }
-    // layer 2 backward (registers: lane's units of half h)
-    bf16x8 dzq[4];
+    float gw3[2][16];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int u = unit_of(b, r, h);
-        const float h2 = f.z2[b][r] > 0.0f ? f.z2[b][r] : 0.0f;
-        gw3[b][r] += dy * h2;
-        const float dz = f.z2[b][r] > 0.0f ? dy * sm.w.w3[u] : 0.0f;
-        dzq[2 * b + (r >> 3)][r & 7] = bq(dz);
-        sm.dz2[wave][u][m] = bq(dz);
+      for (int r = 0; r < 16; ++r) gw3[b][r] = 0.0f;
+    float gb3 = 0.0f;
+    double loss = 0.0;
+    for (int64_t rd = 0; rd < rounds; ++rd) {
+      const int64_t c = (rd * groups + grp) * kWaves + wave;
+      const int64_t e = c * 32 + m;
+      int64_t row = e < n ? (idx ? idx[e] : e) : -1;
+      const bool valid = row >= 0 && row < nrows;
+      if (!valid) row = 0;
+      MlpFwd f;
+      f.run(sm.w, op, F, row, valid, lane);
+      const float err = valid ? f.y - target[row] : 0.0f;
+      const float dy = inv * err;
+      if (h == 0) {
+        loss += (double)err * (double)err;
+        gb3 += dy;
       }
-    // dH1^T (64 x 32 edges) = W2^T dZ2^T, then dZ1 = dH1 * (z1 > 0)
-    floatx16 dh1[2];
+      // layer 2 backward (registers: lane's units of half h)
+      bf16x8 dzq[4];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) dh1[mb][r] = 0.0f;
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        dh1[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A3[mb][s], dzq[s], dh1[mb], 0, 0, 0);
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int u = unit_of(b, r, h);
-        sm.dz1[wave][u][m] = bq(f.z1[b][r] > 0.0f ? dh1[b][r] : 0.0f);
-        sm.h1[wave][u][m] = f.h1[2 * b + (r >> 3)][r & 7];
-      }
-#pragma unroll
-    for (int ee = 0; ee < 8; ++ee) sm.x[wave][8 * h + ee][m] = f.x[ee];
-    __syncthreads();
-    // weight gradients: contractions over the wave's 32 edges in two k-steps
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int e0 = 16 * s + 8 * h;
+        for (int r = 0; r < 16; ++r) {
+          const int u = unit_of(b, r, h);
+          const float h2 = f.z2[b][r] > 0.0f ? f.z2[b][r] : 0.0f;
+          gw3[b][r] += dy * h2;
+          const float dz = f.z2[b][r] > 0.0f ? dy * sm.w.w3[u] : 0.0f;
+          dzq[2 * b + (r >> 3)][r & 7] = bq(dz);
+          sm.dz2[wave][u][m] = bq(dz);
+        }
+      // dH1^T (64 x 32 edges) = W2^T dZ2^T, then dZ1 = dH1 * (z1 > 0)
+      floatx16 dh1[2];
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb) {
-        const bf16x8 a2 = *reinterpret_cast<const bf16x8*>(&sm.dz2[wave][32 * mb + m][e0]);
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-          const bf16x8 b2 = *reinterpret_cast<const bf16x8*>(&sm.h1[wave][32 * nb + m][e0]);
-          g2[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2, g2[mb][nb], 0, 0, 0);
-        }
-        g2[mb][2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, m == 0 ? ones : zeros, g2[mb][2],
-                                                            0, 0, 0);
-        const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(&sm.dz1[wave][32 * mb + m][e0]);
-        const bf16x8 b1 = m < NF ? *reinterpret_cast<const bf16x8*>(&sm.x[wave][m][e0])
-                                 : (m == NF ? ones : zeros);
-        g1[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, g1[mb], 0, 0, 0);
+        for (int r = 0; r < 16; ++r) dh1[mb][r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          dh1[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A3[mb][s], dzq[s], dh1[mb], 0, 0, 0);
       }
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int u = unit_of(b, r, h);
+          sm.dz1[wave][u][m] = bq(f.z1[b][r] > 0.0f ? dh1[b][r] : 0.0f);
+          sm.h1[wave][u][m] = f.h1[2 * b + (r >> 3)][r & 7];
+        }
+#pragma unroll
+      for (int ee = 0; ee < 8; ++ee) sm.x[wave][8 * h + ee][m] = f.x[ee];
+      __syncthreads();
+      // weight gradients: contractions over the wave's 32 edges in two k-steps
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int e0 = 16 * s + 8 * h;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+          const bf16x8 a2 = *reinterpret_cast<const bf16x8*>(&sm.dz2[wave][32 * mb + m][e0]);
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb) {
+            const bf16x8 b2 = *reinterpret_cast<const bf16x8*>(&sm.h1[wave][32 * nb + m][e0]);
+            g2[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2, g2[mb][nb], 0, 0, 0);
+          }
+          g2[mb][2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, m == 0 ? ones : zeros, g2[mb][2],
+                                                              0, 0, 0);
+          const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(&sm.dz1[wave][32 * mb + m][e0]);
+          const bf16x8 b1 = m < NF ? *reinterpret_cast<const bf16x8*>(&sm.x[wave][m][e0])
+                                   : (m == NF ? ones : zeros);
+          g1[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, g1[mb], 0, 0, 0);
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
-  }
-  // dw3: sum over the 32 lanes of each half (same units, different edges)
+    // dw3: sum over the 32 lanes of each half (same units, different edges)
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float v = gw3[b][r];
+      for (int r = 0; r < 16; ++r) {
+        float v = gw3[b][r];
 #pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-      gw3[b][r] = v;
+        for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+        gw3[b][r] = v;
+      }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      gb3 += __shfl_xor(gb3, off);
+      loss += __shfl_xor(loss, off);
     }
+    const int64_t slot = grp * kWaves + wave;
+    float* out = part + slot * kMlpParams;
+    int mo = m, ho = h;  // the stores' addresses are formed here, not kept across groups
+    asm volatile("" : "+v"(mo), "+v"(ho));
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    gb3 += __shfl_xor(gb3, off);
-    loss += __shfl_xor(loss, off);
-  }
-  const int64_t slot = (int64_t)blockIdx.x * kWaves + wave;
-  float* out = part + slot * kMlpParams;
+    for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+      for (int r = 0; r < 16; ++r) {
+        const int row = unit_of(mb, r, ho);  // layer-2 unit (dW2, db2) / layer-1 unit (dW1, db1)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = unit_of(mb, r, h);  // layer-2 unit (dW2, db2) / layer-1 unit (dW1, db1)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) out[kOffW2 + row * NH + 32 * nb + m] = g2[mb][nb][r];
-      if (m == 0) out[kOffB2 + row] = g2[mb][2][r];
-      if (m < NF) out[kOffW1 + row * NF + m] = g1[mb][r];
-      if (m == NF) out[kOffB1 + row] = g1[mb][r];
-      if (m == 0) out[kOffW3 + row] = gw3[mb][r];
+        for (int nb = 0; nb < 2; ++nb) out[kOffW2 + row * NH + 32 * nb + mo] = g2[mb][nb][r];
+        if (mo == 0) out[kOffB2 + row] = g2[mb][2][r];
+        if (mo < NF) out[kOffW1 + row * NF + mo] = g1[mb][r];
+        if (mo == NF) out[kOffB1 + row] = g1[mb][r];
+        if (mo == 0) out[kOffW3 + row] = gw3[mb][r];
+      }
+    if (lane == 0) {
+      out[kOffB3] = gb3;
+      lpart[slot] = loss;
     }
-  if (lane == 0) {
-    out[kOffB3] = gb3;
-    lpart[slot] = loss;
   }
 }
 
@@ -320,7 +326,7 @@ __global__ __launch_bounds__(kT) void k_mlp_grad(const float* __restrict__ p,
 // slots is one serial chain of up to 2048 of them.  Here 32 threads share a
 // parameter (slots g, g + 32, ... each, eight loads in flight) and their sums
 // are added in order from LDS; the block after the last takes the loss.
-// 65536 edges: 590 -> 13 us with 2048 slots (43 MB), 7 with 1024.
+// 65536 edges (2048 slots, 43 MB): 590 -> 13 us.
 constexpr int kRedT = 1024, kRedC = 32, kRedG = kRedT / kRedC;
 __global__ __launch_bounds__(kRedT) void k_mlp_reduce(const float* __restrict__ part, int64_t slots,
                                                       const double* __restrict__ lpart, int64_t n,
@@ -747,10 +753,10 @@ unsigned grid_cap(int64_t n, int64_t cap) {
 
 int64_t mlp_grad_slots(int64_t n) {
   const int64_t chunks = (n + 31) / 32;
-  int64_t blocks = (chunks + kWaves - 1) / kWaves;
-  if (blocks > kMlpGradBlocks) blocks = kMlpGradBlocks;
-  if (blocks < 1) blocks = 1;
-  return blocks * kWaves;
+  int64_t groups = (chunks + kWaves - 1) / kWaves;
+  if (groups > kMlpGradGroups) groups = kMlpGradGroups;
+  if (groups < 1) groups = 1;
+  return groups * kWaves;
 }
 
 hipError_t launch_mlp_forward(const float* p, const float* F, int64_t n, float* y, hipStream_t s) {
@@ -768,9 +774,9 @@ hipError_t launch_mlp_forward(const float* p, const float* F, int64_t n, float* 
 hipError_t launch_mlp_grad(const float* p, const float* F, int64_t nrows, const float* target,
                            const int64_t* idx, int64_t n, float* part, double* lpart, float* grad,
                            double* loss, hipStream_t s) {
-  const int64_t slots = mlp_grad_slots(n);
-  k_mlp_grad<<<dim3((unsigned)(slots / kWaves)), dim3(kT), 0, s>>>(p, F, nrows, target, idx, n,
-                                                                  part, lpart);
+  const int64_t slots = mlp_grad_slots(n), groups = slots / kWaves;
+  const unsigned grid = (unsigned)(groups < kMlpGradGrid ? groups : kMlpGradGrid);
+  k_mlp_grad<<<dim3(grid), dim3(kT), 0, s>>>(p, F, nrows, target, idx, n, groups, part, lpart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const unsigned nred = (unsigned)((kMlpParams + kRedC - 1) / kRedC) + 1;  // + the loss block

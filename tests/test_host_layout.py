@@ -65,3 +65,13 @@ def test_loads_clear_only_the_h_partials(layout):
 def test_batches_take_the_faster_kernels(layout, n, Ne, Na, small, fp32, split):
     for precision, grouped in ((0, fp32), (1, split)):
         assert layout("batch", n, Ne, Na, precision) == [[int(small < grouped)]], (precision, grouped)
+
+
+@pytest.mark.parametrize("n", [1, 4000, 65536, 65537, 300000])
+def test_partial_gradients_sum_few_edges(n):
+    """The warm start's partial gradients (FP32 sums over the edges of a wave,
+    added in FP64) number up to 2048, so that each sums no more edges than that
+    many share; the workspace has a slot of 5313 floats for each."""
+    chunks = -(-n // 32)
+    slots = min(-(-chunks // 4), 512) * 4
+    assert panda.load_library().panda_mlp_grad_workspace_bytes(n) >= slots * panda.MLP_PARAMS * 4
