@@ -124,7 +124,7 @@ hipError_t launch_tanimoto_store(const float* X, int64_t ldx, const float* Y, in
 // R = T(P, W) of the iteration (Eq. 3).
 hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const float* W, int64_t ldw,
                        int64_t Nep, int64_t Nap, int64_t Ne, int64_t Na, const double* nP,
-                       const double* nWc, float* R, float* part, const int32_t* gate,
+                       const double* nWc, float* R, int64_t ldr, float* part, const int32_t* gate,
                        hipStream_t s);
 
 // A = T(W, C) fused with the W update of Eq. 2 and per-tile h partials (Eq. 7).

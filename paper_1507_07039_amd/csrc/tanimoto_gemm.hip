@@ -196,9 +196,9 @@ hipError_t launch_corr(const float* Zt, int64_t Gp, int64_t Sp, int64_t S, int64
 
 hipError_t launch_resp(const float* P, int64_t ldp, const double* dP, const float* W, int64_t ldw,
                        int64_t Nep, int64_t Nap, int64_t Ne, int64_t Na, const double* nP,
-                       const double* nWc, float* R, float* part, const int32_t* gate,
+                       const double* nWc, float* R, int64_t ldr, float* part, const int32_t* gate,
                        hipStream_t s) {
-  EpiStoreT epi{R, ldw, Ne, Na, nP, nWc, dP, W, ldw};
+  EpiStoreT epi{R, ldr, Ne, Na, nP, nWc, dP, W, ldw};
   return rect_f32(OpsF32{P, ldp, W, ldw, Ne, Ne}, Nep, Nap, Nep, epi, part, gate, s);
 }
 

@@ -14,8 +14,9 @@ namespace {
 
 struct FeatLayout {
   float* S;  // Nep x Nap: A0, then S = (R0 + A0) / 2
-  float* R;  // Nep x Nap: R0, then S - W0
-  float* part;  // split tiles of the two products
+  // split tiles of the two products, where the context's own may hold W^T's
+  // planes (a tiled one in the FP32 form); null for a small network
+  float* part;
   double *dr, *dc, *omP, *omC, *tmpP, *yP, *a, *zP, *b, *tmpC, *yC, *d, *zC, *c;
   double *LinvP, *LinvC, *mom, *zsW, *zsS, *zsD;
   VecRefHost* vref;
@@ -29,8 +30,7 @@ size_t feat_layout(int64_t Ne, int64_t Na, char* base, FeatLayout* L) {
   Carver cv{base};
   FeatLayout l;
   l.S = cv.take<float>((size_t)Nep * Nap);
-  l.R = cv.take<float>((size_t)Nep * Nap);
-  l.part = cv.take<float>(rect_partial_floats());
+  l.part = small_net(Ne, Na) ? nullptr : cv.take<float>(rect_partial_floats());
   l.dr = cv.take<double>((size_t)Ne);
   l.dc = cv.take<double>((size_t)Na);
   double** sixNe[] = {&l.omP, &l.tmpP, &l.yP, &l.a, &l.zP, &l.c};
@@ -75,17 +75,20 @@ panda_status panda_ws_features(panda_ctx* c, const float* omegaP, const float* o
   double* const dP = diag_p_of(c, c->host->t);
   float* W0 = nullptr;
   PANDA_TRY(ctx_current_w(c, &W0));
-  // one-step similarities R0 = T(P0, W0) (into R) and A0 = T(W0, C0) (into S)
-  HIP_TRY(launch_resp(c->P, Nep, dP, W0, Nap, Nep, Nap, Ne, Na, c->nP, c->nWc, L.R, L.part,
-                      nullptr, s));
+  // one-step similarities R0 = T(P0, W0) and A0 = T(W0, C0) (into S); R0, then S -
+  // W0, lie dense in F until the features are written there
+  float* const part = c->w_in_place ? L.part : c->skpart;
+  float* const R = F;
+  HIP_TRY(launch_resp(c->P, Nep, dP, W0, Nap, Nep, Nap, Ne, Na, c->nP, c->nWc, R, Na, part, nullptr,
+                      s));
   HIP_TRY(launch_tanimoto_store(W0, Nap, c->C, Nap, Nep, Nap, Nap, Ne, Na, Na, c->nWr, c->nC, L.S,
-                                Nap, L.part, nullptr, s, c->dC));
-  HIP_TRY(launch_half_sum(L.R, L.S, Ne, Na, Nap, s));
+                                Nap, part, nullptr, s, c->dC));
+  HIP_TRY(launch_half_sum(R, Na, L.S, Nap, Ne, Na, s));
   // statistics of W0, S and S - W0 (tau)
   HIP_TRY(launch_zscore_stats(W0, Ne, Na, Nap, L.zsW, s));
   HIP_TRY(launch_zscore_stats(L.S, Ne, Na, Nap, L.zsS, s));
-  HIP_TRY(launch_ws_affine(L.S, Nap, W0, Nap, Ne, Na, 1.0, -1.0, L.R, Nap, s));
-  HIP_TRY(launch_zscore_stats(L.R, Ne, Na, Nap, L.zsD, s));
+  HIP_TRY(launch_ws_affine(L.S, Nap, W0, Nap, Ne, Na, 1.0, -1.0, R, Na, s));
+  HIP_TRY(launch_zscore_stats(R, Ne, Na, Na, L.zsD, s));
   // degrees and the two sketch bases
   HIP_TRY(launch_degrees(W0, Ne, Na, Nap, L.dr, L.dc, s));
   // the sketches use the whole P0 and C0: their diagonals go back in for now

@@ -60,8 +60,9 @@ struct VecRefHost {
 };
 // out[3 k + {0, 1, 2}] = mean, variance, mean square of vector k (device table).
 hipError_t launch_vec_moments(const VecRefHost* vecs, int count, double* out, hipStream_t s);
-hipError_t launch_half_sum(const float* R, float* A, int64_t rows, int64_t cols, int64_t ld,
-                           hipStream_t s);
+// A = (R + A) / 2 over rows x cols.
+hipError_t launch_half_sum(const float* R, int64_t ldr, float* A, int64_t lda, int64_t rows,
+                           int64_t cols, hipStream_t s);
 hipError_t launch_ws_stats(const double* m, const double* zW, const double* zS, double2* st,
                            hipStream_t s);
 hipError_t launch_ws_assemble(int64_t Ne, int64_t Na, const float* W0, const float* S, int64_t ld,

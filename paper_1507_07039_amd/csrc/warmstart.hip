@@ -675,12 +675,13 @@ __global__ __launch_bounds__(kT) void k_vec_moments(const VecRef* __restrict__ v
 }
 
 // S = (R0 + A0) / 2 in place of A0.
-__global__ __launch_bounds__(kT) void k_half_sum(const float* __restrict__ R, float* __restrict__ A,
-                                                 int64_t rows, int64_t cols, int64_t ld) {
+__global__ __launch_bounds__(kT) void k_half_sum(const float* __restrict__ R, int64_t ldr,
+                                                 float* __restrict__ A, int64_t lda, int64_t rows,
+                                                 int64_t cols) {
   const int64_t n = rows * cols;
   for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < n; e += (int64_t)gridDim.x * kT) {
-    const int64_t o = (e / cols) * ld + e % cols;
-    A[o] = (float)(0.5 * ((double)R[o] + (double)A[o]));
+    const int64_t i = e / cols, j = e - i * cols, o = i * lda + j;
+    A[o] = (float)(0.5 * ((double)R[i * ldr + j] + (double)A[o]));
   }
 }
 
@@ -851,9 +852,9 @@ hipError_t launch_vec_moments(const VecRefHost* vecs, int count, double* out, hi
   return hipGetLastError();
 }
 
-hipError_t launch_half_sum(const float* R, float* A, int64_t rows, int64_t cols, int64_t ld,
-                           hipStream_t s) {
-  k_half_sum<<<grid_cap(rows * cols, 8192), dim3(kT), 0, s>>>(R, A, rows, cols, ld);
+hipError_t launch_half_sum(const float* R, int64_t ldr, float* A, int64_t lda, int64_t rows,
+                           int64_t cols, hipStream_t s) {
+  k_half_sum<<<grid_cap(rows * cols, 8192), dim3(kT), 0, s>>>(R, ldr, A, lda, rows, cols);
   return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 // What the host code of libpanda.so decides about sizes and layouts, printed
 // for test_host_layout.py to check: no GPU, and no device memory behind the
-// pointers.  usage: host_layout fold | hpart | batch n Ne Na precision
+// pointers.  usage: host_layout fold | hpart | batch n Ne Na precision | small Ne Na
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -40,6 +40,10 @@ int main(int argc, char** argv) {
   if (argc == 6 && !strcmp(argv[1], "batch")) {  // whether n such networks take the small kernels
     const std::vector<int64_t> Ne(atoi(argv[2]), atoi(argv[3])), Na(atoi(argv[2]), atoi(argv[4]));
     printf("%d\n", (int)small_batch((int32_t)Ne.size(), Ne.data(), Na.data(), atoi(argv[5])));
+    return 0;
+  }
+  if (argc == 4 && !strcmp(argv[1], "small")) {  // whether one network does
+    printf("%d\n", (int)small_net(atoi(argv[2]), atoi(argv[3])));
     return 0;
   }
   if (argc != 2) return 2;

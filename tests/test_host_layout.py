@@ -75,3 +75,15 @@ def test_partial_gradients_sum_few_edges(n):
     chunks = -(-n // 32)
     slots = min(-(-chunks // 4), 512) * 4
     assert panda.load_library().panda_mlp_grad_workspace_bytes(n) >= slots * panda.MLP_PARAMS * 4
+
+
+@pytest.mark.parametrize("Ne,Na", [(40, 400), (3, 11), (500, 500), (200, 4000), (700, 18000)])
+def test_features_need_little_scratch(layout, Ne, Na):
+    """The features' workspace: one padded N_e x N_a matrix, the vectors, and for
+    networks past the small kernels (whose contexts are far larger) 64 MiB of
+    split tiles."""
+    up = lambda n, m: -(-n // m) * m  # noqa: E731
+    need = up(Ne, 64) * up(Na, 128) * 4 + 8 * 40 * (Ne + Na) + (1 << 18)
+    if not layout("small", Ne, Na)[0][0]:
+        need += 64 << 20
+    assert 0 < panda.load_library().panda_ws_features_workspace_bytes(Ne, Na) <= need
