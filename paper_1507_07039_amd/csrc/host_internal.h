@@ -107,6 +107,7 @@ struct panda_ctx {
   double* hpart;
   double2* cstat;
   double* csq;
+  int64_t crows;    // rows of C whose squares a load sums in one slot of csq
   uint32_t* corder;  // launch order of the upper C tiles
   uint32_t* corder_r;  // the same with the R tiles of the next iteration (not in a batch)
   bool small;       // iterates in the small kernels (small_internal.h)

@@ -85,7 +85,7 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
   Carver cv{base};
   const size_t nw = (size_t)Nep * (size_t)Nap;
   // bf16 planes of the operands: two, or three for the FP32 form
-  const bool sm = small_net(Ne, Na);
+  const bool sm = spec.batched ? small_net(Ne, Na) : small_run(Ne, Na, precision);
   const int np = sm && !spec.batched ? 0 : precision == PANDA_PREC_BF16X3 ? 2 : spec.batched ? 0 : 3;
   const bool in_place = np == 3;  // one buffer for W and R
   float* w0 = cv.take<float>(nw);
@@ -153,6 +153,7 @@ size_t ctx_layout(int64_t Ne, int64_t Na, int32_t precision, const LayoutSpec& s
     c->nh = spec.hpart_tiles;  // h partials that the tiled A + W products may add up
     c->cstat = cs;
     c->csq = cq;
+    c->crows = sm ? kSmallTile : kPT;
     c->corder = co;
     c->corder_r = cor;
     c->small = sm && !spec.batched;
@@ -490,7 +491,7 @@ panda_status ctx_load(panda_ctx* c, const float* W, const float* P, const float*
   a.hpart = c->hpart;  // partials the A + W product never writes add zeros
   a.nh = c->nh;
   a.slots = c->csq;
-  a.crows = small_net(Ne, Na) ? kSmallTile : kPT;
+  a.crows = c->crows;
   a.Pp = c->Pp;
   a.np = c->np;
   a.t = t;

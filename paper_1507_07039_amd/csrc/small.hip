@@ -19,6 +19,8 @@
 // block reads what another of its launch writes.  The diagonal of P, which
 // every R tile of a row reads and one writes, alternates between two vectors
 // by the parity of t.
+#include "panda.h"
+
 #include "epilogues.h"
 #include "small_internal.h"
 #include "update_device.h"
@@ -518,15 +520,26 @@ __global__ __launch_bounds__(kNT, 4) void k_small_finish(const BInst* __restrict
 
 // ------------------------------------------------------------ launchers --
 
-// Microseconds an iteration here / with the tiled kernels of the FP32 form:
-// 40 x 400 24 / 73, 500 x 500 41 / 97, 750 x 750 82 / 113, 300 x 1500 79 / 98,
-// 100 x 2000 70 / 90, 150 x 2000 96 / 95; past the line 1000 x 1000 142 / 131,
-// 100 x 3000 148 / 103, 40 x 4000 172 / 130 (the small tiles read C at a third
-// of its bandwidth).  The split-BF16 form takes them as well: its networks
-// of these sizes wait for launches, not for the matrix cores.
+// Past this line the tiled kernels win in either form: us an iteration here /
+// there in the FP32 form, 1000 x 1000 142 / 131, 100 x 3000 148 / 103, 40 x
+// 4000 172 / 130 (the small tiles read C at a third of its bandwidth).
 // With few genes every sum over them is short, and takes no planes (kShortK).
 bool small_net(int64_t Ne, int64_t Na) {
   return Na <= kShortK || (Ne <= 2048 && Na <= 2048 && Ne * Na * (Ne + Na) <= 900000000);
+}
+
+// us an iteration here / in the tiled kernels of the FP32 form / of the split
+// one: 40 x 400 25 / 72 / 77, 500 x 500 39 / 93 / 102, 750 x 750 82 / 112 / 97,
+// 500 x 1000 66 / 100 / 88, 300 x 1500 81 / 97 / 84, 2000 x 150 98 / 211 / 166,
+// 128 x 2048 75 / 92 / 79.  With more tiles of A than CUs some CU takes two,
+// each over all of K = N_a, and near the long end of the range that costs more
+// than the launches saved: 129 x 1700 82 / 94 / 81, 192 x 1900 93 / 93 / 84, 192
+// x 2048 97 / 93 / 81; up to 1600 genes neither form loses 3 % (288 x 1600 87 /
+// 98 / 86).
+constexpr int64_t kChip = 256;  // CUs
+bool small_run(int64_t Ne, int64_t Na, int32_t precision) {
+  const int64_t longest = precision == PANDA_PREC_BF16X3 ? 1600 : 1900;
+  return small_net(Ne, Na) && (Na <= longest || small_tiles(Ne) * small_tiles(Na) <= kChip);
 }
 
 hipError_t launch_small_avail(const BInst* bi, const BInst& one, int n, SmallDims mx,

@@ -12,8 +12,10 @@ constexpr int64_t kSmallTile = 32;
 inline int64_t small_tiles(int64_t n) { return (n + kSmallTile - 1) / kSmallTile; }
 inline int64_t small_h_slots(int64_t Ne, int64_t Na) { return small_tiles(Ne) * small_tiles(Na); }
 
-// Whether a network of this size takes the small kernels.
+// Whether a network of this size can take the small kernels (a batch of such
+// networks chooses by small_batch), and whether one iterated alone does.
 bool small_net(int64_t Ne, int64_t Na);
+bool small_run(int64_t Ne, int64_t Na, int32_t precision);
 
 struct SmallRule {
   Rule r;

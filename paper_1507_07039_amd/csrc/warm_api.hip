@@ -30,7 +30,7 @@ size_t feat_layout(int64_t Ne, int64_t Na, char* base, FeatLayout* L) {
   Carver cv{base};
   FeatLayout l;
   l.S = cv.take<float>((size_t)Nep * Nap);
-  l.part = small_net(Ne, Na) ? nullptr : cv.take<float>(rect_partial_floats());
+  l.part = small_run(Ne, Na, PANDA_PREC_FP32) ? nullptr : cv.take<float>(rect_partial_floats());
   l.dr = cv.take<double>((size_t)Ne);
   l.dc = cv.take<double>((size_t)Na);
   double** sixNe[] = {&l.omP, &l.tmpP, &l.yP, &l.a, &l.zP, &l.c};

@@ -1,6 +1,7 @@
 // What the host code of libpanda.so decides about sizes and layouts, printed
 // for test_host_layout.py to check: no GPU, and no device memory behind the
-// pointers.  usage: host_layout fold | hpart | batch n Ne Na precision | small Ne Na
+// pointers.  usage: host_layout fold | hpart | batch n Ne Na precision | small Ne Na |
+// run Ne Na precision
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -44,6 +45,10 @@ int main(int argc, char** argv) {
   }
   if (argc == 4 && !strcmp(argv[1], "small")) {  // whether one network does
     printf("%d\n", (int)small_net(atoi(argv[2]), atoi(argv[3])));
+    return 0;
+  }
+  if (argc == 5 && !strcmp(argv[1], "run")) {  // and whether it does when iterated alone
+    printf("%d\n", (int)small_run(atoi(argv[2]), atoi(argv[3]), atoi(argv[4])));
     return 0;
   }
   if (argc != 2) return 2;

@@ -220,6 +220,38 @@ def test_tiled_extreme_entry(torch, pd, where, bad, packed):
         assert torch.isfinite(got).all()
 
 
+# the line past which a network that could take the small kernels iterates in
+# the tiled ones (more than 256 tiles of W, and more than 1900 genes in the FP32
+# form or 1600 in the split one), and the longest such networks
+@pytest.mark.parametrize("Ne,Na,precision", [(129, 1901, 0), (192, 2048, 0), (161, 1601, 1), (192, 2048, 1)])
+@pytest.mark.parametrize("packed", [0, 1])
+def test_tiled_steps_within_the_small_rule(torch, pd, Ne, Na, precision, packed):
+    """As test_tiled_steps (the same bounds), with features taken after two
+    iterations, which leave the run as it was."""
+    import ctypes as ct
+    f = pd.load_library()._ZN5panda9small_runElli
+    f.restype, f.argtypes = ct.c_bool, [ct.c_int64, ct.c_int64, ct.c_int32]
+    assert not tiled(pd, Ne, Na) and not f(Ne, Na, precision)
+    tol = 1e-3 if precision else 1e-4
+    o = pd.default_options(tol=0.0, packed_c=packed, precision=precision)
+    net = gpu_net(torch, Ne + Na, Ne, Na)
+    a, b = pd.Context(Ne, Na, o), pd.Context(Ne, Na, o)
+    a.load(*net)
+    b.load(*net)
+    for t in range(1, 4):
+        before = a.state()[:3]
+        h, tt = a.iterate()
+        want = step64(torch, *(M.double() for M in before), t, {})
+        assert tt == t and abs(h - want[3]) <= 0.1 * tol * want[3]
+        for g, w in zip(a.state()[:3], want):
+            close(g, w, tol)
+        assert b.iterate() == (h, tt)
+        if t == 2 and not packed:
+            b.features(*(torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda()
+                         for x in I.sketch_matrices(5, Ne, Na)))
+    assert all(torch.equal(x, y) for x, y in zip(a.state()[:3], b.state()[:3]))
+
+
 # ------------------------------------------------------- warm start, tiled context --
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("steps", [0, 2])

@@ -67,6 +67,21 @@ def test_batches_take_the_faster_kernels(layout, n, Ne, Na, small, fp32, split):
         assert layout("batch", n, Ne, Na, precision) == [[int(small < grouped)]], (precision, grouped)
 
 
+# the same for one network, the tiled kernels of either form beside the small
+# ones; a choice within 3 % of the better is not told apart
+@pytest.mark.parametrize("Ne,Na,small,fp32,split", [
+    (40, 400, 25, 72, 77), (500, 500, 39, 93, 102), (750, 750, 82, 112, 97), (500, 1000, 66, 100, 88),
+    (500, 1100, 89, 102, 88), (300, 1500, 81, 97, 84), (256, 1600, 85, 95, 84), (288, 1600, 87, 98, 86),
+    (128, 1700, 64, 91, 80), (129, 1700, 82, 94, 81), (256, 1700, 91, 97, 82), (224, 1800, 92, 95, 85),
+    (128, 1900, 71, 91, 82), (129, 1900, 92, 93, 83), (128, 2048, 75, 92, 79), (129, 2000, 94, 93, 83),
+    (192, 2048, 97, 93, 81), (64, 2048, 73, 87, 79), (1200, 420, 97, 138, 137), (2000, 150, 98, 211, 166),
+    (2048, 190, 101, 233, 195), (2000, 40, 75, 189, 157)])
+def test_networks_take_the_faster_kernels(layout, Ne, Na, small, fp32, split):
+    for precision, tiled in ((0, fp32), (1, split)):
+        took = small if layout("run", Ne, Na, precision) == [[1]] else tiled
+        assert took <= 1.03 * min(small, tiled), precision
+
+
 @pytest.mark.parametrize("n", [1, 4000, 65536, 65537, 300000])
 def test_partial_gradients_sum_few_edges(n):
     """The warm start's partial gradients (FP32 sums over the edges of a wave,
