@@ -24,6 +24,8 @@
  *     normalisation) synchronise that stream before returning.
  *   - Arguments are validated on the host before any device work; a failed
  *     validation returns PANDA_ERR_ARG and enqueues nothing.
+ *   - P and C are taken to be symmetric.  Where the two triangles of one differ
+ *     (by rounding, say), which of them a product reads is not specified.
  *   - Network sizes: 1 <= N_e <= 65536 TFs and 1 <= N_a <= 262144 genes (so
  *     every grid and tile index stays in range); outside them the calls
  *     return PANDA_ERR_ARG and the *_workspace_bytes() calls return 0.
@@ -76,8 +78,11 @@ typedef enum {
  *                      C stays FP32 (split while it is staged for the
  *                      products); the extra workspace is the hi/lo planes of
  *                      W (two layouts) and P, about 4 * Ne * Na * 2 bytes.
- * Networks of a few hundred nodes a side, whose iterations wait for launches
- * rather than matrix cores, take the same FP32 kernels in both forms. */
+ * Small networks, whose iterations wait for launches rather than matrix cores,
+ * take the same FP32 kernels in both forms: up to 2048 nodes a side with
+ * Ne * Na * (Ne + Na) <= 9e8 (766 x 766, 40 x 2048) or at most eight genes,
+ * unless measurements favour the others (a run of 129 or more TFs over some
+ * 1600 to 2048 genes, a batch large enough to fill the chip). */
 enum { PANDA_PREC_FP32 = 0, PANDA_PREC_BF16X3 = 1 };
 
 /* Scope of the z-score of Sec. II-A (the paper says only that each network

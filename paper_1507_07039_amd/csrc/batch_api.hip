@@ -22,9 +22,10 @@ LayoutSpec batch_spec(int64_t Ne, int64_t Na) {
 // Estimates of an iteration's time in both sets of kernels, fitted to 74
 // batches of equal networks (20 x 100 to 100 x 2000 and 2000 x 100, 2 to 1000
 // of them, both forms; the small kernels' within 8 %, the grouped ones' within
-// 20 %).  One network leaves the chip idle, and there the small kernels win at
-// every size that small_net takes; many fill it, and then their 32 x 32 tiles run
-// at a third of the grouped kernels' rate.  us an iteration, small / grouped
+// 20 %).  A batch of one leaves the chip idle, and there the small kernels win
+// at every size that small_net takes (the grouped ones do not cut a tile's K);
+// many networks fill it, and then the 32 x 32 tiles run at a third of the grouped
+// kernels' rate.  us an iteration, small / grouped
 // FP32 / grouped split-BF16:
 //   20 of 125 x 125   37 /  150 / 139     2 of 100 x 2000   133 / 285 / 184
 //   16 of 40 x 400    57 /  172 / 128     8 of 100 x 2000   469 / 377 / 239

@@ -430,7 +430,8 @@ __device__ __forceinline__ void split_pair3(float a, float b, unsigned (&o)[3]) 
 // networks (57 x 4999 to 661 x 9787, 238 GFLOP) 2.81 -> 1.62 ms (880 TFLOP/s
 // of bf16), its C update 1.74 -> 1.11, W W^T 0.15 -> 0.11; a similarity of 700
 // x 2001 x 5003 167 -> 94 us; correlations of 18000 genes over 200 samples
-// 890 -> 760 us (1.3 GB written).  The error against 64 bits falls to between
+// 938 -> 668 us on average over 21 launches (871 -> 563 the shortest; with the
+// 16-byte stores of corr_sym_epilogue).  The error against 64 bits falls to between
 // a third and 0.8 of what it was.
 //
 // KS: how K is summed (KSum).  Folded as there, but in registers (a choice of

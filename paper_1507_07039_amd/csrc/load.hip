@@ -250,9 +250,11 @@ __global__ __launch_bounds__(kLT) void k_store(StoreArgs a) {
   }
 }
 
-// Position of C tile (I, J) in coreg_order_fill's order: the columns of
-// super-tiles before J's, the super-tiles above I's in its own, the tiles
-// before it there.
+// The order of the upper C tiles (kCoregGroup): super-tiles of g x g tiles,
+// column of super-tiles after column and downwards in each, the tiles of one
+// column by column.  So tile (I, J) comes after the columns of super-tiles
+// before J's, the super-tiles above I's in its own, and the tiles before it
+// there.
 __device__ __forceinline__ int64_t order_of(int64_t I, int64_t J, int64_t nT, int64_t g) {
   const int64_t J0 = J / g * g, J1 = J0 + g < nT ? J0 + g : nT, I0 = I / g * g;
   const int64_t before = J0 * (J0 + 1) / 2 + I0 * (J1 - J0);

@@ -58,8 +58,9 @@ struct PackArgs {
 };
 hipError_t launch_pack_xy(const PackArgs& a, hipStream_t s);
 
-// The launch orders of the C update (see coreg_order_fill) written on the
-// device; corder_r (with the next R's tiles) may be null.
+// The launch orders of the C update, written on the device: the upper tiles by
+// super-tiles of group x group, and, unless corder_r is null, the same order
+// with the next R's tiles after each XCD's share of C tiles.
 hipError_t launch_order(int64_t Nep, int64_t Nap, int group, uint32_t* corder, uint32_t* corder_r,
                         hipStream_t s);
 

@@ -414,10 +414,11 @@ panda_status enqueue_iteration(panda_ctx* c) {
   return PANDA_OK;
 }
 
-// Whether the buffer that W shares holds R and the planes alone hold W: after
-// an iteration that updated P and C (the one that converges does not, unless
-// update_last: then its W stays where the A product left it and the planes
-// hold the W before).  The state is that of the last read-back.
+// Whether the buffer that W shares holds R and the planes alone hold W.  An
+// iteration that updates P and C ends that way: it writes the planes of its
+// new W and the next R over W.  One that does not (the converging one without
+// update_last) leaves its W in the buffer, and in the planes the W before.
+// The state is that of the last read-back.
 bool w_in_planes(const panda_ctx* c) {
   return c->w_in_place && c->r_next && (!c->host->conv || c->rule.update_last);
 }

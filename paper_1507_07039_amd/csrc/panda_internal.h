@@ -240,11 +240,9 @@ hipError_t launch_put_diag(float* M, int64_t n, int64_t ld, const double* d, hip
 // t, the gates, and the current-W selector back to buffer 0.
 hipError_t launch_state_set(DevState* st, int32_t t, int32_t active, int32_t run_pc,
                             hipStream_t s);
-// Squared norms of the rows / columns of a rows x cols matrix with leading
 // Row and column squared norms of W (padded Nep x ldw, real Ne x Na) in one
 // pass over it, plus its np bf16 planes (of W, Wr, with the lower bits where np
-// is 3; of W^T, Wt).  scr holds
-// w_norm_scratch_doubles().
+// is 3; of W^T, Wt).  scr holds w_norm_scratch_doubles().
 size_t w_norm_scratch_doubles(int64_t Nep, int64_t Nap);
 hipError_t launch_w_norms(const float* W, int64_t Ne, int64_t Na, int64_t ldw, int64_t Nep,
                           double* nr, double* nc, double* scr, Planes Wr, Planes Wt, int np,

@@ -373,7 +373,7 @@ __device__ __forceinline__ Mom mom_block(const Mom& a, double* red) {
 // m2 NaN.  Scratch: mean, std and the non-finite flag at [kZsBlocks],
 // [kZsBlocks + 1], [kZsBlocks + 2]; the block moments from kZsPart on.
 // 18000 x 18000: two passes of 733 us (a 64-bit division per entry to find
-// its row) -> one of 0.3 ms.
+// its row) -> one of 0.42 ms.
 template <bool VEC, int U>
 __global__ __launch_bounds__(kRT) void k_zs_moments(const float* __restrict__ M, int64_t rows,
                                                     int64_t cols, int64_t ld, int64_t per_row,
